@@ -20,7 +20,8 @@ DEVICE_SOURCES = ["rbd_diag.hip", "rbd_noalloc.hip"]
 TOPO_SOURCE = "rbd_kern_topo.hip"
 # Device headers the run-time compiler instantiates for a new topology; their
 # text is embedded in the library.
-JIT_HEADERS = ["rbd_kernels.hpp", "rbd_kernel_ids.hpp", "rbd_lane.hpp", "rbd_shared.hpp"]
+JIT_HEADERS = ["rbd_kernels.hpp", "rbd_kernel_ids.hpp", "rbd_lane.hpp", "rbd_shared.hpp", "rbd_team.hpp",
+               "rbd_team_plan.hpp"]
 
 # Packed FP32 (v_pk_*_f32) is switched off for every HIP translation unit.
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function", "-Wno-unused-variable",
@@ -44,7 +45,7 @@ PREBUILT = {
 # way: topology name (compiled or PREBUILT) -> frames.
 PREBUILT_FRAMES = {"humanoid30": [6, 22], "chain7": [3], "quadruped13f": [3]}
 JIT_DIR = os.path.join(PKG, "_jit")
-N_KERNELS = 40  # RBD_N_KERNELS
+N_KERNELS = 48  # RBD_N_KERNELS
 
 
 def _precompile_one(args):
@@ -171,9 +172,10 @@ def _jobs():
 
 
 # What each kind of object is compiled from (for incremental builds).
-DEVICE_DEPS = [TOPO_SOURCE, "rbd_kernels.hpp", "rbd_kernel_ids.hpp", "rbd_lane.hpp", "rbd_shared.hpp",
-               "rbd_topologies.hpp"]
-HOST_HEADERS = ["rbd_internal.hpp", "rbd_shared.hpp", "rbd_kernel_ids.hpp", "rbd_topologies.hpp"]
+DEVICE_DEPS = [TOPO_SOURCE, "rbd_kernels.hpp", "rbd_kernel_ids.hpp", "rbd_lane.hpp", "rbd_shared.hpp", "rbd_team.hpp",
+               "rbd_team_plan.hpp", "rbd_topologies.hpp"]
+HOST_HEADERS = ["rbd_internal.hpp", "rbd_shared.hpp", "rbd_kernel_ids.hpp", "rbd_team_plan.hpp",
+                "rbd_topologies.hpp"]
 
 
 def _inputs_hash(obj: str, cmd) -> str:
@@ -229,7 +231,7 @@ def build(verbose: bool = False, jobs: int = 0, resource_usage: bool = False, in
     work = []
     # the largest topologies first, so the longest compiles start early
     for name in reversed(topologies()):
-        for part in (8, 2, 7, 4, 6, 5, 3, 1):
+        for part in (8, 2, 7, 4, 6, 5, 3, 1, 10, 11, 12, 9):
             obj = os.path.join(out_dir, f"kern_{name}_p{part}.o")
             cmd = [HIPCC, *DEVICE, *COMMON, f"-DRBD_TOPO={name}", f"-DRBD_PART={part}", "-c",
                    os.path.join(CSRC, TOPO_SOURCE), "-o", obj]

@@ -307,6 +307,7 @@ rbd_status rbd_model_create(const rbd_tree_desc* desc, int device, rbd_model** o
   m->floating = floating;
   m->nq = n + (floating ? 6 : 0);
   m->nv = n + (floating ? 5 : 0);
+  if (m->nv > kTeamMinDofs) m->team = team_plan(floating, n, desc->parent);
   m->tab_floats = tab.size();
   if (host_only) {  // tables kept on the host, no kernels
     m->h_tab = std::move(tab);

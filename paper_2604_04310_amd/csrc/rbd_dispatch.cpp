@@ -23,7 +23,11 @@ static_assert(kOpFwdDyn == RBD_OP_FWD_DYN && kOpRnea == RBD_OP_RNEA && kOpFwdDyn
   void kernels_##name##_p5(const void**);                                                                    \
   void kernels_##name##_p6(const void**);                                                                    \
   void kernels_##name##_p7(const void**);                                                                    \
-  void kernels_##name##_p8(const void**);
+  void kernels_##name##_p8(const void**);                                                                    \
+  void kernels_##name##_p9(const void**);                                                                    \
+  void kernels_##name##_p10(const void**);                                                                   \
+  void kernels_##name##_p11(const void**);                                                                   \
+  void kernels_##name##_p12(const void**);
 RBD_TOPOLOGIES(RBD_DECL)
 #undef RBD_DECL
 
@@ -41,7 +45,8 @@ using FillFn = void (*)(const void**);
 static const FillFn k_fill[][kParts] = {
 #define RBD_TAB(name, fr, ...)                                                                            \
   {&kernels_##name##_p1, &kernels_##name##_p2, &kernels_##name##_p3, &kernels_##name##_p4, \
-   &kernels_##name##_p5, &kernels_##name##_p6, &kernels_##name##_p7, &kernels_##name##_p8},
+   &kernels_##name##_p5, &kernels_##name##_p6, &kernels_##name##_p7, &kernels_##name##_p8, \
+   &kernels_##name##_p9, &kernels_##name##_p10, &kernels_##name##_p11, &kernels_##name##_p12},
     RBD_TOPOLOGIES(RBD_TAB)
 #undef RBD_TAB
 };
@@ -120,6 +125,15 @@ static inline Shape plain_shape(int64_t batch) { return {dim3(grid_for(batch)), 
 // (scalar-base addressing is chosen in the kernels themselves).
 static inline bool large(const rbd_model* m) { return m->nv > 16; }
 
+// Whether the model's tree is shared out over a team of waves, and the shape
+// of such a launch: one block per 64 instances.
+static inline bool teamed(const rbd_model* m, int64_t batch) {
+  return m->team.waves > 1 && (m->nv > kTeamAlwaysDofs || batch <= kOneWavePerSimd);
+}
+static inline Shape team_shape(const rbd_model* m, int64_t batch) {
+  return {dim3((unsigned)((batch + kTileLanes - 1) / kTileLanes)), dim3((unsigned)(m->team.waves * kTileLanes))};
+}
+
 // Launches kernel `id` of the model's set; args point to the kernel's
 // arguments in order.
 static rbd_status launch(const rbd_model* m, KernelId id, Shape sh, void** args, hipStream_t s, const char* what) {
@@ -178,6 +192,10 @@ rbd_status launch_rnea(const rbd_model* m, int64_t batch, int64_t ld, const floa
   else id = qdd ? KID_RNEA : KID_RNEA_BIAS;
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &qd, &qdd, &fext, &tau};
+  if (teamed(m, batch)) {
+    id = fext ? (qdd ? KID_RNEA_EXT_TEAM : KID_RNEA_BIAS_EXT_TEAM) : (qdd ? KID_RNEA_TEAM : KID_RNEA_BIAS_TEAM);
+    return launch(m, id, team_shape(m, batch), a, s, "rbd_rnea");
+  }
   return launch(m, id, plain_shape(batch), a, s, "rbd_rnea");
 }
 
@@ -195,6 +213,8 @@ rbd_status launch_fwd_dyn(const rbd_model* m, int64_t batch, int64_t ld, const f
   const KernelId id = fext ? (pre ? KID_FWD_DYN_PRE_EXT : KID_FWD_DYN_EXT) : (pre ? KID_FWD_DYN_PRE : KID_FWD_DYN);
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &qd, &tau, &fext, &qdd};
+  if (teamed(m, batch))
+    return launch(m, fext ? KID_FWD_DYN_TEAM_EXT : KID_FWD_DYN_TEAM, team_shape(m, batch), a, s, "rbd_fwd_dyn");
   return launch(m, id, heavy_shape(batch), a, s, "rbd_fwd_dyn");
 }
 
@@ -294,6 +314,8 @@ rbd_status launch_fwd_dyn_vjp(const rbd_model* m, int64_t batch, int64_t ld, con
   const bool ext = gfext || (fext && (gq || gqd));
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &qd, &tau, &gqdd, &gq, &gqd, &gtau, &fext, &gfext};
+  if (teamed(m, batch) && (gq || gqd || gfext))
+    return launch(m, ext ? KID_VJP_EXT_TEAM : KID_VJP_TEAM, team_shape(m, batch), a, s, "rbd_fwd_dyn_vjp");
   if (large(m) && (gq || gqd || gfext)) {
     const unsigned grid = (unsigned)((batch + kTileLanes - 1) / kTileLanes);
     const unsigned lds = (unsigned)(2 * m->nv * kTileLanes * sizeof(float));
@@ -338,7 +360,11 @@ rbd_status launch_packed(const rbd_model* m, int op, const void* d_table, int gr
   const float* tab = m->d_tab;
   const uint8_t* t = static_cast<const uint8_t*>(d_table);
   void* a[] = {&tab, &t};
-  return launch(m, id, Shape{dim3((unsigned)grid), dim3(kBlock)}, a, s, "packed launch");
+  // `grid` blocks of kBlock lanes stride over the tiles, or as many teams
+  const Shape sh = m->team.waves > 1
+                       ? Shape{dim3((unsigned)grid * (kBlock / kTileLanes)), dim3((unsigned)(m->team.waves * kTileLanes))}
+                       : Shape{dim3((unsigned)grid), dim3(kBlock)};
+  return launch(m, id, sh, a, s, "packed launch");
 }
 
 }  // namespace rbd

@@ -11,6 +11,7 @@
 #include "rbd.h"
 #include "rbd_kernel_ids.hpp"
 #include "rbd_shared.hpp"
+#include "rbd_team_plan.hpp"
 
 namespace rbd {
 // The kernels serving a model: those of a topology compiled ahead of time
@@ -37,6 +38,7 @@ struct rbd_model {
   std::vector<float> h_tab;    // the tables of a host-only model (device -1)
   std::vector<int32_t> parent; // topology (for run-time compiled per-frame kernels)
   size_t tab_floats = 0;
+  rbd::TeamPlan team;          // how a team of waves shares the tree (waves = 0: it does not)
   uint64_t uid = 0;            // unique over the process (a new model never reuses one)
 };
 

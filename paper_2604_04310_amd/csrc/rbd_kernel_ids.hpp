@@ -6,7 +6,8 @@
 // matrix; 2 forward dynamics and the packed forward / inverse dynamics
 // launches; 3 the adjoint and its packed launch; 4 the articulated-body
 // algorithm; 5 the external-force variants; 6 the forward-mode derivative;
-// 7 the controllers; 8 the derivatives with external forces.
+// 7 the controllers; 8 the derivatives with external forces;
+// 9 to 11 the kernels of a team of waves (dynamics; derivatives; the rest).
 #pragma once
 
 #define RBD_KERNELS(X)                                    \
@@ -49,7 +50,15 @@
   X(KID_RNEA_VJP, 3, k_rnea_vjp<TP>)                      \
   X(KID_RNEA_VJP_EXT, 8, k_rnea_vjp<TP, true>)            \
   X(KID_VJP_SPLIT, 3, k_fwd_dyn_vjp_split<TP>)            \
-  X(KID_VJP_EXT_SPLIT, 8, k_fwd_dyn_vjp_split<TP, true>)
+  X(KID_VJP_EXT_SPLIT, 8, k_fwd_dyn_vjp_split<TP, true>) \
+  X(KID_FWD_DYN_TEAM, 9, k_fwd_dyn_team<TP, false>)       \
+  X(KID_FWD_DYN_TEAM_EXT, 9, k_fwd_dyn_team<TP, true>)    \
+  X(KID_VJP_TEAM, 10, k_fwd_dyn_vjp_team<TP, false>)      \
+  X(KID_VJP_EXT_TEAM, 10, k_fwd_dyn_vjp_team<TP, true>)   \
+  X(KID_RNEA_TEAM, 9, k_rnea_team<TP, true, false>)       \
+  X(KID_RNEA_BIAS_TEAM, 9, k_rnea_team<TP, false, false>) \
+  X(KID_RNEA_EXT_TEAM, 9, k_rnea_team<TP, true, true>)    \
+  X(KID_RNEA_BIAS_EXT_TEAM, 9, k_rnea_team<TP, false, true>)
 
 namespace rbd {
 
@@ -60,6 +69,6 @@ enum KernelId : int {
   KID_COUNT
 };
 
-constexpr int kParts = 8;
+constexpr int kParts = 12;
 
 }  // namespace rbd

@@ -8,6 +8,7 @@
 
 #include "rbd_lane.hpp"
 #include "rbd_shared.hpp"
+#include "rbd_team.hpp"
 
 namespace rbd {
 
@@ -100,6 +101,9 @@ RBD_DI void preload_inputs(float (&x)[n], float (&y)[n], const A& a, const B& b)
   });
 }
 
+// A tree that always runs as a team (Team::kAlways) launches the team's kernel
+// of an operation in place of the one below, which is then left empty.
+
 template <class TP>
 __global__ __launch_bounds__(kBlock) void k_fk(const float* __restrict__ tab, int64_t batch, int64_t ld,
                                                const float* __restrict__ q, float* __restrict__ T) {
@@ -127,24 +131,26 @@ __global__ __launch_bounds__(kBlock) void k_rnea(const float* __restrict__ tab, 
                                                  const float* __restrict__ q, const float* __restrict__ qd,
                                                  const float* __restrict__ qdd, const float* __restrict__ fext,
                                                  float* __restrict__ tau) {
-  RBD_LANE_IO(TP);
-  const uint32_t b = lane_id();
-  if (b >= batch) return;
-  if constexpr (PRE && !EXT) {
-    constexpr int NQ = TP::NQ, NV = TP::NV;
-    float qv[NQ], qdv[NV], qddv[NV];
-    const In qi{q, ld, b}, qdi{qd, ld, b}, qddi{HAS_QDD ? qdd : qd, ld, b};
-    sfor<0, NQ>([&](auto K_) __attribute__((always_inline)) { qv[decltype(K_)::value] = qi(decltype(K_)::value); });
-    sfor<0, NV>([&](auto K_) __attribute__((always_inline)) {
-      qdv[decltype(K_)::value] = qdi(decltype(K_)::value);
-      if constexpr (HAS_QDD) qddv[decltype(K_)::value] = qddi(decltype(K_)::value);
-    });
-    rnea_lane<TP, HAS_QDD>(tab, RegView{qv}, RegView{qdv}, RegView{HAS_QDD ? qddv : qdv}, Out{tau, ld, b});
-  } else if constexpr (EXT)
-    rnea_lane<TP, HAS_QDD>(tab, In{q, ld, b}, In{qd, ld, b}, In{HAS_QDD ? qdd : q, ld, b}, Out{tau, ld, b},
-                           FextIn{{fext, ld, b}});
-  else
-    rnea_lane<TP, HAS_QDD>(tab, In{q, ld, b}, In{qd, ld, b}, In{HAS_QDD ? qdd : q, ld, b}, Out{tau, ld, b});
+  if constexpr (!Team<TP>::kAlways) {
+    RBD_LANE_IO(TP);
+    const uint32_t b = lane_id();
+    if (b >= batch) return;
+    if constexpr (PRE && !EXT) {
+      constexpr int NQ = TP::NQ, NV = TP::NV;
+      float qv[NQ], qdv[NV], qddv[NV];
+      const In qi{q, ld, b}, qdi{qd, ld, b}, qddi{HAS_QDD ? qdd : qd, ld, b};
+      sfor<0, NQ>([&](auto K_) __attribute__((always_inline)) { qv[decltype(K_)::value] = qi(decltype(K_)::value); });
+      sfor<0, NV>([&](auto K_) __attribute__((always_inline)) {
+        qdv[decltype(K_)::value] = qdi(decltype(K_)::value);
+        if constexpr (HAS_QDD) qddv[decltype(K_)::value] = qddi(decltype(K_)::value);
+      });
+      rnea_lane<TP, HAS_QDD>(tab, RegView{qv}, RegView{qdv}, RegView{HAS_QDD ? qddv : qdv}, Out{tau, ld, b});
+    } else if constexpr (EXT)
+      rnea_lane<TP, HAS_QDD>(tab, In{q, ld, b}, In{qd, ld, b}, In{HAS_QDD ? qdd : q, ld, b}, Out{tau, ld, b},
+                             FextIn{{fext, ld, b}});
+    else
+      rnea_lane<TP, HAS_QDD>(tab, In{q, ld, b}, In{qd, ld, b}, In{HAS_QDD ? qdd : q, ld, b}, Out{tau, ld, b});
+  }
 }
 
 template <class TP>
@@ -183,24 +189,26 @@ __global__ __launch_bounds__(kBlock) void k_fwd_dyn(const float* __restrict__ ta
                                                     const float* __restrict__ q, const float* __restrict__ qd,
                                                     const float* __restrict__ tau, const float* __restrict__ fext,
                                                     float* __restrict__ qdd) {
-  RBD_LANE_IO(TP);
-  const uint32_t b = lane_id();
-  if (b >= batch) return;
-  const auto fx = fext_view<EXT>(fext, ld, b);
-  if constexpr (PRE) {
-    constexpr int NQ = TP::NQ, NV = TP::NV;
-    float qv[NQ], qdv[NV], tv[NV];
-    const In qi{q, ld, b}, qdi{qd, ld, b}, ti{tau, ld, b};
-    sfor<0, NQ>([&](auto K_) __attribute__((always_inline)) { qv[decltype(K_)::value] = qi(decltype(K_)::value); });
-    sfor<0, NV>([&](auto K_) __attribute__((always_inline)) {
-      qdv[decltype(K_)::value] = qdi(decltype(K_)::value);
-      tv[decltype(K_)::value] = ti(decltype(K_)::value);
-    });
-    fwd_dyn_lane<TP, 1>(tab, RegView{qv}, RegView{qdv}, RhsOne<RegView>{RegView{tv}}, SinkOne<Out>{Out{qdd, ld, b}},
-                        fx);
-  } else {
-    fwd_dyn_lane<TP, 1>(tab, In{q, ld, b}, In{qd, ld, b}, RhsOne<In>{In{tau, ld, b}}, SinkOne<Out>{Out{qdd, ld, b}},
-                        fx);
+  if constexpr (!Team<TP>::kAlways) {
+    RBD_LANE_IO(TP);
+    const uint32_t b = lane_id();
+    if (b >= batch) return;
+    const auto fx = fext_view<EXT>(fext, ld, b);
+    if constexpr (PRE) {
+      constexpr int NQ = TP::NQ, NV = TP::NV;
+      float qv[NQ], qdv[NV], tv[NV];
+      const In qi{q, ld, b}, qdi{qd, ld, b}, ti{tau, ld, b};
+      sfor<0, NQ>([&](auto K_) __attribute__((always_inline)) { qv[decltype(K_)::value] = qi(decltype(K_)::value); });
+      sfor<0, NV>([&](auto K_) __attribute__((always_inline)) {
+        qdv[decltype(K_)::value] = qdi(decltype(K_)::value);
+        tv[decltype(K_)::value] = ti(decltype(K_)::value);
+      });
+      fwd_dyn_lane<TP, 1>(tab, RegView{qv}, RegView{qdv}, RhsOne<RegView>{RegView{tv}}, SinkOne<Out>{Out{qdd, ld, b}},
+                          fx);
+    } else {
+      fwd_dyn_lane<TP, 1>(tab, In{q, ld, b}, In{qd, ld, b}, RhsOne<In>{In{tau, ld, b}}, SinkOne<Out>{Out{qdd, ld, b}},
+                          fx);
+    }
   }
 }
 
@@ -322,54 +330,56 @@ __global__ __launch_bounds__(kBlock) void k_fwd_dyn_vjp(const float* __restrict_
                                                         const float* __restrict__ tau,
                                                         const float* __restrict__ gqdd, float* gq, float* gqd,
                                                         float* gtau, const float* __restrict__ fext, float* gfext) {
-  static_assert(!EXT || MODE >= 1, "external forces: modes 1 to 3");
-  RBD_LANE_IO(TP);
-  const uint32_t b = lane_id();
-  if (b >= batch) return;
-  const In qi{q, ld, b}, qdi{qd, ld, b}, ti{tau, ld, b}, gi{gqdd, ld, b};
-  const OutOpt<OutAlias> gqo{OutAlias{gq, ld, b}, gq != nullptr};
-  // the external-force views (nothing without EXT)
-  auto fx_view = [&](const float* p, int64_t l) __attribute__((always_inline)) {
-    if constexpr (EXT) return FextOpt{{p, l, b}};
-    else return NoFext{};
-  };
-  auto gf_view = [&](int64_t l) __attribute__((always_inline)) {
-    if constexpr (EXT) return GFOut{{gfext, l, b}};
-    else return NoGF{};
-  };
-  if constexpr (MODE == 3) {
-    // the two sweeps, the second on fresh views (its own table and input
-    // pointers and row stride): a large tree's first sweep uses every
-    // register, and values kept for the second one spill (measured: 1028 ->
-    // 400 B/lane of scratch, 126 -> 108 us for the humanoid). Each wave parks
-    // in its region of the block's dynamic LDS: [qdd rows | lam rows].
-    extern __shared__ float lds_park[];
-    constexpr int NV = TP::NV;
-    float* const w = lds_park + (threadIdx.x / kTileLanes) * (2 * NV * kTileLanes) + (threadIdx.x % kTileLanes);
-    fwd_dyn_lane<TP, 2>(tab, qi, qdi, RhsTwo<In>{ti, gi}, SinkTwo<LdsRow>{LdsRow{w}, LdsRow{w + NV * kTileLanes}},
-                        fx_view(fext, ld));
-    if (gtau) {
-      sfor<0, NV>([&](auto K_) __attribute__((always_inline)) {
-        constexpr int K = decltype(K_)::value;
-        Out{gtau, ld, b}(K, w[(NV + K) * kTileLanes]);
-      });
+  if constexpr (MODE == 0 || !Team<TP>::kAlways) {
+    static_assert(!EXT || MODE >= 1, "external forces: modes 1 to 3");
+    RBD_LANE_IO(TP);
+    const uint32_t b = lane_id();
+    if (b >= batch) return;
+    const In qi{q, ld, b}, qdi{qd, ld, b}, ti{tau, ld, b}, gi{gqdd, ld, b};
+    const OutOpt<OutAlias> gqo{OutAlias{gq, ld, b}, gq != nullptr};
+    // the external-force views (nothing without EXT)
+    auto fx_view = [&](const float* p, int64_t l) __attribute__((always_inline)) {
+      if constexpr (EXT) return FextOpt{{p, l, b}};
+      else return NoFext{};
+    };
+    auto gf_view = [&](int64_t l) __attribute__((always_inline)) {
+      if constexpr (EXT) return GFOut{{gfext, l, b}};
+      else return NoGF{};
+    };
+    if constexpr (MODE == 3) {
+      // the two sweeps, the second on fresh views (its own table and input
+      // pointers and row stride): a large tree's first sweep uses every
+      // register, and values kept for the second one spill (measured: 1028 ->
+      // 400 B/lane of scratch, 126 -> 108 us for the humanoid). Each wave parks
+      // in its region of the block's dynamic LDS: [qdd rows | lam rows].
+      extern __shared__ float lds_park[];
+      constexpr int NV = TP::NV;
+      float* const w = lds_park + (threadIdx.x / kTileLanes) * (2 * NV * kTileLanes) + (threadIdx.x % kTileLanes);
+      fwd_dyn_lane<TP, 2>(tab, qi, qdi, RhsTwo<In>{ti, gi}, SinkTwo<LdsRow>{LdsRow{w}, LdsRow{w + NV * kTileLanes}},
+                          fx_view(fext, ld));
+      if (gtau) {
+        sfor<0, NV>([&](auto K_) __attribute__((always_inline)) {
+          constexpr int K = decltype(K_)::value;
+          Out{gtau, ld, b}(K, w[(NV + K) * kTileLanes]);
+        });
+      }
+      sweep_boundary();
+      const int64_t l2 = opaque(ld);
+      // (issuing this sweep's q and qd loads at its start cut the spill from 536
+      // to 24 B/lane but measured 79.2 against 77.0 us for the humanoid at 32768)
+      id_adjoint_lane<TP>(opaque_table(tab), In{opaque(q), l2, b}, In{opaque(qd), l2, b}, LdsRow::In{w},
+                          LdsRow::In{w + NV * kTileLanes}, OutOpt<OutAlias>{OutAlias{gq, l2, b}, gq != nullptr},
+                          OutOpt<OutAlias>{OutAlias{gqd, l2, b}, gqd != nullptr}, fx_view(opaque(fext), l2),
+                          gf_view(l2));
+    } else if constexpr (MODE == 2) {
+      const OutAliasP pd{{gqd, ld, b}}, pt{{gtau, ld, b}};
+      vjp_lane_parked<TP>(tab, qi, qdi, ti, gi, gqo, pd, pt, InAlias{gqd, ld, b}, InAlias{gtau, ld, b},
+                          fx_view(fext, ld), gf_view(ld));
+    } else {
+      vjp_lane<TP, MODE == 1>(tab, qi, qdi, ti, gi, gqo, OutOpt<OutAlias>{OutAlias{gqd, ld, b}, gqd != nullptr},
+                              OutOpt<OutAlias>{OutAlias{gtau, ld, b}, gtau != nullptr}, fx_view(fext, ld),
+                              gf_view(ld));
     }
-    sweep_boundary();
-    const int64_t l2 = opaque(ld);
-    // (issuing this sweep's q and qd loads at its start cut the spill from 536
-    // to 24 B/lane but measured 79.2 against 77.0 us for the humanoid at 32768)
-    id_adjoint_lane<TP>(opaque_table(tab), In{opaque(q), l2, b}, In{opaque(qd), l2, b}, LdsRow::In{w},
-                        LdsRow::In{w + NV * kTileLanes}, OutOpt<OutAlias>{OutAlias{gq, l2, b}, gq != nullptr},
-                        OutOpt<OutAlias>{OutAlias{gqd, l2, b}, gqd != nullptr}, fx_view(opaque(fext), l2),
-                        gf_view(l2));
-  } else if constexpr (MODE == 2) {
-    const OutAliasP pd{{gqd, ld, b}}, pt{{gtau, ld, b}};
-    vjp_lane_parked<TP>(tab, qi, qdi, ti, gi, gqo, pd, pt, InAlias{gqd, ld, b}, InAlias{gtau, ld, b},
-                        fx_view(fext, ld), gf_view(ld));
-  } else {
-    vjp_lane<TP, MODE == 1>(tab, qi, qdi, ti, gi, gqo, OutOpt<OutAlias>{OutAlias{gqd, ld, b}, gqd != nullptr},
-                            OutOpt<OutAlias>{OutAlias{gtau, ld, b}, gtau != nullptr}, fx_view(fext, ld),
-                            gf_view(ld));
   }
 }
 
@@ -385,55 +395,57 @@ __global__ __launch_bounds__(2 * kTileLanes) void k_fwd_dyn_vjp_split(
     const float* __restrict__ tab, int64_t batch, int64_t ld, const float* __restrict__ q,
     const float* __restrict__ qd, const float* __restrict__ tau, const float* __restrict__ gqdd, float* gq,
     float* gqd, float* gtau, const float* __restrict__ fext, float* gfext) {
-  RBD_LANE_IO(TP);
-  constexpr int NQ = TP::NQ, NV = TP::NV;
-  extern __shared__ float lds_vjp[];
-  const uint32_t lane = threadIdx.x % kTileLanes;
-  const bool solver = threadIdx.x >= kTileLanes;
-  const uint32_t b = blockIdx.x * kTileLanes + lane;
-  const bool valid = b < batch;
-  float* const qpark = lds_vjp + lane;
-  float* const lpark = lds_vjp + NV * kTileLanes + lane;
-  auto fx_view = [&](const float* p, int64_t l) __attribute__((always_inline)) {
-    if constexpr (EXT) return FextOpt{{p, l, b}};
-    else return NoFext{};
-  };
-  auto gf_view = [&](int64_t l) __attribute__((always_inline)) {
-    if constexpr (EXT) return GFOut{{gfext, l, b}};
-    else return NoGF{};
-  };
-  if (!solver) {
-    if (valid) {
-      if constexpr (EXT) {
-        fwd_dyn_lane<TP, 1>(tab, In{q, ld, b}, In{qd, ld, b}, RhsOne<In>{In{tau, ld, b}},
-                            SinkOne<LdsRow>{LdsRow{qpark}}, fx_view(fext, ld));
-      } else {
-        // every input load at entry, as in k_fwd_dyn for large trees
-        float qv[NQ], qdv[NV], tv[NV];
-        preload_inputs<NQ>(qv, In{q, ld, b});
-        preload_inputs<NV>(qdv, tv, In{qd, ld, b}, In{tau, ld, b});
-        fwd_dyn_lane<TP, 1>(tab, RegView{qv}, RegView{qdv}, RhsOne<RegView>{RegView{tv}},
-                            SinkOne<LdsRow>{LdsRow{qpark}});
+  if constexpr (!Team<TP>::kAlways) {
+    RBD_LANE_IO(TP);
+    constexpr int NQ = TP::NQ, NV = TP::NV;
+    extern __shared__ float lds_vjp[];
+    const uint32_t lane = threadIdx.x % kTileLanes;
+    const bool solver = threadIdx.x >= kTileLanes;
+    const uint32_t b = blockIdx.x * kTileLanes + lane;
+    const bool valid = b < batch;
+    float* const qpark = lds_vjp + lane;
+    float* const lpark = lds_vjp + NV * kTileLanes + lane;
+    auto fx_view = [&](const float* p, int64_t l) __attribute__((always_inline)) {
+      if constexpr (EXT) return FextOpt{{p, l, b}};
+      else return NoFext{};
+    };
+    auto gf_view = [&](int64_t l) __attribute__((always_inline)) {
+      if constexpr (EXT) return GFOut{{gfext, l, b}};
+      else return NoGF{};
+    };
+    if (!solver) {
+      if (valid) {
+        if constexpr (EXT) {
+          fwd_dyn_lane<TP, 1>(tab, In{q, ld, b}, In{qd, ld, b}, RhsOne<In>{In{tau, ld, b}},
+                              SinkOne<LdsRow>{LdsRow{qpark}}, fx_view(fext, ld));
+        } else {
+          // every input load at entry, as in k_fwd_dyn for large trees
+          float qv[NQ], qdv[NV], tv[NV];
+          preload_inputs<NQ>(qv, In{q, ld, b});
+          preload_inputs<NV>(qdv, tv, In{qd, ld, b}, In{tau, ld, b});
+          fwd_dyn_lane<TP, 1>(tab, RegView{qv}, RegView{qdv}, RhsOne<RegView>{RegView{tv}},
+                              SinkOne<LdsRow>{LdsRow{qpark}});
+        }
+      }
+    } else if (valid) {
+      fwd_dyn_lane<TP, 1, In, In, RhsOne<In>, SinkOne<LdsRow>, NoFext, false>(
+          tab, In{q, ld, b}, In{qd, ld, b}, RhsOne<In>{In{gqdd, ld, b}}, SinkOne<LdsRow>{LdsRow{lpark}});
+      if (gtau) {
+        sfor<0, NV>([&](auto K_) __attribute__((always_inline)) {
+          constexpr int K = decltype(K_)::value;
+          Out{gtau, ld, b}(K, lpark[K * kTileLanes]);
+        });
       }
     }
-  } else if (valid) {
-    fwd_dyn_lane<TP, 1, In, In, RhsOne<In>, SinkOne<LdsRow>, NoFext, false>(
-        tab, In{q, ld, b}, In{qd, ld, b}, RhsOne<In>{In{gqdd, ld, b}}, SinkOne<LdsRow>{LdsRow{lpark}});
-    if (gtau) {
-      sfor<0, NV>([&](auto K_) __attribute__((always_inline)) {
-        constexpr int K = decltype(K_)::value;
-        Out{gtau, ld, b}(K, lpark[K * kTileLanes]);
-      });
+    __syncthreads();
+    if (!solver && valid) {
+      sweep_boundary();
+      const int64_t l2 = opaque(ld);
+      id_adjoint_lane<TP>(opaque_table(tab), In{opaque(q), l2, b}, In{opaque(qd), l2, b}, LdsRow::In{qpark},
+                          LdsRow::In{lpark}, OutOpt<OutAlias>{OutAlias{gq, l2, b}, gq != nullptr},
+                          OutOpt<OutAlias>{OutAlias{gqd, l2, b}, gqd != nullptr}, fx_view(opaque(fext), l2),
+                          gf_view(l2));
     }
-  }
-  __syncthreads();
-  if (!solver && valid) {
-    sweep_boundary();
-    const int64_t l2 = opaque(ld);
-    id_adjoint_lane<TP>(opaque_table(tab), In{opaque(q), l2, b}, In{opaque(qd), l2, b}, LdsRow::In{qpark},
-                        LdsRow::In{lpark}, OutOpt<OutAlias>{OutAlias{gq, l2, b}, gq != nullptr},
-                        OutOpt<OutAlias>{OutAlias{gqd, l2, b}, gqd != nullptr}, fx_view(opaque(fext), l2),
-                        gf_view(l2));
   }
 }
 
@@ -684,46 +696,358 @@ __global__ __launch_bounds__(kBlock) void k_osc(const float* __restrict__ tab, i
                         InAlias{tau, l2, b});
 }
 
+// =================================================================== teams of waves
+// The kernels of a team (rbd_team.hpp): a block is one team, 64 instances, all
+// lanes reach every barrier (lanes past the batch redo its last instance and
+// store the same values to it).
+
+// Entry c of an input or of LDS rows: of the wave's branches from `br` (moved),
+// of the trunk from `tk`. DOF as for team_load.
+template <class TP, bool DOF, class B, class T>
+struct TeamView {
+  B br;
+  T tk;
+  RBD_DI float operator()(int c) const {
+    const int i = DOF ? TP::body_of(c) : (TP::kFree ? (c < 7 ? 0 : c - 6) : c);
+    return Team<TP>::trunk(i) ? tk(c) : br(c);
+  }
+};
+template <class TP, bool DOF, class I>
+RBD_DI TeamView<TP, DOF, I, I> team_in(const float* p, int64_t off, int64_t ld, uint32_t b) {
+  return {I{p + off, ld, b}, I{p, ld, b}};
+}
+
+// The team's external-force views: of the calling wave's branches and of the trunk.
+template <bool EXT>
+RBD_DI auto team_fext(const float* fext, int64_t ld, int shift, uint32_t b) {
+  return fext_view<EXT>(fext + 6 * shift * ld, ld, b);
+}
+// The same where the forces may be absent (null: zero).
+template <bool EXT>
+RBD_DI auto team_fext_opt(const float* fext, int64_t ld, int shift, uint32_t b) {
+  if constexpr (EXT) return FextOpt{{fext ? fext + 6 * shift * ld : nullptr, ld, b}};
+  else return NoFext{};
+}
+
+// Where a team finds the arrays of its instances: structure-of-arrays batches,
+// or one instance per row of N (the serving runtime's requests). `shift` bodies
+// further on for branches.
+template <class TP>
+struct SoaIo {
+  using I = InT<kScalarBase<TP>>;
+  using O = OutT<kScalarBase<TP>>;
+  int64_t ld;
+  template <int N>
+  RBD_DI I in(const float* p, int shift, uint32_t b) const {
+    return {p + shift * ld, ld, b};
+  }
+  template <int N>
+  RBD_DI O out(float* p, int shift, uint32_t b) const {
+    return {p + shift * ld, ld, b};
+  }
+  // an output that may be absent
+  template <int N>
+  RBD_DI OutOpt<O> opt(float* p, int shift, uint32_t b) const {
+    return {{p ? p + shift * ld : nullptr, ld, b}, p != nullptr};
+  }
+  RBD_DI SoaIo fresh() const { return {opaque(ld)}; }
+};
+struct RowIo {
+  using I = InRow;
+  using O = OutRow;
+  template <int N>
+  RBD_DI I in(const float* p, int shift, uint32_t b) const {
+    return I(p + (int64_t)b * N + shift);
+  }
+  template <int N>
+  RBD_DI O out(float* p, int shift, uint32_t b) const {
+    return O(p + (int64_t)b * N + shift);
+  }
+  template <int N>
+  RBD_DI O opt(float* p, int shift, uint32_t b) const {
+    return out<N>(p, shift, b);
+  }
+  RBD_DI RowIo fresh() const { return {}; }
+};
+// Role W's entries of an input (above: of the trunk bodies above them too; the
+// owner: of the whole trunk).
+template <class TP, int W, bool ABOVE, bool DOF, class IO, int n>
+RBD_DI void team_read(float (&x)[n], const IO& io, const float* p, const TeamLane& tl, bool owner) {
+  constexpr int N = DOF ? TP::NV : TP::NQ;
+  const auto tk = io.template in<N>(p, 0, tl.b);
+  team_load<TP, W, ABOVE, DOF>(x, io.template in<N>(p, tl.shift, tl.b), tk);
+  if constexpr (Team<TP>::may_own(W)) {
+    if (owner) team_load_trunk<TP, DOF>(x, tk);
+  }
+}
+
+// Rows of LDS of the blocks below.
+template <class TP>
+struct TeamLds {
+  using Fd = TeamRows<TP, 16, true, 1>;
+  using Fd2 = TeamRows<TP, 16, true, 2>;
+  using Id = TeamRows<TP, 6, false, 0>;
+  template <bool EXT>
+  using Adj = TeamRows<TP, EXT ? 30 : 18, false, 0>;
+  static constexpr int kFd = Fd::total() + TrunkRows<TP>::total();
+  static constexpr int kId = Id::total();
+  // the solve's rows, which afterwards hold [qdd | lam | what the adjoint hands to the trunk], then x
+  template <bool EXT>
+  static constexpr int vjp_rows() {
+    const int adj = 2 * TP::NV + Adj<EXT>::total();
+    return Fd2::total() > adj ? Fd2::total() : adj;
+  }
+  template <bool EXT>
+  static constexpr int vjp() {
+    return vjp_rows<EXT>() + 2 * TrunkRows<TP>::total();
+  }
+};
+
+// Forward dynamics of the calling wave's 64 instances. Bound: the longest
+// branch's and the trunk's chain of vector instructions while the batch leaves
+// SIMDs idle (humanoid, one lane per instance before, a team now: 33.8 -> 13.9
+// us at batch 64, 34.9 -> 14.6 at 16384), their issue rate after that (37.2 ->
+// 20.4 at 32768, 39.5 -> 35.1 at 65536, 160 -> 121 at 262144). The factor's rows
+// stay in their wave's registers between the phases: 198, so that two blocks fit
+// a compute unit; the LDS rows (60 KB) allow two as well.
+template <class TP, bool EXT, int W, class IO>
+RBD_DI void team_fwd_dyn(const TeamLane& tl, const float* __restrict__ tab, const IO& io, float* lds_rows,
+                         const float* q, const float* qd, const float* tau, const float* fext, int64_t ld, float* qdd) {
+  using TM = Team<TP>;
+  using ROWS = typename TeamLds<TP>::Fd;
+  constexpr int NQ = TP::NQ, NV = TP::NV;
+  const LdsCol lds{lds_rows + tl.lane};
+  const bool owner = TM::may_own(W) && tl.wave == TM::kOwner;
+  float qv[NQ], qdv[NV], tv[NV];
+  team_read<TP, W, true, false>(qv, io, q, tl, owner);
+  team_read<TP, W, true, true>(qdv, io, qd, tl, owner);
+  team_read<TP, W, false, true>(tv, io, tau, tl, owner);
+  Ltl<TP, 1> F, Ft;
+  const RhsOne<RegView> rhs{RegView{tv}};
+  const auto out = io.template out<NV>(qdd, tl.shift, tl.b), out_t = io.template out<NV>(qdd, 0, tl.b);
+  using O = typename IO::O;
+  team_fd<TP, W, 1, ROWS>(tl, owner, tab, RegView{qv}, RegView{qdv}, rhs, rhs, team_fext<EXT>(fext, ld, tl.shift, tl.b),
+                          team_fext<EXT>(fext, ld, 0, tl.b), lds, lds.at(ROWS::total()), F, Ft, SinkOne<O>{out},
+                          SinkOne<O>{out_t});
+}
+
+template <class TP, bool EXT>
+__global__ __launch_bounds__(Team<TP>::kThreads, 2) void k_fwd_dyn_team(
+    const float* __restrict__ tab, int64_t batch, int64_t ld, const float* __restrict__ q,
+    const float* __restrict__ qd, const float* __restrict__ tau, const float* __restrict__ fext,
+    float* __restrict__ qdd) {
+  if constexpr (Team<TP>::kOn) {
+    __shared__ float lds_team[TeamLds<TP>::kFd * kTileLanes];
+    team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
+      team_fwd_dyn<TP, EXT, decltype(W_)::value>(tl, tab, SoaIo<TP>{ld}, lds_team, q, qd, tau, fext, ld, qdd);
+    });
+  }
+}
+
+// Inverse dynamics: the same without the factor (humanoid 17.5 -> 8.6 us at
+// batch 20001, 22.6 -> 14.1 at 65536, 57 -> 47 at 262144, where the 139 MB it
+// reads and writes take 27).
+template <class TP, bool HAS_QDD, bool EXT, int W, class IO>
+RBD_DI void team_rnea(const TeamLane& tl, const float* __restrict__ tab, const IO& io, float* lds_rows, const float* q,
+                      const float* qd, const float* qdd, const float* fext, int64_t ld, float* tau) {
+  using TM = Team<TP>;
+  using ROWS = typename TeamLds<TP>::Id;
+  constexpr int NQ = TP::NQ, NV = TP::NV;
+  const LdsCol lds{lds_rows + tl.lane};
+  const bool owner = TM::may_own(W) && tl.wave == TM::kOwner;
+  float qv[NQ], qdv[NV], av[NV];
+  team_read<TP, W, true, false>(qv, io, q, tl, owner);
+  team_read<TP, W, true, true>(qdv, io, qd, tl, owner);
+  if constexpr (HAS_QDD) team_read<TP, W, true, true>(av, io, qdd, tl, owner);
+  const RegView qr{qv}, qdr{qdv}, ar{av};
+  TeamFd<TP, EXT> s;
+  team_id_up<TP, W, ROWS, HAS_QDD>(tab, tab + tl.shift * kBodyStride, qr, qdr, ar,
+                                   team_fext<EXT>(fext, ld, tl.shift, tl.b), s, lds.at(team_base<TP, ROWS, W>(tl)),
+                                   io.template out<NV>(tau, tl.shift, tl.b));
+  if constexpr (TM::may_own(W)) {
+    if (owner) team_id_trunk_down<TP, W, HAS_QDD>(tab, qr, qdr, ar, team_fext<EXT>(fext, ld, 0, tl.b), s);
+  }
+  __syncthreads();
+  if constexpr (TM::may_own(W)) {
+    if (owner) team_id_trunk<TP, ROWS>(tab, s, lds, io.template out<NV>(tau, 0, tl.b));
+  }
+}
+
+template <class TP, bool HAS_QDD, bool EXT>
+__global__ __launch_bounds__(Team<TP>::kThreads) void k_rnea_team(
+    const float* __restrict__ tab, int64_t batch, int64_t ld, const float* __restrict__ q,
+    const float* __restrict__ qd, const float* __restrict__ qdd, const float* __restrict__ fext,
+    float* __restrict__ tau) {
+  if constexpr (Team<TP>::kOn) {
+    __shared__ float lds_team[TeamLds<TP>::kId * kTileLanes];
+    team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
+      team_rnea<TP, HAS_QDD, EXT, decltype(W_)::value>(tl, tab, SoaIo<TP>{ld}, lds_team, q, qd, qdd, fext, ld, tau);
+    });
+  }
+}
+
+// A wave's view of an output that may be absent, its branches `off` further on.
+RBD_DI OutOpt<Out> team_out(float* p, int64_t off, int64_t ld, uint32_t b) {
+  return {Out{p ? p + off : nullptr, ld, b}, p != nullptr};
+}
+template <bool EXT>
+RBD_DI auto team_gf(float* p, int64_t ld, int shift, uint32_t b) {
+  if constexpr (EXT) return GFOut{{p ? p + 6 * shift * ld : nullptr, ld, b}};
+  else return NoGF{};
+}
+
+// Forward dynamics' adjoint: the solve with both right-hand sides, after which
+// the waves park qdd and lam in LDS (the trunk's are there already), then the
+// adjoint sweep, branches first, on fresh views and loading where it uses (held
+// in registers, its inputs and qdd and lam spilled 220 B/lane at two waves per
+// SIMD). Humanoid: 65.3 -> 25.8 us at batch 64, 74.4 -> 37.3 at 32768, 86.9 ->
+// 67.6 at 65536, 169 -> 125 at 131072.
+template <class TP, bool EXT, int W, class IO>
+RBD_DI void team_fwd_dyn_vjp(const TeamLane& tl, const float* __restrict__ tab, const IO& io, float* lds_rows,
+                             const float* q, const float* qd, const float* tau, const float* gqdd, float* gq,
+                             float* gqd, float* gtau, const float* fext, float* gfext, int64_t ld) {
+  using TM = Team<TP>;
+  using ROWS = typename TeamLds<TP>::Fd2;
+  using AROWS = typename TeamLds<TP>::template Adj<EXT>;
+  constexpr int NQ = TP::NQ, NV = TP::NV, T = TrunkRows<TP>::total();
+  const LdsCol lds{lds_rows + tl.lane}, xrow = lds.at(TeamLds<TP>::template vjp_rows<EXT>()), park = lds.at(tl.shift);
+  const uint32_t b = tl.b;
+  const bool owner = TM::may_own(W) && tl.wave == TM::kOwner;
+  {
+    float qv[NQ], qdv[NV], tv[NV], gv[NV];
+    team_read<TP, W, true, false>(qv, io, q, tl, owner);
+    team_read<TP, W, true, true>(qdv, io, qd, tl, owner);
+    team_read<TP, W, false, true>(tv, io, tau, tl, owner);
+    team_read<TP, W, false, true>(gv, io, gqdd, tl, owner);
+    Ltl<TP, 2> F, Ft;
+    const RhsTwo<RegView> rhs{RegView{tv}, RegView{gv}};
+    const auto gt = io.template opt<NV>(gtau, tl.shift, b), gt_t = io.template opt<NV>(gtau, 0, b);
+    team_fd<TP, W, 2, ROWS>(
+        tl, owner, tab, RegView{qv}, RegView{qdv}, rhs, rhs, team_fext_opt<EXT>(fext, ld, tl.shift, b),
+        team_fext_opt<EXT>(fext, ld, 0, b), lds, xrow, F, Ft,
+        [&](int r, int k, float x) __attribute__((always_inline)) {
+          park.put(r * NV + k, x);
+          if (r == 1) gt(k, x);
+        },
+        [&](int r, int k, float x) __attribute__((always_inline)) {
+          if (r == 1) gt_t(k, x);
+        });
+  }
+  sweep_boundary();
+  const IO io2 = io.fresh();
+  const int64_t l2 = EXT ? opaque(ld) : ld;
+  const float* const t2 = opaque_table(tab);
+  const float* const q2 = opaque(q);
+  const float* const qd2 = opaque(qd);
+  using I = typename IO::I;
+  const TeamView<TP, false, I, I> qr{io2.template in<NQ>(q2, tl.shift, b), io2.template in<NQ>(q2, 0, b)};
+  const TeamView<TP, true, I, I> qdr{io2.template in<NV>(qd2, tl.shift, b), io2.template in<NV>(qd2, 0, b)};
+  const auto solved = [&](int r) __attribute__((always_inline)) {
+    auto br = [=](int k) __attribute__((always_inline)) { return park.get(r * NV + k); };
+    auto tk = [=](int k) __attribute__((always_inline)) { return xrow.get(r * T + TrunkRows<TP>::row(k)); };
+    return TeamView<TP, true, decltype(br), decltype(tk)>{br, tk};
+  };
+  const auto xr = solved(0), lr = solved(1);
+  const LdsCol adj = lds.at(2 * NV);
+  AdjState<TP, EXT, EXT> s;
+  team_adj_up<TP, W, AROWS>(t2, t2 + tl.shift * kBodyStride, s, qr, qdr, xr, lr,
+                            io2.template opt<NQ>(gq, tl.shift, b), io2.template opt<NV>(gqd, tl.shift, b),
+                            team_fext_opt<EXT>(fext, l2, tl.shift, b), team_gf<EXT>(gfext, l2, tl.shift, b), NoGF{},
+                            adj.at(team_base<TP, AROWS, W>(tl)));
+  if constexpr (TM::may_own(W)) {
+    if (owner)
+      team_adj_trunk_down<TP, W>(t2, s, qr, qdr, xr, lr, team_fext_opt<EXT>(fext, l2, 0, b),
+                                 team_gf<EXT>(gfext, l2, 0, b));
+  }
+  __syncthreads();
+  if constexpr (TM::may_own(W)) {
+    if (owner)
+      team_adj_trunk<TP, AROWS>(t2, s, qr, qdr, io2.template opt<NQ>(gq, 0, b), io2.template opt<NV>(gqd, 0, b),
+                                NoGF{}, adj);
+  }
+}
+
+template <class TP, bool EXT>
+__global__ __launch_bounds__(Team<TP>::kThreads, EXT ? 1 : 2) void k_fwd_dyn_vjp_team(
+    const float* __restrict__ tab, int64_t batch, int64_t ld, const float* __restrict__ q,
+    const float* __restrict__ qd, const float* __restrict__ tau, const float* __restrict__ gqdd, float* gq, float* gqd,
+    float* gtau, const float* __restrict__ fext, float* gfext) {
+  if constexpr (Team<TP>::kOn) {
+    __shared__ float lds_team[TeamLds<TP>::template vjp<EXT>() * kTileLanes];
+    team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
+      team_fwd_dyn_vjp<TP, EXT, decltype(W_)::value>(tl, tab, SoaIo<TP>{ld}, lds_team, q, qd, tau, gqdd, gq, gqd,
+                                                     gtau, fext, gfext, ld);
+    });
+  }
+}
+
 // ---- packed launch for the serving runtime. One launch serves many requests
 // of one (model, operation): the work is cut into tiles of 64 instances (one
 // wave), every tile belongs to one request, and a fixed grid of waves strides
 // over the tiles, so the same launch (and a graph that captured it) serves any
-// number of requests. Request arrays are instance-major, exactly as the client
+// number of requests. A tree that is shared out over a team gives every tile to
+// a block, any other to a wave. Request arrays are instance-major, exactly as the client
 // handed them over: coordinate c of instance i at p[i * n + c].
 template <class TP, int OP>
-__global__ __launch_bounds__(kBlock) void k_packed(const float* __restrict__ tab,
-                                                   const uint8_t* __restrict__ table) {
+__global__ __launch_bounds__(Team<TP>::kOn ? Team<TP>::kThreads : kBlock, Team<TP>::kOn ? 2 : 1) void k_packed(
+    const float* __restrict__ tab, const uint8_t* __restrict__ table) {
   const PackedHdr* hdr = reinterpret_cast<const PackedHdr*>(table);
   const int32_t* tile_req = reinterpret_cast<const int32_t*>(table + sizeof(PackedHdr));
   const PackedReq* reqs = reinterpret_cast<const PackedReq*>(table + hdr->req_offset);
   const int n_tiles = hdr->n_tiles;
-  const int lane = threadIdx.x & (kTileLanes - 1);
-  const int wave = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kTileLanes);
-  const int n_waves = (int)(((int64_t)gridDim.x * blockDim.x) / kTileLanes);
-  constexpr int NQ = TP::NQ, NV = TP::NV;
-  for (int t = wave; t < n_tiles; t += n_waves) {
-    const int r = __builtin_amdgcn_readfirstlane(tile_req[t]);
-    const PackedReq& R = reqs[r];
-    const int64_t i = (int64_t)(t - R.first_tile) * kTileLanes + lane;
-    if (i >= R.batch) continue;
-    const InRow q{R.in[0] + i * NQ}, qd{R.in[1] + i * NV}, x2{R.in[2] + i * NV};
-    if constexpr (OP == kOpFwdDyn) {
-      fwd_dyn_lane<TP, 1>(tab, q, qd, RhsOne<InRow>{x2}, SinkOne<OutRow>{OutRow{R.out[0] + i * NV}});
-    } else if constexpr (OP == kOpRnea) {
-      rnea_lane<TP, true>(tab, q, qd, x2, OutRow{R.out[0] + i * NV});
-    } else {
-      float* gqd = R.out[1] + i * NV;
-      float* gtau = R.out[2] + i * NV;
-      if constexpr (NV > 16) {
-        // the two sweeps on fresh views, as in k_fwd_dyn_vjp
-        fwd_dyn_lane<TP, 2>(tab, q, qd, RhsTwo<InRow>{x2, InRow{R.in[3] + i * NV}},
-                            SinkTwo<RowAlias>{RowAlias{gqd}, RowAlias{gtau}});
-        sweep_boundary();
-        id_adjoint_lane<TP>(opaque_table(tab), InRow{opaque(R.in[0]) + i * NQ}, InRow{opaque(R.in[1]) + i * NV},
-                            RowAlias::In{gqd}, RowAlias::In{gtau}, OutRow{R.out[0] + i * NQ}, RowAlias{gqd});
+  if constexpr (Team<TP>::kOn) {
+    // a team per tile, the same code as the direct calls
+    using L = TeamLds<TP>;
+    constexpr int kRows = OP == kOpFwdDyn ? L::kFd : (OP == kOpRnea ? L::kId : L::template vjp<false>());
+    __shared__ float lds_team[kRows * kTileLanes];
+    for (int t = blockIdx.x; t < n_tiles; t += gridDim.x) {
+      const PackedReq& R = reqs[__builtin_amdgcn_readfirstlane(tile_req[t])];
+      const float* const q = R.in[0];
+      const float* const qd = R.in[1];
+      const float* const x2 = R.in[2];
+      const RowIo io{};
+      team_roles<TP>((t - R.first_tile) * kTileLanes, R.batch,
+                     [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
+        constexpr int W = decltype(W_)::value;
+        if constexpr (OP == kOpFwdDyn)
+          team_fwd_dyn<TP, false, W>(tl, tab, io, lds_team, q, qd, x2, nullptr, 0, R.out[0]);
+        else if constexpr (OP == kOpRnea)
+          team_rnea<TP, true, false, W>(tl, tab, io, lds_team, q, qd, x2, nullptr, 0, R.out[0]);
+        else
+          team_fwd_dyn_vjp<TP, false, W>(tl, tab, io, lds_team, q, qd, x2, R.in[3], R.out[0], R.out[1], R.out[2],
+                                         nullptr, nullptr, 0);
+      });
+      __syncthreads();  // the next tile reuses the rows
+    }
+  } else {
+    const int lane = threadIdx.x & (kTileLanes - 1);
+    const int wave = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kTileLanes);
+    const int n_waves = (int)(((int64_t)gridDim.x * blockDim.x) / kTileLanes);
+    constexpr int NQ = TP::NQ, NV = TP::NV;
+    for (int t = wave; t < n_tiles; t += n_waves) {
+      const int r = __builtin_amdgcn_readfirstlane(tile_req[t]);
+      const PackedReq& R = reqs[r];
+      const int64_t i = (int64_t)(t - R.first_tile) * kTileLanes + lane;
+      if (i >= R.batch) continue;
+      const InRow q{R.in[0] + i * NQ}, qd{R.in[1] + i * NV}, x2{R.in[2] + i * NV};
+      if constexpr (OP == kOpFwdDyn) {
+        fwd_dyn_lane<TP, 1>(tab, q, qd, RhsOne<InRow>{x2}, SinkOne<OutRow>{OutRow{R.out[0] + i * NV}});
+      } else if constexpr (OP == kOpRnea) {
+        rnea_lane<TP, true>(tab, q, qd, x2, OutRow{R.out[0] + i * NV});
       } else {
-        vjp_lane_parked<TP>(tab, q, qd, x2, InRow{R.in[3] + i * NV}, OutRow{R.out[0] + i * NQ}, RowAlias{gqd},
-                            RowAlias{gtau}, RowAlias::In{gqd}, RowAlias::In{gtau});
+        float* gqd = R.out[1] + i * NV;
+        float* gtau = R.out[2] + i * NV;
+        if constexpr (NV > 16) {
+          // the two sweeps on fresh views, as in k_fwd_dyn_vjp
+          fwd_dyn_lane<TP, 2>(tab, q, qd, RhsTwo<InRow>{x2, InRow{R.in[3] + i * NV}},
+                              SinkTwo<RowAlias>{RowAlias{gqd}, RowAlias{gtau}});
+          sweep_boundary();
+          id_adjoint_lane<TP>(opaque_table(tab), InRow{opaque(R.in[0]) + i * NQ}, InRow{opaque(R.in[1]) + i * NV},
+                              RowAlias::In{gqd}, RowAlias::In{gtau}, OutRow{R.out[0] + i * NQ}, RowAlias{gqd});
+        } else {
+          vjp_lane_parked<TP>(tab, q, qd, x2, InRow{R.in[3] + i * NV}, OutRow{R.out[0] + i * NQ}, RowAlias{gqd},
+                              RowAlias{gtau}, RowAlias::In{gqd}, RowAlias::In{gtau});
+        }
       }
     }
   }

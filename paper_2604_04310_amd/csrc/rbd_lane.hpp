@@ -38,6 +38,8 @@ namespace rbd {
 // =================================================================== topology
 // A kinematic tree as a type: FREE says body 0 is a floating base, P... are
 // the parents (depth-first order, parent[i] < i, -1 = world).
+template <class TP>
+struct TreeTables;
 template <bool FREE, int... P>
 struct Tree {
   static constexpr int N = sizeof...(P);
@@ -54,54 +56,61 @@ struct Tree {
   static constexpr int nvb(int i) { return free_body(i) ? 6 : 1; }
   static constexpr int vofs(int i) { return (FREE && i > 0) ? i + 5 : i; }
   static constexpr int qofs(int i) { return (FREE && i > 0) ? i + 6 : i; }
+  // What the queries below look up (evaluated once; the loops over bodies and
+  // DoFs ask tens of thousands of times): the last body of a subtree, a DoF's
+  // depth, parent and last descendant, and where its row of L starts.
+  struct Tab {
+    int last[N], ddepth[NV], dpar[NV], dlast[NV], loff[NV + 1];
+  };
+  static constexpr Tab make_tab() {
+    Tab t = {};
+    for (int i = N - 1; i >= 0; --i) {
+      if (t.last[i] < i) t.last[i] = i;
+      const int p = par_.v[i];
+      if (p >= 0 && t.last[p] < t.last[i]) t.last[p] = t.last[i];
+    }
+    for (int k = 0; k < NV; ++k) {
+      const int i = body_of(k);
+      if (FREE && k < 6) t.dpar[k] = k - 1;
+      else t.dpar[k] = par_.v[i] < 0 ? -1 : vofs(par_.v[i]) + nvb(par_.v[i]) - 1;
+      t.ddepth[k] = t.dpar[k] < 0 ? 0 : t.ddepth[t.dpar[k]] + 1;
+      t.dlast[k] = t.last[i] == 0 ? vofs(0) + nvb(0) - 1 : vofs(t.last[i]);
+      t.loff[k + 1] = t.loff[k] + t.ddepth[k];
+    }
+    return t;
+  }
   // j is i or an ancestor of i
-  static constexpr bool is_anc(int j, int i) {
-    for (int k = i; k >= 0; k = parent(k))
-      if (k == j) return true;
-    return false;
-  }
+  static constexpr bool is_anc(int j, int i) { return j <= i && i <= last(j); }
   // last body of the subtree rooted at i (depth-first numbering)
-  static constexpr int last(int i) {
-    int m = i;
-    for (int k = i + 1; k < N; ++k)
-      if (is_anc(i, k)) m = k;
-    return m;
-  }
+  static constexpr int last(int i) { return TreeTables<Tree>::v.last[i]; }
   static constexpr bool depth_first() {
     for (int i = 0; i < N; ++i) {
       if (parent(i) >= i || parent(i) < -1) return false;
-      for (int k = i + 1; k <= last(i); ++k)
-        if (!is_anc(i, k)) return false;
+      for (int k = i + 1; k <= last(i); ++k) {
+        int j = k;
+        while (j > i) j = parent(j);
+        if (j != i) return false;
+      }
     }
     return true;
   }
   // ---- DoF-level tree (a free base is a chain of 6 DoFs)
   static constexpr int body_of(int k) { return FREE ? (k < 6 ? 0 : k - 5) : k; }
-  static constexpr int dpar(int k) {
-    if (FREE && k < 6) return k - 1;
-    const int p = parent(body_of(k));
-    return p < 0 ? -1 : vofs(p) + nvb(p) - 1;
-  }
-  static constexpr int ddepth(int k) {
-    int d = 0;
-    for (int j = dpar(k); j >= 0; j = dpar(j)) ++d;
-    return d;
-  }
+  static constexpr int dpar(int k) { return TreeTables<Tree>::v.dpar[k]; }
+  static constexpr int ddepth(int k) { return TreeTables<Tree>::v.ddepth[k]; }
   // j is a strict ancestor DoF of k
-  static constexpr bool is_danc(int j, int k) {
-    for (int t = dpar(k); t >= 0; t = dpar(t))
-      if (t == j) return true;
-    return false;
-  }
-  static constexpr int loff(int k) {
-    int o = 0;
-    for (int t = 0; t < k; ++t) o += ddepth(t);
-    return o;
-  }
+  static constexpr bool is_danc(int j, int k) { return j < k && k <= TreeTables<Tree>::v.dlast[j]; }
+  // last descendant DoF of k (its descendants are k + 1 .. dlast(k))
+  static constexpr int dlast(int k) { return TreeTables<Tree>::v.dlast[k]; }
+  static constexpr int loff(int k) { return TreeTables<Tree>::v.loff[k]; }
   static constexpr int nnz() { return loff(NV); }  // off-diagonal entries of L
   // position of L[k][j] (j a strict ancestor of k) in the packed factor
   static constexpr int lidx(int k, int j) { return loff(k) + ddepth(k) - 1 - ddepth(j); }
   static_assert(N >= 1 && N <= 64, "1..64 bodies");
+};
+template <class TP>
+struct TreeTables {
+  static constexpr typename TP::Tab v = TP::make_tab();
 };
 
 template <int I>
@@ -475,103 +484,104 @@ RBD_DI Frc fext_body(const FX& fx, const M3& Rw, V3 pw) {
 }
 
 // =================================================================== FK
+// World pose of body I's joint-aligned frame from its parent's, as FK and the
+// Jacobians use it.
+template <class TP, int I, class QI>
+RBD_DI void fk_pose(const float* __restrict__ t, const QI& q, M3* Rw, V3* pw) {
+  constexpr int P = TP::parent(I);
+  if constexpr (TP::free_body(I)) {
+    Rw[I] = quat_rot(q(3), q(4), q(5), q(6));
+    pw[I] = {q(0), q(1), q(2)};
+  } else {
+    const M3 R = joint_rot<I>(t, q(cidx<TP::qofs(I)>));
+    const V3 r = load_r<I>(t);
+    if constexpr (P < 0) {
+      Rw[I] = R;
+      pw[I] = r;
+    } else {
+      Rw[I] = mulMM(Rw[P], R);
+      pw[I] = pw[P] + mul(Rw[P], r);
+    }
+  }
+}
+// Its pose in the user's body axes, Rw C^T, as rows 12 I .. 12 I + 11.
+template <class TP, int I, class TO>
+RBD_DI void fk_write(const float* __restrict__ t, const M3* Rw, const V3* pw, const TO& T) {
+  const float* C = t + I * kBodyStride + kOffC;
+  M3 Cm;
+#pragma unroll
+  for (int e = 0; e < 9; ++e) Cm.a[e] = C[e];
+  const M3 Ro = cidx<TP::free_body(I) ? 1 : 0> ? Rw[I] : mulMMT(Rw[I], Cm);
+#pragma unroll
+  for (int r = 0; r < 3; ++r) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) T(12 * I + 4 * r + c, Ro.a[3 * r + c]);
+    T(12 * I + 4 * r + 3, r == 0 ? pw[I].x : (r == 1 ? pw[I].y : pw[I].z));
+  }
+}
 // World pose of every body in the user's body axes: [R | p] row-major.
 template <class TP, class QI, class TO>
 RBD_DI void fk_lane(const float* __restrict__ t, const QI& q, const TO& T) {
-  constexpr int N = TP::N;
-  M3 Rw[N];
-  V3 pw[N];
-  sfor<0, N>([&](auto I_) __attribute__((always_inline)) {
+  M3 Rw[TP::N];
+  V3 pw[TP::N];
+  sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
     constexpr int I = decltype(I_)::value;
-    constexpr int P = TP::parent(I);
-    if constexpr (TP::free_body(I)) {
-      Rw[I] = quat_rot(q(3), q(4), q(5), q(6));
-      pw[I] = {q(0), q(1), q(2)};
-    } else {
-      const M3 R = joint_rot<I>(t, q(cidx<TP::qofs(I)>));
-      const V3 r = load_r<I>(t);
-      if constexpr (P < 0) {
-        Rw[I] = R;
-        pw[I] = r;
-      } else {
-        Rw[I] = mulMM(Rw[P], R);
-        pw[I] = pw[P] + mul(Rw[P], r);
-      }
-    }
-    // user body axes: Rw C^T
-    const float* C = t + I * kBodyStride + kOffC;
-    M3 Cm;
-#pragma unroll
-    for (int e = 0; e < 9; ++e) Cm.a[e] = C[e];
-    const M3 Ro = cidx<TP::free_body(I) ? 1 : 0> ? Rw[I] : mulMMT(Rw[I], Cm);
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c) T(12 * I + 4 * r + c, Ro.a[3 * r + c]);
-      T(12 * I + 4 * r + 3, r == 0 ? pw[I].x : (r == 1 ? pw[I].y : pw[I].z));
-    }
+    fk_pose<TP, I>(t, q, Rw, pw);
+    fk_write<TP, I>(t, Rw, pw, T);
   });
 }
 
 // =================================================================== Jacobian
+// The Jacobians of the requested frames of body K.
+template <class TP, int K>
+RBD_DI void jac_frames(const M3* Rw, const V3* pw, const JacSlots& js, float* __restrict__ J, int64_t ld,
+                       uint32_t lane) {
+  constexpr int N = TP::N, NV = TP::NV;
+  const int beg = js.beg[K], end = js.beg[K + 1];
+  for (int s = beg; s < end; ++s) {
+    float* __restrict__ Jf = J + (int64_t)js.slot[s] * 6 * NV * ld;
+    auto put = [&](int r, int c, float v) __attribute__((always_inline)) {
+      __builtin_nontemporal_store(v, lane_ptr(Jf + (int64_t)(r * NV + c) * ld, lane));
+    };
+    sfor<0, N>([&](auto A_) __attribute__((always_inline)) {
+      constexpr int A = decltype(A_)::value;
+      constexpr int c0 = TP::vofs(A);
+      if constexpr (TP::is_anc(A, K)) {
+        const V3 d = pw[K] - pw[A];
+        if constexpr (TP::free_body(A)) {
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            const V3 col = {Rw[A].a[c], Rw[A].a[3 + c], Rw[A].a[6 + c]};
+            const V3 lin = cross(col, d);
+            put(0, c0 + c, col.x); put(1, c0 + c, col.y); put(2, c0 + c, col.z);
+            put(3, c0 + c, 0.0f); put(4, c0 + c, 0.0f); put(5, c0 + c, 0.0f);
+            put(0, c0 + 3 + c, lin.x); put(1, c0 + 3 + c, lin.y); put(2, c0 + 3 + c, lin.z);
+            put(3, c0 + 3 + c, col.x); put(4, c0 + 3 + c, col.y); put(5, c0 + 3 + c, col.z);
+          }
+        } else {
+          const V3 z = {Rw[A].a[2], Rw[A].a[5], Rw[A].a[8]};
+          const V3 lin = cross(z, d);
+          put(0, c0, lin.x); put(1, c0, lin.y); put(2, c0, lin.z);
+          put(3, c0, z.x); put(4, c0, z.y); put(5, c0, z.z);
+        }
+      } else {
+#pragma unroll
+        for (int c = 0; c < cidx<TP::nvb(A)>; ++c)
+#pragma unroll
+          for (int r = 0; r < 6; ++r) put(r, c0 + c, 0.0f);
+      }
+    });
+  }
+}
 template <class TP, class QI>
 RBD_DI void jac_lane(const float* __restrict__ t, const QI& q, const JacSlots& js, float* __restrict__ J, int64_t ld,
                      uint32_t lane) {
-  constexpr int N = TP::N, NV = TP::NV;
-  M3 Rw[N];
-  V3 pw[N];
-  sfor<0, N>([&](auto K_) __attribute__((always_inline)) {
+  M3 Rw[TP::N];
+  V3 pw[TP::N];
+  sfor<0, TP::N>([&](auto K_) __attribute__((always_inline)) {
     constexpr int K = decltype(K_)::value;
-    constexpr int P = TP::parent(K);
-    if constexpr (TP::free_body(K)) {
-      Rw[K] = quat_rot(q(3), q(4), q(5), q(6));
-      pw[K] = {q(0), q(1), q(2)};
-    } else {
-      const M3 R = joint_rot<K>(t, q(cidx<TP::qofs(K)>));
-      const V3 r = load_r<K>(t);
-      if constexpr (P < 0) {
-        Rw[K] = R;
-        pw[K] = r;
-      } else {
-        Rw[K] = mulMM(Rw[P], R);
-        pw[K] = pw[P] + mul(Rw[P], r);
-      }
-    }
-    const int beg = js.beg[K], end = js.beg[K + 1];
-    for (int s = beg; s < end; ++s) {
-      float* __restrict__ Jf = J + (int64_t)js.slot[s] * 6 * NV * ld;
-      auto put = [&](int r, int c, float v) __attribute__((always_inline)) {
-        __builtin_nontemporal_store(v, lane_ptr(Jf + (int64_t)(r * NV + c) * ld, lane));
-      };
-      sfor<0, N>([&](auto A_) __attribute__((always_inline)) {
-        constexpr int A = decltype(A_)::value;
-        constexpr int c0 = TP::vofs(A);
-        if constexpr (TP::is_anc(A, K)) {
-          const V3 d = pw[K] - pw[A];
-          if constexpr (TP::free_body(A)) {
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-              const V3 col = {Rw[A].a[c], Rw[A].a[3 + c], Rw[A].a[6 + c]};
-              const V3 lin = cross(col, d);
-              put(0, c0 + c, col.x); put(1, c0 + c, col.y); put(2, c0 + c, col.z);
-              put(3, c0 + c, 0.0f); put(4, c0 + c, 0.0f); put(5, c0 + c, 0.0f);
-              put(0, c0 + 3 + c, lin.x); put(1, c0 + 3 + c, lin.y); put(2, c0 + 3 + c, lin.z);
-              put(3, c0 + 3 + c, col.x); put(4, c0 + 3 + c, col.y); put(5, c0 + 3 + c, col.z);
-            }
-          } else {
-            const V3 z = {Rw[A].a[2], Rw[A].a[5], Rw[A].a[8]};
-            const V3 lin = cross(z, d);
-            put(0, c0, lin.x); put(1, c0, lin.y); put(2, c0, lin.z);
-            put(3, c0, z.x); put(4, c0, z.y); put(5, c0, z.z);
-          }
-        } else {
-#pragma unroll
-          for (int c = 0; c < cidx<TP::nvb(A)>; ++c)
-#pragma unroll
-            for (int r = 0; r < 6; ++r) put(r, c0 + c, 0.0f);
-        }
-      });
-    }
+    fk_pose<TP, K>(t, q, Rw, pw);
+    jac_frames<TP, K>(Rw, pw, js, J, ld, lane);
   });
 }
 
@@ -667,6 +677,40 @@ RBD_DI float base_block(const Inr& I, int r, int c) {
 }
 
 // =================================================================== CRBA
+// The rows and columns of M of body J against itself and its ancestors; put(r,
+// c, v) writes an entry.
+template <class TP, int J, class PUT>
+RBD_DI void crba_write(const float* __restrict__ t, const M3* R, const Inr& Ic, const PUT& put) {
+  if constexpr (TP::free_body(J)) {
+#pragma unroll
+    for (int r = 0; r < 6; ++r)
+#pragma unroll
+      for (int c = 0; c < 6; ++c) put(r, c, base_block(Ic, r, c));
+  } else {
+    constexpr int k = TP::vofs(J);
+    put(k, k, Ic.zz);
+    auto emit = [&](auto A_, const Frc& F) __attribute__((always_inline)) {
+      constexpr int A = decltype(A_)::value;
+      if constexpr (TP::free_body(A)) {
+        const float e[6] = {F.f.x, F.f.y, F.f.z, F.n.x, F.n.y, F.n.z};
+#pragma unroll
+        for (int c = 0; c < 6; ++c) { put(k, c, e[c]); put(c, k, e[c]); }
+      } else {
+        put(k, cidx<TP::vofs(A)>, F.n.z);
+        put(cidx<TP::vofs(A)>, k, F.n.z);
+      }
+    };
+    walk_up<TP, J>(t, R, inr_col_z(Ic), emit);
+  }
+}
+// Row K's entries for DoFs that are neither its ancestors nor its descendants.
+template <class TP, int K, class PUT>
+RBD_DI void crba_zeros(const PUT& put) {
+  sfor<0, TP::NV>([&](auto L_) __attribute__((always_inline)) {
+    constexpr int L = decltype(L_)::value;
+    if constexpr (L != K && !TP::is_danc(L, K) && !TP::is_danc(K, L)) put(K, L, 0.0f);
+  });
+}
 template <class TP, class QI>
 RBD_DI void crba_lane(const float* __restrict__ t, const QI& q, float* __restrict__ Mp, int64_t ld, uint32_t lane) {
   constexpr int N = TP::N, NV = TP::NV;
@@ -679,28 +723,8 @@ RBD_DI void crba_lane(const float* __restrict__ t, const QI& q, float* __restric
   auto backward = [&](auto J_) __attribute__((always_inline)) {
     constexpr int J = decltype(J_)::value;
     constexpr int P = TP::parent(J);
-    if constexpr (TP::free_body(J)) {
-#pragma unroll
-      for (int r = 0; r < 6; ++r)
-#pragma unroll
-        for (int c = 0; c < 6; ++c) put(r, c, base_block(Ic[J], r, c));
-    } else {
-      constexpr int k = TP::vofs(J);
-      put(k, k, Ic[J].zz);
-      auto emit = [&](auto A_, const Frc& F) __attribute__((always_inline)) {
-        constexpr int A = decltype(A_)::value;
-        if constexpr (TP::free_body(A)) {
-          const float e[6] = {F.f.x, F.f.y, F.f.z, F.n.x, F.n.y, F.n.z};
-#pragma unroll
-          for (int c = 0; c < 6; ++c) { put(k, c, e[c]); put(c, k, e[c]); }
-        } else {
-          put(k, cidx<TP::vofs(A)>, F.n.z);
-          put(cidx<TP::vofs(A)>, k, F.n.z);
-        }
-      };
-      walk_up<TP, J>(t, R, inr_col_z(Ic[J]), emit);
-      if constexpr (P >= 0) xinr_acc(R[J], load_r<J>(t), Ic[J], Ic[P]);
-    }
+    crba_write<TP, J>(t, R, Ic[J], put);
+    if constexpr (P >= 0) xinr_acc(R[J], load_r<J>(t), Ic[J], Ic[P]);
   };
 
   sfor<0, N>([&](auto I_) __attribute__((always_inline)) {
@@ -713,14 +737,7 @@ RBD_DI void crba_lane(const float* __restrict__ t, const QI& q, float* __restric
     Ic[I] = load_inr<I>(t);
     close_subtrees<TP, I, I>(backward);
   });
-  // entries between DoFs of which neither is an ancestor of the other are zero
-  sfor<0, NV>([&](auto K_) __attribute__((always_inline)) {
-    constexpr int K = decltype(K_)::value;
-    sfor<0, NV>([&](auto L_) __attribute__((always_inline)) {
-      constexpr int L = decltype(L_)::value;
-      if constexpr (L != K && !TP::is_danc(L, K) && !TP::is_danc(K, L)) put(K, L, 0.0f);
-    });
-  });
+  sfor<0, NV>([&](auto K_) __attribute__((always_inline)) { crba_zeros<TP, decltype(K_)::value>(put); });
 }
 
 // =================================================================== branch-sparse L^T L
@@ -747,15 +764,20 @@ struct AllRhs {
 struct NoRhs {
   static constexpr bool on(int, int) { return false; }
 };
+// Which DoFs' rows a row sums over (all of its descendants', unless a part of
+// the tree is factored elsewhere).
+struct AllDofs {
+  static constexpr bool on(int) { return true; }
+};
 
 // Row K given row K of M (Mr[j] for ancestors j, Mkk) and b_K.
-template <class TP, int K, int NRHS, class MASK = AllRhs>
+template <class TP, int K, int NRHS, class MASK = AllRhs, class DOFS = AllDofs>
 RBD_DI void ltl_row(Ltl<TP, NRHS>& F, const float* Mr, float Mkk, const float* bk) {
   constexpr int NV = TP::NV;
   float D = Mkk;
-  sfor<K + 1, NV>([&](auto D_) __attribute__((always_inline)) {
+  sfor<K + 1, cidx<TP::dlast(K)> + 1>([&](auto D_) __attribute__((always_inline)) {
     constexpr int Dd = decltype(D_)::value;
-    if constexpr (TP::is_danc(K, Dd)) D = D - F.L[cidx<TP::lidx(Dd, K)>] * F.L[cidx<TP::lidx(Dd, K)>];
+    if constexpr (DOFS::on(Dd)) D = D - F.L[cidx<TP::lidx(Dd, K)>] * F.L[cidx<TP::lidx(Dd, K)>];
   });
   const float inv = frsq(D);
   F.Linv[K] = inv;
@@ -763,9 +785,9 @@ RBD_DI void ltl_row(Ltl<TP, NRHS>& F, const float* Mr, float Mkk, const float* b
     constexpr int Jd = decltype(J_)::value;
     if constexpr (TP::is_danc(Jd, K)) {
       float acc = Mr[Jd];
-      sfor<K + 1, NV>([&](auto D_) __attribute__((always_inline)) {
+      sfor<K + 1, cidx<TP::dlast(K)> + 1>([&](auto D_) __attribute__((always_inline)) {
         constexpr int Dd = decltype(D_)::value;
-        if constexpr (TP::is_danc(K, Dd)) acc = acc - F.L[cidx<TP::lidx(Dd, K)>] * F.L[cidx<TP::lidx(Dd, Jd)>];
+        if constexpr (DOFS::on(Dd)) acc = acc - F.L[cidx<TP::lidx(Dd, K)>] * F.L[cidx<TP::lidx(Dd, Jd)>];
       });
       F.L[cidx<TP::lidx(K, Jd)>] = acc * inv;
     }
@@ -774,9 +796,9 @@ RBD_DI void ltl_row(Ltl<TP, NRHS>& F, const float* Mr, float Mkk, const float* b
     constexpr int r = decltype(R_)::value;
     if constexpr (MASK::on(r, K)) {
       float acc = bk[r];
-      sfor<K + 1, NV>([&](auto D_) __attribute__((always_inline)) {
+      sfor<K + 1, cidx<TP::dlast(K)> + 1>([&](auto D_) __attribute__((always_inline)) {
         constexpr int Dd = decltype(D_)::value;
-        if constexpr (TP::is_danc(K, Dd) && MASK::on(r, Dd)) acc = acc - F.L[cidx<TP::lidx(Dd, K)>] * F.y[r][Dd];
+        if constexpr (DOFS::on(Dd) && MASK::on(r, Dd)) acc = acc - F.L[cidx<TP::lidx(Dd, K)>] * F.y[r][Dd];
       });
       F.y[r][K] = acc * inv;
     }
@@ -799,8 +821,9 @@ RBD_DI void ltl_base_rows(Ltl<TP, NRHS>& F, const Inr& Ic, const BK& bk, MASK = 
   });
 }
 
-// L x = y, root to leaves; sink(r, k, x_k).
-template <class TP, int NRHS, class SINK>
+// L x = y, root to leaves; sink(r, k, x_k). DOFS selects an ancestor-closed
+// set of DoFs.
+template <class TP, int NRHS, class DOFS = AllDofs, class SINK>
 RBD_DI void ltl_back(const Ltl<TP, NRHS>& F, const SINK& sink) {
   constexpr int NV = TP::NV;
   sfor<0, NRHS>([&](auto R_) __attribute__((always_inline)) {
@@ -808,13 +831,15 @@ RBD_DI void ltl_back(const Ltl<TP, NRHS>& F, const SINK& sink) {
     float x[NV];
     sfor<0, NV>([&](auto K_) __attribute__((always_inline)) {
       constexpr int K = decltype(K_)::value;
-      float acc = F.y[r][K];
-      sfor<0, K>([&](auto J_) __attribute__((always_inline)) {
-        constexpr int Jd = decltype(J_)::value;
-        if constexpr (TP::is_danc(Jd, K)) acc = acc - F.L[cidx<TP::lidx(K, Jd)>] * x[Jd];
-      });
-      x[K] = acc * F.Linv[K];
-      sink(r, K, x[K]);
+      if constexpr (DOFS::on(K)) {
+        float acc = F.y[r][K];
+        sfor<0, K>([&](auto J_) __attribute__((always_inline)) {
+          constexpr int Jd = decltype(J_)::value;
+          if constexpr (TP::is_danc(Jd, K)) acc = acc - F.L[cidx<TP::lidx(K, Jd)>] * x[Jd];
+        });
+        x[K] = acc * F.Linv[K];
+        sink(r, K, x[K]);
+      }
     });
   });
 }
@@ -828,9 +853,9 @@ RBD_DI void ltl_solve_y(Ltl<TP, 1>& F, const B& b) {
   sfor_rev<0, NV>([&](auto K_) __attribute__((always_inline)) {
     constexpr int K = decltype(K_)::value;
     float acc = b(K);
-    sfor<K + 1, NV>([&](auto D_) __attribute__((always_inline)) {
+    sfor<K + 1, cidx<TP::dlast(K)> + 1>([&](auto D_) __attribute__((always_inline)) {
       constexpr int Dd = decltype(D_)::value;
-      if constexpr (TP::is_danc(K, Dd)) acc = acc - F.L[cidx<TP::lidx(Dd, K)>] * F.y[0][Dd];
+      acc = acc - F.L[cidx<TP::lidx(Dd, K)>] * F.y[0][Dd];
     });
     F.y[0][K] = acc * F.Linv[K];
   });
@@ -1003,144 +1028,168 @@ RBD_DI void ltl_factor_lane(const float* __restrict__ t, const QI& q, Ltl<TP, 1>
 // the body-frame force changes by -eta_i x* F_i plus dF_i in body coordinates.
 // A tangent dqdd of the accelerations (DQDD with kOn) adds S dqdd_i to da_i:
 // then the sweep is the full tangent of inverse dynamics.
-template <class TP, class QI, class QDI, class QDDI, class DQI, class DQDI, class DTI, class OUT, class FX = NoFext,
-          class DFX = NoFext, class DQDD = NoFext>
-RBD_DI void id_tangent_lane(const float* __restrict__ t, const QI& q, const QDI& qd, const QDDI& qdd,
-                            const DQI& dq, const DQDI& dqd, const DTI& dtau, const OUT& out, const FX& fx = FX{},
-                            const DFX& dfx = DFX{}, const DQDD& dqdd = DQDD{}) {
-  constexpr int N = TP::N;
-  constexpr bool kExt = FX::kOn || DFX::kOn;
-  constexpr int NE = kExt ? N : 1;
+//
+// The sweep's state, and its steps for one body: tan_motion (from the
+// parent's motion), tan_force, and tan_close (the subtree's outputs, and what
+// it adds to the parent's totals).
+template <class TP, bool EXT>
+struct TanState {
+  static constexpr bool kExt = EXT;
+  static constexpr int N = TP::N, NE = kExt ? N : 1;
   M3 Rw[NE];
   V3 pw[NE];
   Mot eta[NE];
   M3 R[N];
   Mot v[N], a[N], dv[N], da[N];
   Frc f[N], df[N];
-  const V3 g = load_g<TP>(t);
-  const V3 mg = {-g.x, -g.y, -g.z};
+};
 
-  auto backward = [&](auto J_) __attribute__((always_inline)) {
-    constexpr int J = decltype(J_)::value;
-    constexpr int P = TP::parent(J);
-    if constexpr (TP::free_body(J)) {
-      const float hb[6] = {df[J].f.x, df[J].f.y, df[J].f.z, df[J].n.x, df[J].n.y, df[J].n.z};
+template <class TP, int J, class ST, class DQI, class DTI, class OUT>
+RBD_DI void tan_close(const float* __restrict__ t, ST& st, const DQI& dq, const DTI& dtau, const OUT& out) {
+  constexpr int P = TP::parent(J);
+  if constexpr (TP::free_body(J)) {
+    const float hb[6] = {st.df[J].f.x, st.df[J].f.y, st.df[J].f.z, st.df[J].n.x, st.df[J].n.y, st.df[J].n.z};
 #pragma unroll
-      for (int c = 0; c < 6; ++c) out(c, dtau(c) - hb[c]);
-    } else {
-      constexpr int k = TP::vofs(J);
-      out(k, dtau(k) - df[J].n.z);
-      if constexpr (P >= 0) {
-        const V3 r = load_r<J>(t);
-        const float e = dq(cidx<TP::qofs(J)>);
-        // df + dq S x* f: S x* [n; f] = [(-n_y, n_x, 0); (-f_y, f_x, 0)]
-        Frc d = df[J];
-        d.n.x = __builtin_fmaf(-e, f[J].n.y, d.n.x);
-        d.n.y = __builtin_fmaf(e, f[J].n.x, d.n.y);
-        d.f.x = __builtin_fmaf(-e, f[J].f.y, d.f.x);
-        d.f.y = __builtin_fmaf(e, f[J].f.x, d.f.y);
-        xfrc_acc(R[J], r, d, df[P]);
-        xfrc_acc(R[J], r, f[J], f[P]);
-      }
+    for (int c = 0; c < 6; ++c) out(c, dtau(c) - hb[c]);
+  } else {
+    constexpr int k = TP::vofs(J);
+    out(k, dtau(k) - st.df[J].n.z);
+    if constexpr (P >= 0) {
+      const V3 r = load_r<J>(t);
+      const float e = dq(cidx<TP::qofs(J)>);
+      // df + dq S x* f: S x* [n; f] = [(-n_y, n_x, 0); (-f_y, f_x, 0)]
+      Frc d = st.df[J];
+      d.n.x = __builtin_fmaf(-e, st.f[J].n.y, d.n.x);
+      d.n.y = __builtin_fmaf(e, st.f[J].n.x, d.n.y);
+      d.f.x = __builtin_fmaf(-e, st.f[J].f.y, d.f.x);
+      d.f.y = __builtin_fmaf(e, st.f[J].f.x, d.f.y);
+      xfrc_acc(st.R[J], r, d, st.df[P]);
+      xfrc_acc(st.R[J], r, st.f[J], st.f[P]);
     }
-  };
+  }
+}
 
-  sfor<0, N>([&](auto I_) __attribute__((always_inline)) {
-    constexpr int I = decltype(I_)::value;
-    constexpr int P = TP::parent(I);
+template <class TP, int I, class ST, class QI, class QDI, class QDDI, class DQI, class DQDI, class DQDD>
+RBD_DI void tan_motion(const float* __restrict__ t, V3 mg, ST& st, const QI& q, const QDI& qd, const QDDI& qdd,
+                       const DQI& dq, const DQDI& dqd, const DQDD& dqdd) {
+  constexpr bool kExt = ST::kExt;
+  constexpr int P = TP::parent(I);
+  if constexpr (TP::free_body(I)) {
+    const float w = q(3), x = q(4), y = q(5), z = q(6);
+    const float dw = dq(3), dx = dq(4), dy = dq(5), dz = dq(6);
+    st.R[I] = quat_rot(w, x, y, z);
+    // d(R^T mg) with R = N(quat) / |quat|^2: dR = (dN - R ds) / s, ds = 2 quat . dquat
+    const float s = frcp(w * w + x * x + y * y + z * z);
+    const float ds = 2.0f * (w * dw + x * dx + y * dy + z * dz);
+    M3 dN;
+    dN.a[0] = 2.0f * (w * dw + x * dx - y * dy - z * dz);
+    dN.a[1] = 2.0f * (dx * y + x * dy - dw * z - w * dz);
+    dN.a[2] = 2.0f * (dx * z + x * dz + dw * y + w * dy);
+    dN.a[3] = 2.0f * (dx * y + x * dy + dw * z + w * dz);
+    dN.a[4] = 2.0f * (w * dw - x * dx + y * dy - z * dz);
+    dN.a[5] = 2.0f * (dy * z + y * dz - dw * x - w * dx);
+    dN.a[6] = 2.0f * (dx * z + x * dz - dw * y - w * dy);
+    dN.a[7] = 2.0f * (dy * z + y * dz + dw * x + w * dx);
+    dN.a[8] = 2.0f * (w * dw - x * dx - y * dy + z * dz);
+    const V3 ag = mulT(st.R[I], mg);
+    const V3 dag = s * (mulT(dN, mg) - ds * ag);
+    st.v[I] = {{qd(3), qd(4), qd(5)}, {qd(0), qd(1), qd(2)}};
+    st.a[I] = {{qdd(3), qdd(4), qdd(5)}, ag + V3{qdd(0), qdd(1), qdd(2)}};
+    st.dv[I] = {{dqd(3), dqd(4), dqd(5)}, {dqd(0), dqd(1), dqd(2)}};
+    st.da[I] = {{0.0f, 0.0f, 0.0f}, dag};
+    if constexpr (DQDD::kOn) st.da[I] = st.da[I] + Mot{{dqdd(3), dqdd(4), dqdd(5)}, {dqdd(0), dqdd(1), dqdd(2)}};
+  } else {
+    st.R[I] = joint_rot<I>(t, q(cidx<TP::qofs(I)>));
+    const float w = qd(cidx<TP::vofs(I)>);
+    const float dw = dqd(cidx<TP::vofs(I)>);
+    const float e = dq(cidx<TP::qofs(I)>);
+    Mot ap, dap;
+    if constexpr (P < 0) {
+      st.v[I] = {{0.0f, 0.0f, w}, {0.0f, 0.0f, 0.0f}};
+      st.dv[I] = {{0.0f, 0.0f, dw}, {0.0f, 0.0f, 0.0f}};
+      ap = {{0.0f, 0.0f, 0.0f}, mulT(st.R[I], mg)};
+      dap = {{0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}};
+    } else {
+      const V3 r = load_r<I>(t);
+      st.v[I] = xmot(st.R[I], r, st.v[P]);
+      st.v[I].w.z = st.v[I].w.z + w;
+      st.dv[I] = xmot(st.R[I], r, st.dv[P]);
+      // - e S x (X v_p): the x, y parts of v_i
+      st.dv[I].w.x = __builtin_fmaf(e, st.v[I].w.y, st.dv[I].w.x);
+      st.dv[I].w.y = __builtin_fmaf(-e, st.v[I].w.x, st.dv[I].w.y);
+      st.dv[I].v.x = __builtin_fmaf(e, st.v[I].v.y, st.dv[I].v.x);
+      st.dv[I].v.y = __builtin_fmaf(-e, st.v[I].v.x, st.dv[I].v.y);
+      st.dv[I].w.z = st.dv[I].w.z + dw;
+      ap = xmot(st.R[I], r, st.a[P]);
+      dap = xmot(st.R[I], r, st.da[P]);
+    }
+    // - e S x (X a_p)
+    dap.w.x = __builtin_fmaf(e, ap.w.y, dap.w.x);
+    dap.w.y = __builtin_fmaf(-e, ap.w.x, dap.w.y);
+    dap.v.x = __builtin_fmaf(e, ap.v.y, dap.v.x);
+    dap.v.y = __builtin_fmaf(-e, ap.v.x, dap.v.y);
+    // v x S w and its tangent dv x S w + v x S dw
+    st.a[I] = ap;
+    st.a[I].w.x = __builtin_fmaf(w, st.v[I].w.y, st.a[I].w.x);
+    st.a[I].w.y = __builtin_fmaf(-w, st.v[I].w.x, st.a[I].w.y);
+    st.a[I].v.x = __builtin_fmaf(w, st.v[I].v.y, st.a[I].v.x);
+    st.a[I].v.y = __builtin_fmaf(-w, st.v[I].v.x, st.a[I].v.y);
+    st.a[I].w.z = st.a[I].w.z + qdd(cidx<TP::vofs(I)>);
+    st.da[I] = dap;
+    st.da[I].w.x = __builtin_fmaf(w, st.dv[I].w.y, __builtin_fmaf(dw, st.v[I].w.y, st.da[I].w.x));
+    st.da[I].w.y = __builtin_fmaf(-w, st.dv[I].w.x, __builtin_fmaf(-dw, st.v[I].w.x, st.da[I].w.y));
+    st.da[I].v.x = __builtin_fmaf(w, st.dv[I].v.y, __builtin_fmaf(dw, st.v[I].v.y, st.da[I].v.x));
+    st.da[I].v.y = __builtin_fmaf(-w, st.dv[I].v.x, __builtin_fmaf(-dw, st.v[I].v.x, st.da[I].v.y));
+    if constexpr (DQDD::kOn) st.da[I].w.z = st.da[I].w.z + dqdd(cidx<TP::vofs(I)>);
+  }
+  if constexpr (kExt) {
+    world_pose<TP, I>(t, q, st.R[I], st.Rw, st.pw);
     if constexpr (TP::free_body(I)) {
       const float w = q(3), x = q(4), y = q(5), z = q(6);
       const float dw = dq(3), dx = dq(4), dy = dq(5), dz = dq(6);
-      R[I] = quat_rot(w, x, y, z);
-      // d(R^T mg) with R = N(quat) / |quat|^2: dR = (dN - R ds) / s, ds = 2 quat . dquat
-      const float s = frcp(w * w + x * x + y * y + z * z);
-      const float ds = 2.0f * (w * dw + x * dx + y * dy + z * dz);
-      M3 dN;
-      dN.a[0] = 2.0f * (w * dw + x * dx - y * dy - z * dz);
-      dN.a[1] = 2.0f * (dx * y + x * dy - dw * z - w * dz);
-      dN.a[2] = 2.0f * (dx * z + x * dz + dw * y + w * dy);
-      dN.a[3] = 2.0f * (dx * y + x * dy + dw * z + w * dz);
-      dN.a[4] = 2.0f * (w * dw - x * dx + y * dy - z * dz);
-      dN.a[5] = 2.0f * (dy * z + y * dz - dw * x - w * dx);
-      dN.a[6] = 2.0f * (dx * z + x * dz - dw * y - w * dy);
-      dN.a[7] = 2.0f * (dy * z + y * dz + dw * x + w * dx);
-      dN.a[8] = 2.0f * (w * dw - x * dx - y * dy + z * dz);
-      const V3 ag = mulT(R[I], mg);
-      const V3 dag = s * (mulT(dN, mg) - ds * ag);
-      v[I] = {{qd(3), qd(4), qd(5)}, {qd(0), qd(1), qd(2)}};
-      a[I] = {{qdd(3), qdd(4), qdd(5)}, ag + V3{qdd(0), qdd(1), qdd(2)}};
-      dv[I] = {{dqd(3), dqd(4), dqd(5)}, {dqd(0), dqd(1), dqd(2)}};
-      da[I] = {{0.0f, 0.0f, 0.0f}, dag};
-      if constexpr (DQDD::kOn) da[I] = da[I] + Mot{{dqdd(3), dqdd(4), dqdd(5)}, {dqdd(0), dqdd(1), dqdd(2)}};
+      const float s2 = 2.0f * frcp(w * w + x * x + y * y + z * z);
+      // vec(conj(quat) (x) dquat) = w du - dw u - u x du
+      const V3 u = {x, y, z}, du = {dx, dy, dz};
+      const V3 th = s2 * (w * du - dw * u - cross(u, du));
+      st.eta[I] = {th, mulT(st.R[I], V3{dq(0), dq(1), dq(2)})};
     } else {
-      R[I] = joint_rot<I>(t, q(cidx<TP::qofs(I)>));
-      const float w = qd(cidx<TP::vofs(I)>);
-      const float dw = dqd(cidx<TP::vofs(I)>);
-      const float e = dq(cidx<TP::qofs(I)>);
-      Mot ap, dap;
-      if constexpr (P < 0) {
-        v[I] = {{0.0f, 0.0f, w}, {0.0f, 0.0f, 0.0f}};
-        dv[I] = {{0.0f, 0.0f, dw}, {0.0f, 0.0f, 0.0f}};
-        ap = {{0.0f, 0.0f, 0.0f}, mulT(R[I], mg)};
-        dap = {{0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}};
-      } else {
-        const V3 r = load_r<I>(t);
-        v[I] = xmot(R[I], r, v[P]);
-        v[I].w.z = v[I].w.z + w;
-        dv[I] = xmot(R[I], r, dv[P]);
-        // - e S x (X v_p): the x, y parts of v_i
-        dv[I].w.x = __builtin_fmaf(e, v[I].w.y, dv[I].w.x);
-        dv[I].w.y = __builtin_fmaf(-e, v[I].w.x, dv[I].w.y);
-        dv[I].v.x = __builtin_fmaf(e, v[I].v.y, dv[I].v.x);
-        dv[I].v.y = __builtin_fmaf(-e, v[I].v.x, dv[I].v.y);
-        dv[I].w.z = dv[I].w.z + dw;
-        ap = xmot(R[I], r, a[P]);
-        dap = xmot(R[I], r, da[P]);
-      }
-      // - e S x (X a_p)
-      dap.w.x = __builtin_fmaf(e, ap.w.y, dap.w.x);
-      dap.w.y = __builtin_fmaf(-e, ap.w.x, dap.w.y);
-      dap.v.x = __builtin_fmaf(e, ap.v.y, dap.v.x);
-      dap.v.y = __builtin_fmaf(-e, ap.v.x, dap.v.y);
-      // v x S w and its tangent dv x S w + v x S dw
-      a[I] = ap;
-      a[I].w.x = __builtin_fmaf(w, v[I].w.y, a[I].w.x);
-      a[I].w.y = __builtin_fmaf(-w, v[I].w.x, a[I].w.y);
-      a[I].v.x = __builtin_fmaf(w, v[I].v.y, a[I].v.x);
-      a[I].v.y = __builtin_fmaf(-w, v[I].v.x, a[I].v.y);
-      a[I].w.z = a[I].w.z + qdd(cidx<TP::vofs(I)>);
-      da[I] = dap;
-      da[I].w.x = __builtin_fmaf(w, dv[I].w.y, __builtin_fmaf(dw, v[I].w.y, da[I].w.x));
-      da[I].w.y = __builtin_fmaf(-w, dv[I].w.x, __builtin_fmaf(-dw, v[I].w.x, da[I].w.y));
-      da[I].v.x = __builtin_fmaf(w, dv[I].v.y, __builtin_fmaf(dw, v[I].v.y, da[I].v.x));
-      da[I].v.y = __builtin_fmaf(-w, dv[I].v.x, __builtin_fmaf(-dw, v[I].v.x, da[I].v.y));
-      if constexpr (DQDD::kOn) da[I].w.z = da[I].w.z + dqdd(cidx<TP::vofs(I)>);
+      if constexpr (P < 0) st.eta[I] = {{0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}};
+      else st.eta[I] = xmot(st.R[I], load_r<I>(t), st.eta[P]);
+      st.eta[I].w.z = st.eta[I].w.z + dq(cidx<TP::qofs(I)>);
     }
-    const Inr Ib = load_inr<I>(t);
-    const Frc Iv = imul(Ib, v[I]);
-    f[I] = imul(Ib, a[I]) + crf(v[I], Iv);
-    df[I] = imul(Ib, da[I]) + crf(dv[I], Iv) + crf(v[I], imul(Ib, dv[I]));
-    if constexpr (kExt) {
-      world_pose<TP, I>(t, q, R[I], Rw, pw);
-      if constexpr (TP::free_body(I)) {
-        const float w = q(3), x = q(4), y = q(5), z = q(6);
-        const float dw = dq(3), dx = dq(4), dy = dq(5), dz = dq(6);
-        const float s2 = 2.0f * frcp(w * w + x * x + y * y + z * z);
-        // vec(conj(quat) (x) dquat) = w du - dw u - u x du
-        const V3 u = {x, y, z}, du = {dx, dy, dz};
-        const V3 th = s2 * (w * du - dw * u - cross(u, du));
-        eta[I] = {th, mulT(R[I], V3{dq(0), dq(1), dq(2)})};
-      } else {
-        constexpr int P = TP::parent(I);
-        if constexpr (P < 0) eta[I] = {{0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}};
-        else eta[I] = xmot(R[I], load_r<I>(t), eta[P]);
-        eta[I].w.z = eta[I].w.z + dq(cidx<TP::qofs(I)>);
-      }
-      const Frc fe = fext_body<I>(fx, Rw[I], pw[I]);
-      const Frc dfe = fext_body<I>(dfx, Rw[I], pw[I]) - crf(eta[I], fe);
-      f[I] = f[I] - fe;
-      df[I] = df[I] - dfe;
-    }
+  }
+}
+
+template <class TP, int I, class ST, class FX, class DFX>
+RBD_DI void tan_force(const float* __restrict__ t, ST& st, const FX& fx, const DFX& dfx) {
+  constexpr bool kExt = ST::kExt;
+  const Inr Ib = load_inr<I>(t);
+  const Frc Iv = imul(Ib, st.v[I]);
+  st.f[I] = imul(Ib, st.a[I]) + crf(st.v[I], Iv);
+  st.df[I] = imul(Ib, st.da[I]) + crf(st.dv[I], Iv) + crf(st.v[I], imul(Ib, st.dv[I]));
+  if constexpr (kExt) {
+    const Frc fe = fext_body<I>(fx, st.Rw[I], st.pw[I]);
+    const Frc dfe = fext_body<I>(dfx, st.Rw[I], st.pw[I]) - crf(st.eta[I], fe);
+    st.f[I] = st.f[I] - fe;
+    st.df[I] = st.df[I] - dfe;
+  }
+}
+
+template <class TP, class QI, class QDI, class QDDI, class DQI, class DQDI, class DTI, class OUT, class FX = NoFext,
+          class DFX = NoFext, class DQDD = NoFext>
+RBD_DI void id_tangent_lane(const float* __restrict__ t, const QI& q, const QDI& qd, const QDDI& qdd,
+                            const DQI& dq, const DQDI& dqd, const DTI& dtau, const OUT& out, const FX& fx = FX{},
+                            const DFX& dfx = DFX{}, const DQDD& dqdd = DQDD{}) {
+  TanState<TP, FX::kOn || DFX::kOn> st;
+  const V3 g = load_g<TP>(t);
+  const V3 mg = {-g.x, -g.y, -g.z};
+  auto backward = [&](auto J_) __attribute__((always_inline)) {
+    tan_close<TP, decltype(J_)::value>(t, st, dq, dtau, out);
+  };
+  sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
+    constexpr int I = decltype(I_)::value;
+    tan_motion<TP, I>(t, mg, st, q, qd, qdd, dq, dqd, dqdd);
+    tan_force<TP, I>(t, st, fx, dfx);
     close_subtrees<TP, I, I>(backward);
   });
 }
@@ -1174,14 +1223,15 @@ RBD_DI void id_tangent_lane(const float* __restrict__ t, const QI& q, const QDI&
 // The force cotangent g_F_i = J_i lam is mu_i in world axes at the world origin.
 // With GQDD (kOn), S^T abar = M lam is written too: abar is the composite
 // force of the accelerations mu (no velocity, no gravity).
-template <class TP, class QI, class QDI, class QDD, class LAM, class GQ, class GQD, class FX = NoFext, class GF = NoGF,
-          class GQDD = NoGF>
-RBD_DI void id_adjoint_lane(const float* __restrict__ t, const QI& q, const QDI& qd, const QDD& qdd, const LAM& lam,
-                            const GQ& gq, const GQD& gqd, const FX& fx = FX{}, const GF& gf = GF{},
-                            const GQDD& gqdd = GQDD{}) {
-  constexpr int N = TP::N;
-  constexpr bool kExt = FX::kOn, kW = FX::kOn || GF::kOn;
-  constexpr int NE = kExt ? N : 1, NW = kW ? N : 1;
+//
+// The sweep's state, and its steps for one body: adj_motion (from the parent's
+// motion), adj_force, and adj_close (the subtree's outputs, and what it adds
+// to the parent's totals).
+template <class TP, bool EXT, bool GF>
+struct AdjState {
+  static constexpr int N = TP::N;
+  static constexpr bool kExt = EXT, kW = EXT || GF;
+  static constexpr int NE = kExt ? N : 1, NW = kW ? N : 1;
   M3 Rw[NW];
   V3 pw[NW];
   Frc Fs[NE], Ws[NE];  // subtree sums of F_i and of mu_i x* F_i, in body coordinates
@@ -1192,141 +1242,166 @@ RBD_DI void id_adjoint_lane(const float* __restrict__ t, const QI& q, const QDI&
   Mot v[N], a[N], mu[N];
   float ap[N][4];  // (X a_parent) w.x, w.y, v.x, v.y
   Frc f[N], ab[N], vb[N];
+};
+
+template <class TP, int J, class ST, class QI, class QDI, class GQ, class GQD, class GQDD>
+RBD_DI void adj_close(const float* __restrict__ t, V3 g, ST& s, const QI& q, const QDI& qd, const GQ& gq,
+                      const GQD& gqd, const GQDD& gqdd) {
+  constexpr bool kExt = ST::kExt;
+  constexpr int P = TP::parent(J);
+  const Inr Ib = load_inr<J>(t);
+  const Frc abar = imul(Ib, s.mu[J]) + s.ab[J];
+  Frc vbar = imul(Ib, crm(s.mu[J], s.v[J])) - crf(s.mu[J], imul(Ib, s.v[J])) + s.vb[J];
+  if constexpr (GQDD::kOn) {
+    if constexpr (TP::free_body(J)) {
+      gqdd(0, abar.f.x); gqdd(1, abar.f.y); gqdd(2, abar.f.z);
+      gqdd(3, abar.n.x); gqdd(4, abar.n.y); gqdd(5, abar.n.z);
+    } else {
+      gqdd(cidx<TP::vofs(J)>, abar.n.z);
+    }
+  }
+  if constexpr (TP::free_body(J)) {
+    gqd(0, -vbar.f.x); gqd(1, -vbar.f.y); gqd(2, -vbar.f.z);
+    gqd(3, -vbar.n.x); gqd(4, -vbar.n.y); gqd(5, -vbar.n.z);
+    // d/dquat of <abar.f, R^T(-g)> = -g^T R abar, with R = N(quat) / |quat|^2
+    const float w = q(3), x = q(4), y = q(5), z = q(6);
+    const float is = frcp(w * w + x * x + y * y + z * z);
+    const V3 u = {x, y, z}, A = abar.f;
+    const float gA = dot(g, A), uA = dot(u, A), gu = dot(g, u);
+    const V3 axg = cross(A, g);
+    const float gRA = dot(g, mul(s.R0, A));  // g^T R abar
+    const float dw = 2.0f * w * gA + 2.0f * dot(u, axg);
+    const float dx = -2.0f * x * gA + 2.0f * g.x * uA + 2.0f * gu * A.x + 2.0f * w * axg.x;
+    const float dy = -2.0f * y * gA + 2.0f * g.y * uA + 2.0f * gu * A.y + 2.0f * w * axg.y;
+    const float dz = -2.0f * z * gA + 2.0f * g.z * uA + 2.0f * gu * A.z + 2.0f * w * axg.z;
+    // dPhi/dquat_k = -(g^T dN/dquat_k abar - 2 quat_k g^T R abar) / |quat|^2; output -dPhi
+    float g4[4] = {(dw - 2.0f * w * gRA) * is, (dx - 2.0f * x * gRA) * is, (dy - 2.0f * y * gRA) * is,
+                   (dz - 2.0f * z * gRA) * is};
+    V3 gp = {0.0f, 0.0f, 0.0f};
+    if constexpr (kExt) {
+      // position: R Wsub_0.f; quaternion: Wsub_0.n . (2 / |quat|^2) vec(conj(quat) (x) e_k)
+      gp = mul(s.R0, s.Ws[J].f);
+      const V3 n = s.Ws[J].n;
+      const float s2 = 2.0f * is;
+      g4[0] = __builtin_fmaf(s2, -x * n.x - y * n.y - z * n.z, g4[0]);
+      g4[1] = __builtin_fmaf(s2, w * n.x - z * n.y + y * n.z, g4[1]);
+      g4[2] = __builtin_fmaf(s2, z * n.x + w * n.y - x * n.z, g4[2]);
+      g4[3] = __builtin_fmaf(s2, -y * n.x + x * n.y + w * n.z, g4[3]);
+    }
+    gq(0, gp.x); gq(1, gp.y); gq(2, gp.z);
+    gq(3, g4[0]); gq(4, g4[1]); gq(5, g4[2]); gq(6, g4[3]);
+  } else {
+    const float w = qd(cidx<TP::vofs(J)>);
+    // (S qd) x* abar = w [(-n_y, n_x, 0); (-f_y, f_x, 0)]
+    vbar.n.x = vbar.n.x - w * abar.n.y;
+    vbar.n.y = vbar.n.y + w * abar.n.x;
+    vbar.f.x = vbar.f.x - w * abar.f.y;
+    vbar.f.y = vbar.f.y + w * abar.f.x;
+    // S^T (v x* abar) = z of (w x n + v x f)
+    const float vxa = s.v[J].w.x * abar.n.y - s.v[J].w.y * abar.n.x + s.v[J].v.x * abar.f.y - s.v[J].v.y * abar.f.x;
+    gqd(cidx<TP::vofs(J)>, -(vbar.n.z - vxa));
+    // <vbar, -S x (X v_p)>: (X v_p) has the x, y parts of v
+    float dq = vbar.n.x * s.v[J].w.y - vbar.n.y * s.v[J].w.x + vbar.f.x * s.v[J].v.y - vbar.f.y * s.v[J].v.x;
+    dq = dq + abar.n.x * s.ap[J][1] - abar.n.y * s.ap[J][0] + abar.f.x * s.ap[J][3] - abar.f.y * s.ap[J][2];
+    float dq_ext = 0.0f;
+    if constexpr (kExt) {
+      // <S, Wsub - (X mu_p) x* Fsub>: (X mu_p) has the x, y parts of mu
+      const Frc& Fsj = s.Fs[J];
+      dq_ext = s.Ws[J].n.z - (s.mu[J].w.x * Fsj.n.y - s.mu[J].w.y * Fsj.n.x + s.mu[J].v.x * Fsj.f.y - s.mu[J].v.y * Fsj.f.x);
+    }
+    if constexpr (P >= 0) {
+      // <X mu_p, S x* f>: (X mu_p) has the x, y parts of mu
+      dq = dq - s.mu[J].w.x * s.f[J].n.y + s.mu[J].w.y * s.f[J].n.x - s.mu[J].v.x * s.f[J].f.y + s.mu[J].v.y * s.f[J].f.x;
+      const V3 r = load_r<J>(t);
+      const M3 RJ = joint_rot_cs<J>(t, s.cq[J], s.sq[J]);
+      xfrc_acc(RJ, r, s.f[J], s.f[P]);
+      xfrc_acc(RJ, r, abar, s.ab[P]);
+      xfrc_acc(RJ, r, vbar, s.vb[P]);
+      if constexpr (kExt) {
+        xfrc_acc(RJ, r, s.Fs[J], s.Fs[P]);
+        xfrc_acc(RJ, r, s.Ws[J], s.Ws[P]);
+      }
+    }
+    gq(cidx<TP::qofs(J)>, dq_ext - dq);
+  }
+}
+
+template <class TP, int I, class ST, class QI, class QDI, class QDD, class LAM>
+RBD_DI void adj_motion(const float* __restrict__ t, V3 mg, ST& s, const QI& q, const QDI& qd, const QDD& qdd,
+                       const LAM& lam) {
+  constexpr bool kW = ST::kW;
+  constexpr int P = TP::parent(I);
+  if constexpr (TP::free_body(I)) {
+    s.R0 = quat_rot(q(3), q(4), q(5), q(6));
+    s.v[I] = {{qd(3), qd(4), qd(5)}, {qd(0), qd(1), qd(2)}};
+    s.a[I] = {{qdd(3), qdd(4), qdd(5)}, mulT(s.R0, mg) + V3{qdd(0), qdd(1), qdd(2)}};
+    s.mu[I] = {{lam(3), lam(4), lam(5)}, {lam(0), lam(1), lam(2)}};
+  } else {
+    fsincos(q(cidx<TP::qofs(I)>), s.sq[I], s.cq[I]);
+    const M3 RI = joint_rot_cs<I>(t, s.cq[I], s.sq[I]);
+    const float w = qd(cidx<TP::vofs(I)>);
+    Mot apI;
+    if constexpr (P < 0) {
+      s.v[I] = {{0.0f, 0.0f, w}, {0.0f, 0.0f, 0.0f}};
+      apI = {{0.0f, 0.0f, 0.0f}, mulT(RI, mg)};
+      s.mu[I] = {{0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}};
+    } else {
+      const V3 r = load_r<I>(t);
+      s.v[I] = xmot(RI, r, s.v[P]);
+      s.v[I].w.z = s.v[I].w.z + w;
+      apI = xmot(RI, r, s.a[P]);
+      s.mu[I] = xmot(RI, r, s.mu[P]);
+    }
+    s.ap[I][0] = apI.w.x; s.ap[I][1] = apI.w.y; s.ap[I][2] = apI.v.x; s.ap[I][3] = apI.v.y;
+    s.a[I] = apI;
+    s.a[I].w.z = s.a[I].w.z + qdd(cidx<TP::vofs(I)>);
+    s.a[I].w.x = s.a[I].w.x + w * s.v[I].w.y;
+    s.a[I].w.y = s.a[I].w.y - w * s.v[I].w.x;
+    s.a[I].v.x = s.a[I].v.x + w * s.v[I].v.y;
+    s.a[I].v.y = s.a[I].v.y - w * s.v[I].v.x;
+    s.mu[I].w.z = s.mu[I].w.z + lam(cidx<TP::vofs(I)>);
+  }
+  if constexpr (kW) {
+    if constexpr (TP::free_body(I)) world_pose<TP, I>(t, q, s.R0, s.Rw, s.pw);
+    else world_pose<TP, I>(t, q, joint_rot_cs<I>(t, s.cq[I], s.sq[I]), s.Rw, s.pw);
+  }
+}
+
+template <class TP, int I, class ST, class FX, class GF>
+RBD_DI void adj_force(const float* __restrict__ t, ST& s, const FX& fx, const GF& gf) {
+  constexpr bool kExt = ST::kExt;
+  const Inr Ib = load_inr<I>(t);
+  s.f[I] = imul(Ib, s.a[I]) + crf(s.v[I], imul(Ib, s.v[I]));
+  s.ab[I] = Frc{{0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}};
+  s.vb[I] = Frc{{0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}};
+  if constexpr (kExt) {
+    s.Fs[I] = fext_body<I>(fx, s.Rw[I], s.pw[I]);
+    s.Ws[I] = crf(s.mu[I], s.Fs[I]);
+  }
+  if constexpr (GF::kOn) {
+    // g_F = [v_O; w] in world axes: w = R mu.w, v_O = R mu.v + p x w
+    const V3 wv = mul(s.Rw[I], s.mu[I].w);
+    const V3 vo = cross_add(s.pw[I], wv, mul(s.Rw[I], s.mu[I].v));
+    gf(6 * I, vo.x); gf(6 * I + 1, vo.y); gf(6 * I + 2, vo.z);
+    gf(6 * I + 3, wv.x); gf(6 * I + 4, wv.y); gf(6 * I + 5, wv.z);
+  }
+}
+
+template <class TP, class QI, class QDI, class QDD, class LAM, class GQ, class GQD, class FX = NoFext, class GF = NoGF,
+          class GQDD = NoGF>
+RBD_DI void id_adjoint_lane(const float* __restrict__ t, const QI& q, const QDI& qd, const QDD& qdd, const LAM& lam,
+                            const GQ& gq, const GQD& gqd, const FX& fx = FX{}, const GF& gf = GF{},
+                            const GQDD& gqdd = GQDD{}) {
+  AdjState<TP, FX::kOn, GF::kOn> s;
   const V3 g = load_g<TP>(t);
   const V3 mg = {-g.x, -g.y, -g.z};
-
   auto backward = [&](auto J_) __attribute__((always_inline)) {
-    constexpr int J = decltype(J_)::value;
-    constexpr int P = TP::parent(J);
-    const Inr Ib = load_inr<J>(t);
-    const Frc abar = imul(Ib, mu[J]) + ab[J];
-    Frc vbar = imul(Ib, crm(mu[J], v[J])) - crf(mu[J], imul(Ib, v[J])) + vb[J];
-    if constexpr (GQDD::kOn) {
-      if constexpr (TP::free_body(J)) {
-        gqdd(0, abar.f.x); gqdd(1, abar.f.y); gqdd(2, abar.f.z);
-        gqdd(3, abar.n.x); gqdd(4, abar.n.y); gqdd(5, abar.n.z);
-      } else {
-        gqdd(cidx<TP::vofs(J)>, abar.n.z);
-      }
-    }
-    if constexpr (TP::free_body(J)) {
-      gqd(0, -vbar.f.x); gqd(1, -vbar.f.y); gqd(2, -vbar.f.z);
-      gqd(3, -vbar.n.x); gqd(4, -vbar.n.y); gqd(5, -vbar.n.z);
-      // d/dquat of <abar.f, R^T(-g)> = -g^T R abar, with R = N(quat) / |quat|^2
-      const float w = q(3), x = q(4), y = q(5), z = q(6);
-      const float s = frcp(w * w + x * x + y * y + z * z);
-      const V3 u = {x, y, z}, A = abar.f;
-      const float gA = dot(g, A), uA = dot(u, A), gu = dot(g, u);
-      const V3 axg = cross(A, g);
-      const float gRA = dot(g, mul(R0, A));  // g^T R abar
-      const float dw = 2.0f * w * gA + 2.0f * dot(u, axg);
-      const float dx = -2.0f * x * gA + 2.0f * g.x * uA + 2.0f * gu * A.x + 2.0f * w * axg.x;
-      const float dy = -2.0f * y * gA + 2.0f * g.y * uA + 2.0f * gu * A.y + 2.0f * w * axg.y;
-      const float dz = -2.0f * z * gA + 2.0f * g.z * uA + 2.0f * gu * A.z + 2.0f * w * axg.z;
-      // dPhi/dquat_k = -(g^T dN/dquat_k abar - 2 quat_k g^T R abar) / |quat|^2; output -dPhi
-      float g4[4] = {(dw - 2.0f * w * gRA) * s, (dx - 2.0f * x * gRA) * s, (dy - 2.0f * y * gRA) * s,
-                     (dz - 2.0f * z * gRA) * s};
-      V3 gp = {0.0f, 0.0f, 0.0f};
-      if constexpr (kExt) {
-        // position: R Wsub_0.f; quaternion: Wsub_0.n . (2 / |quat|^2) vec(conj(quat) (x) e_k)
-        gp = mul(R0, Ws[J].f);
-        const V3 n = Ws[J].n;
-        const float s2 = 2.0f * s;
-        g4[0] = __builtin_fmaf(s2, -x * n.x - y * n.y - z * n.z, g4[0]);
-        g4[1] = __builtin_fmaf(s2, w * n.x - z * n.y + y * n.z, g4[1]);
-        g4[2] = __builtin_fmaf(s2, z * n.x + w * n.y - x * n.z, g4[2]);
-        g4[3] = __builtin_fmaf(s2, -y * n.x + x * n.y + w * n.z, g4[3]);
-      }
-      gq(0, gp.x); gq(1, gp.y); gq(2, gp.z);
-      gq(3, g4[0]); gq(4, g4[1]); gq(5, g4[2]); gq(6, g4[3]);
-    } else {
-      const float w = qd(cidx<TP::vofs(J)>);
-      // (S qd) x* abar = w [(-n_y, n_x, 0); (-f_y, f_x, 0)]
-      vbar.n.x = vbar.n.x - w * abar.n.y;
-      vbar.n.y = vbar.n.y + w * abar.n.x;
-      vbar.f.x = vbar.f.x - w * abar.f.y;
-      vbar.f.y = vbar.f.y + w * abar.f.x;
-      // S^T (v x* abar) = z of (w x n + v x f)
-      const float vxa = v[J].w.x * abar.n.y - v[J].w.y * abar.n.x + v[J].v.x * abar.f.y - v[J].v.y * abar.f.x;
-      gqd(cidx<TP::vofs(J)>, -(vbar.n.z - vxa));
-      // <vbar, -S x (X v_p)>: (X v_p) has the x, y parts of v
-      float dq = vbar.n.x * v[J].w.y - vbar.n.y * v[J].w.x + vbar.f.x * v[J].v.y - vbar.f.y * v[J].v.x;
-      dq = dq + abar.n.x * ap[J][1] - abar.n.y * ap[J][0] + abar.f.x * ap[J][3] - abar.f.y * ap[J][2];
-      float dq_ext = 0.0f;
-      if constexpr (kExt) {
-        // <S, Wsub - (X mu_p) x* Fsub>: (X mu_p) has the x, y parts of mu
-        const Frc& Fsj = Fs[J];
-        dq_ext = Ws[J].n.z - (mu[J].w.x * Fsj.n.y - mu[J].w.y * Fsj.n.x + mu[J].v.x * Fsj.f.y - mu[J].v.y * Fsj.f.x);
-      }
-      if constexpr (P >= 0) {
-        // <X mu_p, S x* f>: (X mu_p) has the x, y parts of mu
-        dq = dq - mu[J].w.x * f[J].n.y + mu[J].w.y * f[J].n.x - mu[J].v.x * f[J].f.y + mu[J].v.y * f[J].f.x;
-        const V3 r = load_r<J>(t);
-        const M3 RJ = joint_rot_cs<J>(t, cq[J], sq[J]);
-        xfrc_acc(RJ, r, f[J], f[P]);
-        xfrc_acc(RJ, r, abar, ab[P]);
-        xfrc_acc(RJ, r, vbar, vb[P]);
-        if constexpr (kExt) {
-          xfrc_acc(RJ, r, Fs[J], Fs[P]);
-          xfrc_acc(RJ, r, Ws[J], Ws[P]);
-        }
-      }
-      gq(cidx<TP::qofs(J)>, dq_ext - dq);
-    }
+    adj_close<TP, decltype(J_)::value>(t, g, s, q, qd, gq, gqd, gqdd);
   };
-
-  sfor<0, N>([&](auto I_) __attribute__((always_inline)) {
+  sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
     constexpr int I = decltype(I_)::value;
-    constexpr int P = TP::parent(I);
-    if constexpr (TP::free_body(I)) {
-      R0 = quat_rot(q(3), q(4), q(5), q(6));
-      v[I] = {{qd(3), qd(4), qd(5)}, {qd(0), qd(1), qd(2)}};
-      a[I] = {{qdd(3), qdd(4), qdd(5)}, mulT(R0, mg) + V3{qdd(0), qdd(1), qdd(2)}};
-      mu[I] = {{lam(3), lam(4), lam(5)}, {lam(0), lam(1), lam(2)}};
-    } else {
-      fsincos(q(cidx<TP::qofs(I)>), sq[I], cq[I]);
-      const M3 RI = joint_rot_cs<I>(t, cq[I], sq[I]);
-      const float w = qd(cidx<TP::vofs(I)>);
-      Mot apI;
-      if constexpr (P < 0) {
-        v[I] = {{0.0f, 0.0f, w}, {0.0f, 0.0f, 0.0f}};
-        apI = {{0.0f, 0.0f, 0.0f}, mulT(RI, mg)};
-        mu[I] = {{0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}};
-      } else {
-        const V3 r = load_r<I>(t);
-        v[I] = xmot(RI, r, v[P]);
-        v[I].w.z = v[I].w.z + w;
-        apI = xmot(RI, r, a[P]);
-        mu[I] = xmot(RI, r, mu[P]);
-      }
-      ap[I][0] = apI.w.x; ap[I][1] = apI.w.y; ap[I][2] = apI.v.x; ap[I][3] = apI.v.y;
-      a[I] = apI;
-      a[I].w.z = a[I].w.z + qdd(cidx<TP::vofs(I)>);
-      a[I].w.x = a[I].w.x + w * v[I].w.y;
-      a[I].w.y = a[I].w.y - w * v[I].w.x;
-      a[I].v.x = a[I].v.x + w * v[I].v.y;
-      a[I].v.y = a[I].v.y - w * v[I].v.x;
-      mu[I].w.z = mu[I].w.z + lam(cidx<TP::vofs(I)>);
-    }
-    const Inr Ib = load_inr<I>(t);
-    f[I] = imul(Ib, a[I]) + crf(v[I], imul(Ib, v[I]));
-    ab[I] = Frc{{0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}};
-    vb[I] = Frc{{0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}};
-    if constexpr (kW) {
-      if constexpr (TP::free_body(I)) world_pose<TP, I>(t, q, R0, Rw, pw);
-      else world_pose<TP, I>(t, q, joint_rot_cs<I>(t, cq[I], sq[I]), Rw, pw);
-    }
-    if constexpr (kExt) {
-      Fs[I] = fext_body<I>(fx, Rw[I], pw[I]);
-      Ws[I] = crf(mu[I], Fs[I]);
-    }
-    if constexpr (GF::kOn) {
-      // g_F = [v_O; w] in world axes: w = R mu.w, v_O = R mu.v + p x w
-      const V3 wv = mul(Rw[I], mu[I].w);
-      const V3 vo = cross_add(pw[I], wv, mul(Rw[I], mu[I].v));
-      gf(6 * I, vo.x); gf(6 * I + 1, vo.y); gf(6 * I + 2, vo.z);
-      gf(6 * I + 3, wv.x); gf(6 * I + 4, wv.y); gf(6 * I + 5, wv.z);
-    }
+    adj_motion<TP, I>(t, mg, s, q, qd, qdd, lam);
+    adj_force<TP, I>(t, s, fx, gf);
     close_subtrees<TP, I, I>(backward);
   });
 }

@@ -1,0 +1,712 @@
+// A team of waves per 64 instances: lane l of every wave of a block works on
+// the same instance, each wave on its own branches of the tree, and the wave
+// that owns the trunk finishes it.
+//
+// One lane doing a whole tree is one serial chain: the humanoid's forward
+// dynamics is 16 thousand vector instructions whatever the batch, and its
+// registers admit one wave per SIMD, which then issues one instruction every
+// 5.8 cycles. Split by branches, the chain is the longest branch, the trunk
+// bodies above it and the trunk (118 tenths of a body of 300, rbd_team_plan.hpp),
+// a batch fills four times as many waves, and a wave holds only its own rows of
+// the factor, so two waves fit on a SIMD and hide each other's latency.
+//
+// The branches of different waves meet in the trunk only: what a branch hands
+// over is the force and the composite inertia it exerts on the trunk body it
+// hangs on, and its share of the trunk's rows of the factor (the Schur
+// complement sum_D L[D][K] L[D][J] over its DoFs D, and the same with y), all
+// parked in LDS as rows of 64 lanes. The trunk's solution goes back the same
+// way.
+#pragma once
+
+#include "rbd_lane.hpp"
+#include "rbd_team_plan.hpp"
+
+namespace rbd {
+
+template <class TP>
+struct Team {
+  static constexpr TeamPlan kPlan = team_plan(TP::kFree, TP::N, TP::par_.v);
+  static constexpr bool kOn = TP::NV > kTeamMinDofs && kPlan.waves > 1;
+  static constexpr bool kAlways = kOn && TP::NV > kTeamAlwaysDofs;
+  static constexpr int kWaves = kOn ? kPlan.waves : 1;
+  static constexpr int kThreads = kWaves * kTileLanes;
+  static constexpr int kOwner = kPlan.owner;
+
+  static constexpr bool trunk(int i) { return kPlan.wave[i] < 0; }
+  static constexpr bool in(int w, int i) { return kPlan.wave[i] == w; }
+  // trunk body a carries branches of wave w (directly or through other trunk bodies)
+  static constexpr bool above(int w, int a) {
+    if (!trunk(a)) return false;
+    for (int i = a + 1; i <= TP::last(a); ++i)
+      if (in(w, i)) return true;
+    return false;
+  }
+  // a branch of wave w hangs on trunk body a
+  static constexpr bool attach(int w, int a) {
+    if (!trunk(a)) return false;
+    for (int i = a + 1; i <= TP::last(a); ++i)
+      if (in(w, i) && TP::parent(i) == a) return true;
+    return false;
+  }
+  // wave w runs its own code (another wave's code with moved bodies otherwise)
+  static constexpr bool own_code(int w) { return kPlan.role[w] == w; }
+  // wave w or the waves that run its code include the owner
+  static constexpr bool may_own(int w) { return kPlan.role[kOwner] == w; }
+};
+
+// What the waves hand to the trunk: rows of LDS (64 lanes each). For every
+// trunk body a wave's branches hang on, A rows (forces and the like); for
+// every trunk DoF K above them, S = true: ddepth(K) + 1 rows of the Schur
+// complement (K's ancestors, then K) and R rows of right-hand sides.
+// (Tables, looked up with constant indices, fold away wherever they are asked.)
+template <class TP, int A, bool S, int R>
+struct TeamRowTab {
+  int arow[kTeamWaves][TP::N], krow[kTeamWaves][TP::NV], base[kTeamWaves + 1];
+  static constexpr TeamRowTab make() {
+    TeamRowTab t = {};
+    for (int w = 0; w < Team<TP>::kWaves; ++w) {
+      int n = 0;
+      for (int a = 0; a < TP::N; ++a) {
+        t.arow[w][a] = n;
+        n += Team<TP>::attach(w, a) ? A : 0;
+      }
+      for (int k = 0; k < TP::NV; ++k) {
+        t.krow[w][k] = n;
+        if (Team<TP>::above(w, TP::body_of(k))) n += (S ? TP::ddepth(k) + 1 : 0) + R;
+      }
+      t.base[w + 1] = t.base[w] + n;
+    }
+    return t;
+  }
+};
+template <class TP, int A, bool S, int R>
+struct TeamRows {
+  static constexpr int kRhs = R;
+  static constexpr TeamRowTab<TP, A, S, R> v = TeamRowTab<TP, A, S, R>::make();
+  static constexpr int arow(int w, int a) { return v.arow[w][a]; }
+  // entry (k, j) of the Schur complement, j an ancestor of k or k itself
+  static constexpr int srow(int w, int k, int j) { return v.krow[w][k] + TP::ddepth(j); }
+  static constexpr int yrow(int w, int k, int r) { return v.krow[w][k] + (S ? TP::ddepth(k) + 1 : 0) + r; }
+  static constexpr int base(int w) { return v.base[w]; }  // first row of wave w
+  static constexpr int total() { return v.base[Team<TP>::kWaves]; }
+};
+// Rows of the trunk's DoFs, in order (the trunk's solution).
+template <class TP>
+struct TrunkRowTab {
+  int row[TP::NV + 1];
+  static constexpr TrunkRowTab make() {
+    TrunkRowTab t = {};
+    for (int k = 0; k < TP::NV; ++k) t.row[k + 1] = t.row[k] + (Team<TP>::trunk(TP::body_of(k)) ? 1 : 0);
+    return t;
+  }
+};
+template <class TP>
+struct TrunkRows {
+  static constexpr TrunkRowTab<TP> v = TrunkRowTab<TP>::make();
+  static constexpr int row(int k) { return v.row[k]; }
+  static constexpr int total() { return v.row[TP::NV]; }
+};
+
+// A lane's column of a run of LDS rows.
+struct LdsCol {
+  float* p;
+  RBD_DI void put(int row, float v) const { p[row * kTileLanes] = v; }
+  RBD_DI float get(int row) const { return p[row * kTileLanes]; }
+  RBD_DI LdsCol at(int row) const { return {p + row * kTileLanes}; }
+};
+RBD_DI void put_frc(const LdsCol& c, int row, const Frc& f) {
+  c.put(row, f.n.x); c.put(row + 1, f.n.y); c.put(row + 2, f.n.z);
+  c.put(row + 3, f.f.x); c.put(row + 4, f.f.y); c.put(row + 5, f.f.z);
+}
+RBD_DI Frc get_frc(const LdsCol& c, int row) {
+  return {{c.get(row), c.get(row + 1), c.get(row + 2)}, {c.get(row + 3), c.get(row + 4), c.get(row + 5)}};
+}
+RBD_DI void put_inr(const LdsCol& c, int row, const Inr& I) {
+  c.put(row, I.m); c.put(row + 1, I.h.x); c.put(row + 2, I.h.y); c.put(row + 3, I.h.z);
+  c.put(row + 4, I.xx); c.put(row + 5, I.yy); c.put(row + 6, I.zz);
+  c.put(row + 7, I.xy); c.put(row + 8, I.xz); c.put(row + 9, I.yz);
+}
+RBD_DI Inr get_inr(const LdsCol& c, int row) {
+  return {c.get(row), {c.get(row + 1), c.get(row + 2), c.get(row + 3)}, c.get(row + 4), c.get(row + 5),
+          c.get(row + 6), c.get(row + 7), c.get(row + 8), c.get(row + 9)};
+}
+
+// Where a wave finds its own branches: the wave that runs the code of role W
+// with its bodies moved by `shift` reads and writes branch rows that much
+// further on; trunk rows stay where they are.
+struct TeamLane {
+  int wave;       // uniform
+  int shift;      // bodies, uniform
+  uint32_t lane;  // 0..63
+  uint32_t b;     // the lane's instance; lanes past the batch redo the last one
+};
+
+// Calls body(ic<W>, TeamLane) with W the role of the calling wave, for the 64
+// instances from `first` of `batch`. The branch is the same for a whole wave,
+// and every wave meets the barriers inside.
+template <class TP, class F>
+RBD_DI void team_roles(uint32_t first, int64_t batch, F&& body) {
+  using TM = Team<TP>;
+  TeamLane tl;
+  tl.wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kTileLanes);
+  tl.lane = threadIdx.x % kTileLanes;
+  const uint32_t b = first + tl.lane;
+  tl.b = b < batch ? b : (uint32_t)(batch - 1);
+  int role = 0;
+  tl.shift = 0;
+  sfor<0, TM::kWaves>([&](auto W_) __attribute__((always_inline)) {
+    constexpr int W = decltype(W_)::value;
+    if (tl.wave == W) {
+      role = TM::kPlan.role[W];
+      tl.shift = TM::kPlan.shift[W];
+    }
+  });
+  sfor<0, TM::kWaves>([&](auto W_) __attribute__((always_inline)) {
+    constexpr int W = decltype(W_)::value;
+    if constexpr (TM::own_code(W)) {
+      if (role == W) body(W_, tl);
+    }
+  });
+}
+
+// The row base of the calling wave among those that run the code of role W.
+template <class TP, class ROWS, int W>
+RBD_DI int team_base(const TeamLane& tl) {
+  using TM = Team<TP>;
+  int base = ROWS::base(W);
+  sfor<W + 1, TM::kWaves>([&](auto V_) __attribute__((always_inline)) {
+    constexpr int V = decltype(V_)::value;
+    if constexpr (TM::kPlan.role[V] == W) {
+      if (tl.wave == V) base = cidx<ROWS::base(V)>;
+    }
+  });
+  return base;
+}
+
+// Loads what role W reads of an input vector: entries of its own branches from
+// the moved view `br`, of the trunk bodies above them (ABOVE) from `tk`.
+// DOF: one entry per DoF (6 for a free base), else the entries of q.
+template <class TP, int W, bool ABOVE, bool DOF, class V, int n>
+RBD_DI void team_load(float (&x)[n], const V& br, const V& tk) {
+  using TM = Team<TP>;
+  sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
+    constexpr int I = decltype(I_)::value;
+    constexpr int o = DOF ? TP::vofs(I) : TP::qofs(I);
+    if constexpr (TM::in(W, I)) {
+      x[o] = br(o);
+    } else if constexpr (ABOVE && TM::above(W, I)) {
+      sfor<0, (TP::free_body(I) ? (DOF ? 6 : 7) : 1)>([&](auto C_) __attribute__((always_inline)) {
+        x[o + decltype(C_)::value] = tk(o + decltype(C_)::value);
+      });
+    }
+  });
+}
+
+// The same for all of the trunk (what the owner reads).
+template <class TP, bool DOF, class V, int n>
+RBD_DI void team_load_trunk(float (&x)[n], const V& tk) {
+  sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
+    constexpr int I = decltype(I_)::value;
+    constexpr int o = DOF ? TP::vofs(I) : TP::qofs(I);
+    if constexpr (Team<TP>::trunk(I)) {
+      sfor<0, (TP::free_body(I) ? (DOF ? 6 : 7) : 1)>([&](auto C_) __attribute__((always_inline)) {
+        x[o + decltype(C_)::value] = tk(o + decltype(C_)::value);
+      });
+    }
+  });
+}
+
+// f(column of rows) for every wave that left rows for trunk body J, in order.
+template <class TP, class ROWS, int J, class F>
+RBD_DI void team_collect(const LdsCol& lds, const F& f) {
+  sfor<0, Team<TP>::kWaves>([&](auto W_) __attribute__((always_inline)) {
+    constexpr int W = decltype(W_)::value;
+    if constexpr (Team<TP>::attach(W, J)) f(lds.at(cidx<ROWS::base(W) + ROWS::arow(W, J)>));
+  });
+}
+
+// =================================================================== forward dynamics
+// The state of the bias and mass-matrix sweep (see fwd_dyn_lane); only the
+// entries of the bodies a wave visits are ever used.
+template <class TP, bool EXT>
+struct TeamFd {
+  M3 R[TP::N];
+  Mot v[TP::N], a[TP::N];
+  Frc f[TP::N];
+  Inr Ic[TP::N];
+  M3 Rw[EXT ? TP::N : 1];
+  V3 pw[EXT ? TP::N : 1];
+};
+
+// Motion of body I from its parent's: joint rotation, velocity, bias
+// acceleration, world pose (external forces only).
+template <class TP, int I, class QI, class QDI, class ST, class FX>
+RBD_DI void team_fd_motion(const float* __restrict__ t, const QI& q, const QDI& qd, V3 mg, ST& s, const FX&) {
+  constexpr int P = TP::parent(I);
+  if constexpr (TP::free_body(I)) {
+    s.R[I] = quat_rot(q(3), q(4), q(5), q(6));
+    s.v[I] = {{qd(3), qd(4), qd(5)}, {qd(0), qd(1), qd(2)}};
+    s.a[I] = {{0.0f, 0.0f, 0.0f}, mulT(s.R[I], mg)};
+  } else {
+    s.R[I] = joint_rot<I>(t, q(cidx<TP::qofs(I)>));
+    const float w = qd(cidx<TP::vofs(I)>);
+    if constexpr (P < 0) {
+      s.v[I] = {{0.0f, 0.0f, w}, {0.0f, 0.0f, 0.0f}};
+      s.a[I] = {{0.0f, 0.0f, 0.0f}, mulT(s.R[I], mg)};
+    } else {
+      const V3 r = load_r<I>(t);
+      s.v[I] = xmot(s.R[I], r, s.v[P]);
+      s.v[I].w.z = s.v[I].w.z + w;
+      s.a[I] = xmot(s.R[I], r, s.a[P]);
+      s.a[I].w.x = s.a[I].w.x + w * s.v[I].w.y;
+      s.a[I].w.y = s.a[I].w.y - w * s.v[I].w.x;
+      s.a[I].v.x = s.a[I].v.x + w * s.v[I].v.y;
+      s.a[I].v.y = s.a[I].v.y - w * s.v[I].v.x;
+    }
+  }
+  if constexpr (FX::kOn) world_pose<TP, I>(t, q, s.R[I], s.Rw, s.pw);
+}
+// Its acceleration with qdd added.
+template <class TP, int I, class ST, class QDDI>
+RBD_DI void team_add_qdd(ST& s, const QDDI& qdd) {
+  if constexpr (TP::free_body(I)) s.a[I] = s.a[I] + Mot{{qdd(3), qdd(4), qdd(5)}, {qdd(0), qdd(1), qdd(2)}};
+  else s.a[I].w.z = s.a[I].w.z + qdd(cidx<TP::vofs(I)>);
+}
+// Its force and inertia.
+template <class TP, int I, class ST, class FX>
+RBD_DI void team_fd_force(const float* __restrict__ t, ST& s, const FX& fx) {
+  const Inr Ib = load_inr<I>(t);
+  s.f[I] = imul(Ib, s.a[I]) + crf(s.v[I], imul(Ib, s.v[I]));
+  if constexpr (FX::kOn) s.f[I] = s.f[I] - fext_body<I>(fx, s.Rw[I], s.pw[I]);
+  s.Ic[I] = Ib;
+}
+
+// The trunk's rows of the factor only see the trunk's own rows: the branches'
+// share has been taken off the mass matrix already.
+template <class TP>
+struct TrunkDofs {
+  static constexpr bool on(int k) { return Team<TP>::trunk(TP::body_of(k)); }
+};
+
+// walk_up over a branch of a wave and on over the trunk.
+template <class TP, int C, class EMIT>
+RBD_DI void team_walk_up(const float* __restrict__ t, const float* __restrict__ tb, const M3* R, Frc F, EMIT& emit) {
+  constexpr int A = TP::parent(C);
+  if constexpr (A >= 0) {
+    F = xfrc(R[C], load_r<C>(Team<TP>::trunk(C) ? t : tb), F);
+    emit(ic<A>{}, F);
+    team_walk_up<TP, A>(t, tb, R, F, emit);
+  }
+}
+
+// Branch W's share of trunk DoF K's right-hand side r.
+template <class TP, int W, int K, int r, class MASK = AllRhs, int NRHS>
+RBD_DI float team_yshare(const Ltl<TP, NRHS>& F) {
+  float acc = 0.0f;
+  sfor<K + 1, cidx<TP::dlast(K)> + 1>([&](auto D_) __attribute__((always_inline)) {
+    constexpr int D = decltype(D_)::value;
+    if constexpr (Team<TP>::in(W, TP::body_of(D)) && MASK::on(r, D))
+      acc = __builtin_fmaf(F.L[cidx<TP::lidx(D, K)>], F.y[r][D], acc);
+  });
+  return acc;
+}
+
+// What a caller adds to the sweep up: after a body's motion, its right-hand
+// sides (the bias force is taken off the first by default), after its row of
+// the factor.
+template <class RHS>
+struct FdHook {
+  const RHS& rhs;
+  template <class I, class ST>
+  RBD_DI void motion(I, const ST&) const {}
+  template <class J, class ST, int n>
+  RBD_DI void sides(J, int k, const ST& s, float (&b)[n]) const {
+#pragma unroll
+    for (int r = 0; r < n; ++r) b[r] = r == 0 ? rhs(r, k) - s.f[J::value].n.z : rhs(r, k);
+  }
+  template <class ST, int n>
+  RBD_DI void base_sides(int k, const ST& s, float (&b)[n]) const {
+    const float hb[6] = {s.f[0].f.x, s.f[0].f.y, s.f[0].f.z, s.f[0].n.x, s.f[0].n.y, s.f[0].n.z};
+#pragma unroll
+    for (int r = 0; r < n; ++r) b[r] = rhs(r, k) - (r == 0 ? hb[k] : 0.0f);
+  }
+  template <class J, class ST, class LF>
+  RBD_DI void closed(J, const ST&, const LF&) const {}
+};
+
+// Role W, up: its branches' rows of the factor, from the leaves to the trunk,
+// and their share of the trunk's (to LDS at `c`; of the right-hand sides the
+// ROWS::kRhs first).
+template <class TP, int W, int NRHS, class ROWS, class MASK = AllRhs, class QV, class QDV, class HOOK, class FX,
+          class ST>
+RBD_DI void team_fd_up(const float* __restrict__ t, const float* __restrict__ tb, const QV& q, const QDV& qd,
+                       HOOK&& hook, const FX& fx, ST& s, Ltl<TP, NRHS>& F, const LdsCol& c) {
+  using TM = Team<TP>;
+  constexpr int N = TP::N, NV = TP::NV;
+  const V3 g = load_g<TP>(t);
+  const V3 mg = {-g.x, -g.y, -g.z};
+  auto backward = [&](auto J_) __attribute__((always_inline)) {
+    constexpr int J = decltype(J_)::value;
+    constexpr int P = TP::parent(J);
+    if constexpr (TM::in(W, J)) {
+      constexpr int k = TP::vofs(J);
+      float Mr[NV];
+      {
+        auto emit = [&](auto A_, const Frc& e) __attribute__((always_inline)) {
+          constexpr int A = decltype(A_)::value;
+          if constexpr (TP::free_body(A)) {
+            Mr[0] = e.f.x; Mr[1] = e.f.y; Mr[2] = e.f.z;
+            Mr[3] = e.n.x; Mr[4] = e.n.y; Mr[5] = e.n.z;
+          } else {
+            Mr[cidx<TP::vofs(A)>] = e.n.z;
+          }
+        };
+        team_walk_up<TP, J>(t, tb, s.R, inr_col_z(s.Ic[J]), emit);
+      }
+      float bk[NRHS];
+      hook.sides(J_, k, s, bk);
+      ltl_row<TP, k, NRHS, MASK>(F, Mr, s.Ic[J].zz, bk);
+      hook.closed(J_, s, F);
+      if constexpr (P >= 0) {
+        const V3 r = load_r<J>(tb);
+        xfrc_acc(s.R[J], r, s.f[J], s.f[P]);
+        xinr_acc(s.R[J], r, s.Ic[J], s.Ic[P]);
+      }
+    }
+  };
+  sfor<0, N>([&](auto I_) __attribute__((always_inline)) {
+    constexpr int I = decltype(I_)::value;
+    if constexpr (TM::above(W, I)) {
+      team_fd_motion<TP, I>(t, q, qd, mg, s, fx);
+      hook.motion(I_, s);
+      if constexpr (TM::attach(W, I)) {  // sums what the branches exert on it
+        s.f[I] = Frc{};
+        s.Ic[I] = Inr{};
+      }
+    } else if constexpr (TM::in(W, I)) {
+      team_fd_motion<TP, I>(tb, q, qd, mg, s, fx);
+      hook.motion(I_, s);
+      team_fd_force<TP, I>(tb, s, fx);
+      close_subtrees<TP, I, I>(backward);
+    }
+  });
+  // to the trunk
+  sfor<0, N>([&](auto I_) __attribute__((always_inline)) {
+    constexpr int I = decltype(I_)::value;
+    if constexpr (TM::attach(W, I)) {
+      put_frc(c, ROWS::arow(W, I), s.f[I]);
+      put_inr(c, ROWS::arow(W, I) + 6, s.Ic[I]);
+    }
+  });
+  sfor<0, NV>([&](auto K_) __attribute__((always_inline)) {
+    constexpr int K = decltype(K_)::value;
+    if constexpr (TM::above(W, TP::body_of(K))) {
+      sfor<0, K + 1>([&](auto J_) __attribute__((always_inline)) {
+        constexpr int J = decltype(J_)::value;
+        if constexpr (J == K || TP::is_danc(J, K)) {
+          float acc = 0.0f;
+          sfor<K + 1, cidx<TP::dlast(K)> + 1>([&](auto D_) __attribute__((always_inline)) {
+            constexpr int D = decltype(D_)::value;
+            if constexpr (TM::in(W, TP::body_of(D)))
+              acc = __builtin_fmaf(F.L[cidx<TP::lidx(D, K)>], F.L[cidx<TP::lidx(D, J)>], acc);
+          });
+          c.put(cidx<ROWS::srow(W, K, J)>, acc);
+        }
+      });
+      sfor<0, ROWS::kRhs>([&](auto R_) __attribute__((always_inline)) {
+        constexpr int r = decltype(R_)::value;
+        c.put(cidx<ROWS::yrow(W, K, r)>, team_yshare<TP, W, K, r>(F));
+      });
+    }
+  });
+}
+
+// The owner's half of the way down: motion, force and inertia of the trunk
+// bodies (those above its own branches have their motion already).
+template <class TP, int W, class QV, class QDV, class FX, class ST>
+RBD_DI void team_fd_trunk_down(const float* __restrict__ t, const QV& q, const QDV& qd, const FX& fx, ST& s) {
+  using TM = Team<TP>;
+  const V3 g = load_g<TP>(t);
+  const V3 mg = {-g.x, -g.y, -g.z};
+  sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
+    constexpr int I = decltype(I_)::value;
+    if constexpr (TM::trunk(I)) {
+      if constexpr (!TM::above(W, I)) team_fd_motion<TP, I>(t, q, qd, mg, s, fx);
+      team_fd_force<TP, I>(t, s, fx);
+    }
+  });
+}
+
+// The trunk, leaves to root: takes over what the branches left in LDS and
+// factors the trunk's rows.
+template <class TP, int NRHS, class ROWS, class MASK = AllRhs, class ST, class HOOK>
+RBD_DI void team_fd_trunk(const float* __restrict__ t, HOOK&& hook, ST& s, const LdsCol& lds, Ltl<TP, NRHS>& F) {
+  using TM = Team<TP>;
+  constexpr int N = TP::N, NV = TP::NV;
+  // row K of the factor: the mass matrix less what the branches have used up
+  auto row = [&](auto K_, float* Mr, float Mkk, float* bk) __attribute__((always_inline)) {
+    constexpr int K = decltype(K_)::value;
+    sfor<0, TM::kWaves>([&](auto W_) __attribute__((always_inline)) {
+      constexpr int W = decltype(W_)::value;
+      if constexpr (TM::above(W, TP::body_of(K))) {
+        const LdsCol c = lds.at(cidx<ROWS::base(W)>);
+        sfor<0, K>([&](auto J_) __attribute__((always_inline)) {
+          constexpr int J = decltype(J_)::value;
+          if constexpr (TP::is_danc(J, K)) Mr[J] = Mr[J] - c.get(cidx<ROWS::srow(W, K, J)>);
+        });
+        Mkk = Mkk - c.get(cidx<ROWS::srow(W, K, K)>);
+#pragma unroll
+        for (int r = 0; r < ROWS::kRhs; ++r) bk[r] = bk[r] - c.get(cidx<ROWS::yrow(W, K, 0)> + r);
+      }
+    });
+    ltl_row<TP, K, NRHS, MASK, TrunkDofs<TP>>(F, Mr, Mkk, bk);
+  };
+  sfor_rev<0, N>([&](auto J_) __attribute__((always_inline)) {
+    constexpr int J = decltype(J_)::value;
+    constexpr int P = TP::parent(J);
+    if constexpr (TM::trunk(J)) {
+      team_collect<TP, ROWS, J>(lds, [&](const LdsCol& c) __attribute__((always_inline)) {
+        s.f[J] = s.f[J] + get_frc(c, 0);
+        s.Ic[J] = s.Ic[J] + get_inr(c, 6);
+      });
+      if constexpr (TP::free_body(J)) {
+        sfor_rev<0, 6>([&](auto K_) __attribute__((always_inline)) {
+          constexpr int K = decltype(K_)::value;
+          float Mr[6], bk[NRHS];
+#pragma unroll
+          for (int j = 0; j < K; ++j) Mr[j] = base_block(s.Ic[J], K, j);
+          hook.base_sides(K, s, bk);
+          row(K_, Mr, base_block(s.Ic[J], K, K), bk);
+        });
+        hook.closed(J_, s, F);
+      } else {
+        constexpr int k = TP::vofs(J);
+        float Mr[NV], bk[NRHS];
+        crba_row<TP, J>(t, s.R, s.Ic[J], Mr);
+        hook.sides(J_, k, s, bk);
+        row(ic<k>{}, Mr, s.Ic[J].zz, bk);
+        hook.closed(J_, s, F);
+        if constexpr (P >= 0) {
+          const V3 r = load_r<J>(t);
+          xfrc_acc(s.R[J], r, s.f[J], s.f[P]);
+          xinr_acc(s.R[J], r, s.Ic[J], s.Ic[P]);
+        }
+      }
+    }
+  });
+}
+
+// Role W, down: x of its branches, given the trunk's (xt(r, k)).
+template <class TP, int W, int NRHS, class XT, class SINK>
+RBD_DI void team_fd_back(const Ltl<TP, NRHS>& F, const XT& xt, const SINK& sink) {
+  using TM = Team<TP>;
+  constexpr int NV = TP::NV;
+  sfor<0, NRHS>([&](auto R_) __attribute__((always_inline)) {
+    constexpr int r = decltype(R_)::value;
+    float x[NV];
+    sfor<0, NV>([&](auto K_) __attribute__((always_inline)) {
+      constexpr int K = decltype(K_)::value;
+      if constexpr (TM::above(W, TP::body_of(K))) {
+        x[K] = xt(r, K);
+      } else if constexpr (TM::in(W, TP::body_of(K))) {
+        float acc = F.y[r][K];
+        sfor<0, K>([&](auto J_) __attribute__((always_inline)) {
+          constexpr int Jd = decltype(J_)::value;
+          if constexpr (TP::is_danc(Jd, K)) acc = acc - F.L[cidx<TP::lidx(K, Jd)>] * x[Jd];
+        });
+        x[K] = acc * F.Linv[K];
+        sink(r, K, x[K]);
+      }
+    });
+  });
+}
+
+// Forward dynamics of role W with NRHS right-hand sides, three phases with a
+// barrier between: the branches up (rhs reads branch entries), the trunk by the
+// owner (rhs_t reads trunk entries), the branches down. q, qd: the role's and,
+// for the owner, the trunk's entries. xrow keeps the trunk's solution, one run
+// of rows per right-hand side; F the role's rows of the factor, Ft the trunk's
+// (owner). sink(r, k, x) gets the role's branches, sink_t the trunk (owner).
+template <class TP, int W, int NRHS, class ROWS, class QV, class QDV, class RHS, class RHST, class FX, class SINK,
+          class SINKT>
+RBD_DI void team_fd(const TeamLane& tl, bool owner, const float* __restrict__ t, const QV& q, const QDV& qd,
+                    const RHS& rhs, const RHST& rhs_t, const FX& fxb, const FX& fx, const LdsCol& lds,
+                    const LdsCol& xrow, Ltl<TP, NRHS>& F, Ltl<TP, NRHS>& Ft, const SINK& sink, const SINKT& sink_t) {
+  using TM = Team<TP>;
+  constexpr int T = TrunkRows<TP>::total();
+  TeamFd<TP, FX::kOn> s;
+  team_fd_up<TP, W, NRHS, ROWS>(t, t + tl.shift * kBodyStride, q, qd, FdHook<RHS>{rhs}, fxb, s, F,
+                                lds.at(team_base<TP, ROWS, W>(tl)));
+  if constexpr (TM::may_own(W)) {
+    if (owner) team_fd_trunk_down<TP, W>(t, q, qd, fx, s);
+  }
+  __syncthreads();
+  if constexpr (TM::may_own(W)) {
+    if (owner) {
+      team_fd_trunk<TP, NRHS, ROWS>(t, FdHook<RHST>{rhs_t}, s, lds, Ft);
+      ltl_back<TP, NRHS, TrunkDofs<TP>>(Ft, [&](int r, int k, float x) __attribute__((always_inline)) {
+        xrow.put(r * T + TrunkRows<TP>::row(k), x);
+        sink_t(r, k, x);
+      });
+    }
+  }
+  __syncthreads();
+  team_fd_back<TP, W, NRHS>(
+      F, [&](int r, int k) __attribute__((always_inline)) { return xrow.get(r * T + TrunkRows<TP>::row(k)); }, sink);
+}
+
+// =================================================================== inverse dynamics
+// Role W: torques of its branches; the force on the trunk goes to LDS.
+template <class TP, int W, class ROWS, bool HAS_QDD, class QV, class QDV, class QDDV, class FX, class ST, class TO>
+RBD_DI void team_id_up(const float* __restrict__ t, const float* __restrict__ tb, const QV& q, const QDV& qd,
+                       const QDDV& qdd, const FX& fx, ST& s, const LdsCol& c, const TO& tau) {
+  using TM = Team<TP>;
+  const V3 g = load_g<TP>(t);
+  const V3 mg = {-g.x, -g.y, -g.z};
+  auto backward = [&](auto J_) __attribute__((always_inline)) {
+    constexpr int J = decltype(J_)::value;
+    constexpr int P = TP::parent(J);
+    if constexpr (TM::in(W, J)) {
+      tau(cidx<TP::vofs(J)>, s.f[J].n.z);
+      if constexpr (P >= 0) xfrc_acc(s.R[J], load_r<J>(tb), s.f[J], s.f[P]);
+    }
+  };
+  sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
+    constexpr int I = decltype(I_)::value;
+    if constexpr (TM::above(W, I)) {
+      team_fd_motion<TP, I>(t, q, qd, mg, s, fx);
+      if constexpr (HAS_QDD) team_add_qdd<TP, I>(s, qdd);
+      if constexpr (TM::attach(W, I)) s.f[I] = Frc{};
+    } else if constexpr (TM::in(W, I)) {
+      team_fd_motion<TP, I>(tb, q, qd, mg, s, fx);
+      if constexpr (HAS_QDD) team_add_qdd<TP, I>(s, qdd);
+      team_fd_force<TP, I>(tb, s, fx);
+      close_subtrees<TP, I, I>(backward);
+    }
+  });
+  sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
+    constexpr int I = decltype(I_)::value;
+    if constexpr (TM::attach(W, I)) put_frc(c, ROWS::arow(W, I), s.f[I]);
+  });
+}
+template <class TP, int W, bool HAS_QDD, class QV, class QDV, class QDDV, class FX, class ST>
+RBD_DI void team_id_trunk_down(const float* __restrict__ t, const QV& q, const QDV& qd, const QDDV& qdd, const FX& fx,
+                               ST& s) {
+  using TM = Team<TP>;
+  const V3 g = load_g<TP>(t);
+  const V3 mg = {-g.x, -g.y, -g.z};
+  sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
+    constexpr int I = decltype(I_)::value;
+    if constexpr (TM::trunk(I)) {
+      if constexpr (!TM::above(W, I)) {
+        team_fd_motion<TP, I>(t, q, qd, mg, s, fx);
+        if constexpr (HAS_QDD) team_add_qdd<TP, I>(s, qdd);
+      }
+      team_fd_force<TP, I>(t, s, fx);
+    }
+  });
+}
+template <class TP, class ROWS, class ST, class TO>
+RBD_DI void team_id_trunk(const float* __restrict__ t, ST& s, const LdsCol& lds, const TO& tau) {
+  using TM = Team<TP>;
+  sfor_rev<0, TP::N>([&](auto J_) __attribute__((always_inline)) {
+    constexpr int J = decltype(J_)::value;
+    constexpr int P = TP::parent(J);
+    if constexpr (TM::trunk(J)) {
+      team_collect<TP, ROWS, J>(
+          lds, [&](const LdsCol& c) __attribute__((always_inline)) { s.f[J] = s.f[J] + get_frc(c, 0); });
+      if constexpr (TP::free_body(J)) {
+        tau(0, s.f[J].f.x); tau(1, s.f[J].f.y); tau(2, s.f[J].f.z);
+        tau(3, s.f[J].n.x); tau(4, s.f[J].n.y); tau(5, s.f[J].n.z);
+      } else {
+        tau(cidx<TP::vofs(J)>, s.f[J].n.z);
+        if constexpr (P >= 0) xfrc_acc(s.R[J], load_r<J>(t), s.f[J], s.f[P]);
+      }
+    }
+  });
+}
+
+// =================================================================== adjoint of inverse dynamics
+// Role W: the outputs of its branches (see id_adjoint_lane); its share of the
+// trunk's totals goes to LDS.
+template <class TP, int W, class ROWS, class ST, class QV, class QDV, class QDDV, class LAM, class GQ, class GQD,
+          class FX, class GF, class GQDD>
+RBD_DI void team_adj_up(const float* __restrict__ t, const float* __restrict__ tb, ST& s, const QV& q, const QDV& qd,
+                        const QDDV& qdd, const LAM& lam, const GQ& gq, const GQD& gqd, const FX& fx, const GF& gf,
+                        const GQDD& gqdd, const LdsCol& c) {
+  using TM = Team<TP>;
+  const V3 g = load_g<TP>(t);
+  const V3 mg = {-g.x, -g.y, -g.z};
+  auto backward = [&](auto J_) __attribute__((always_inline)) {
+    constexpr int J = decltype(J_)::value;
+    if constexpr (TM::in(W, J)) adj_close<TP, J>(tb, g, s, q, qd, gq, gqd, gqdd);
+  };
+  sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
+    constexpr int I = decltype(I_)::value;
+    if constexpr (TM::above(W, I)) {
+      adj_motion<TP, I>(t, mg, s, q, qd, qdd, lam);
+      if constexpr (TM::attach(W, I)) {  // sums what the branches add to its totals
+        s.f[I] = Frc{};
+        s.ab[I] = Frc{};
+        s.vb[I] = Frc{};
+        if constexpr (ST::kExt) {
+          s.Fs[I] = Frc{};
+          s.Ws[I] = Frc{};
+        }
+      }
+    } else if constexpr (TM::in(W, I)) {
+      adj_motion<TP, I>(tb, mg, s, q, qd, qdd, lam);
+      adj_force<TP, I>(tb, s, fx, gf);
+      close_subtrees<TP, I, I>(backward);
+    }
+  });
+  sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
+    constexpr int I = decltype(I_)::value;
+    if constexpr (TM::attach(W, I)) {
+      constexpr int r = ROWS::arow(W, I);
+      put_frc(c, r, s.f[I]);
+      put_frc(c, r + 6, s.ab[I]);
+      put_frc(c, r + 12, s.vb[I]);
+      if constexpr (ST::kExt) {
+        put_frc(c, r + 18, s.Fs[I]);
+        put_frc(c, r + 24, s.Ws[I]);
+      }
+    }
+  });
+}
+template <class TP, int W, class ST, class QV, class QDV, class QDDV, class LAM, class FX, class GF>
+RBD_DI void team_adj_trunk_down(const float* __restrict__ t, ST& s, const QV& q, const QDV& qd, const QDDV& qdd,
+                                const LAM& lam, const FX& fx, const GF& gf) {
+  using TM = Team<TP>;
+  const V3 g = load_g<TP>(t);
+  const V3 mg = {-g.x, -g.y, -g.z};
+  sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
+    constexpr int I = decltype(I_)::value;
+    if constexpr (TM::trunk(I)) {
+      if constexpr (!TM::above(W, I)) adj_motion<TP, I>(t, mg, s, q, qd, qdd, lam);
+      adj_force<TP, I>(t, s, fx, gf);
+    }
+  });
+}
+template <class TP, class ROWS, class ST, class QV, class QDV, class GQ, class GQD, class GQDD>
+RBD_DI void team_adj_trunk(const float* __restrict__ t, ST& s, const QV& q, const QDV& qd, const GQ& gq,
+                           const GQD& gqd, const GQDD& gqdd, const LdsCol& lds) {
+  const V3 g = load_g<TP>(t);
+  sfor_rev<0, TP::N>([&](auto J_) __attribute__((always_inline)) {
+    constexpr int J = decltype(J_)::value;
+    if constexpr (Team<TP>::trunk(J)) {
+      team_collect<TP, ROWS, J>(lds, [&](const LdsCol& c) __attribute__((always_inline)) {
+        s.f[J] = s.f[J] + get_frc(c, 0);
+        s.ab[J] = s.ab[J] + get_frc(c, 6);
+        s.vb[J] = s.vb[J] + get_frc(c, 12);
+        if constexpr (ST::kExt) {
+          s.Fs[J] = s.Fs[J] + get_frc(c, 18);
+          s.Ws[J] = s.Ws[J] + get_frc(c, 24);
+        }
+      });
+      adj_close<TP, J>(t, g, s, q, qd, gq, gqd, gqdd);
+    }
+  });
+}
+
+}  // namespace rbd
