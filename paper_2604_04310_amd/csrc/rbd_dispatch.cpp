@@ -237,6 +237,7 @@ rbd_status launch_fwd_dyn_jvp(const rbd_model* m, int64_t batch, int64_t ld, con
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &qd, &tau, &dq, &dqd, &dtau, &qdd, &dqdd, &fext, &dfext};
   const bool ext = fext || dfext;
+  if (teamed(m, batch)) return launch(m, ext ? KID_JVP_EXT_TEAM : KID_JVP_TEAM, team_shape(m, batch), a, s, "rbd_fwd_dyn_jvp");
   if (large(m) && batch <= kOneWavePerSimd / 2) {
     // two waves per 64 instances: the factor of M on its own wave, in
     // parallel with the solve for qdd and the tangent
@@ -254,6 +255,8 @@ rbd_status launch_rnea_jvp(const rbd_model* m, int64_t batch, int64_t ld, const 
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &qd, &qdd, &dq, &dqd, &dqdd, &dtau, &fext, &dfext};
   const bool ext = fext || dfext;
+  if (teamed(m, batch))
+    return launch(m, ext ? KID_RNEA_JVP_EXT_TEAM : KID_RNEA_JVP_TEAM, team_shape(m, batch), a, s, "rbd_rnea_jvp");
   const KernelId id = ext ? KID_RNEA_JVP_EXT : (preload_inputs(large(m)) ? KID_RNEA_JVP_PRE : KID_RNEA_JVP);
   return launch(m, id, heavy_shape(batch), a, s, "rbd_rnea_jvp");
 }
@@ -266,6 +269,8 @@ rbd_status launch_rnea_vjp(const rbd_model* m, int64_t batch, int64_t ld, const 
   const bool ext = gfext || (fext && gq);
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &qd, &qdd, &lam, &gq, &gqd, &gqdd, &fext, &gfext};
+  if (teamed(m, batch))
+    return launch(m, ext ? KID_RNEA_VJP_EXT_TEAM : KID_RNEA_VJP_TEAM, team_shape(m, batch), a, s, "rbd_rnea_vjp");
   return launch(m, ext ? KID_RNEA_VJP_EXT : KID_RNEA_VJP, heavy_shape(batch), a, s, "rbd_rnea_vjp");
 }
 

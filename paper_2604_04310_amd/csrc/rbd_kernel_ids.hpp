@@ -55,10 +55,16 @@
   X(KID_FWD_DYN_TEAM_EXT, 9, k_fwd_dyn_team<TP, true>)    \
   X(KID_VJP_TEAM, 10, k_fwd_dyn_vjp_team<TP, false>)      \
   X(KID_VJP_EXT_TEAM, 10, k_fwd_dyn_vjp_team<TP, true>)   \
+  X(KID_JVP_TEAM, 11, k_fwd_dyn_jvp_team<TP, false>)      \
+  X(KID_JVP_EXT_TEAM, 11, k_fwd_dyn_jvp_team<TP, true>)   \
   X(KID_RNEA_TEAM, 9, k_rnea_team<TP, true, false>)       \
   X(KID_RNEA_BIAS_TEAM, 9, k_rnea_team<TP, false, false>) \
   X(KID_RNEA_EXT_TEAM, 9, k_rnea_team<TP, true, true>)    \
-  X(KID_RNEA_BIAS_EXT_TEAM, 9, k_rnea_team<TP, false, true>)
+  X(KID_RNEA_BIAS_EXT_TEAM, 9, k_rnea_team<TP, false, true>) \
+  X(KID_RNEA_JVP_TEAM, 12, k_rnea_jvp_team<TP, false>)    \
+  X(KID_RNEA_JVP_EXT_TEAM, 12, k_rnea_jvp_team<TP, true>) \
+  X(KID_RNEA_VJP_TEAM, 12, k_rnea_vjp_team<TP, false>)    \
+  X(KID_RNEA_VJP_EXT_TEAM, 12, k_rnea_vjp_team<TP, true>)
 
 namespace rbd {
 

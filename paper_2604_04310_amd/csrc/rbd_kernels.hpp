@@ -464,45 +464,47 @@ __global__ __launch_bounds__(kBlock) void k_fwd_dyn_jvp(const float* __restrict_
                                                         const float* __restrict__ dtau, float* qdd, float* dqdd,
                                                         const float* __restrict__ fext,
                                                         const float* __restrict__ dfext) {
-  RBD_LANE_IO(TP);
-  const uint32_t b = lane_id();
-  if (b >= batch) return;
-  float* park = qdd ? qdd : dqdd;
-  auto fx_view = [&](const float* p, int64_t l) __attribute__((always_inline)) {
-    if constexpr (EXT) return FextOpt{{p, l, b}};
-    else return NoFext{};
-  };
-  fwd_dyn_lane<TP, 1>(tab, In{q, ld, b}, In{qd, ld, b}, RhsOne<In>{In{tau, ld, b}},
-                      SinkOne<OutAlias>{OutAlias{park, ld, b}}, fx_view(fext, ld));
-  // a large tree gives each sweep fresh views (see k_fwd_dyn_vjp)
-  constexpr bool kFresh = TP::NV > 16;
-  auto view = [](auto x) __attribute__((always_inline)) {
-    if constexpr (kFresh) return opaque(x);
-    else return x;
-  };
-  auto view_table = [](const float* x) __attribute__((always_inline)) {
-    if constexpr (kFresh) return opaque_table(x);
-    else return x;
-  };
-  const int64_t ld2 = view(ld);
-  if constexpr (kFresh && !EXT) {
-    // every input load of the tangent sweep issued at its start, as in k_rnea_jvp
-    constexpr int NQ = TP::NQ, NV = TP::NV;
-    float qv[NQ], qdv[NV], dqv[NQ], dqdv[NV], dtv[NV];
-    preload_inputs<NQ>(qv, dqv, In{view(q), ld2, b}, In{dq, ld2, b});
-    preload_inputs<NV>(qdv, dqdv, In{view(qd), ld2, b}, In{dqd, ld2, b});
-    preload_inputs<NV>(dtv, In{dtau, ld2, b});
-    id_tangent_lane<TP>(view_table(tab), RegView{qv}, RegView{qdv}, InAlias{park, ld2, b}, RegView{dqv},
-                        RegView{dqdv}, RegView{dtv}, OutAlias{dqdd, ld2, b});
-  } else {
-    id_tangent_lane<TP>(view_table(tab), In{view(q), ld2, b}, In{view(qd), ld2, b}, InAlias{park, ld2, b},
-                        In{dq, ld2, b}, In{dqd, ld2, b}, In{dtau, ld2, b}, OutAlias{dqdd, ld2, b},
-                        fx_view(fext, ld2), fx_view(dfext, ld2));
+  if constexpr (!Team<TP>::kAlways) {
+    RBD_LANE_IO(TP);
+    const uint32_t b = lane_id();
+    if (b >= batch) return;
+    float* park = qdd ? qdd : dqdd;
+    auto fx_view = [&](const float* p, int64_t l) __attribute__((always_inline)) {
+      if constexpr (EXT) return FextOpt{{p, l, b}};
+      else return NoFext{};
+    };
+    fwd_dyn_lane<TP, 1>(tab, In{q, ld, b}, In{qd, ld, b}, RhsOne<In>{In{tau, ld, b}},
+                        SinkOne<OutAlias>{OutAlias{park, ld, b}}, fx_view(fext, ld));
+    // a large tree gives each sweep fresh views (see k_fwd_dyn_vjp)
+    constexpr bool kFresh = TP::NV > 16;
+    auto view = [](auto x) __attribute__((always_inline)) {
+      if constexpr (kFresh) return opaque(x);
+      else return x;
+    };
+    auto view_table = [](const float* x) __attribute__((always_inline)) {
+      if constexpr (kFresh) return opaque_table(x);
+      else return x;
+    };
+    const int64_t ld2 = view(ld);
+    if constexpr (kFresh && !EXT) {
+      // every input load of the tangent sweep issued at its start, as in k_rnea_jvp
+      constexpr int NQ = TP::NQ, NV = TP::NV;
+      float qv[NQ], qdv[NV], dqv[NQ], dqdv[NV], dtv[NV];
+      preload_inputs<NQ>(qv, dqv, In{view(q), ld2, b}, In{dq, ld2, b});
+      preload_inputs<NV>(qdv, dqdv, In{view(qd), ld2, b}, In{dqd, ld2, b});
+      preload_inputs<NV>(dtv, In{dtau, ld2, b});
+      id_tangent_lane<TP>(view_table(tab), RegView{qv}, RegView{qdv}, InAlias{park, ld2, b}, RegView{dqv},
+                          RegView{dqdv}, RegView{dtv}, OutAlias{dqdd, ld2, b});
+    } else {
+      id_tangent_lane<TP>(view_table(tab), In{view(q), ld2, b}, In{view(qd), ld2, b}, InAlias{park, ld2, b},
+                          In{dq, ld2, b}, In{dqd, ld2, b}, In{dtau, ld2, b}, OutAlias{dqdd, ld2, b},
+                          fx_view(fext, ld2), fx_view(dfext, ld2));
+    }
+    const int64_t ld3 = view(ld2);
+    fwd_dyn_lane<TP, 1, In, In, RhsOne<InAlias>, SinkOne<OutAlias>, NoFext, false>(
+        view_table(tab), In{view(q), ld3, b}, In{qd, ld3, b}, RhsOne<InAlias>{InAlias{dqdd, ld3, b}},
+        SinkOne<OutAlias>{OutAlias{dqdd, ld3, b}});
   }
-  const int64_t ld3 = view(ld2);
-  fwd_dyn_lane<TP, 1, In, In, RhsOne<InAlias>, SinkOne<OutAlias>, NoFext, false>(
-      view_table(tab), In{view(q), ld3, b}, In{qd, ld3, b}, RhsOne<InAlias>{InAlias{dqdd, ld3, b}},
-      SinkOne<OutAlias>{OutAlias{dqdd, ld3, b}});
 }
 
 // ---- the same tangent on two waves per 64 instances (a block of 128 lanes),
@@ -517,54 +519,56 @@ __global__ __launch_bounds__(2 * kTileLanes) void k_fwd_dyn_jvp_split(
     const float* __restrict__ qd, const float* __restrict__ tau, const float* __restrict__ dq,
     const float* __restrict__ dqd, const float* __restrict__ dtau, float* qdd, float* dqdd,
     const float* __restrict__ fext, const float* __restrict__ dfext) {
-  RBD_LANE_IO(TP);
-  constexpr int NV = TP::NV;
-  extern __shared__ float lds_jvp[];
-  const uint32_t lane = threadIdx.x % kTileLanes;
-  const bool solver = threadIdx.x >= kTileLanes;
-  const uint32_t b = blockIdx.x * kTileLanes + lane;
-  const bool valid = b < batch;
-  float* const rhs = lds_jvp + lane;
-  float* const qpark = lds_jvp + NV * kTileLanes + lane;
-  auto fx_view = [&](const float* p, int64_t l) __attribute__((always_inline)) {
-    if constexpr (EXT) return FextOpt{{p, l, b}};
-    else return NoFext{};
-  };
-  Ltl<TP, 1> F;
-  if (!solver) {
-    if (valid) {
-      fwd_dyn_lane<TP, 1>(tab, In{q, ld, b}, In{qd, ld, b}, RhsOne<In>{In{tau, ld, b}},
-                          SinkOne<LdsRow>{LdsRow{qpark}}, fx_view(fext, ld));
-      if (qdd) {
-        sfor<0, NV>([&](auto K_) __attribute__((always_inline)) {
-          constexpr int K = decltype(K_)::value;
-          Out{qdd, ld, b}(K, qpark[K * kTileLanes]);
-        });
+  if constexpr (!Team<TP>::kAlways) {
+    RBD_LANE_IO(TP);
+    constexpr int NV = TP::NV;
+    extern __shared__ float lds_jvp[];
+    const uint32_t lane = threadIdx.x % kTileLanes;
+    const bool solver = threadIdx.x >= kTileLanes;
+    const uint32_t b = blockIdx.x * kTileLanes + lane;
+    const bool valid = b < batch;
+    float* const rhs = lds_jvp + lane;
+    float* const qpark = lds_jvp + NV * kTileLanes + lane;
+    auto fx_view = [&](const float* p, int64_t l) __attribute__((always_inline)) {
+      if constexpr (EXT) return FextOpt{{p, l, b}};
+      else return NoFext{};
+    };
+    Ltl<TP, 1> F;
+    if (!solver) {
+      if (valid) {
+        fwd_dyn_lane<TP, 1>(tab, In{q, ld, b}, In{qd, ld, b}, RhsOne<In>{In{tau, ld, b}},
+                            SinkOne<LdsRow>{LdsRow{qpark}}, fx_view(fext, ld));
+        if (qdd) {
+          sfor<0, NV>([&](auto K_) __attribute__((always_inline)) {
+            constexpr int K = decltype(K_)::value;
+            Out{qdd, ld, b}(K, qpark[K * kTileLanes]);
+          });
+        }
+        sweep_boundary();
+        const int64_t l2 = opaque(ld);
+        if constexpr (!EXT) {
+          // every input load of the tangent sweep issued at its start, as in k_rnea_jvp
+          constexpr int NQ = TP::NQ;
+          float qv[NQ], qdv[NV], dqv[NQ], dqdv[NV], dtv[NV];
+          preload_inputs<NQ>(qv, dqv, In{opaque(q), l2, b}, In{dq, l2, b});
+          preload_inputs<NV>(qdv, dqdv, In{opaque(qd), l2, b}, In{dqd, l2, b});
+          preload_inputs<NV>(dtv, In{dtau, l2, b});
+          id_tangent_lane<TP>(opaque_table(tab), RegView{qv}, RegView{qdv}, LdsRow::In{qpark}, RegView{dqv},
+                              RegView{dqdv}, RegView{dtv}, LdsRow{rhs});
+        } else {
+          id_tangent_lane<TP>(opaque_table(tab), In{opaque(q), l2, b}, In{opaque(qd), l2, b}, LdsRow::In{qpark},
+                              In{dq, l2, b}, In{dqd, l2, b}, In{dtau, l2, b}, LdsRow{rhs}, fx_view(opaque(fext), l2),
+                              fx_view(opaque(dfext), l2));
+        }
       }
-      sweep_boundary();
-      const int64_t l2 = opaque(ld);
-      if constexpr (!EXT) {
-        // every input load of the tangent sweep issued at its start, as in k_rnea_jvp
-        constexpr int NQ = TP::NQ;
-        float qv[NQ], qdv[NV], dqv[NQ], dqdv[NV], dtv[NV];
-        preload_inputs<NQ>(qv, dqv, In{opaque(q), l2, b}, In{dq, l2, b});
-        preload_inputs<NV>(qdv, dqdv, In{opaque(qd), l2, b}, In{dqd, l2, b});
-        preload_inputs<NV>(dtv, In{dtau, l2, b});
-        id_tangent_lane<TP>(opaque_table(tab), RegView{qv}, RegView{qdv}, LdsRow::In{qpark}, RegView{dqv},
-                            RegView{dqdv}, RegView{dtv}, LdsRow{rhs});
-      } else {
-        id_tangent_lane<TP>(opaque_table(tab), In{opaque(q), l2, b}, In{opaque(qd), l2, b}, LdsRow::In{qpark},
-                            In{dq, l2, b}, In{dqd, l2, b}, In{dtau, l2, b}, LdsRow{rhs}, fx_view(opaque(fext), l2),
-                            fx_view(opaque(dfext), l2));
-      }
+    } else if (valid) {
+      ltl_factor_lane<TP>(tab, In{q, ld, b}, F);
     }
-  } else if (valid) {
-    ltl_factor_lane<TP>(tab, In{q, ld, b}, F);
-  }
-  __syncthreads();
-  if (solver && valid) {
-    ltl_solve_y<TP>(F, LdsRow::In{rhs});
-    ltl_back<TP, 1>(F, [&](int, int k, float v) __attribute__((always_inline)) { Out{dqdd, ld, b}(k, v); });
+    __syncthreads();
+    if (solver && valid) {
+      ltl_solve_y<TP>(F, LdsRow::In{rhs});
+      ltl_back<TP, 1>(F, [&](int, int k, float v) __attribute__((always_inline)) { Out{dqdd, ld, b}(k, v); });
+    }
   }
 }
 
@@ -591,34 +595,36 @@ __global__ __launch_bounds__(kBlock) void k_rnea_jvp(const float* __restrict__ t
                                                      const float* __restrict__ dqd, const float* __restrict__ dqdd,
                                                      float* __restrict__ dtau, const float* __restrict__ fext,
                                                      const float* __restrict__ dfext) {
-  RBD_LANE_IO(TP);
-  const uint32_t b = lane_id();
-  if (b >= batch) return;
-  auto fx_view = [&](const float* p) __attribute__((always_inline)) {
-    if constexpr (EXT) return FextOpt{{p, ld, b}};
-    else return NoFext{};
-  };
-  if constexpr (PRE && !EXT) {
-    constexpr int NQ = TP::NQ, NV = TP::NV;
-    float qv[NQ], qdv[NV], qddv[NV], dqv[NQ], dqdv[NV], dqddv[NV];
-    const In qi{q, ld, b}, qdi{qd, ld, b}, qddi{qdd, ld, b}, dqi{dq, ld, b}, dqdi{dqd, ld, b}, dqddi{dqdd, ld, b};
-    sfor<0, NQ>([&](auto K_) __attribute__((always_inline)) {
-      constexpr int K = decltype(K_)::value;
-      qv[K] = qi(K);
-      dqv[K] = dqi(K);
-    });
-    sfor<0, NV>([&](auto K_) __attribute__((always_inline)) {
-      constexpr int K = decltype(K_)::value;
-      qdv[K] = qdi(K);
-      qddv[K] = qddi(K);
-      dqdv[K] = dqdi(K);
-      dqddv[K] = dqddi(K);
-    });
-    id_tangent_lane<TP>(tab, RegView{qv}, RegView{qdv}, RegView{qddv}, RegView{dqv}, RegView{dqdv}, NoFext{},
-                        Neg<Out>{Out{dtau, ld, b}}, NoFext{}, NoFext{}, On<RegView>{RegView{dqddv}});
-  } else {
-    id_tangent_lane<TP>(tab, In{q, ld, b}, In{qd, ld, b}, In{qdd, ld, b}, In{dq, ld, b}, In{dqd, ld, b}, NoFext{},
-                        Neg<Out>{Out{dtau, ld, b}}, fx_view(fext), fx_view(dfext), On<In>{In{dqdd, ld, b}});
+  if constexpr (!Team<TP>::kAlways) {
+    RBD_LANE_IO(TP);
+    const uint32_t b = lane_id();
+    if (b >= batch) return;
+    auto fx_view = [&](const float* p) __attribute__((always_inline)) {
+      if constexpr (EXT) return FextOpt{{p, ld, b}};
+      else return NoFext{};
+    };
+    if constexpr (PRE && !EXT) {
+      constexpr int NQ = TP::NQ, NV = TP::NV;
+      float qv[NQ], qdv[NV], qddv[NV], dqv[NQ], dqdv[NV], dqddv[NV];
+      const In qi{q, ld, b}, qdi{qd, ld, b}, qddi{qdd, ld, b}, dqi{dq, ld, b}, dqdi{dqd, ld, b}, dqddi{dqdd, ld, b};
+      sfor<0, NQ>([&](auto K_) __attribute__((always_inline)) {
+        constexpr int K = decltype(K_)::value;
+        qv[K] = qi(K);
+        dqv[K] = dqi(K);
+      });
+      sfor<0, NV>([&](auto K_) __attribute__((always_inline)) {
+        constexpr int K = decltype(K_)::value;
+        qdv[K] = qdi(K);
+        qddv[K] = qddi(K);
+        dqdv[K] = dqdi(K);
+        dqddv[K] = dqddi(K);
+      });
+      id_tangent_lane<TP>(tab, RegView{qv}, RegView{qdv}, RegView{qddv}, RegView{dqv}, RegView{dqdv}, NoFext{},
+                          Neg<Out>{Out{dtau, ld, b}}, NoFext{}, NoFext{}, On<RegView>{RegView{dqddv}});
+    } else {
+      id_tangent_lane<TP>(tab, In{q, ld, b}, In{qd, ld, b}, In{qdd, ld, b}, In{dq, ld, b}, In{dqd, ld, b}, NoFext{},
+                          Neg<Out>{Out{dtau, ld, b}}, fx_view(fext), fx_view(dfext), On<In>{In{dqdd, ld, b}});
+    }
   }
 }
 
@@ -633,30 +639,32 @@ __global__ __launch_bounds__(kBlock) void k_rnea_vjp(const float* __restrict__ t
                                                      float* __restrict__ gq, float* __restrict__ gqd,
                                                      float* __restrict__ gqdd, const float* __restrict__ fext,
                                                      float* __restrict__ gfext) {
-  RBD_LANE_IO(TP);
-  const uint32_t b = lane_id();
-  if (b >= batch) return;
-  auto opt = [&](float* p) __attribute__((always_inline)) { return OutOpt<Out>{Out{p, ld, b}, p != nullptr}; };
-  auto fx_view = [&]() __attribute__((always_inline)) {
-    if constexpr (EXT) return FextOpt{{fext, ld, b}};
-    else return NoFext{};
-  };
-  auto gf_view = [&]() __attribute__((always_inline)) {
-    if constexpr (EXT) return Neg<GFOut>{GFOut{{gfext, ld, b}}};
-    else return NoGF{};
-  };
-  if constexpr (TP::NV > 16 && !EXT) {
-    // every input load issued at entry, as in k_rnea_jvp
-    constexpr int NQ = TP::NQ, NV = TP::NV;
-    float qv[NQ], qdv[NV], qddv[NV], lv[NV];
-    preload_inputs<NQ>(qv, In{q, ld, b});
-    preload_inputs<NV>(qdv, qddv, In{qd, ld, b}, In{qdd, ld, b});
-    preload_inputs<NV>(lv, In{lam, ld, b});
-    id_adjoint_lane<TP>(tab, RegView{qv}, RegView{qdv}, RegView{qddv}, RegView{lv}, Neg<OutOpt<Out>>{opt(gq)},
-                        Neg<OutOpt<Out>>{opt(gqd)}, NoFext{}, NoGF{}, On<OutOpt<Out>>{opt(gqdd)});
-  } else {
-    id_adjoint_lane<TP>(tab, In{q, ld, b}, In{qd, ld, b}, In{qdd, ld, b}, In{lam, ld, b}, Neg<OutOpt<Out>>{opt(gq)},
-                        Neg<OutOpt<Out>>{opt(gqd)}, fx_view(), gf_view(), On<OutOpt<Out>>{opt(gqdd)});
+  if constexpr (!Team<TP>::kAlways) {
+    RBD_LANE_IO(TP);
+    const uint32_t b = lane_id();
+    if (b >= batch) return;
+    auto opt = [&](float* p) __attribute__((always_inline)) { return OutOpt<Out>{Out{p, ld, b}, p != nullptr}; };
+    auto fx_view = [&]() __attribute__((always_inline)) {
+      if constexpr (EXT) return FextOpt{{fext, ld, b}};
+      else return NoFext{};
+    };
+    auto gf_view = [&]() __attribute__((always_inline)) {
+      if constexpr (EXT) return Neg<GFOut>{GFOut{{gfext, ld, b}}};
+      else return NoGF{};
+    };
+    if constexpr (TP::NV > 16 && !EXT) {
+      // every input load issued at entry, as in k_rnea_jvp
+      constexpr int NQ = TP::NQ, NV = TP::NV;
+      float qv[NQ], qdv[NV], qddv[NV], lv[NV];
+      preload_inputs<NQ>(qv, In{q, ld, b});
+      preload_inputs<NV>(qdv, qddv, In{qd, ld, b}, In{qdd, ld, b});
+      preload_inputs<NV>(lv, In{lam, ld, b});
+      id_adjoint_lane<TP>(tab, RegView{qv}, RegView{qdv}, RegView{qddv}, RegView{lv}, Neg<OutOpt<Out>>{opt(gq)},
+                          Neg<OutOpt<Out>>{opt(gqd)}, NoFext{}, NoGF{}, On<OutOpt<Out>>{opt(gqdd)});
+    } else {
+      id_adjoint_lane<TP>(tab, In{q, ld, b}, In{qd, ld, b}, In{qdd, ld, b}, In{lam, ld, b}, Neg<OutOpt<Out>>{opt(gq)},
+                          Neg<OutOpt<Out>>{opt(gqd)}, fx_view(), gf_view(), On<OutOpt<Out>>{opt(gqdd)});
+    }
   }
 }
 
@@ -977,6 +985,199 @@ __global__ __launch_bounds__(Team<TP>::kThreads, EXT ? 1 : 2) void k_fwd_dyn_vjp
     team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       team_fwd_dyn_vjp<TP, EXT, decltype(W_)::value>(tl, tab, SoaIo<TP>{ld}, lds_team, q, qd, tau, gqdd, gq, gqd,
                                                      gtau, fext, gfext, ld);
+    });
+  }
+}
+
+// Forward dynamics' tangent: the solve for qdd (parked in LDS), the tangent of
+// inverse dynamics at it on fresh views, and a second solve with the factor
+// that each wave still holds, so M is factored once (humanoid 61.6 -> 24.3 us at
+// batch 2048, 68.5 -> 37.6 at 32768, 110 -> 69 at 65536).
+template <class TP, bool EXT>
+__global__ __launch_bounds__(Team<TP>::kThreads, EXT ? 1 : 2) void k_fwd_dyn_jvp_team(
+    const float* __restrict__ tab, int64_t batch, int64_t ld, const float* __restrict__ q,
+    const float* __restrict__ qd, const float* __restrict__ tau, const float* __restrict__ dq,
+    const float* __restrict__ dqd, const float* __restrict__ dtau, float* qdd, float* dqdd,
+    const float* __restrict__ fext, const float* __restrict__ dfext) {
+  using TM = Team<TP>;
+  if constexpr (TM::kOn) {
+    RBD_LANE_IO(TP);
+    constexpr int NQ = TP::NQ, NV = TP::NV, T = TrunkRows<TP>::total();
+    using ROWS = TeamRows<TP, 16, true, 1>;
+    using TROWS = TeamRows<TP, 12, false, 1>;
+    // after the first solve its rows hold [qdd | what the tangent hands to the trunk]
+    constexpr int kTan = NV + TROWS::total(), kRows = ROWS::total() > kTan ? ROWS::total() : kTan;
+    __shared__ float lds_team[(kRows + T) * kTileLanes];
+    team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
+      constexpr int W = decltype(W_)::value;
+      const LdsCol lds{lds_team + tl.lane}, xrow = lds.at(kRows), park = lds.at(tl.shift);
+      const uint32_t b = tl.b;
+      const int64_t off = tl.shift * ld;
+      const bool owner = TM::may_own(W) && tl.wave == TM::kOwner;
+      Ltl<TP, 1> F, Ft;
+      {
+        float qv[NQ], qdv[NV], tv[NV];
+        team_load<TP, W, true, false>(qv, In{q + off, ld, b}, In{q, ld, b});
+        team_load<TP, W, true, true>(qdv, In{qd + off, ld, b}, In{qd, ld, b});
+        team_load<TP, W, false, true>(tv, In{tau + off, ld, b}, In{tau, ld, b});
+        if constexpr (TM::may_own(W)) {
+          if (owner) {
+            team_load_trunk<TP, false>(qv, In{q, ld, b});
+            team_load_trunk<TP, true>(qdv, In{qd, ld, b});
+            team_load_trunk<TP, true>(tv, In{tau, ld, b});
+          }
+        }
+        const RhsOne<RegView> rhs{RegView{tv}};
+        team_fd<TP, W, 1, ROWS>(
+            tl, owner, tab, RegView{qv}, RegView{qdv}, rhs, rhs, team_fext_opt<EXT>(fext, ld, tl.shift, b),
+            team_fext_opt<EXT>(fext, ld, 0, b), lds, xrow, F, Ft,
+            [&](int, int k, float x) __attribute__((always_inline)) {
+              park.put(k, x);
+              if (qdd) Out{qdd + off, ld, b}(k, x);
+            },
+            [&](int, int k, float x) __attribute__((always_inline)) {
+              if (qdd) Out{qdd, ld, b}(k, x);
+            });
+      }
+      sweep_boundary();
+      const int64_t l2 = opaque(ld), off2 = tl.shift * l2;
+      const float* const t2 = opaque_table(tab);
+      const auto qr = team_in<TP, false, In>(opaque(q), off2, l2, b);
+      const auto qdr = team_in<TP, true, In>(opaque(qd), off2, l2, b);
+      const auto dqr = team_in<TP, false, In>(dq, off2, l2, b);
+      const auto dqdr = team_in<TP, true, In>(dqd, off2, l2, b);
+      const auto dtr = team_in<TP, true, In>(dtau, off2, l2, b);
+      auto xb = [=](int k) __attribute__((always_inline)) { return park.get(k); };
+      auto xt = [=](int k) __attribute__((always_inline)) { return xrow.get(TrunkRows<TP>::row(k)); };
+      const TeamView<TP, true, decltype(xb), decltype(xt)> xr{xb, xt};
+      TanState<TP, EXT> s;
+      float rv[NV];  // dtau - d(ID)
+      const auto keep = [&](int k, float v) __attribute__((always_inline)) { rv[k] = v; };
+      const LdsCol rows = lds.at(NV), c = rows.at(team_base<TP, TROWS, W>(tl));
+      team_tan_up<TP, W, TROWS>(t2, t2 + tl.shift * kBodyStride, s, qr, qdr, xr, dqr, dqdr, NoFext{}, dtr,
+                                team_fext_opt<EXT>(fext, l2, tl.shift, b), team_fext_opt<EXT>(dfext, l2, tl.shift, b),
+                                c, keep);
+      team_solve_y<TP, W, TROWS>(F, RegView{rv}, c);
+      if constexpr (TM::may_own(W)) {
+        if (owner)
+          team_tan_trunk_down<TP, W>(t2, s, qr, qdr, xr, dqr, dqdr, NoFext{}, team_fext_opt<EXT>(fext, l2, 0, b),
+                                     team_fext_opt<EXT>(dfext, l2, 0, b));
+      }
+      __syncthreads();
+      if constexpr (TM::may_own(W)) {
+        if (owner) {
+          team_tan_trunk<TP, TROWS>(t2, s, dqr, dtr, rows, keep);
+          team_solve_trunk<TP, TROWS>(Ft, RegView{rv}, rows, [&](int, int k, float x) __attribute__((always_inline)) {
+            xrow.put(TrunkRows<TP>::row(k), x);
+            Out{dqdd, l2, b}(k, x);
+          });
+        }
+      }
+      __syncthreads();
+      team_fd_back<TP, W, 1>(F, [&](int, int k) __attribute__((always_inline)) { return xt(k); },
+                             SinkOne<Out>{Out{dqdd + off2, l2, b}});
+    });
+  }
+}
+
+// Inverse dynamics' tangent and adjoint: one sweep each, as in the middle of
+// forward dynamics' (inputs loaded at entry). Adjoint of the humanoid: 33.4 ->
+// 12.4 us at batch 64, 38.1 -> 20.9 at 32768, 50.0 -> 36.8 at 65536.
+template <class TP, bool EXT>
+__global__ __launch_bounds__(Team<TP>::kThreads) void k_rnea_jvp_team(
+    const float* __restrict__ tab, int64_t batch, int64_t ld, const float* __restrict__ q,
+    const float* __restrict__ qd, const float* __restrict__ qdd, const float* __restrict__ dq,
+    const float* __restrict__ dqd, const float* __restrict__ dqdd, float* __restrict__ dtau,
+    const float* __restrict__ fext, const float* __restrict__ dfext) {
+  using TM = Team<TP>;
+  if constexpr (TM::kOn) {
+    RBD_LANE_IO(TP);
+    constexpr int NQ = TP::NQ, NV = TP::NV;
+    using ROWS = TeamRows<TP, 12, false, 0>;
+    __shared__ float lds_team[ROWS::total() * kTileLanes];
+    team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
+      constexpr int W = decltype(W_)::value;
+      const LdsCol lds{lds_team + tl.lane};
+      const uint32_t b = tl.b;
+      const int64_t off = tl.shift * ld;
+      const bool owner = TM::may_own(W) && tl.wave == TM::kOwner;
+      float x[6][NQ];
+      const float* const in[6] = {q, dq, qd, qdd, dqd, dqdd};
+      sfor<0, 6>([&](auto A_) __attribute__((always_inline)) {
+        constexpr int A = decltype(A_)::value;
+        team_load<TP, W, true, (A > 1)>(x[A], In{in[A] + off, ld, b}, In{in[A], ld, b});
+        if constexpr (TM::may_own(W)) {
+          if (owner) team_load_trunk<TP, (A > 1)>(x[A], In{in[A], ld, b});
+        }
+      });
+      const RegView qr{x[0]}, dqr{x[1]}, qdr{x[2]}, ar{x[3]}, dqdr{x[4]};
+      const On<RegView> dar{RegView{x[5]}};
+      TanState<TP, EXT> s;
+      team_tan_up<TP, W, ROWS>(tab, tab + tl.shift * kBodyStride, s, qr, qdr, ar, dqr, dqdr, dar, NoFext{},
+                               team_fext_opt<EXT>(fext, ld, tl.shift, b), team_fext_opt<EXT>(dfext, ld, tl.shift, b),
+                               lds.at(team_base<TP, ROWS, W>(tl)), Neg<Out>{Out{dtau + off, ld, b}});
+      if constexpr (TM::may_own(W)) {
+        if (owner)
+          team_tan_trunk_down<TP, W>(tab, s, qr, qdr, ar, dqr, dqdr, dar, team_fext_opt<EXT>(fext, ld, 0, b),
+                                     team_fext_opt<EXT>(dfext, ld, 0, b));
+      }
+      __syncthreads();
+      if constexpr (TM::may_own(W)) {
+        if (owner) team_tan_trunk<TP, ROWS>(tab, s, dqr, NoFext{}, lds, Neg<Out>{Out{dtau, ld, b}});
+      }
+    });
+  }
+}
+
+template <class TP, bool EXT>
+__global__ __launch_bounds__(Team<TP>::kThreads) void k_rnea_vjp_team(
+    const float* __restrict__ tab, int64_t batch, int64_t ld, const float* __restrict__ q,
+    const float* __restrict__ qd, const float* __restrict__ qdd, const float* __restrict__ lam,
+    float* __restrict__ gq, float* __restrict__ gqd, float* __restrict__ gqdd, const float* __restrict__ fext,
+    float* __restrict__ gfext) {
+  using TM = Team<TP>;
+  if constexpr (TM::kOn) {
+    RBD_LANE_IO(TP);
+    constexpr int NQ = TP::NQ, NV = TP::NV;
+    using ROWS = TeamRows<TP, EXT ? 30 : 18, false, 0>;
+    __shared__ float lds_team[ROWS::total() * kTileLanes];
+    team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
+      constexpr int W = decltype(W_)::value;
+      const LdsCol lds{lds_team + tl.lane};
+      const uint32_t b = tl.b;
+      const int64_t off = tl.shift * ld;
+      const bool owner = TM::may_own(W) && tl.wave == TM::kOwner;
+      float x[4][NQ];
+      const float* const in[4] = {q, qd, qdd, lam};
+      sfor<0, 4>([&](auto A_) __attribute__((always_inline)) {
+        constexpr int A = decltype(A_)::value;
+        team_load<TP, W, true, (A > 0)>(x[A], In{in[A] + off, ld, b}, In{in[A], ld, b});
+        if constexpr (TM::may_own(W)) {
+          if (owner) team_load_trunk<TP, (A > 0)>(x[A], In{in[A], ld, b});
+        }
+      });
+      const RegView qr{x[0]}, qdr{x[1]}, ar{x[2]}, lr{x[3]};
+      const auto neg = [&](float* p, int64_t o) __attribute__((always_inline)) {
+        return Neg<OutOpt<Out>>{team_out(p, o, ld, b)};
+      };
+      const auto gf = [&](int shift) __attribute__((always_inline)) {
+        if constexpr (EXT) return Neg<GFOut>{team_gf<EXT>(gfext, ld, shift, b)};
+        else return NoGF{};
+      };
+      AdjState<TP, EXT, EXT> s;
+      team_adj_up<TP, W, ROWS>(tab, tab + tl.shift * kBodyStride, s, qr, qdr, ar, lr, neg(gq, off), neg(gqd, off),
+                               team_fext_opt<EXT>(fext, ld, tl.shift, b), gf(tl.shift),
+                               On<OutOpt<Out>>{team_out(gqdd, off, ld, b)}, lds.at(team_base<TP, ROWS, W>(tl)));
+      if constexpr (TM::may_own(W)) {
+        if (owner)
+          team_adj_trunk_down<TP, W>(tab, s, qr, qdr, ar, lr, team_fext_opt<EXT>(fext, ld, 0, b), gf(0));
+      }
+      __syncthreads();
+      if constexpr (TM::may_own(W)) {
+        if (owner)
+          team_adj_trunk<TP, ROWS>(tab, s, qr, qdr, neg(gq, 0), neg(gqd, 0), On<OutOpt<Out>>{team_out(gqdd, 0, ld, b)},
+                                   lds);
+      }
     });
   }
 }

@@ -709,4 +709,113 @@ RBD_DI void team_adj_trunk(const float* __restrict__ t, ST& s, const QV& q, cons
   });
 }
 
+// =================================================================== tangent of inverse dynamics
+// Role W: the outputs of its branches (see id_tangent_lane); the forces on
+// the trunk and their tangents go to LDS.
+template <class TP, int W, class ROWS, class ST, class QV, class QDV, class QDDV, class DQV, class DQDV, class DQDDV,
+          class DT, class FX, class DFX, class OUT>
+RBD_DI void team_tan_up(const float* __restrict__ t, const float* __restrict__ tb, ST& s, const QV& q, const QDV& qd,
+                        const QDDV& qdd, const DQV& dq, const DQDV& dqd, const DQDDV& dqdd, const DT& dtau,
+                        const FX& fx, const DFX& dfx, const LdsCol& c, const OUT& out) {
+  using TM = Team<TP>;
+  const V3 g = load_g<TP>(t);
+  const V3 mg = {-g.x, -g.y, -g.z};
+  auto backward = [&](auto J_) __attribute__((always_inline)) {
+    constexpr int J = decltype(J_)::value;
+    if constexpr (TM::in(W, J)) tan_close<TP, J>(tb, s, dq, dtau, out);
+  };
+  sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
+    constexpr int I = decltype(I_)::value;
+    if constexpr (TM::above(W, I)) {
+      tan_motion<TP, I>(t, mg, s, q, qd, qdd, dq, dqd, dqdd);
+      if constexpr (TM::attach(W, I)) {
+        s.f[I] = Frc{};
+        s.df[I] = Frc{};
+      }
+    } else if constexpr (TM::in(W, I)) {
+      tan_motion<TP, I>(tb, mg, s, q, qd, qdd, dq, dqd, dqdd);
+      tan_force<TP, I>(tb, s, fx, dfx);
+      close_subtrees<TP, I, I>(backward);
+    }
+  });
+  sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
+    constexpr int I = decltype(I_)::value;
+    if constexpr (TM::attach(W, I)) {
+      put_frc(c, ROWS::arow(W, I), s.f[I]);
+      put_frc(c, ROWS::arow(W, I) + 6, s.df[I]);
+    }
+  });
+}
+template <class TP, int W, class ST, class QV, class QDV, class QDDV, class DQV, class DQDV, class DQDDV, class FX,
+          class DFX>
+RBD_DI void team_tan_trunk_down(const float* __restrict__ t, ST& s, const QV& q, const QDV& qd, const QDDV& qdd,
+                                const DQV& dq, const DQDV& dqd, const DQDDV& dqdd, const FX& fx, const DFX& dfx) {
+  using TM = Team<TP>;
+  const V3 g = load_g<TP>(t);
+  const V3 mg = {-g.x, -g.y, -g.z};
+  sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
+    constexpr int I = decltype(I_)::value;
+    if constexpr (TM::trunk(I)) {
+      if constexpr (!TM::above(W, I)) tan_motion<TP, I>(t, mg, s, q, qd, qdd, dq, dqd, dqdd);
+      tan_force<TP, I>(t, s, fx, dfx);
+    }
+  });
+}
+template <class TP, class ROWS, class ST, class DQV, class DT, class OUT>
+RBD_DI void team_tan_trunk(const float* __restrict__ t, ST& s, const DQV& dq, const DT& dtau, const LdsCol& lds,
+                           const OUT& out) {
+  sfor_rev<0, TP::N>([&](auto J_) __attribute__((always_inline)) {
+    constexpr int J = decltype(J_)::value;
+    if constexpr (Team<TP>::trunk(J)) {
+      team_collect<TP, ROWS, J>(lds, [&](const LdsCol& c) __attribute__((always_inline)) {
+        s.f[J] = s.f[J] + get_frc(c, 0);
+        s.df[J] = s.df[J] + get_frc(c, 6);
+      });
+      tan_close<TP, J>(t, s, dq, dtau, out);
+    }
+  });
+}
+
+// y of L^T y = b over role W's branches for a factor that is there already,
+// and its share of the trunk's right-hand side (to LDS).
+template <class TP, int W, class ROWS, class B>
+RBD_DI void team_solve_y(Ltl<TP, 1>& F, const B& b, const LdsCol& c) {
+  using TM = Team<TP>;
+  sfor_rev<0, TP::NV>([&](auto K_) __attribute__((always_inline)) {
+    constexpr int K = decltype(K_)::value;
+    constexpr bool kOwn = TM::in(W, TP::body_of(K));
+    if constexpr (kOwn || TM::above(W, TP::body_of(K))) {
+      float acc = kOwn ? b(K) : 0.0f;
+      sfor<K + 1, cidx<TP::dlast(K)> + 1>([&](auto D_) __attribute__((always_inline)) {
+        constexpr int D = decltype(D_)::value;
+        if constexpr (TM::in(W, TP::body_of(D)))
+          acc = __builtin_fmaf(kOwn ? -F.L[cidx<TP::lidx(D, K)>] : F.L[cidx<TP::lidx(D, K)>], F.y[0][D], acc);
+      });
+      if constexpr (kOwn) F.y[0][K] = acc * F.Linv[K];
+      else c.put(cidx<ROWS::yrow(W, K, 0)>, acc);
+    }
+  });
+}
+// The trunk's y, then x.
+template <class TP, class ROWS, class B, class SINK>
+RBD_DI void team_solve_trunk(Ltl<TP, 1>& F, const B& b, const LdsCol& lds, const SINK& sink) {
+  using TM = Team<TP>;
+  sfor_rev<0, TP::NV>([&](auto K_) __attribute__((always_inline)) {
+    constexpr int K = decltype(K_)::value;
+    if constexpr (TM::trunk(TP::body_of(K))) {
+      float acc = b(K);
+      sfor<0, TM::kWaves>([&](auto W_) __attribute__((always_inline)) {
+        constexpr int W = decltype(W_)::value;
+        if constexpr (TM::above(W, TP::body_of(K))) acc = acc - lds.get(cidx<ROWS::base(W) + ROWS::yrow(W, K, 0)>);
+      });
+      sfor<K + 1, cidx<TP::dlast(K)> + 1>([&](auto D_) __attribute__((always_inline)) {
+        constexpr int D = decltype(D_)::value;
+        if constexpr (TM::trunk(TP::body_of(D))) acc = acc - F.L[cidx<TP::lidx(D, K)>] * F.y[0][D];
+      });
+      F.y[0][K] = acc * F.Linv[K];
+    }
+  });
+  ltl_back<TP, 1, TrunkDofs<TP>>(F, sink);
+}
+
 }  // namespace rbd
