@@ -130,6 +130,14 @@ static inline bool large(const rbd_model* m) { return m->nv > 16; }
 static inline bool teamed(const rbd_model* m, int64_t batch) {
   return m->team.waves > 1 && (m->nv > kTeamAlwaysDofs || batch <= kOneWavePerSimd);
 }
+// The same for the operations that mostly write (poses, Jacobians, mass
+// matrices): one instance per lane reaches the memory's rate once the batch
+// fills the SIMDs, and writes longer runs of a row at a time than the waves of
+// a team (humanoid, team against one lane: mass matrix 17 / 36 us at 16384, 33 /
+// 42 at 32768, 66 / 58 at 65536; poses 10 / 17 at 32768, 24 / 18 at 65536).
+static inline bool teamed_store(const rbd_model* m, int64_t batch) {
+  return m->team.waves > 1 && batch <= kOneWavePerSimd / 2;
+}
 static inline Shape team_shape(const rbd_model* m, int64_t batch) {
   return {dim3((unsigned)((batch + kTileLanes - 1) / kTileLanes)), dim3((unsigned)(m->team.waves * kTileLanes))};
 }
@@ -159,6 +167,7 @@ rbd_status launch_fk(const rbd_model* m, int64_t batch, int64_t ld, const float*
   if (batch == 0) return RBD_OK;
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &T};
+  if (teamed_store(m, batch)) return launch(m, KID_FK_TEAM, team_shape(m, batch), a, s, "rbd_fk");
   return launch(m, KID_FK, plain_shape(batch), a, s, "rbd_fk");
 }
 
@@ -178,6 +187,7 @@ rbd_status launch_jacobian(const rbd_model* m, int64_t batch, int64_t ld, const 
   }
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &js, &J};
+  if (teamed_store(m, batch)) return launch(m, KID_JACOBIAN_TEAM, team_shape(m, batch), a, s, "rbd_jacobian");
   return launch(m, KID_JACOBIAN, plain_shape(batch), a, s, "rbd_jacobian");
 }
 
@@ -203,6 +213,7 @@ rbd_status launch_crba(const rbd_model* m, int64_t batch, int64_t ld, const floa
   if (batch == 0) return RBD_OK;
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &M};
+  if (teamed_store(m, batch)) return launch(m, KID_CRBA_TEAM, team_shape(m, batch), a, s, "rbd_crba");
   return launch(m, KID_CRBA, plain_shape(batch), a, s, "rbd_crba");
 }
 

@@ -61,6 +61,9 @@
   X(KID_RNEA_BIAS_TEAM, 9, k_rnea_team<TP, false, false>) \
   X(KID_RNEA_EXT_TEAM, 9, k_rnea_team<TP, true, true>)    \
   X(KID_RNEA_BIAS_EXT_TEAM, 9, k_rnea_team<TP, false, true>) \
+  X(KID_FK_TEAM, 12, k_fk_team<TP>)                       \
+  X(KID_JACOBIAN_TEAM, 12, k_jacobian_team<TP>)           \
+  X(KID_CRBA_TEAM, 12, k_crba_team<TP>)                   \
   X(KID_RNEA_JVP_TEAM, 12, k_rnea_jvp_team<TP, false>)    \
   X(KID_RNEA_JVP_EXT_TEAM, 12, k_rnea_jvp_team<TP, true>) \
   X(KID_RNEA_VJP_TEAM, 12, k_rnea_vjp_team<TP, false>)    \

@@ -1080,6 +1080,137 @@ __global__ __launch_bounds__(Team<TP>::kThreads, EXT ? 1 : 2) void k_fwd_dyn_jvp
   }
 }
 
+// Poses: every wave walks the trunk above its branches again and writes its
+// own bodies, the owner the trunk's (humanoid 16.6 -> 6.0 us at batch 1024, 17.2
+// -> 10.0 at 32768; larger batches run one instance per lane).
+template <class TP>
+__global__ __launch_bounds__(Team<TP>::kThreads) void k_fk_team(const float* __restrict__ tab, int64_t batch,
+                                                               int64_t ld, const float* __restrict__ q,
+                                                               float* __restrict__ T) {
+  using TM = Team<TP>;
+  if constexpr (TM::kOn) {
+    team_waves<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
+      constexpr int W = decltype(W_)::value;
+      constexpr bool kOwner = W == TM::kOwner;
+      M3 Rw[TP::N];
+      V3 pw[TP::N];
+      float qv[TP::NQ];
+      const In qi{q, ld, tl.b};
+      team_load<TP, W, true, false>(qv, qi, qi);
+      if constexpr (kOwner) team_load_trunk<TP, false>(qv, qi);
+      sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
+        constexpr int I = decltype(I_)::value;
+        constexpr bool kMine = TM::in(W, I) || (kOwner && TM::trunk(I));
+        if constexpr (kMine || TM::above(W, I)) fk_pose<TP, I>(tab, RegView{qv}, Rw, pw);
+        if constexpr (kMine) fk_write<TP, I>(tab, Rw, pw, OutNT{T, ld, tl.b});
+      });
+    });
+  }
+}
+
+// Jacobians: the frames of a body are written by the wave that has the body
+// (humanoid, feet and hands: 45.5 -> 10.8 us at batch 1024, 46.7 -> 16.5 at
+// 16384, where the 56 MB it writes take 11).
+template <class TP>
+__global__ __launch_bounds__(Team<TP>::kThreads) void k_jacobian_team(const float* __restrict__ tab, int64_t batch,
+                                                                     int64_t ld, const float* __restrict__ q,
+                                                                     JacSlots js, float* __restrict__ J) {
+  using TM = Team<TP>;
+  if constexpr (TM::kOn) {
+    team_waves<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
+      constexpr int W = decltype(W_)::value;
+      constexpr bool kOwner = W == TM::kOwner;
+      M3 Rw[TP::N];
+      V3 pw[TP::N];
+      float qv[TP::NQ];
+      const In qi{q, ld, tl.b};
+      team_load<TP, W, true, false>(qv, qi, qi);
+      if constexpr (kOwner) team_load_trunk<TP, false>(qv, qi);
+      sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
+        constexpr int I = decltype(I_)::value;
+        constexpr bool kMine = TM::in(W, I) || (kOwner && TM::trunk(I));
+        if constexpr (kMine || TM::above(W, I)) fk_pose<TP, I>(tab, RegView{qv}, Rw, pw);
+        if constexpr (kMine) jac_frames<TP, I>(Rw, pw, js, J, ld, tl.b);
+      });
+    });
+  }
+}
+
+// Mass matrix: the rows of a body are written by the wave that has it; the
+// composite inertias of the branches reach the trunk through LDS (humanoid 31.8
+// -> 12.0 us at batch 64, 35.6 -> 17.3 at 16384, where the 83 MB it writes take
+// 16).
+template <class TP>
+__global__ __launch_bounds__(Team<TP>::kThreads) void k_crba_team(const float* __restrict__ tab, int64_t batch,
+                                                                 int64_t ld, const float* __restrict__ q,
+                                                                 float* __restrict__ M) {
+  using TM = Team<TP>;
+  if constexpr (TM::kOn) {
+    constexpr int N = TP::N, NV = TP::NV;
+    using ROWS = TeamRows<TP, 10, false, 0>;
+    __shared__ float lds_team[ROWS::total() * kTileLanes];
+    team_waves<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
+      constexpr int W = decltype(W_)::value;
+      constexpr bool kOwner = W == TM::kOwner;
+      const LdsCol lds{lds_team + tl.lane}, c = lds.at(ROWS::base(W));
+      M3 R[N];
+      Inr Ic[N];
+      float qv[TP::NQ];
+      const In qi{q, ld, tl.b};
+      team_load<TP, W, true, false>(qv, qi, qi);
+      if constexpr (kOwner) team_load_trunk<TP, false>(qv, qi);
+      const RegView qr{qv};
+      auto put = [&](int r, int k, float v) __attribute__((always_inline)) {
+        __builtin_nontemporal_store(v, lane_ptr(M + (int64_t)(r * NV + k) * ld, tl.b));
+      };
+      auto backward = [&](auto J_) __attribute__((always_inline)) {
+        constexpr int J2 = decltype(J_)::value;
+        constexpr int P = TP::parent(J2);
+        if constexpr (TM::in(W, J2)) {
+          crba_write<TP, J2>(tab, R, Ic[J2], put);
+          if constexpr (P >= 0) xinr_acc(R[J2], load_r<J2>(tab), Ic[J2], Ic[P]);
+        }
+      };
+      sfor<0, N>([&](auto I_) __attribute__((always_inline)) {
+        constexpr int I = decltype(I_)::value;
+        if constexpr (TM::in(W, I) || TM::above(W, I) || (kOwner && TM::trunk(I))) {
+          if constexpr (!TP::free_body(I)) R[I] = joint_rot<I>(tab, qr(cidx<TP::qofs(I)>));
+        }
+        if constexpr (TM::attach(W, I)) Ic[I] = Inr{};
+        if constexpr (TM::in(W, I)) {
+          Ic[I] = load_inr<I>(tab);
+          close_subtrees<TP, I, I>(backward);
+        }
+      });
+      sfor<0, N>([&](auto I_) __attribute__((always_inline)) {
+        constexpr int I = decltype(I_)::value;
+        if constexpr (TM::attach(W, I)) put_inr(c, ROWS::arow(W, I), Ic[I]);
+      });
+      sfor<0, NV>([&](auto K_) __attribute__((always_inline)) {
+        constexpr int K = decltype(K_)::value;
+        if constexpr (TM::in(W, TP::body_of(K)) || (kOwner && TM::trunk(TP::body_of(K)))) crba_zeros<TP, K>(put);
+      });
+      __syncthreads();
+      if constexpr (kOwner) {
+        sfor<0, N>([&](auto I_) __attribute__((always_inline)) {
+          constexpr int I = decltype(I_)::value;
+          if constexpr (TM::trunk(I)) Ic[I] = load_inr<I>(tab);
+        });
+        sfor_rev<0, N>([&](auto J_) __attribute__((always_inline)) {
+          constexpr int J2 = decltype(J_)::value;
+          constexpr int P = TP::parent(J2);
+          if constexpr (TM::trunk(J2)) {
+            team_collect<TP, ROWS, J2>(
+                lds, [&](const LdsCol& x) __attribute__((always_inline)) { Ic[J2] = Ic[J2] + get_inr(x, 0); });
+            crba_write<TP, J2>(tab, R, Ic[J2], put);
+            if constexpr (P >= 0) xinr_acc(R[J2], load_r<J2>(tab), Ic[J2], Ic[P]);
+          }
+        });
+      }
+    });
+  }
+}
+
 // Inverse dynamics' tangent and adjoint: one sweep each, as in the middle of
 // forward dynamics' (inputs loaded at entry). Adjoint of the humanoid: 33.4 ->
 // 12.4 us at batch 64, 38.1 -> 20.9 at 32768, 50.0 -> 36.8 at 65536.

@@ -169,6 +169,22 @@ RBD_DI void team_roles(uint32_t first, int64_t batch, F&& body) {
   });
 }
 
+// The same with every wave running its own code (its bodies in place): for
+// what differs between copies of a branch, as the zeros of a matrix's rows do.
+template <class TP, class F>
+RBD_DI void team_waves(uint32_t first, int64_t batch, F&& body) {
+  TeamLane tl;
+  tl.wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kTileLanes);
+  tl.shift = 0;
+  tl.lane = threadIdx.x % kTileLanes;
+  const uint32_t b = first + tl.lane;
+  tl.b = b < batch ? b : (uint32_t)(batch - 1);
+  sfor<0, Team<TP>::kWaves>([&](auto W_) __attribute__((always_inline)) {
+    constexpr int W = decltype(W_)::value;
+    if (tl.wave == W) body(W_, tl);
+  });
+}
+
 // The row base of the calling wave among those that run the code of role W.
 template <class TP, class ROWS, int W>
 RBD_DI int team_base(const TeamLane& tl) {
