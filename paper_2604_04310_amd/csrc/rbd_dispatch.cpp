@@ -313,7 +313,7 @@ rbd_status launch_osc(const rbd_model* m, int64_t batch, int64_t ld, const float
   if (batch == 0) return RBD_OK;
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &qd, &tgt, &kp, &kd, &kn, &tau};
-  return launch_frame(m, true, frame, heavy_shape(batch), a, s, "rbd_osc");
+  return launch_frame(m, true, frame, m->team.waves > 1 ? team_shape(m, batch) : heavy_shape(batch), a, s, "rbd_osc");
 }
 
 // Between the solve and the adjoint sweep, q-double-dot and lam park: for a

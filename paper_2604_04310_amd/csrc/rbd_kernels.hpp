@@ -680,30 +680,6 @@ __global__ __launch_bounds__(kBlock) void k_diff_ik(const float* __restrict__ ta
   diff_ik_lane<TP, E>(tab, In{q, ld, b}, In{tgt, ld, b}, gain, lam2, Out{qd, ld, b});
 }
 
-// Two sweeps (bias force with the null-space solve, then the task-space
-// solve), the second on fresh views; the torques written by the first are read
-// back by the second, so tau is not restrict-qualified. Inputs are loaded
-// where they are used (preloading them, as k_fwd_dyn does for large trees,
-// held 83 more registers and measured 99 us against 81 us for the humanoid at
-// batch 65536 with the sweeps fused).
-template <class TP, int E = TP::N - 1>
-__global__ __launch_bounds__(kBlock) void k_osc(const float* __restrict__ tab, int64_t batch, int64_t ld,
-                                                const float* __restrict__ q, const float* __restrict__ qd,
-                                                const float* __restrict__ tgt, float kp, float kd, float kn,
-                                                float* tau) {
-  RBD_LANE_IO(TP);
-  const uint32_t b = lane_id();
-  if (b >= batch) return;
-  float ypath[TP::NV], astar[6];
-  osc_sweep_bias<TP, E>(tab, In{q, ld, b}, In{qd, ld, b}, In{tgt, ld, b}, kp, kd, kn, OutAlias{tau, ld, b}, ypath,
-                        astar);
-  sweep_boundary();
-  // the second sweep on fresh views (see k_fwd_dyn_vjp)
-  const int64_t l2 = opaque(ld);
-  osc_sweep_task<TP, E>(opaque_table(tab), In{opaque(q), l2, b}, ypath, astar, OutAlias{tau, l2, b},
-                        InAlias{tau, l2, b});
-}
-
 // =================================================================== teams of waves
 // The kernels of a team (rbd_team.hpp): a block is one team, 64 instances, all
 // lanes reach every barrier (lanes past the batch redo its last instance and
@@ -1310,6 +1286,144 @@ __global__ __launch_bounds__(Team<TP>::kThreads) void k_rnea_vjp_team(
                                    lds);
       }
     });
+  }
+}
+
+// Operational-space control of frame E. One instance per lane: two sweeps
+// (bias force with the null-space solve, then the task-space
+// solve), the second on fresh views; the torques written by the first are read
+// back by the second, so tau is not restrict-qualified. Inputs are loaded
+// where they are used (preloading them, as k_fwd_dyn does for large trees,
+// held 83 more registers and measured 99 us against 81 us for the humanoid at
+// batch 65536 with the sweeps fused).
+// A team: branches up, the trunk and the 6x6 task solve by the owner, then J^T z
+// on E's branch by the wave that has it; path torques are held back until z is
+// known.
+template <class TP, int E = TP::N - 1>
+__global__ __launch_bounds__(Team<TP>::kOn ? Team<TP>::kThreads : kBlock, Team<TP>::kOn ? 2 : 1) void k_osc(
+    const float* __restrict__ tab, int64_t batch, int64_t ld, const float* __restrict__ q,
+    const float* __restrict__ qd, const float* __restrict__ tgt, float kp, float kd, float kn, float* tau) {
+  using TM = Team<TP>;
+  if constexpr (TM::kOn) {
+    RBD_LANE_IO(TP);
+    constexpr int NQ = TP::NQ, NV = TP::NV;
+    using ROWS = TeamRows<TP, 16, true, 1>;
+    using EROWS = OscRows<TP, E>;
+    using MASK = OscRhs<TP, E>;
+    __shared__ float lds_team[(ROWS::total() + EROWS::total()) * kTileLanes];
+    team_waves<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
+      constexpr int W = decltype(W_)::value;
+      constexpr bool kOwner = W == TM::kOwner, kTask = W == EROWS::kWave;
+      const LdsCol lds{lds_team + tl.lane}, ex = lds.at(ROWS::total());
+      const uint32_t b = tl.b;
+      float qv[NQ], qdv[NV], held[NV];
+      const In qi{q, ld, b}, qdi{qd, ld, b}, ti{tgt, ld, b};
+      team_load<TP, W, true, false>(qv, qi, qi);
+      team_load<TP, W, true, true>(qdv, qdi, qdi);
+      if constexpr (kOwner) {
+        team_load_trunk<TP, false>(qv, qi);
+        team_load_trunk<TP, true>(qdv, qdi);
+      }
+      const RegView qr{qv}, qdr{qdv};
+      const Out to{tau, ld, b};
+      const auto hold = [&](int k, float v) __attribute__((always_inline)) {
+        if (TP::is_anc(TP::body_of(k), E)) held[k] = v;
+        else to(k, v);
+      };
+      struct State : TeamFd<TP, false> {
+        V3 p0;
+      } s;
+      if constexpr (TP::kFree) {
+        if constexpr (TM::above(W, 0) || kOwner) s.p0 = {qv[0], qv[1], qv[2]};
+      }
+      OscHook<TP, E, RegView, In, decltype(hold)> hook{tab, qdr, ti, hold, kp, kd, kn};
+      hook.init();
+      Ltl<TP, kTask ? 7 : 1> F;
+      team_fd_up<TP, W, kTask ? 7 : 1, ROWS, MASK>(tab, tab, qr, qdr, hook, NoFext{}, s, F, lds.at(ROWS::base(W)));
+      if constexpr (kTask) {
+        sfor<0, NV>([&](auto K_) __attribute__((always_inline)) {
+          constexpr int K = decltype(K_)::value;
+          if constexpr (TM::above(W, TP::body_of(K)) && TP::is_anc(TP::body_of(K), E)) {
+            sfor<0, 6>([&](auto R_) __attribute__((always_inline)) {
+              constexpr int r = decltype(R_)::value;
+              ex.put(cidx<EROWS::yrow(K)> + r, team_yshare<TP, W, K, r + 1, MASK>(F));
+            });
+          }
+        });
+        int n = EROWS::kG;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+#pragma unroll
+          for (int j = 0; j <= i; ++j) ex.put(n++, hook.G[i][j]);
+          ex.put(EROWS::kA + i, hook.a[i]);
+        }
+        if constexpr (EROWS::anchor() >= 0) {
+#pragma unroll
+          for (int i = 0; i < 9; ++i) ex.put(EROWS::kT + i, hook.A.a[i]);
+          ex.put(EROWS::kT + 9, hook.o.x); ex.put(EROWS::kT + 10, hook.o.y); ex.put(EROWS::kT + 11, hook.o.z);
+        }
+      }
+      if constexpr (kOwner) {
+        // the trunk's motion (its hook starts afresh: a wave may own both E and the trunk)
+        team_fd_trunk_down<TP, W>(tab, qr, qdr, NoFext{}, s);
+      }
+      __syncthreads();
+      float z[6];
+      if constexpr (kOwner) {
+        OscHook<TP, E, RegView, In, decltype(hold)> top{tab, qdr, ti, hold, kp, kd, kn};
+        top.init();
+        if constexpr (EROWS::kWave >= 0) {
+          int n = EROWS::kG;
+#pragma unroll
+          for (int i = 0; i < 6; ++i) {
+#pragma unroll
+            for (int j = 0; j <= i; ++j) top.G[i][j] = ex.get(n++);
+            top.a[i] = ex.get(EROWS::kA + i);
+          }
+          if constexpr (EROWS::anchor() >= 0) {
+#pragma unroll
+            for (int i = 0; i < 9; ++i) top.A.a[i] = ex.get(EROWS::kT + i);
+            top.o = {ex.get(EROWS::kT + 9), ex.get(EROWS::kT + 10), ex.get(EROWS::kT + 11)};
+          }
+        } else {
+          sfor<0, E + 1>([&](auto I_) __attribute__((always_inline)) {
+            if constexpr (TP::is_anc(decltype(I_)::value, E)) top.motion(I_, s);
+          });
+        }
+        Ltl<TP, 7> Ft;
+        team_fd_trunk<TP, 7, ROWS, MASK>(tab, OscTrunkHook<TP, E, decltype(top)>{top, ex}, s, lds, Ft);
+        chol6_solve(top.G, top.a, z);
+#pragma unroll
+        for (int i = 0; i < 6; ++i) lds.put(i, z[i]);
+        sfor<0, NV>([&](auto K_) __attribute__((always_inline)) {
+          constexpr int K = decltype(K_)::value;
+          if constexpr (TM::trunk(TP::body_of(K)) && TP::is_anc(TP::body_of(K), E))
+            to(K, held[K] + top.task_torque(K, z));
+        });
+      }
+      __syncthreads();
+      if constexpr (kTask) {
+#pragma unroll
+        for (int i = 0; i < 6; ++i) z[i] = lds.get(i);
+        sfor<0, NV>([&](auto K_) __attribute__((always_inline)) {
+          constexpr int K = decltype(K_)::value;
+          if constexpr (TM::in(W, TP::body_of(K)) && TP::is_anc(TP::body_of(K), E))
+            to(K, held[K] + hook.task_torque(K, z));
+        });
+      }
+    });
+  } else {
+    RBD_LANE_IO(TP);
+    const uint32_t b = lane_id();
+    if (b >= batch) return;
+    float ypath[TP::NV], astar[6];
+    osc_sweep_bias<TP, E>(tab, In{q, ld, b}, In{qd, ld, b}, In{tgt, ld, b}, kp, kd, kn, OutAlias{tau, ld, b}, ypath,
+                          astar);
+    sweep_boundary();
+    // the second sweep on fresh views (see k_fwd_dyn_vjp)
+    const int64_t l2 = opaque(ld);
+    osc_sweep_task<TP, E>(opaque_table(tab), In{opaque(q), l2, b}, ypath, astar, OutAlias{tau, l2, b},
+                          InAlias{tau, l2, b});
   }
 }
 

@@ -834,4 +834,158 @@ RBD_DI void team_solve_trunk(Ltl<TP, 1>& F, const B& b, const LdsCol& lds, const
   ltl_back<TP, 1, TrunkDofs<TP>>(F, sink);
 }
 
+// =================================================================== operational-space control
+// One sweep over the factor (see osc_sweep_bias and osc_sweep_task, which on
+// one lane are two: with all seven right-hand sides one lane spills). Right-hand
+// side 0 is tau_null; 1 to 6 are the rows of J in E's axes and only exist on
+// E's path. The wave that has E hands the trunk, besides its rows, its share of
+// right-hand sides 1 to 6, of Lambda^-1 and of the task acceleration, and the
+// transform that the path's next body needs.
+template <class TP, int E>
+struct OscRhs {
+  static constexpr bool on(int r, int k) { return r == 0 || TP::is_anc(TP::body_of(k), E); }
+};
+template <class TP, int E>
+struct OscRows {  // rows that the wave of E adds: y shares (6 a DoF), then G, a*, and A and o
+  static constexpr int kWave = Team<TP>::kPlan.wave[E];  // -1: E is a trunk body
+  static constexpr int yrow(int k) { return 6 * TrunkRows<TP>::row(k); }
+  static constexpr int kG = 6 * TrunkRows<TP>::total(), kA = kG + 21, kT = kA + 6;
+  static constexpr int total() { return kWave < 0 ? 0 : kT + 12; }
+  // the trunk body that E's branch hangs on (-1: the world)
+  static constexpr int anchor() {
+    int i = E;
+    while (i >= 0 && !Team<TP>::trunk(i)) i = TP::parent(i);
+    return i;
+  }
+};
+
+// What OSC adds to a sweep up: tau_null, and on E's path the task's
+// right-hand sides and sums. tau(k, v) takes h + tau_null.
+template <class TP, int E, class QD, class TGT, class TO>
+struct OscHook {
+  const float* t;
+  const QD& qd;
+  const TGT& tgt;
+  const TO& tau;
+  float kp, kd, kn;
+  M3 Rw[TP::N];
+  V3 pw[TP::N];
+  M3 A = {{1.0f, 0.0f, 0.0f, 0.0f, 1.0f, 0.0f, 0.0f, 0.0f, 1.0f}};  // axes and origin of the next path
+  V3 o = {0.0f, 0.0f, 0.0f};                                         // body to close, in E's frame
+  float G[6][6], a[6];  // shares of Lambda^-1 and of a* - J M^-1 tau_null
+  float col[TP::NV][6];  // J, by DoF
+  RBD_DI void init() {
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+      a[i] = 0.0f;
+#pragma unroll
+      for (int j = 0; j < 6; ++j) G[i][j] = 0.0f;
+    }
+  }
+  template <class I_, class ST>
+  RBD_DI void motion(I_, const ST& s) {
+    constexpr int I = I_::value;
+    if constexpr (TP::is_anc(I, E)) {
+      struct Q0 {
+        const ST& s;
+        RBD_DI float operator()(int c) const { return c == 0 ? s.p0.x : (c == 1 ? s.p0.y : s.p0.z); }
+      };
+      world_pose<TP, I>(t, Q0{s}, s.R[I], Rw, pw);
+    }
+    if constexpr (I == E) {
+      float err[6];
+      pose_error<TP, E>(t, Rw[E], pw[E], tgt, err);
+      const V3 el = mulT(Rw[E], V3{err[0], err[1], err[2]}), ea = mulT(Rw[E], V3{err[3], err[4], err[5]});
+      const float e6[6] = {el.x, el.y, el.z, ea.x, ea.y, ea.z};
+      const float tw[6] = {s.v[E].v.x, s.v[E].v.y, s.v[E].v.z, s.v[E].w.x, s.v[E].w.y, s.v[E].w.z};
+#pragma unroll
+      for (int i = 0; i < 6; ++i) a[i] = a[i] + (kp * e6[i] - kd * tw[i]);
+    }
+  }
+  template <class J_, class ST, int n>
+  RBD_DI void sides(J_, int k, const ST& s, float (&b)[n]) {
+    constexpr int J = J_::value;
+    b[0] = -kn * qd(k);
+    tau(k, s.f[J].n.z + b[0]);
+    if constexpr (n > 1 && TP::is_anc(J, E)) {
+      const V3 z = {A.a[2], A.a[5], A.a[8]};
+      const V3 lin = cross(o, z);
+      col[k][0] = lin.x; col[k][1] = lin.y; col[k][2] = lin.z;
+      col[k][3] = z.x; col[k][4] = z.y; col[k][5] = z.z;
+#pragma unroll
+      for (int i = 0; i < 6; ++i) b[i + 1] = col[k][i];
+    }
+  }
+  template <class ST, int n>
+  RBD_DI void base_sides(int k, const ST& s, float (&b)[n]) {
+    const float hb[6] = {s.f[0].f.x, s.f[0].f.y, s.f[0].f.z, s.f[0].n.x, s.f[0].n.y, s.f[0].n.z};
+    b[0] = -kn * qd(k);
+    tau(k, __builtin_fmaf(-kn, qd(k), hb[k]));
+    if constexpr (n > 1) {  // the base is on every path
+      const int c = k % 3;
+      const V3 ax = {A.a[c], A.a[3 + c], A.a[6 + c]};
+      const V3 lin = k < 3 ? ax : cross(o, ax);
+      col[k][0] = lin.x; col[k][1] = lin.y; col[k][2] = lin.z;
+      col[k][3] = k < 3 ? 0.0f : ax.x; col[k][4] = k < 3 ? 0.0f : ax.y; col[k][5] = k < 3 ? 0.0f : ax.z;
+#pragma unroll
+      for (int i = 0; i < 6; ++i) b[i + 1] = col[k][i];
+    }
+  }
+  template <class J_, class ST, int n>
+  RBD_DI void closed(J_, const ST& s, const Ltl<TP, n>& F) {
+    constexpr int J = J_::value;
+    if constexpr (n > 1 && TP::is_anc(J, E)) {
+      sfor<0, cidx<TP::nvb(J)>>([&](auto C_) __attribute__((always_inline)) {
+        constexpr int k = TP::vofs(J) + decltype(C_)::value;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+          a[i] = __builtin_fmaf(-F.y[i + 1][k], F.y[0][k], a[i]);
+#pragma unroll
+          for (int j = 0; j <= i; ++j) G[i][j] = __builtin_fmaf(F.y[i + 1][k], F.y[j + 1][k], G[i][j]);
+        }
+      });
+      if constexpr (TP::parent(J) >= 0) {
+        A = mulMMT(A, s.R[J]);
+        o = o - mul(A, load_r<J>(t));
+      }
+    }
+  }
+  // J^T z of DoF k
+  RBD_DI float task_torque(int k, const float (&z)[6]) const {
+    float x = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) x = __builtin_fmaf(col[k][i], z[i], x);
+    return x;
+  }
+};
+
+// The trunk's: takes the wave of E's share off right-hand sides 1 to 6.
+template <class TP, int E, class H>
+struct OscTrunkHook {
+  using EROWS = OscRows<TP, E>;
+  H& h;
+  const LdsCol& ex;
+  template <bool ON, int n>
+  RBD_DI void share(int k, float (&b)[n]) {
+    if constexpr (ON && EROWS::kWave >= 0) {
+#pragma unroll
+      for (int r = 0; r < 6; ++r) b[r + 1] = b[r + 1] - ex.get(EROWS::yrow(k) + r);
+    }
+  }
+  template <class J, class ST, int n>
+  RBD_DI void sides(J j, int k, const ST& s, float (&b)[n]) {
+    h.sides(j, k, s, b);
+    share<TP::is_anc(J::value, E)>(k, b);
+  }
+  template <class ST, int n>
+  RBD_DI void base_sides(int k, const ST& s, float (&b)[n]) {
+    h.base_sides(k, s, b);
+    share<true>(k, b);
+  }
+  template <class J, class ST, class LF>
+  RBD_DI void closed(J j, const ST& s, const LF& F) {
+    h.closed(j, s, F);
+  }
+};
+
 }  // namespace rbd
