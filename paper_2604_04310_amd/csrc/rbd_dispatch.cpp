@@ -238,6 +238,7 @@ rbd_status launch_aba(const rbd_model* m, int64_t batch, int64_t ld, const float
   const KernelId id = fext ? (pre ? KID_ABA_PRE_EXT : KID_ABA_EXT) : (pre ? KID_ABA_PRE : KID_ABA);
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &qd, &tau, &fext, &qdd};
+  if (teamed(m, batch)) return launch(m, fext ? KID_ABA_EXT_TEAM : KID_ABA_TEAM, team_shape(m, batch), a, s, "rbd_aba");
   return launch(m, id, heavy_shape(batch), a, s, "rbd_aba");
 }
 

@@ -67,7 +67,9 @@
   X(KID_RNEA_JVP_TEAM, 12, k_rnea_jvp_team<TP, false>)    \
   X(KID_RNEA_JVP_EXT_TEAM, 12, k_rnea_jvp_team<TP, true>) \
   X(KID_RNEA_VJP_TEAM, 12, k_rnea_vjp_team<TP, false>)    \
-  X(KID_RNEA_VJP_EXT_TEAM, 12, k_rnea_vjp_team<TP, true>)
+  X(KID_RNEA_VJP_EXT_TEAM, 12, k_rnea_vjp_team<TP, true>) \
+  X(KID_ABA_TEAM, 9, k_aba_team<TP, false>)               \
+  X(KID_ABA_EXT_TEAM, 9, k_aba_team<TP, true>)
 
 namespace rbd {
 

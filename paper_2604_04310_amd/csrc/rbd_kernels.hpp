@@ -14,29 +14,6 @@ namespace rbd {
 
 RBD_DI uint32_t lane_id() { return blockIdx.x * blockDim.x + threadIdx.x; }
 
-// The same pointer value, hidden from the optimiser (an empty asm on its
-// scalar register, no instruction). A kernel that runs several sweeps gives
-// each its own copies of the table and input pointers and of the row stride,
-// so model constants, inputs, row addresses and what is computed from them
-// (joint sines and cosines) are reloaded and recomputed in each sweep instead
-// of being held in registers across all of them.
-// The asm operand keeps the pointer's address space (global for inputs,
-// constant for the model table), so loads through the copy stay global loads
-// with a scalar base, and table reads stay scalar loads.
-RBD_DI const float* opaque(const float* p) {
-  auto g = (const __attribute__((address_space(1))) float*)p;
-  asm volatile("" : "+s"(g));
-  return (const float*)g;
-}
-RBD_DI const float* opaque_table(const float* p) {
-  auto c = (const __attribute__((address_space(4))) float*)p;
-  asm volatile("" : "+s"(c));
-  return (const float*)c;
-}
-RBD_DI int64_t opaque(int64_t x) {
-  asm volatile("" : "+s"(x));
-  return x;
-}
 // Views of outputs that a later sweep of the same kernel reads back: not
 // restrict-qualified, so the compiler keeps every load before the store that
 // later overwrites the same element.
@@ -219,22 +196,24 @@ __global__ __launch_bounds__(kBlock) void k_aba(const float* __restrict__ tab, i
                                                 const float* __restrict__ q, const float* __restrict__ qd,
                                                 const float* __restrict__ tau, const float* __restrict__ fext,
                                                 float* __restrict__ qdd) {
-  RBD_LANE_IO(TP);
-  const uint32_t b = lane_id();
-  if (b >= batch) return;
-  const auto fx = fext_view<EXT>(fext, ld, b);
-  if constexpr (PRE) {
-    constexpr int NQ = TP::NQ, NV = TP::NV;
-    float qv[NQ], qdv[NV], tv[NV];
-    const In qi{q, ld, b}, qdi{qd, ld, b}, ti{tau, ld, b};
-    sfor<0, NQ>([&](auto K_) __attribute__((always_inline)) { qv[decltype(K_)::value] = qi(decltype(K_)::value); });
-    sfor<0, NV>([&](auto K_) __attribute__((always_inline)) {
-      qdv[decltype(K_)::value] = qdi(decltype(K_)::value);
-      tv[decltype(K_)::value] = ti(decltype(K_)::value);
-    });
-    aba_lane<TP>(tab, RegView{qv}, RegView{qdv}, RegView{tv}, Out{qdd, ld, b}, fx);
-  } else {
-    aba_lane<TP>(tab, In{q, ld, b}, In{qd, ld, b}, In{tau, ld, b}, Out{qdd, ld, b}, fx);
+  if constexpr (!Team<TP>::kAlways) {
+    RBD_LANE_IO(TP);
+    const uint32_t b = lane_id();
+    if (b >= batch) return;
+    const auto fx = fext_view<EXT>(fext, ld, b);
+    if constexpr (PRE) {
+      constexpr int NQ = TP::NQ, NV = TP::NV;
+      float qv[NQ], qdv[NV], tv[NV];
+      const In qi{q, ld, b}, qdi{qd, ld, b}, ti{tau, ld, b};
+      sfor<0, NQ>([&](auto K_) __attribute__((always_inline)) { qv[decltype(K_)::value] = qi(decltype(K_)::value); });
+      sfor<0, NV>([&](auto K_) __attribute__((always_inline)) {
+        qdv[decltype(K_)::value] = qdi(decltype(K_)::value);
+        tv[decltype(K_)::value] = ti(decltype(K_)::value);
+      });
+      aba_lane<TP>(tab, RegView{qv}, RegView{qdv}, RegView{tv}, Out{qdd, ld, b}, fx);
+    } else {
+      aba_lane<TP>(tab, In{q, ld, b}, In{qd, ld, b}, In{tau, ld, b}, Out{qdd, ld, b}, fx);
+    }
   }
 }
 
@@ -934,7 +913,7 @@ RBD_DI void team_fwd_dyn_vjp(const TeamLane& tl, const float* __restrict__ tab, 
   const auto xr = solved(0), lr = solved(1);
   const LdsCol adj = lds.at(2 * NV);
   AdjState<TP, EXT, EXT> s;
-  team_adj_up<TP, W, AROWS>(t2, t2 + tl.shift * kBodyStride, s, qr, qdr, xr, lr,
+  team_adj_up<TP, W, AROWS>(t2, opaque_table(tab + tl.shift * kBodyStride), s, qr, qdr, xr, lr,
                             io2.template opt<NQ>(gq, tl.shift, b), io2.template opt<NV>(gqd, tl.shift, b),
                             team_fext_opt<EXT>(fext, l2, tl.shift, b), team_gf<EXT>(gfext, l2, tl.shift, b), NoGF{},
                             adj.at(team_base<TP, AROWS, W>(tl)));
@@ -1030,7 +1009,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads, EXT ? 1 : 2) void k_fwd_dyn_jvp
       float rv[NV];  // dtau - d(ID)
       const auto keep = [&](int k, float v) __attribute__((always_inline)) { rv[k] = v; };
       const LdsCol rows = lds.at(NV), c = rows.at(team_base<TP, TROWS, W>(tl));
-      team_tan_up<TP, W, TROWS>(t2, t2 + tl.shift * kBodyStride, s, qr, qdr, xr, dqr, dqdr, NoFext{}, dtr,
+      team_tan_up<TP, W, TROWS>(t2, opaque_table(tab + tl.shift * kBodyStride), s, qr, qdr, xr, dqr, dqdr, NoFext{}, dtr,
                                 team_fext_opt<EXT>(fext, l2, tl.shift, b), team_fext_opt<EXT>(dfext, l2, tl.shift, b),
                                 c, keep);
       team_solve_y<TP, W, TROWS>(F, RegView{rv}, c);
@@ -1052,6 +1031,55 @@ __global__ __launch_bounds__(Team<TP>::kThreads, EXT ? 1 : 2) void k_fwd_dyn_jvp
       __syncthreads();
       team_fd_back<TP, W, 1>(F, [&](int, int k) __attribute__((always_inline)) { return xt(k); },
                              SinkOne<Out>{Out{dqdd + off2, l2, b}});
+    });
+  }
+}
+
+// Forward dynamics by the articulated-body algorithm: branches up, the trunk up
+// and down, branches down.
+template <class TP, bool EXT>
+__global__ __launch_bounds__(Team<TP>::kThreads, EXT ? 2 : 3) void k_aba_team(
+    const float* __restrict__ tab, int64_t batch, int64_t ld, const float* __restrict__ q,
+    const float* __restrict__ qd, const float* __restrict__ tau, const float* __restrict__ fext,
+    float* __restrict__ qdd) {
+  using TM = Team<TP>;
+  if constexpr (TM::kOn) {
+    constexpr int NQ = TP::NQ, NV = TP::NV;
+    using ROWS = TeamRows<TP, 27, false, 0>;
+    __shared__ float lds_team[(ROWS::total() + 6 * TrunkRows<TP>::body(TP::N)) * kTileLanes];
+    team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
+      constexpr int W = decltype(W_)::value;
+      const LdsCol lds{lds_team + tl.lane}, acc = lds.at(ROWS::total());
+      const SoaIo<TP> io{ld};
+      const bool owner = TM::may_own(W) && tl.wave == TM::kOwner;
+      const float* const t = opaque_table(tab);
+      const float* const tb = opaque_table(tab + tl.shift * kBodyStride);
+      float qv[NQ], qdv[NV], tv[NV];
+      team_read<TP, W, true, false>(qv, io, q, tl, owner);
+      team_read<TP, W, true, true>(qdv, io, qd, tl, owner);
+      team_read<TP, W, false, true>(tv, io, tau, tl, owner);
+      const RegView qr{qv}, qdr{qdv}, tr{tv};
+      const auto fx = team_fext<EXT>(fext, ld, 0, tl.b);
+      using FX = std::decay_t<decltype(fx)>;
+      AbaState<TP, EXT> s;
+      team_aba_up<TP, W, ROWS>(t, tb, s, qr, qdr, tr, team_fext<EXT>(fext, ld, tl.shift, tl.b),
+                               lds.at(team_base<TP, ROWS, W>(tl)));
+      if constexpr (TM::may_own(W)) {
+        if (owner) {
+          sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
+            constexpr int I = decltype(I_)::value;
+            // (those above its branches have their motion, but the forces are read with the moved view)
+            if constexpr (TM::trunk(I) && (EXT || !TM::above(W, I))) aba_motion<TP, I>(t, s, qr, qdr, fx);
+          });
+        }
+      }
+      __syncthreads();
+      if constexpr (TM::may_own(W)) {
+        if (owner)
+          team_aba_trunk<TP, ROWS, FX>(t, s, qr, qdr, tr, lds, acc, io.template out<NV>(qdd, 0, tl.b));
+      }
+      __syncthreads();
+      team_aba_down<TP, W>(opaque_table(t), opaque_table(tb), s, qr, qdr, acc, io.template out<NV>(qdd, tl.shift, tl.b));
     });
   }
 }
@@ -1254,6 +1282,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads) void k_rnea_vjp_team(
       const uint32_t b = tl.b;
       const int64_t off = tl.shift * ld;
       const bool owner = TM::may_own(W) && tl.wave == TM::kOwner;
+      const float* const t = opaque_table(tab);
       float x[4][NQ];
       const float* const in[4] = {q, qd, qdd, lam};
       sfor<0, 4>([&](auto A_) __attribute__((always_inline)) {
@@ -1272,17 +1301,17 @@ __global__ __launch_bounds__(Team<TP>::kThreads) void k_rnea_vjp_team(
         else return NoGF{};
       };
       AdjState<TP, EXT, EXT> s;
-      team_adj_up<TP, W, ROWS>(tab, tab + tl.shift * kBodyStride, s, qr, qdr, ar, lr, neg(gq, off), neg(gqd, off),
+      team_adj_up<TP, W, ROWS>(t, opaque_table(tab + tl.shift * kBodyStride), s, qr, qdr, ar, lr, neg(gq, off), neg(gqd, off),
                                team_fext_opt<EXT>(fext, ld, tl.shift, b), gf(tl.shift),
                                On<OutOpt<Out>>{team_out(gqdd, off, ld, b)}, lds.at(team_base<TP, ROWS, W>(tl)));
       if constexpr (TM::may_own(W)) {
         if (owner)
-          team_adj_trunk_down<TP, W>(tab, s, qr, qdr, ar, lr, team_fext_opt<EXT>(fext, ld, 0, b), gf(0));
+          team_adj_trunk_down<TP, W>(t, s, qr, qdr, ar, lr, team_fext_opt<EXT>(fext, ld, 0, b), gf(0));
       }
       __syncthreads();
       if constexpr (TM::may_own(W)) {
         if (owner)
-          team_adj_trunk<TP, ROWS>(tab, s, qr, qdr, neg(gq, 0), neg(gqd, 0), On<OutOpt<Out>>{team_out(gqdd, 0, ld, b)},
+          team_adj_trunk<TP, ROWS>(t, s, qr, qdr, neg(gq, 0), neg(gqd, 0), On<OutOpt<Out>>{team_out(gqdd, 0, ld, b)},
                                    lds);
       }
     });
@@ -1324,6 +1353,7 @@ __global__ __launch_bounds__(Team<TP>::kOn ? Team<TP>::kThreads : kBlock, Team<T
         team_load_trunk<TP, false>(qv, qi);
         team_load_trunk<TP, true>(qdv, qdi);
       }
+      const float* const t = opaque_table(tab);
       const RegView qr{qv}, qdr{qdv};
       const Out to{tau, ld, b};
       const auto hold = [&](int k, float v) __attribute__((always_inline)) {
@@ -1336,10 +1366,10 @@ __global__ __launch_bounds__(Team<TP>::kOn ? Team<TP>::kThreads : kBlock, Team<T
       if constexpr (TP::kFree) {
         if constexpr (TM::above(W, 0) || kOwner) s.p0 = {qv[0], qv[1], qv[2]};
       }
-      OscHook<TP, E, RegView, In, decltype(hold)> hook{tab, qdr, ti, hold, kp, kd, kn};
+      OscHook<TP, E, RegView, In, decltype(hold)> hook{t, qdr, ti, hold, kp, kd, kn};
       hook.init();
       Ltl<TP, kTask ? 7 : 1> F;
-      team_fd_up<TP, W, kTask ? 7 : 1, ROWS, MASK>(tab, tab, qr, qdr, hook, NoFext{}, s, F, lds.at(ROWS::base(W)));
+      team_fd_up<TP, W, kTask ? 7 : 1, ROWS, MASK>(t, t, qr, qdr, hook, NoFext{}, s, F, lds.at(ROWS::base(W)));
       if constexpr (kTask) {
         sfor<0, NV>([&](auto K_) __attribute__((always_inline)) {
           constexpr int K = decltype(K_)::value;
@@ -1365,12 +1395,12 @@ __global__ __launch_bounds__(Team<TP>::kOn ? Team<TP>::kThreads : kBlock, Team<T
       }
       if constexpr (kOwner) {
         // the trunk's motion (its hook starts afresh: a wave may own both E and the trunk)
-        team_fd_trunk_down<TP, W>(tab, qr, qdr, NoFext{}, s);
+        team_fd_trunk_down<TP, W>(t, qr, qdr, NoFext{}, s);
       }
       __syncthreads();
       float z[6];
       if constexpr (kOwner) {
-        OscHook<TP, E, RegView, In, decltype(hold)> top{tab, qdr, ti, hold, kp, kd, kn};
+        OscHook<TP, E, RegView, In, decltype(hold)> top{t, qdr, ti, hold, kp, kd, kn};
         top.init();
         if constexpr (EROWS::kWave >= 0) {
           int n = EROWS::kG;
@@ -1391,7 +1421,7 @@ __global__ __launch_bounds__(Team<TP>::kOn ? Team<TP>::kThreads : kBlock, Team<T
           });
         }
         Ltl<TP, 7> Ft;
-        team_fd_trunk<TP, 7, ROWS, MASK>(tab, OscTrunkHook<TP, E, decltype(top)>{top, ex}, s, lds, Ft);
+        team_fd_trunk<TP, 7, ROWS, MASK>(t, OscTrunkHook<TP, E, decltype(top)>{top, ex}, s, lds, Ft);
         chol6_solve(top.G, top.a, z);
 #pragma unroll
         for (int i = 0; i < 6; ++i) lds.put(i, z[i]);

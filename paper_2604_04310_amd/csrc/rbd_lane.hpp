@@ -358,6 +358,30 @@ RBD_DI M3 quat_rot(float w, float x, float y, float z) {
   return R;
 }
 
+// The same pointer value, hidden from the optimiser (an empty asm on its
+// scalar register, no instruction). A kernel that runs several sweeps gives
+// each its own copies of the table and input pointers and of the row stride,
+// so model constants, inputs, row addresses and what is computed from them
+// (joint sines and cosines) are reloaded and recomputed in each sweep instead
+// of being held in registers across all of them.
+// The asm operand keeps the pointer's address space (global for inputs,
+// constant for the model table), so loads through the copy stay global loads
+// with a scalar base, and table reads stay scalar loads.
+RBD_DI const float* opaque(const float* p) {
+  auto g = (const __attribute__((address_space(1))) float*)p;
+  asm volatile("" : "+s"(g));
+  return (const float*)g;
+}
+RBD_DI const float* opaque_table(const float* p) {
+  auto c = (const __attribute__((address_space(4))) float*)p;
+  asm volatile("" : "+s"(c));
+  return (const float*)c;
+}
+RBD_DI int64_t opaque(int64_t x) {
+  asm volatile("" : "+s"(x));
+  return x;
+}
+
 // Column of a composite inertia for S = [e_z; 0]: I S = [Ibar e_z; -h x e_z]
 RBD_DI Frc inr_col_z(const Inr& I) { return {{I.xz, I.yz, I.zz}, {-I.h.y, I.h.x, 0.0f}}; }
 
@@ -889,7 +913,7 @@ RBD_DI void crba_row(const float* __restrict__ t, const M3* R, const Inr& IcJ, f
 // and a final root-to-leaves sweep solves L x = y.
 // BIAS = false solves M x = rhs alone (no bias force, qd unused).
 template <class TP, int NRHS, class QI, class QDI, class RHS, class SINK, class FX = NoFext, bool BIAS = true>
-RBD_DI void fwd_dyn_lane(const float* __restrict__ t, const QI& q, const QDI& qd, const RHS& rhs, const SINK& sink,
+RBD_DI void fwd_dyn_lane(const float* __restrict__ tab, const QI& q, const QDI& qd, const RHS& rhs, const SINK& sink,
                          const FX& fx = FX{}) {
   constexpr int N = TP::N, NV = TP::NV;
   constexpr int NW = FX::kOn ? N : 1;
@@ -900,12 +924,19 @@ RBD_DI void fwd_dyn_lane(const float* __restrict__ t, const QI& q, const QDI& qd
   Frc f[N];
   Inr Ic[N];
   Ltl<TP, NRHS> F;
+  const float* const t = opaque_table(tab);
   const V3 g = load_g<TP>(t);
   const V3 mg = {-g.x, -g.y, -g.z};
 
   auto backward = [&](auto J_) __attribute__((always_inline)) {
     constexpr int J = decltype(J_)::value;
     constexpr int P = TP::parent(J);
+    // a body's own inertia enters its composite when its first child closes (a
+    // leaf's, when it closes itself), read again there: held since the forward
+    // step, the inertias filled the scalar registers, and moving spilled ones
+    // was 7 % of a 7-joint chain's vector instructions (2350 -> 2195)
+    const float* const tc = opaque_table(t);
+    if constexpr (TP::last(J) == J) Ic[J] = load_inr<J>(tc);
     if constexpr (TP::free_body(J)) {
       if constexpr (BIAS) {
         const float hb[6] = {f[J].f.x, f[J].f.y, f[J].f.z, f[J].n.x, f[J].n.y, f[J].n.z};
@@ -926,6 +957,7 @@ RBD_DI void fwd_dyn_lane(const float* __restrict__ t, const QI& q, const QDI& qd
       if constexpr (P >= 0) {
         const V3 r = load_r<J>(t);
         if constexpr (BIAS) xfrc_acc(R[J], r, f[J], f[P]);
+        if constexpr (J == P + 1) Ic[P] = load_inr<P>(tc);
         xinr_acc(R[J], r, Ic[J], Ic[P]);
       }
     }
@@ -958,15 +990,14 @@ RBD_DI void fwd_dyn_lane(const float* __restrict__ t, const QI& q, const QDI& qd
         a[I].v.y = a[I].v.y - w * v[I].v.x;
       }
     }
-    const Inr Ib = load_inr<I>(t);
     if constexpr (BIAS) {
+      const Inr Ib = load_inr<I>(t);
       f[I] = imul(Ib, a[I]) + crf(v[I], imul(Ib, v[I]));
       if constexpr (FX::kOn) {
         world_pose<TP, I>(t, q, R[I], Rw, pw);
         f[I] = f[I] - fext_body<I>(fx, Rw[I], pw[I]);
       }
     }
-    Ic[I] = Ib;
     close_subtrees<TP, I, I>(backward);
   });
 
@@ -977,13 +1008,16 @@ RBD_DI void fwd_dyn_lane(const float* __restrict__ t, const QI& q, const QDI& qd
 // fwd_dyn_lane (joint rotations down, CRBA rows and factor rows as subtrees
 // close) without right-hand sides and without the solve.
 template <class TP, class QI>
-RBD_DI void ltl_factor_lane(const float* __restrict__ t, const QI& q, Ltl<TP, 1>& F) {
+RBD_DI void ltl_factor_lane(const float* __restrict__ tab, const QI& q, Ltl<TP, 1>& F) {
   constexpr int N = TP::N, NV = TP::NV;
   M3 R[N];
   Inr Ic[N];
+  const float* const t = opaque_table(tab);
   auto backward = [&](auto J_) __attribute__((always_inline)) {
     constexpr int J = decltype(J_)::value;
     constexpr int P = TP::parent(J);
+    const float* const tc = opaque_table(t);  // as in fwd_dyn_lane
+    if constexpr (TP::last(J) == J) Ic[J] = load_inr<J>(tc);
     if constexpr (TP::free_body(J)) {
       ltl_base_rows<TP, 1>(F, Ic[J], [](int, int) __attribute__((always_inline)) { return 0.0f; }, NoRhs{});
     } else {
@@ -991,6 +1025,7 @@ RBD_DI void ltl_factor_lane(const float* __restrict__ t, const QI& q, Ltl<TP, 1>
       crba_row<TP, J>(t, R, Ic[J], Mr);
       const float bk[1] = {0.0f};
       ltl_row<TP, TP::vofs(J), 1, NoRhs>(F, Mr, Ic[J].zz, bk);
+      if constexpr (J == P + 1 && P >= 0) Ic[P] = load_inr<P>(tc);
       if constexpr (P >= 0) xinr_acc(R[J], load_r<J>(t), Ic[J], Ic[P]);
     }
   };
@@ -998,7 +1033,6 @@ RBD_DI void ltl_factor_lane(const float* __restrict__ t, const QI& q, Ltl<TP, 1>
     constexpr int I = decltype(I_)::value;
     if constexpr (TP::free_body(I)) R[I] = quat_rot(q(3), q(4), q(5), q(6));
     else R[I] = joint_rot<I>(t, q(cidx<TP::qofs(I)>));
-    Ic[I] = load_inr<I>(t);
     close_subtrees<TP, I, I>(backward);
   });
 }
@@ -1177,10 +1211,11 @@ RBD_DI void tan_force(const float* __restrict__ t, ST& st, const FX& fx, const D
 
 template <class TP, class QI, class QDI, class QDDI, class DQI, class DQDI, class DTI, class OUT, class FX = NoFext,
           class DFX = NoFext, class DQDD = NoFext>
-RBD_DI void id_tangent_lane(const float* __restrict__ t, const QI& q, const QDI& qd, const QDDI& qdd,
+RBD_DI void id_tangent_lane(const float* __restrict__ tab, const QI& q, const QDI& qd, const QDDI& qdd,
                             const DQI& dq, const DQDI& dqd, const DTI& dtau, const OUT& out, const FX& fx = FX{},
                             const DFX& dfx = DFX{}, const DQDD& dqdd = DQDD{}) {
   TanState<TP, FX::kOn || DFX::kOn> st;
+  const float* const t = opaque_table(tab);
   const V3 g = load_g<TP>(t);
   const V3 mg = {-g.x, -g.y, -g.z};
   auto backward = [&](auto J_) __attribute__((always_inline)) {
@@ -1249,7 +1284,8 @@ RBD_DI void adj_close(const float* __restrict__ t, V3 g, ST& s, const QI& q, con
                       const GQD& gqd, const GQDD& gqdd) {
   constexpr bool kExt = ST::kExt;
   constexpr int P = TP::parent(J);
-  const Inr Ib = load_inr<J>(t);
+  const float* const tc = opaque_table(t);  // read again, not held since the forward step
+  const Inr Ib = load_inr<J>(tc);
   const Frc abar = imul(Ib, s.mu[J]) + s.ab[J];
   Frc vbar = imul(Ib, crm(s.mu[J], s.v[J])) - crf(s.mu[J], imul(Ib, s.v[J])) + s.vb[J];
   if constexpr (GQDD::kOn) {
@@ -1312,8 +1348,8 @@ RBD_DI void adj_close(const float* __restrict__ t, V3 g, ST& s, const QI& q, con
     if constexpr (P >= 0) {
       // <X mu_p, S x* f>: (X mu_p) has the x, y parts of mu
       dq = dq - s.mu[J].w.x * s.f[J].n.y + s.mu[J].w.y * s.f[J].n.x - s.mu[J].v.x * s.f[J].f.y + s.mu[J].v.y * s.f[J].f.x;
-      const V3 r = load_r<J>(t);
-      const M3 RJ = joint_rot_cs<J>(t, s.cq[J], s.sq[J]);
+      const V3 r = load_r<J>(tc);
+      const M3 RJ = joint_rot_cs<J>(tc, s.cq[J], s.sq[J]);
       xfrc_acc(RJ, r, s.f[J], s.f[P]);
       xfrc_acc(RJ, r, abar, s.ab[P]);
       xfrc_acc(RJ, r, vbar, s.vb[P]);
@@ -1389,10 +1425,11 @@ RBD_DI void adj_force(const float* __restrict__ t, ST& s, const FX& fx, const GF
 
 template <class TP, class QI, class QDI, class QDD, class LAM, class GQ, class GQD, class FX = NoFext, class GF = NoGF,
           class GQDD = NoGF>
-RBD_DI void id_adjoint_lane(const float* __restrict__ t, const QI& q, const QDI& qd, const QDD& qdd, const LAM& lam,
+RBD_DI void id_adjoint_lane(const float* __restrict__ tab, const QI& q, const QDI& qd, const QDD& qdd, const LAM& lam,
                             const GQ& gq, const GQD& gqd, const FX& fx = FX{}, const GF& gf = GF{},
                             const GQDD& gqdd = GQDD{}) {
   AdjState<TP, FX::kOn, GF::kOn> s;
+  const float* const t = opaque_table(tab);
   const V3 g = load_g<TP>(t);
   const V3 mg = {-g.x, -g.y, -g.z};
   auto backward = [&](auto J_) __attribute__((always_inline)) {
@@ -1596,11 +1633,13 @@ RBD_DI Mot ainr_solve(const AInr& I, const Frc& rhs) {
 // subtracted from pA; a free base solves its 6x6 articulated inertia
 // directly. A parent's accumulators start at its first child's contribution,
 // so a chain body holds none while its subtree runs.
-template <class TP, class QI, class QDI, class TI, class QDDO, class FX = NoFext>
-RBD_DI void aba_lane(const float* __restrict__ t, const QI& q, const QDI& qd, const TI& tau, const QDDO& qdd,
-                     const FX& fx = FX{}) {
-  constexpr int N = TP::N;
-  constexpr int NW = FX::kOn ? N : 1;
+//
+// The sweeps' state, and their steps for one body: aba_motion (velocity), aba_close
+// (the subtree's articulated inertia and bias force, added to the parent's; FIRST:
+// the parent has none yet), aba_down (acceleration).
+template <class TP, bool EXT>
+struct AbaState {
+  static constexpr int N = TP::N, NW = EXT ? N : 1;
   M3 Rw[NW];
   V3 pw[NW];
   Frc fe[NW];  // external force in body coordinates, subtracted from pA
@@ -1611,132 +1650,156 @@ RBD_DI void aba_lane(const float* __restrict__ t, const QI& q, const QDI& qd, co
   AInr acc[N];
   Frc accp[N];
   Mot a0;  // free base: total spatial acceleration (gravity included)
+};
+template <class TP>
+struct AbaDown {
+  Mot a[TP::N], vv[TP::N];
+};
+
+template <class TP, int J, bool FIRST, class FX, class ST, class QDI, class TI>
+RBD_DI void aba_close(const float* __restrict__ t, ST& s, const QDI& qd, const TI& tau) {
+  constexpr int P = TP::parent(J);
+  constexpr bool kKids = TP::last(J) > J;
+  const float* const tc = opaque_table(t);  // read again, not held since the velocity pass
+  const Inr Ib = load_inr<J>(tc);
+  Frc bias = crf(s.v[J], imul(Ib, s.v[J]));
+  if constexpr (FX::kOn) bias = bias - s.fe[J];
+  AInr IA;
+  Frc pA;
+  if constexpr (kKids) {
+    IA = s.acc[J];
+    ainr_add_rigid(IA, Ib);
+    pA = s.accp[J] + bias;
+  } else {
+    IA = ainr_rigid(Ib);
+    pA = bias;
+  }
+  if constexpr (TP::free_body(J)) {
+    const Frc b = {{tau(3) - pA.n.x, tau(4) - pA.n.y, tau(5) - pA.n.z}, {tau(0) - pA.f.x, tau(1) - pA.f.y, tau(2) - pA.f.z}};
+    s.a0 = ainr_solve(IA, b);
+  } else {
+    const Frc U = {{IA.a02, IA.a12, IA.a22}, {IA.b[6], IA.b[7], IA.b[8]}};
+    const float invD = frcp(IA.a22);
+    const float u = tau(cidx<TP::vofs(J)>) - pA.n.z;
+    const Frc W = {invD * U.n, invD * U.f};
+    s.Ud[J] = W;
+    s.ud[J] = u * invD;
+    if constexpr (P >= 0) {
+      AInrP Ia;
+      Ia.a00 = __builtin_fmaf(-U.n.x, W.n.x, IA.a00);
+      Ia.a11 = __builtin_fmaf(-U.n.y, W.n.y, IA.a11);
+      Ia.a01 = __builtin_fmaf(-U.n.x, W.n.y, IA.a01);
+      const float uf[3] = {W.f.x, W.f.y, W.f.z};
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        Ia.b[k] = __builtin_fmaf(-U.n.x, uf[k], IA.b[k]);
+        Ia.b[3 + k] = __builtin_fmaf(-U.n.y, uf[k], IA.b[3 + k]);
+      }
+      Ia.c00 = __builtin_fmaf(-U.f.x, W.f.x, IA.c00);
+      Ia.c11 = __builtin_fmaf(-U.f.y, W.f.y, IA.c11);
+      Ia.c22 = __builtin_fmaf(-U.f.z, W.f.z, IA.c22);
+      Ia.c01 = __builtin_fmaf(-U.f.x, W.f.y, IA.c01);
+      Ia.c02 = __builtin_fmaf(-U.f.x, W.f.z, IA.c02);
+      Ia.c12 = __builtin_fmaf(-U.f.y, W.f.z, IA.c12);
+      // pa = pA + Ia c + U u / D; c = w [wy, -wx, 0; vy, -vx, 0]
+      const float w = qd(cidx<TP::vofs(J)>);
+      const float cwx = w * s.v[J].w.y, cwy = -w * s.v[J].w.x, cvx = w * s.v[J].v.y, cvy = -w * s.v[J].v.x;
+      const float ud_ = s.ud[J];
+      Frc pa;
+      pa.n.x = pA.n.x + Ia.a00 * cwx + Ia.a01 * cwy + Ia.b[0] * cvx + Ia.b[1] * cvy + U.n.x * ud_;
+      pa.n.y = pA.n.y + Ia.a01 * cwx + Ia.a11 * cwy + Ia.b[3] * cvx + Ia.b[4] * cvy + U.n.y * ud_;
+      pa.n.z = pA.n.z + U.n.z * ud_;
+      pa.f.x = pA.f.x + Ia.b[0] * cwx + Ia.b[3] * cwy + Ia.c00 * cvx + Ia.c01 * cvy + U.f.x * ud_;
+      pa.f.y = pA.f.y + Ia.b[1] * cwx + Ia.b[4] * cwy + Ia.c01 * cvx + Ia.c11 * cvy + U.f.y * ud_;
+      pa.f.z = pA.f.z + Ia.b[2] * cwx + Ia.b[5] * cwy + Ia.c02 * cvx + Ia.c12 * cvy + U.f.z * ud_;
+      const V3 r = load_r<J>(tc);
+      const M3 RJ = joint_rot_cs<J>(tc, s.cq[J], s.sq[J]);
+        xainr_acc<FIRST>(RJ, r, Ia, s.acc[P]);
+      if constexpr (FIRST) s.accp[P] = xfrc(RJ, r, pa);
+      else xfrc_acc(RJ, r, pa, s.accp[P]);
+    }
+  }
+}
+
+template <class TP, int I, class FX, class ST, class QI, class QDI>
+RBD_DI void aba_motion(const float* __restrict__ t, ST& s, const QI& q, const QDI& qd, const FX& fx) {
+  constexpr int P = TP::parent(I);
+  if constexpr (TP::free_body(I)) {
+    s.v[I] = {{qd(3), qd(4), qd(5)}, {qd(0), qd(1), qd(2)}};
+    if constexpr (FX::kOn) world_pose<TP, I>(t, q, quat_rot(q(3), q(4), q(5), q(6)), s.Rw, s.pw);
+  } else {
+    fsincos(q(cidx<TP::qofs(I)>), s.sq[I], s.cq[I]);
+    const float w = qd(cidx<TP::vofs(I)>);
+    const M3 RI = joint_rot_cs<I>(t, s.cq[I], s.sq[I]);
+    if constexpr (P < 0) {
+      s.v[I] = {{0.0f, 0.0f, w}, {0.0f, 0.0f, 0.0f}};
+    } else {
+      s.v[I] = xmot(RI, load_r<I>(t), s.v[P]);
+      s.v[I].w.z = s.v[I].w.z + w;
+    }
+    if constexpr (FX::kOn) world_pose<TP, I>(t, q, RI, s.Rw, s.pw);
+  }
+  if constexpr (FX::kOn) s.fe[I] = fext_body<I>(fx, s.Rw[I], s.pw[I]);
+}
+
+template <class TP, int I, class ST, class QI, class QDI, class QDDO>
+RBD_DI void aba_down(const float* __restrict__ t, V3 mg, const ST& s, AbaDown<TP>& d, const QI& q, const QDI& qd,
+                     const QDDO& qdd) {
+  constexpr int P = TP::parent(I);
+  if constexpr (TP::free_body(I)) {
+    const V3 ag = mulT(quat_rot(q(3), q(4), q(5), q(6)), mg);
+    d.a[I] = s.a0;
+    d.vv[I] = {{qd(3), qd(4), qd(5)}, {qd(0), qd(1), qd(2)}};
+    qdd(0, s.a0.v.x - ag.x); qdd(1, s.a0.v.y - ag.y); qdd(2, s.a0.v.z - ag.z);
+    qdd(3, s.a0.w.x); qdd(4, s.a0.w.y); qdd(5, s.a0.w.z);
+  } else {
+    float sn, cs;
+    fsincos(q(cidx<TP::qofs(I)>), sn, cs);
+    const M3 RI = joint_rot_cs<I>(t, cs, sn);
+    const float w = qd(cidx<TP::vofs(I)>);
+    Mot ap;
+    if constexpr (P < 0) {
+      d.vv[I] = {{0.0f, 0.0f, w}, {0.0f, 0.0f, 0.0f}};
+      ap = {{0.0f, 0.0f, 0.0f}, mulT(RI, mg)};
+    } else {
+      const V3 r = load_r<I>(t);
+      d.vv[I] = xmot(RI, r, d.vv[P]);
+      d.vv[I].w.z = d.vv[I].w.z + w;
+      ap = xmot(RI, r, d.a[P]);
+      ap.w.x = __builtin_fmaf(w, d.vv[I].w.y, ap.w.x);
+      ap.w.y = __builtin_fmaf(-w, d.vv[I].w.x, ap.w.y);
+      ap.v.x = __builtin_fmaf(w, d.vv[I].v.y, ap.v.x);
+      ap.v.y = __builtin_fmaf(-w, d.vv[I].v.x, ap.v.y);
+    }
+    const float x = s.ud[I] - pair(s.Ud[I], ap);
+    qdd(cidx<TP::vofs(I)>, x);
+    ap.w.z = ap.w.z + x;
+    d.a[I] = ap;
+  }
+}
+
+template <class TP, class QI, class QDI, class TI, class QDDO, class FX = NoFext>
+RBD_DI void aba_lane(const float* __restrict__ tab, const QI& q, const QDI& qd, const TI& tau, const QDDO& qdd,
+                     const FX& fx = FX{}) {
+  AbaState<TP, FX::kOn> s;
+  const float* const t = opaque_table(tab);
   const V3 g = load_g<TP>(t);
   const V3 mg = {-g.x, -g.y, -g.z};
-
   auto close = [&](auto J_) __attribute__((always_inline)) {
     constexpr int J = decltype(J_)::value;
-    constexpr int P = TP::parent(J);
-    constexpr bool kKids = TP::last(J) > J;
-    const Inr Ib = load_inr<J>(t);
-    Frc bias = crf(v[J], imul(Ib, v[J]));
-    if constexpr (FX::kOn) bias = bias - fe[J];
-    AInr IA;
-    Frc pA;
-    if constexpr (kKids) {
-      IA = acc[J];
-      ainr_add_rigid(IA, Ib);
-      pA = accp[J] + bias;
-    } else {
-      IA = ainr_rigid(Ib);
-      pA = bias;
-    }
-    if constexpr (TP::free_body(J)) {
-      const Frc b = {{tau(3) - pA.n.x, tau(4) - pA.n.y, tau(5) - pA.n.z}, {tau(0) - pA.f.x, tau(1) - pA.f.y, tau(2) - pA.f.z}};
-      a0 = ainr_solve(IA, b);
-    } else {
-      const Frc U = {{IA.a02, IA.a12, IA.a22}, {IA.b[6], IA.b[7], IA.b[8]}};
-      const float invD = frcp(IA.a22);
-      const float u = tau(cidx<TP::vofs(J)>) - pA.n.z;
-      const Frc W = {invD * U.n, invD * U.f};
-      Ud[J] = W;
-      ud[J] = u * invD;
-      if constexpr (P >= 0) {
-        AInrP Ia;
-        Ia.a00 = __builtin_fmaf(-U.n.x, W.n.x, IA.a00);
-        Ia.a11 = __builtin_fmaf(-U.n.y, W.n.y, IA.a11);
-        Ia.a01 = __builtin_fmaf(-U.n.x, W.n.y, IA.a01);
-        const float uf[3] = {W.f.x, W.f.y, W.f.z};
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          Ia.b[k] = __builtin_fmaf(-U.n.x, uf[k], IA.b[k]);
-          Ia.b[3 + k] = __builtin_fmaf(-U.n.y, uf[k], IA.b[3 + k]);
-        }
-        Ia.c00 = __builtin_fmaf(-U.f.x, W.f.x, IA.c00);
-        Ia.c11 = __builtin_fmaf(-U.f.y, W.f.y, IA.c11);
-        Ia.c22 = __builtin_fmaf(-U.f.z, W.f.z, IA.c22);
-        Ia.c01 = __builtin_fmaf(-U.f.x, W.f.y, IA.c01);
-        Ia.c02 = __builtin_fmaf(-U.f.x, W.f.z, IA.c02);
-        Ia.c12 = __builtin_fmaf(-U.f.y, W.f.z, IA.c12);
-        // pa = pA + Ia c + U u / D; c = w [wy, -wx, 0; vy, -vx, 0]
-        const float w = qd(cidx<TP::vofs(J)>);
-        const float cwx = w * v[J].w.y, cwy = -w * v[J].w.x, cvx = w * v[J].v.y, cvy = -w * v[J].v.x;
-        const float ud_ = ud[J];
-        Frc pa;
-        pa.n.x = pA.n.x + Ia.a00 * cwx + Ia.a01 * cwy + Ia.b[0] * cvx + Ia.b[1] * cvy + U.n.x * ud_;
-        pa.n.y = pA.n.y + Ia.a01 * cwx + Ia.a11 * cwy + Ia.b[3] * cvx + Ia.b[4] * cvy + U.n.y * ud_;
-        pa.n.z = pA.n.z + U.n.z * ud_;
-        pa.f.x = pA.f.x + Ia.b[0] * cwx + Ia.b[3] * cwy + Ia.c00 * cvx + Ia.c01 * cvy + U.f.x * ud_;
-        pa.f.y = pA.f.y + Ia.b[1] * cwx + Ia.b[4] * cwy + Ia.c01 * cvx + Ia.c11 * cvy + U.f.y * ud_;
-        pa.f.z = pA.f.z + Ia.b[2] * cwx + Ia.b[5] * cwy + Ia.c02 * cvx + Ia.c12 * cvy + U.f.z * ud_;
-        const V3 r = load_r<J>(t);
-        const M3 RJ = joint_rot_cs<J>(t, cq[J], sq[J]);
-        constexpr bool kFirst = (J == P + 1);
-        xainr_acc<kFirst>(RJ, r, Ia, acc[P]);
-        if constexpr (kFirst) accp[P] = xfrc(RJ, r, pa);
-        else xfrc_acc(RJ, r, pa, accp[P]);
-      }
-    }
+    aba_close<TP, J, (J == TP::parent(J) + 1), FX>(t, s, qd, tau);
   };
-
   // velocity pass (root to leaves) with the articulated pass on subtree close
-  sfor<0, N>([&](auto I_) __attribute__((always_inline)) {
+  sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
     constexpr int I = decltype(I_)::value;
-    constexpr int P = TP::parent(I);
-    if constexpr (TP::free_body(I)) {
-      v[I] = {{qd(3), qd(4), qd(5)}, {qd(0), qd(1), qd(2)}};
-      if constexpr (FX::kOn) world_pose<TP, I>(t, q, quat_rot(q(3), q(4), q(5), q(6)), Rw, pw);
-    } else {
-      fsincos(q(cidx<TP::qofs(I)>), sq[I], cq[I]);
-      const float w = qd(cidx<TP::vofs(I)>);
-      const M3 RI = joint_rot_cs<I>(t, cq[I], sq[I]);
-      if constexpr (P < 0) {
-        v[I] = {{0.0f, 0.0f, w}, {0.0f, 0.0f, 0.0f}};
-      } else {
-        v[I] = xmot(RI, load_r<I>(t), v[P]);
-        v[I].w.z = v[I].w.z + w;
-      }
-      if constexpr (FX::kOn) world_pose<TP, I>(t, q, RI, Rw, pw);
-    }
-    if constexpr (FX::kOn) fe[I] = fext_body<I>(fx, Rw[I], pw[I]);
+    aba_motion<TP, I>(t, s, q, qd, fx);
     close_subtrees<TP, I, I>(close);
   });
-
   // acceleration pass (root to leaves), velocities rebuilt on the way
-  Mot a[N], vv[N];
-  sfor<0, N>([&](auto I_) __attribute__((always_inline)) {
-    constexpr int I = decltype(I_)::value;
-    constexpr int P = TP::parent(I);
-    if constexpr (TP::free_body(I)) {
-      const V3 ag = mulT(quat_rot(q(3), q(4), q(5), q(6)), mg);
-      a[I] = a0;
-      vv[I] = {{qd(3), qd(4), qd(5)}, {qd(0), qd(1), qd(2)}};
-      qdd(0, a0.v.x - ag.x); qdd(1, a0.v.y - ag.y); qdd(2, a0.v.z - ag.z);
-      qdd(3, a0.w.x); qdd(4, a0.w.y); qdd(5, a0.w.z);
-    } else {
-      float s, c;
-      fsincos(q(cidx<TP::qofs(I)>), s, c);
-      const M3 RI = joint_rot_cs<I>(t, c, s);
-      const float w = qd(cidx<TP::vofs(I)>);
-      Mot ap;
-      if constexpr (P < 0) {
-        vv[I] = {{0.0f, 0.0f, w}, {0.0f, 0.0f, 0.0f}};
-        ap = {{0.0f, 0.0f, 0.0f}, mulT(RI, mg)};
-      } else {
-        const V3 r = load_r<I>(t);
-        vv[I] = xmot(RI, r, vv[P]);
-        vv[I].w.z = vv[I].w.z + w;
-        ap = xmot(RI, r, a[P]);
-        ap.w.x = __builtin_fmaf(w, vv[I].w.y, ap.w.x);
-        ap.w.y = __builtin_fmaf(-w, vv[I].w.x, ap.w.y);
-        ap.v.x = __builtin_fmaf(w, vv[I].v.y, ap.v.x);
-        ap.v.y = __builtin_fmaf(-w, vv[I].v.x, ap.v.y);
-      }
-      const float x = ud[I] - pair(Ud[I], ap);
-      qdd(cidx<TP::vofs(I)>, x);
-      ap.w.z = ap.w.z + x;
-      a[I] = ap;
-    }
+  AbaDown<TP> d;
+  const float* const td = opaque_table(t);
+  sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
+    aba_down<TP, decltype(I_)::value>(td, mg, s, d, q, qd, qdd);
   });
 }
 

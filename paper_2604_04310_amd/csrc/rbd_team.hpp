@@ -105,6 +105,11 @@ struct TrunkRows {
   static constexpr TrunkRowTab<TP> v = TrunkRowTab<TP>::make();
   static constexpr int row(int k) { return v.row[k]; }
   static constexpr int total() { return v.row[TP::NV]; }
+  static constexpr int body(int i) {  // trunk bodies before body i
+    int n = 0;
+    for (int j = 0; j < i; ++j) n += Team<TP>::trunk(j) ? 1 : 0;
+    return n;
+  }
 };
 
 // A lane's column of a run of LDS rows.
@@ -288,7 +293,7 @@ RBD_DI void team_add_qdd(ST& s, const QDDI& qdd) {
   if constexpr (TP::free_body(I)) s.a[I] = s.a[I] + Mot{{qdd(3), qdd(4), qdd(5)}, {qdd(0), qdd(1), qdd(2)}};
   else s.a[I].w.z = s.a[I].w.z + qdd(cidx<TP::vofs(I)>);
 }
-// Its force and inertia.
+// Its force.
 template <class TP, int I, class ST, class FX>
 RBD_DI void team_fd_force(const float* __restrict__ t, ST& s, const FX& fx) {
   const Inr Ib = load_inr<I>(t);
@@ -366,6 +371,9 @@ RBD_DI void team_fd_up(const float* __restrict__ t, const float* __restrict__ tb
     constexpr int P = TP::parent(J);
     if constexpr (TM::in(W, J)) {
       constexpr int k = TP::vofs(J);
+      // own inertias are read again where they enter (see fwd_dyn_lane)
+      const float* const tc = opaque_table(tb);
+      if constexpr (TP::last(J) == J) s.Ic[J] = load_inr<J>(tc);
       float Mr[NV];
       {
         auto emit = [&](auto A_, const Frc& e) __attribute__((always_inline)) {
@@ -386,6 +394,7 @@ RBD_DI void team_fd_up(const float* __restrict__ t, const float* __restrict__ tb
       if constexpr (P >= 0) {
         const V3 r = load_r<J>(tb);
         xfrc_acc(s.R[J], r, s.f[J], s.f[P]);
+        if constexpr (J == P + 1 && TM::in(W, P)) s.Ic[P] = load_inr<P>(tc);
         xinr_acc(s.R[J], r, s.Ic[J], s.Ic[P]);
       }
     }
@@ -437,7 +446,7 @@ RBD_DI void team_fd_up(const float* __restrict__ t, const float* __restrict__ tb
   });
 }
 
-// The owner's half of the way down: motion, force and inertia of the trunk
+// The owner's half of the way down: motion and force of the trunk
 // bodies (those above its own branches have their motion already).
 template <class TP, int W, class QV, class QDV, class FX, class ST>
 RBD_DI void team_fd_trunk_down(const float* __restrict__ t, const QV& q, const QDV& qd, const FX& fx, ST& s) {
@@ -477,6 +486,10 @@ RBD_DI void team_fd_trunk(const float* __restrict__ t, HOOK&& hook, ST& s, const
     });
     ltl_row<TP, K, NRHS, MASK, TrunkDofs<TP>>(F, Mr, Mkk, bk);
   };
+  sfor<0, N>([&](auto I_) __attribute__((always_inline)) {
+    constexpr int I = decltype(I_)::value;
+    if constexpr (TM::trunk(I)) s.Ic[I] = load_inr<I>(t);
+  });
   sfor_rev<0, N>([&](auto J_) __attribute__((always_inline)) {
     constexpr int J = decltype(J_)::value;
     constexpr int P = TP::parent(J);
@@ -545,13 +558,14 @@ RBD_DI void team_fd_back(const Ltl<TP, NRHS>& F, const XT& xt, const SINK& sink)
 // (owner). sink(r, k, x) gets the role's branches, sink_t the trunk (owner).
 template <class TP, int W, int NRHS, class ROWS, class QV, class QDV, class RHS, class RHST, class FX, class SINK,
           class SINKT>
-RBD_DI void team_fd(const TeamLane& tl, bool owner, const float* __restrict__ t, const QV& q, const QDV& qd,
+RBD_DI void team_fd(const TeamLane& tl, bool owner, const float* __restrict__ tab, const QV& q, const QDV& qd,
                     const RHS& rhs, const RHST& rhs_t, const FX& fxb, const FX& fx, const LdsCol& lds,
                     const LdsCol& xrow, Ltl<TP, NRHS>& F, Ltl<TP, NRHS>& Ft, const SINK& sink, const SINKT& sink_t) {
   using TM = Team<TP>;
   constexpr int T = TrunkRows<TP>::total();
   TeamFd<TP, FX::kOn> s;
-  team_fd_up<TP, W, NRHS, ROWS>(t, t + tl.shift * kBodyStride, q, qd, FdHook<RHS>{rhs}, fxb, s, F,
+  const float* const t = opaque_table(tab);
+  team_fd_up<TP, W, NRHS, ROWS>(t, opaque_table(tab + tl.shift * kBodyStride), q, qd, FdHook<RHS>{rhs}, fxb, s, F,
                                 lds.at(team_base<TP, ROWS, W>(tl)));
   if constexpr (TM::may_own(W)) {
     if (owner) team_fd_trunk_down<TP, W>(t, q, qd, fx, s);
@@ -832,6 +846,112 @@ RBD_DI void team_solve_trunk(Ltl<TP, 1>& F, const B& b, const LdsCol& lds, const
     }
   });
   ltl_back<TP, 1, TrunkDofs<TP>>(F, sink);
+}
+
+// =================================================================== articulated-body algorithm
+RBD_DI void put_ainr(const LdsCol& c, int row, const AInr& I) {
+  const float x[12] = {I.a00, I.a11, I.a22, I.a01, I.a02, I.a12, I.c00, I.c11, I.c22, I.c01, I.c02, I.c12};
+#pragma unroll
+  for (int e = 0; e < 12; ++e) c.put(row + e, x[e]);
+#pragma unroll
+  for (int e = 0; e < 9; ++e) c.put(row + 12 + e, I.b[e]);
+}
+RBD_DI void add_ainr(const LdsCol& c, int row, AInr& I) {
+  float* const x[12] = {&I.a00, &I.a11, &I.a22, &I.a01, &I.a02, &I.a12, &I.c00, &I.c11, &I.c22, &I.c01, &I.c02, &I.c12};
+#pragma unroll
+  for (int e = 0; e < 12; ++e) *x[e] = *x[e] + c.get(row + e);
+#pragma unroll
+  for (int e = 0; e < 9; ++e) I.b[e] = I.b[e] + c.get(row + 12 + e);
+}
+
+// Role W, up (see aba_lane): the articulated inertia and bias force that its
+// branches add to the trunk bodies they hang on go to LDS (27 rows a body).
+template <class TP, int W, class ROWS, class ST, class QV, class QDV, class TV, class FX>
+RBD_DI void team_aba_up(const float* __restrict__ t, const float* __restrict__ tb, ST& s, const QV& q, const QDV& qd,
+                        const TV& tau, const FX& fx, const LdsCol& c) {
+  using TM = Team<TP>;
+  auto close = [&](auto J_) __attribute__((always_inline)) {
+    constexpr int J = decltype(J_)::value;
+    constexpr int P = TP::parent(J);
+    if constexpr (TM::in(W, J)) {
+      constexpr bool kFirst = J == P + 1 && P >= 0 && !TM::trunk(P < 0 ? 0 : P);
+      aba_close<TP, J, kFirst, FX>(tb, s, qd, tau);
+    }
+  };
+  sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
+    constexpr int I = decltype(I_)::value;
+    if constexpr (TM::above(W, I)) {
+      aba_motion<TP, I>(t, s, q, qd, fx);
+      if constexpr (TM::attach(W, I)) {
+        s.acc[I] = AInr{};
+        s.accp[I] = Frc{};
+      }
+    } else if constexpr (TM::in(W, I)) {
+      aba_motion<TP, I>(tb, s, q, qd, fx);
+      close_subtrees<TP, I, I>(close);
+    }
+  });
+  sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
+    constexpr int I = decltype(I_)::value;
+    if constexpr (TM::attach(W, I)) {
+      put_ainr(c, ROWS::arow(W, I), s.acc[I]);
+      put_frc(c, ROWS::arow(W, I) + 21, s.accp[I]);
+    }
+  });
+}
+// The trunk, up and down; `acc` takes the accelerations that the branches start
+// from, 6 rows per trunk body.
+template <class TP, class ROWS, class FX, class ST, class QV, class QDV, class TV, class OUT>
+RBD_DI void team_aba_trunk(const float* __restrict__ t, ST& s, const QV& q, const QDV& qd, const TV& tau,
+                           const LdsCol& lds, const LdsCol& acc, const OUT& qdd) {
+  using TM = Team<TP>;
+  const V3 g = load_g<TP>(t);
+  const V3 mg = {-g.x, -g.y, -g.z};
+  sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
+    constexpr int I = decltype(I_)::value;
+    if constexpr (TM::trunk(I)) {
+      s.acc[I] = AInr{};
+      s.accp[I] = Frc{};
+    }
+  });
+  sfor_rev<0, TP::N>([&](auto J_) __attribute__((always_inline)) {
+    constexpr int J = decltype(J_)::value;
+    if constexpr (TM::trunk(J)) {
+      team_collect<TP, ROWS, J>(lds, [&](const LdsCol& c) __attribute__((always_inline)) {
+        add_ainr(c, 0, s.acc[J]);
+        s.accp[J] = s.accp[J] + get_frc(c, 21);
+      });
+      aba_close<TP, J, false, FX>(t, s, qd, tau);
+    }
+  });
+  AbaDown<TP> d;
+  sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
+    constexpr int I = decltype(I_)::value;
+    if constexpr (TM::trunk(I)) {
+      aba_down<TP, I>(t, mg, s, d, q, qd, qdd);
+      const Frc a = {d.a[I].w, d.a[I].v};
+      put_frc(acc, 6 * cidx<TrunkRows<TP>::body(I)>, a);
+    }
+  });
+}
+// Role W, down.
+template <class TP, int W, class ST, class QV, class QDV, class OUT>
+RBD_DI void team_aba_down(const float* __restrict__ t, const float* __restrict__ tb, const ST& s, const QV& q,
+                          const QDV& qd, const LdsCol& acc, const OUT& qdd) {
+  using TM = Team<TP>;
+  const V3 g = load_g<TP>(t);
+  const V3 mg = {-g.x, -g.y, -g.z};
+  AbaDown<TP> d;
+  sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
+    constexpr int I = decltype(I_)::value;
+    if constexpr (TM::attach(W, I)) {
+      const Frc a = get_frc(acc, 6 * cidx<TrunkRows<TP>::body(I)>);
+      d.a[I] = {a.n, a.f};
+      d.vv[I] = s.v[I];
+    } else if constexpr (TM::in(W, I)) {
+      aba_down<TP, I>(tb, mg, s, d, q, qd, qdd);
+    }
+  });
 }
 
 // =================================================================== operational-space control
