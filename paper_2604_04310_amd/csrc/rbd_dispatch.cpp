@@ -224,8 +224,9 @@ rbd_status launch_fwd_dyn(const rbd_model* m, int64_t batch, int64_t ld, const f
   const KernelId id = fext ? (pre ? KID_FWD_DYN_PRE_EXT : KID_FWD_DYN_EXT) : (pre ? KID_FWD_DYN_PRE : KID_FWD_DYN);
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &qd, &tau, &fext, &qdd};
+  // (a team runs the articulated-body form: faster and more accurate there, see team_aba)
   if (teamed(m, batch))
-    return launch(m, fext ? KID_FWD_DYN_TEAM_EXT : KID_FWD_DYN_TEAM, team_shape(m, batch), a, s, "rbd_fwd_dyn");
+    return launch(m, fext ? KID_ABA_EXT_TEAM : KID_ABA_TEAM, team_shape(m, batch), a, s, "rbd_fwd_dyn");
   return launch(m, id, heavy_shape(batch), a, s, "rbd_fwd_dyn");
 }
 
@@ -249,7 +250,8 @@ rbd_status launch_fwd_dyn_jvp(const rbd_model* m, int64_t batch, int64_t ld, con
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &qd, &tau, &dq, &dqd, &dtau, &qdd, &dqdd, &fext, &dfext};
   const bool ext = fext || dfext;
-  if (teamed(m, batch)) return launch(m, ext ? KID_JVP_EXT_TEAM : KID_JVP_TEAM, team_shape(m, batch), a, s, "rbd_fwd_dyn_jvp");
+  if (teamed(m, batch))
+    return launch(m, ext ? KID_JVP_EXT_TEAM : KID_JVP_TEAM, team_shape(m, batch), a, s, "rbd_fwd_dyn_jvp");
   if (large(m) && batch <= kOneWavePerSimd / 2) {
     // two waves per 64 instances: the factor of M on its own wave, in
     // parallel with the solve for qdd and the tangent
@@ -378,9 +380,8 @@ rbd_status launch_packed(const rbd_model* m, int op, const void* d_table, int gr
   const uint8_t* t = static_cast<const uint8_t*>(d_table);
   void* a[] = {&tab, &t};
   // `grid` blocks of kBlock lanes stride over the tiles, or as many teams
-  const Shape sh = m->team.waves > 1
-                       ? Shape{dim3((unsigned)grid * (kBlock / kTileLanes)), dim3((unsigned)(m->team.waves * kTileLanes))}
-                       : Shape{dim3((unsigned)grid), dim3(kBlock)};
+  Shape sh{dim3((unsigned)grid), dim3(kBlock)};
+  if (m->team.waves > 1) sh = team_shape(m, (int64_t)grid * kBlock);
   return launch(m, id, sh, a, s, "packed launch");
 }
 

@@ -51,8 +51,6 @@
   X(KID_RNEA_VJP_EXT, 8, k_rnea_vjp<TP, true>)            \
   X(KID_VJP_SPLIT, 3, k_fwd_dyn_vjp_split<TP>)            \
   X(KID_VJP_EXT_SPLIT, 8, k_fwd_dyn_vjp_split<TP, true>) \
-  X(KID_FWD_DYN_TEAM, 9, k_fwd_dyn_team<TP, false>)       \
-  X(KID_FWD_DYN_TEAM_EXT, 9, k_fwd_dyn_team<TP, true>)    \
   X(KID_VJP_TEAM, 10, k_fwd_dyn_vjp_team<TP, false>)      \
   X(KID_VJP_EXT_TEAM, 10, k_fwd_dyn_vjp_team<TP, true>)   \
   X(KID_JVP_TEAM, 11, k_fwd_dyn_jvp_team<TP, false>)      \

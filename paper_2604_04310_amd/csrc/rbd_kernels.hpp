@@ -747,12 +747,12 @@ RBD_DI void team_read(float (&x)[n], const IO& io, const float* p, const TeamLan
 // Rows of LDS of the blocks below.
 template <class TP>
 struct TeamLds {
-  using Fd = TeamRows<TP, 16, true, 1>;
+  using Aba = TeamRows<TP, 27, false, 0>;
   using Fd2 = TeamRows<TP, 16, true, 2>;
   using Id = TeamRows<TP, 6, false, 0>;
   template <bool EXT>
   using Adj = TeamRows<TP, EXT ? 30 : 18, false, 0>;
-  static constexpr int kFd = Fd::total() + TrunkRows<TP>::total();
+  static constexpr int kAba = Aba::total() + 6 * TrunkRows<TP>::body(TP::N);  // and the trunk's accelerations
   static constexpr int kId = Id::total();
   // the solve's rows, which afterwards hold [qdd | lam | what the adjoint hands to the trunk], then x
   template <bool EXT>
@@ -766,48 +766,69 @@ struct TeamLds {
   }
 };
 
-// Forward dynamics of the calling wave's 64 instances. Bound: the longest
-// branch's and the trunk's chain of vector instructions while the batch leaves
-// SIMDs idle (humanoid, one lane per instance before, a team now: 33.8 -> 13.9
-// us at batch 64, 34.9 -> 14.6 at 16384), their issue rate after that (37.2 ->
-// 20.4 at 32768, 39.5 -> 35.1 at 65536, 160 -> 121 at 262144). The factor's rows
-// stay in their wave's registers between the phases: 198, so that two blocks fit
-// a compute unit; the LDS rows (60 KB) allow two as well.
+// Forward dynamics of the calling wave's 64 instances, by the articulated-body
+// algorithm for either entry point: branches up, the trunk up and down, branches
+// down. Shared out over a team it needs a third of the L^T L form's hand-over
+// (27 rows of LDS per trunk body against 16 and the trunk's rows of the factor)
+// and few enough registers (168) for three waves per SIMD, and it is the more
+// accurate of the two (humanoid: 1.9e-7 against 1.0e-6 in the Frobenius norm,
+// 2.5e-7 against 5.7e-7 with contact forces). Bound: the longest branch's and
+// the trunk's chain of vector instructions while the batch leaves SIMDs idle,
+// their issue rate after that. Humanoid, against one lane per instance (L^T L):
+// 33.8 -> 12.4 us at batch 64, 34.9 -> 13.4 at 16384, 37.2 -> 17.6 at 32768, 39.5
+// -> 29.4 at 65536, 160 -> 93 at 262144; the L^T L form as a team took 13.7, 15.0,
+// 20.7, 34.5 and 119.
 template <class TP, bool EXT, int W, class IO>
-RBD_DI void team_fwd_dyn(const TeamLane& tl, const float* __restrict__ tab, const IO& io, float* lds_rows,
-                         const float* q, const float* qd, const float* tau, const float* fext, int64_t ld, float* qdd) {
+RBD_DI void team_aba(const TeamLane& tl, const float* __restrict__ tab, const IO& io, float* lds_rows, const float* q,
+                     const float* qd, const float* tau, const float* fext, int64_t ld, float* qdd) {
   using TM = Team<TP>;
-  using ROWS = typename TeamLds<TP>::Fd;
+  using ROWS = typename TeamLds<TP>::Aba;
   constexpr int NQ = TP::NQ, NV = TP::NV;
-  const LdsCol lds{lds_rows + tl.lane};
+  const LdsCol lds{lds_rows + tl.lane}, acc = lds.at(ROWS::total());
   const bool owner = TM::may_own(W) && tl.wave == TM::kOwner;
+  const float* const t = opaque_table(tab);
+  const float* const tb = opaque_table(tab + tl.shift * kBodyStride);
   float qv[NQ], qdv[NV], tv[NV];
   team_read<TP, W, true, false>(qv, io, q, tl, owner);
   team_read<TP, W, true, true>(qdv, io, qd, tl, owner);
   team_read<TP, W, false, true>(tv, io, tau, tl, owner);
-  Ltl<TP, 1> F, Ft;
-  const RhsOne<RegView> rhs{RegView{tv}};
-  const auto out = io.template out<NV>(qdd, tl.shift, tl.b), out_t = io.template out<NV>(qdd, 0, tl.b);
-  using O = typename IO::O;
-  team_fd<TP, W, 1, ROWS>(tl, owner, tab, RegView{qv}, RegView{qdv}, rhs, rhs, team_fext<EXT>(fext, ld, tl.shift, tl.b),
-                          team_fext<EXT>(fext, ld, 0, tl.b), lds, lds.at(ROWS::total()), F, Ft, SinkOne<O>{out},
-                          SinkOne<O>{out_t});
+  const RegView qr{qv}, qdr{qdv}, tr{tv};
+  const auto fx = team_fext<EXT>(fext, ld, 0, tl.b);
+  using FX = std::decay_t<decltype(fx)>;
+  AbaState<TP, EXT> s;
+  team_aba_up<TP, W, ROWS>(t, tb, s, qr, qdr, tr, team_fext<EXT>(fext, ld, tl.shift, tl.b),
+                           lds.at(team_base<TP, ROWS, W>(tl)));
+  if constexpr (TM::may_own(W)) {
+    if (owner) {
+      sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
+        constexpr int I = decltype(I_)::value;
+        // (those above its branches have their motion, but the forces were read with the moved view)
+        if constexpr (TM::trunk(I) && (EXT || !TM::above(W, I))) aba_motion<TP, I>(t, s, qr, qdr, fx);
+      });
+    }
+  }
+  __syncthreads();
+  if constexpr (TM::may_own(W)) {
+    if (owner) team_aba_trunk<TP, ROWS, FX>(t, s, qr, qdr, tr, lds, acc, io.template out<NV>(qdd, 0, tl.b));
+  }
+  __syncthreads();
+  team_aba_down<TP, W>(opaque_table(t), opaque_table(tb), s, qr, qdr, acc, io.template out<NV>(qdd, tl.shift, tl.b));
 }
 
 template <class TP, bool EXT>
-__global__ __launch_bounds__(Team<TP>::kThreads, 2) void k_fwd_dyn_team(
+__global__ __launch_bounds__(Team<TP>::kThreads, EXT ? 2 : 3) void k_aba_team(
     const float* __restrict__ tab, int64_t batch, int64_t ld, const float* __restrict__ q,
     const float* __restrict__ qd, const float* __restrict__ tau, const float* __restrict__ fext,
     float* __restrict__ qdd) {
   if constexpr (Team<TP>::kOn) {
-    __shared__ float lds_team[TeamLds<TP>::kFd * kTileLanes];
+    __shared__ float lds_team[TeamLds<TP>::kAba * kTileLanes];
     team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
-      team_fwd_dyn<TP, EXT, decltype(W_)::value>(tl, tab, SoaIo<TP>{ld}, lds_team, q, qd, tau, fext, ld, qdd);
+      team_aba<TP, EXT, decltype(W_)::value>(tl, tab, SoaIo<TP>{ld}, lds_team, q, qd, tau, fext, ld, qdd);
     });
   }
 }
 
-// Inverse dynamics: the same without the factor (humanoid 17.5 -> 8.6 us at
+// Inverse dynamics: the way up alone (humanoid 17.5 -> 8.6 us at
 // batch 20001, 22.6 -> 14.1 at 65536, 57 -> 47 at 262144, where the 139 MB it
 // reads and writes take 27).
 template <class TP, bool HAS_QDD, bool EXT, int W, class IO>
@@ -1009,7 +1030,8 @@ __global__ __launch_bounds__(Team<TP>::kThreads, EXT ? 1 : 2) void k_fwd_dyn_jvp
       float rv[NV];  // dtau - d(ID)
       const auto keep = [&](int k, float v) __attribute__((always_inline)) { rv[k] = v; };
       const LdsCol rows = lds.at(NV), c = rows.at(team_base<TP, TROWS, W>(tl));
-      team_tan_up<TP, W, TROWS>(t2, opaque_table(tab + tl.shift * kBodyStride), s, qr, qdr, xr, dqr, dqdr, NoFext{}, dtr,
+      const float* const tb2 = opaque_table(tab + tl.shift * kBodyStride);
+      team_tan_up<TP, W, TROWS>(t2, tb2, s, qr, qdr, xr, dqr, dqdr, NoFext{}, dtr,
                                 team_fext_opt<EXT>(fext, l2, tl.shift, b), team_fext_opt<EXT>(dfext, l2, tl.shift, b),
                                 c, keep);
       team_solve_y<TP, W, TROWS>(F, RegView{rv}, c);
@@ -1031,55 +1053,6 @@ __global__ __launch_bounds__(Team<TP>::kThreads, EXT ? 1 : 2) void k_fwd_dyn_jvp
       __syncthreads();
       team_fd_back<TP, W, 1>(F, [&](int, int k) __attribute__((always_inline)) { return xt(k); },
                              SinkOne<Out>{Out{dqdd + off2, l2, b}});
-    });
-  }
-}
-
-// Forward dynamics by the articulated-body algorithm: branches up, the trunk up
-// and down, branches down.
-template <class TP, bool EXT>
-__global__ __launch_bounds__(Team<TP>::kThreads, EXT ? 2 : 3) void k_aba_team(
-    const float* __restrict__ tab, int64_t batch, int64_t ld, const float* __restrict__ q,
-    const float* __restrict__ qd, const float* __restrict__ tau, const float* __restrict__ fext,
-    float* __restrict__ qdd) {
-  using TM = Team<TP>;
-  if constexpr (TM::kOn) {
-    constexpr int NQ = TP::NQ, NV = TP::NV;
-    using ROWS = TeamRows<TP, 27, false, 0>;
-    __shared__ float lds_team[(ROWS::total() + 6 * TrunkRows<TP>::body(TP::N)) * kTileLanes];
-    team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
-      constexpr int W = decltype(W_)::value;
-      const LdsCol lds{lds_team + tl.lane}, acc = lds.at(ROWS::total());
-      const SoaIo<TP> io{ld};
-      const bool owner = TM::may_own(W) && tl.wave == TM::kOwner;
-      const float* const t = opaque_table(tab);
-      const float* const tb = opaque_table(tab + tl.shift * kBodyStride);
-      float qv[NQ], qdv[NV], tv[NV];
-      team_read<TP, W, true, false>(qv, io, q, tl, owner);
-      team_read<TP, W, true, true>(qdv, io, qd, tl, owner);
-      team_read<TP, W, false, true>(tv, io, tau, tl, owner);
-      const RegView qr{qv}, qdr{qdv}, tr{tv};
-      const auto fx = team_fext<EXT>(fext, ld, 0, tl.b);
-      using FX = std::decay_t<decltype(fx)>;
-      AbaState<TP, EXT> s;
-      team_aba_up<TP, W, ROWS>(t, tb, s, qr, qdr, tr, team_fext<EXT>(fext, ld, tl.shift, tl.b),
-                               lds.at(team_base<TP, ROWS, W>(tl)));
-      if constexpr (TM::may_own(W)) {
-        if (owner) {
-          sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
-            constexpr int I = decltype(I_)::value;
-            // (those above its branches have their motion, but the forces are read with the moved view)
-            if constexpr (TM::trunk(I) && (EXT || !TM::above(W, I))) aba_motion<TP, I>(t, s, qr, qdr, fx);
-          });
-        }
-      }
-      __syncthreads();
-      if constexpr (TM::may_own(W)) {
-        if (owner)
-          team_aba_trunk<TP, ROWS, FX>(t, s, qr, qdr, tr, lds, acc, io.template out<NV>(qdd, 0, tl.b));
-      }
-      __syncthreads();
-      team_aba_down<TP, W>(opaque_table(t), opaque_table(tb), s, qr, qdr, acc, io.template out<NV>(qdd, tl.shift, tl.b));
     });
   }
 }
@@ -1301,7 +1274,8 @@ __global__ __launch_bounds__(Team<TP>::kThreads) void k_rnea_vjp_team(
         else return NoGF{};
       };
       AdjState<TP, EXT, EXT> s;
-      team_adj_up<TP, W, ROWS>(t, opaque_table(tab + tl.shift * kBodyStride), s, qr, qdr, ar, lr, neg(gq, off), neg(gqd, off),
+      const float* const tb = opaque_table(tab + tl.shift * kBodyStride);
+      team_adj_up<TP, W, ROWS>(t, tb, s, qr, qdr, ar, lr, neg(gq, off), neg(gqd, off),
                                team_fext_opt<EXT>(fext, ld, tl.shift, b), gf(tl.shift),
                                On<OutOpt<Out>>{team_out(gqdd, off, ld, b)}, lds.at(team_base<TP, ROWS, W>(tl)));
       if constexpr (TM::may_own(W)) {
@@ -1465,7 +1439,12 @@ __global__ __launch_bounds__(Team<TP>::kOn ? Team<TP>::kThreads : kBlock, Team<T
 // a block, any other to a wave. Request arrays are instance-major, exactly as the client
 // handed them over: coordinate c of instance i at p[i * n + c].
 template <class TP, int OP>
-__global__ __launch_bounds__(Team<TP>::kOn ? Team<TP>::kThreads : kBlock, Team<TP>::kOn ? 2 : 1) void k_packed(
+struct PackedShape {  // threads of a block and waves per SIMD to leave registers for
+  static constexpr int kThreads = Team<TP>::kOn ? Team<TP>::kThreads : kBlock;
+  static constexpr int kOcc = !Team<TP>::kOn ? 1 : (OP == kOpFwdDyn ? 3 : 2);
+};
+template <class TP, int OP>
+__global__ __launch_bounds__((PackedShape<TP, OP>::kThreads), (PackedShape<TP, OP>::kOcc)) void k_packed(
     const float* __restrict__ tab, const uint8_t* __restrict__ table) {
   const PackedHdr* hdr = reinterpret_cast<const PackedHdr*>(table);
   const int32_t* tile_req = reinterpret_cast<const int32_t*>(table + sizeof(PackedHdr));
@@ -1474,7 +1453,7 @@ __global__ __launch_bounds__(Team<TP>::kOn ? Team<TP>::kThreads : kBlock, Team<T
   if constexpr (Team<TP>::kOn) {
     // a team per tile, the same code as the direct calls
     using L = TeamLds<TP>;
-    constexpr int kRows = OP == kOpFwdDyn ? L::kFd : (OP == kOpRnea ? L::kId : L::template vjp<false>());
+    constexpr int kRows = OP == kOpFwdDyn ? L::kAba : (OP == kOpRnea ? L::kId : L::template vjp<false>());
     __shared__ float lds_team[kRows * kTileLanes];
     for (int t = blockIdx.x; t < n_tiles; t += gridDim.x) {
       const PackedReq& R = reqs[__builtin_amdgcn_readfirstlane(tile_req[t])];
@@ -1486,7 +1465,7 @@ __global__ __launch_bounds__(Team<TP>::kOn ? Team<TP>::kThreads : kBlock, Team<T
                      [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
         constexpr int W = decltype(W_)::value;
         if constexpr (OP == kOpFwdDyn)
-          team_fwd_dyn<TP, false, W>(tl, tab, io, lds_team, q, qd, x2, nullptr, 0, R.out[0]);
+          team_aba<TP, false, W>(tl, tab, io, lds_team, q, qd, x2, nullptr, 0, R.out[0]);
         else if constexpr (OP == kOpRnea)
           team_rnea<TP, true, false, W>(tl, tab, io, lds_team, q, qd, x2, nullptr, 0, R.out[0]);
         else
