@@ -556,17 +556,18 @@ RBD_DI void fk_lane(const float* __restrict__ t, const QI& q, const TO& T) {
 }
 
 // =================================================================== Jacobian
-// The Jacobians of the requested frames of body K.
+// The Jacobians of the requested frames of body K, row after row: the row
+// pointer runs on by ld from store to store. (Addressed as (r nv + c) ld, the
+// rows' offsets were computed ahead for all bodies and frames, and the thousands
+// of scalar registers that held them were spilled.)
 template <class TP, int K>
 RBD_DI void jac_frames(const M3* Rw, const V3* pw, const JacSlots& js, float* __restrict__ J, int64_t ld,
                        uint32_t lane) {
   constexpr int N = TP::N, NV = TP::NV;
   const int beg = js.beg[K], end = js.beg[K + 1];
   for (int s = beg; s < end; ++s) {
-    float* __restrict__ Jf = J + (int64_t)js.slot[s] * 6 * NV * ld;
-    auto put = [&](int r, int c, float v) __attribute__((always_inline)) {
-      __builtin_nontemporal_store(v, lane_ptr(Jf + (int64_t)(r * NV + c) * ld, lane));
-    };
+    float* __restrict__ row = J + (int64_t)js.slot[s] * 6 * NV * ld;
+    V3 lin[NV], ang[NV];  // the columns of K and its ancestors
     sfor<0, N>([&](auto A_) __attribute__((always_inline)) {
       constexpr int A = decltype(A_)::value;
       constexpr int c0 = TP::vofs(A);
@@ -576,24 +577,30 @@ RBD_DI void jac_frames(const M3* Rw, const V3* pw, const JacSlots& js, float* __
 #pragma unroll
           for (int c = 0; c < 3; ++c) {
             const V3 col = {Rw[A].a[c], Rw[A].a[3 + c], Rw[A].a[6 + c]};
-            const V3 lin = cross(col, d);
-            put(0, c0 + c, col.x); put(1, c0 + c, col.y); put(2, c0 + c, col.z);
-            put(3, c0 + c, 0.0f); put(4, c0 + c, 0.0f); put(5, c0 + c, 0.0f);
-            put(0, c0 + 3 + c, lin.x); put(1, c0 + 3 + c, lin.y); put(2, c0 + 3 + c, lin.z);
-            put(3, c0 + 3 + c, col.x); put(4, c0 + 3 + c, col.y); put(5, c0 + 3 + c, col.z);
+            lin[c0 + c] = col;
+            ang[c0 + c] = {0.0f, 0.0f, 0.0f};
+            lin[c0 + 3 + c] = cross(col, d);
+            ang[c0 + 3 + c] = col;
           }
         } else {
           const V3 z = {Rw[A].a[2], Rw[A].a[5], Rw[A].a[8]};
-          const V3 lin = cross(z, d);
-          put(0, c0, lin.x); put(1, c0, lin.y); put(2, c0, lin.z);
-          put(3, c0, z.x); put(4, c0, z.y); put(5, c0, z.z);
+          lin[c0] = cross(z, d);
+          ang[c0] = z;
         }
-      } else {
-#pragma unroll
-        for (int c = 0; c < cidx<TP::nvb(A)>; ++c)
-#pragma unroll
-          for (int r = 0; r < 6; ++r) put(r, c0 + c, 0.0f);
       }
+    });
+    sfor<0, 6>([&](auto R_) __attribute__((always_inline)) {
+      constexpr int r = decltype(R_)::value;
+      sfor<0, NV>([&](auto C_) __attribute__((always_inline)) {
+        constexpr int c = decltype(C_)::value;
+        float v = 0.0f;
+        if constexpr (TP::is_anc(TP::body_of(c), K)) {
+          const V3 x = r < 3 ? lin[c] : ang[c];
+          v = r % 3 == 0 ? x.x : (r % 3 == 1 ? x.y : x.z);
+        }
+        __builtin_nontemporal_store(v, lane_ptr(row, lane));
+        row += ld;
+      });
     });
   }
 }
