@@ -109,7 +109,6 @@ __global__ __launch_bounds__(kBlock) void k_rnea(const float* __restrict__ tab, 
                                                  const float* __restrict__ qdd, const float* __restrict__ fext,
                                                  float* __restrict__ tau) {
   if constexpr (!Team<TP>::kAlways) {
-    RBD_LANE_IO(TP);
     const uint32_t b = lane_id();
     if (b >= batch) return;
     if constexpr (PRE && !EXT) {
@@ -167,7 +166,6 @@ __global__ __launch_bounds__(kBlock) void k_fwd_dyn(const float* __restrict__ ta
                                                     const float* __restrict__ tau, const float* __restrict__ fext,
                                                     float* __restrict__ qdd) {
   if constexpr (!Team<TP>::kAlways) {
-    RBD_LANE_IO(TP);
     const uint32_t b = lane_id();
     if (b >= batch) return;
     const auto fx = fext_view<EXT>(fext, ld, b);

@@ -402,8 +402,10 @@ RBD_DI T* lane_ptr(T* row, uint32_t lane) {
   return reinterpret_cast<T*>(reinterpret_cast<B*>(row) + (lane << 2));
 }
 // SB selects that form; without it the compiler forms a 64-bit address per
-// lane, which measured faster for small trees (more waves per SIMD hide the
-// extra instructions, and their kernels are short) and slower for large ones.
+// lane, four issue slots each. Kernels of one sweep (forward and inverse
+// dynamics) use the scalar-base form at any size (7-joint arm at 2^20: 57.8 ->
+// 54.9 us); those of several sweeps are slower with it for small trees (tangent
+// 43.9 -> 47.4 us at 2^18, adjoint 37.7 -> 39.9), faster for large ones.
 template <bool SB>
 struct InT {
   const float* __restrict__ base;
@@ -426,7 +428,7 @@ struct OutT {
 };
 using In = InT<true>;
 using Out = OutT<true>;
-// The form a tree's kernels use: the scalar-base form above 16 DoFs.
+// The form of a tree's kernels of several sweeps: scalar-base above 16 DoFs.
 template <class TP>
 inline constexpr bool kScalarBase = TP::NV > 16;
 // Streaming output: a non-temporal store, for the large outputs written once
@@ -616,6 +618,99 @@ RBD_DI void jac_lane(const float* __restrict__ t, const QI& q, const JacSlots& j
   });
 }
 
+// =================================================================== Newton-Euler steps
+// The forward half of inverse dynamics in classical accelerations: a = [dw; a']
+// with a' the acceleration of the body's origin itself (the spatial one plus w
+// x v), gravity included. Linear velocities drop out (of the base's but for a'),
+// so a body takes about 100 vector instructions where the spatial form, I a + v
+// x* I v, takes 130.
+// a' of a point at r in a body: a' + dw x r + w x (w x r)
+RBD_DI V3 point_acc(const Mot& a, V3 w, V3 r) { return cross_add(a.w, r, cross_add(w, cross(w, r), a.v)); }
+// The force that gives a body this motion, about its origin.
+RBD_DI Frc body_force(const Inr& I, V3 w, const Mot& a) {
+  return {cross_add(w, isym(I, w), cross_add(I.h, a.v, isym(I, a.w))),
+          cross_add(w, cross(w, I.h), cross_add(a.w, I.h, I.m * a.v))};
+}
+// A revolute root turns about its own z axis at rest: w = (0, 0, w), dw = (0, 0,
+// its qdd).
+template <class TP, int I>
+inline constexpr bool kTurning = TP::parent(I) < 0 && !TP::free_body(I);
+// Body I's force from its motion.
+template <class TP, int I, bool QDD>
+RBD_DI Frc body_force(const float* __restrict__ t, const Mot* v, const Mot* a) {
+  const Inr Ib = load_inr<I>(t);
+  if constexpr (kTurning<TP, I>) {
+    const float w2 = v[I].w.z * v[I].w.z;
+    const V3 x = a[I].v;
+    const V3 hx = cross(Ib.h, x);
+    Frc f = {{__builtin_fmaf(-w2, Ib.yz, hx.x), __builtin_fmaf(w2, Ib.xz, hx.y), hx.z},
+             {__builtin_fmaf(-w2, Ib.h.x, Ib.m * x.x), __builtin_fmaf(-w2, Ib.h.y, Ib.m * x.y), Ib.m * x.z}};
+    if constexpr (QDD) {
+      const float e = a[I].w.z;
+      f.n = {__builtin_fmaf(e, Ib.xz, f.n.x), __builtin_fmaf(e, Ib.yz, f.n.y), __builtin_fmaf(e, Ib.zz, f.n.z)};
+      f.f.x = __builtin_fmaf(-e, Ib.h.y, f.f.x);
+      f.f.y = __builtin_fmaf(e, Ib.h.x, f.f.y);
+    }
+    return f;
+  } else {
+    return body_force(Ib, v[I].w, a[I]);
+  }
+}
+// Motion of body I from its parent's, without its own qdd (QDD: the parent's
+// has its; else the bias acceleration).
+template <class TP, int I, bool QDD, class QI, class QDI>
+RBD_DI void body_motion(const float* __restrict__ t, const QI& q, const QDI& qd, V3 mg, M3* R, Mot* v, Mot* a) {
+  constexpr int P = TP::parent(I);
+  if constexpr (TP::free_body(I)) {
+    R[I] = quat_rot(q(3), q(4), q(5), q(6));
+    v[I] = {{qd(3), qd(4), qd(5)}, {qd(0), qd(1), qd(2)}};
+    a[I] = {{0.0f, 0.0f, 0.0f}, cross_add(v[I].w, v[I].v, mulT(R[I], mg))};
+  } else {
+    R[I] = joint_rot<I>(t, q(cidx<TP::qofs(I)>));
+    const float w = qd(cidx<TP::vofs(I)>);
+    if constexpr (P < 0) {
+      v[I] = {{0.0f, 0.0f, w}, {0.0f, 0.0f, 0.0f}};
+      a[I] = {{0.0f, 0.0f, 0.0f}, mulT(R[I], mg)};
+    } else {
+      const V3 r = load_r<I>(t);
+      if constexpr (kTurning<TP, (P < 0 ? 0 : P)>) {
+        const float wp = v[P].w.z, w2 = wp * wp;
+        const V3 z = {R[I].a[6], R[I].a[7], R[I].a[8]};  // the parent's axis in I's frame
+        v[I] = {wp * z, mulT(R[I], wp * V3{-r.y, r.x, 0.0f})};
+        V3 x = {__builtin_fmaf(-w2, r.x, a[P].v.x), __builtin_fmaf(-w2, r.y, a[P].v.y), a[P].v.z};
+        a[I].w = {0.0f, 0.0f, 0.0f};
+        if constexpr (QDD) {
+          const float e = a[P].w.z;
+          x.x = __builtin_fmaf(-e, r.y, x.x);
+          x.y = __builtin_fmaf(e, r.x, x.y);
+          a[I].w = e * z;
+        }
+        a[I].v = mulT(R[I], x);
+        v[I].w.z = v[I].w.z + w;
+        if constexpr (QDD) {
+          a[I].w.x = a[I].w.x + w * v[I].w.y;
+          a[I].w.y = a[I].w.y - w * v[I].w.x;
+        } else {
+          a[I].w.x = w * v[I].w.y;
+          a[I].w.y = -w * v[I].w.x;
+        }
+      } else {
+        v[I] = xmot(R[I], r, v[P]);  // (its linear part is only ever computed where something reads it)
+        v[I].w.z = v[I].w.z + w;
+        a[I] = {mulT(R[I], a[P].w), mulT(R[I], point_acc(a[P], v[P].w, r))};
+        a[I].w.x = a[I].w.x + w * v[I].w.y;
+        a[I].w.y = a[I].w.y - w * v[I].w.x;
+      }
+    }
+  }
+}
+// a with qdd added.
+template <class TP, int I, class QDDI>
+RBD_DI void add_qdd(Mot* a, const QDDI& qdd) {
+  if constexpr (TP::free_body(I)) a[I] = a[I] + Mot{{qdd(3), qdd(4), qdd(5)}, {qdd(0), qdd(1), qdd(2)}};
+  else a[I].w.z = a[I].w.z + qdd(cidx<TP::vofs(I)>);
+}
+
 // =================================================================== RNEA
 // tau = ID(q, qd, qdd) - sum_i J_i^T F_ext,i; qdd may be absent (bias force),
 // external forces too (NoFext). Depth-first: the backward step of a body runs
@@ -647,33 +742,9 @@ RBD_DI void rnea_lane(const float* __restrict__ t, const QI& q, const QDI& qd, c
 
   sfor<0, N>([&](auto I_) __attribute__((always_inline)) {
     constexpr int I = decltype(I_)::value;
-    constexpr int P = TP::parent(I);
-    if constexpr (TP::free_body(I)) {
-      R[I] = quat_rot(q(3), q(4), q(5), q(6));
-      v[I] = {{qd(3), qd(4), qd(5)}, {qd(0), qd(1), qd(2)}};
-      a[I] = {{0.0f, 0.0f, 0.0f}, mulT(R[I], mg)};
-      if constexpr (HAS_QDD) a[I] = a[I] + Mot{{qdd(3), qdd(4), qdd(5)}, {qdd(0), qdd(1), qdd(2)}};
-    } else {
-      R[I] = joint_rot<I>(t, q(cidx<TP::qofs(I)>));
-      const float w = qd(cidx<TP::vofs(I)>);
-      if constexpr (P < 0) {
-        v[I] = {{0.0f, 0.0f, w}, {0.0f, 0.0f, 0.0f}};
-        a[I] = {{0.0f, 0.0f, 0.0f}, mulT(R[I], mg)};
-      } else {
-        const V3 r = load_r<I>(t);
-        v[I] = xmot(R[I], r, v[P]);
-        v[I].w.z = v[I].w.z + w;
-        a[I] = xmot(R[I], r, a[P]);
-        // + v x (S qd) = w * [wy, -wx, 0; vy, -vx, 0]
-        a[I].w.x = a[I].w.x + w * v[I].w.y;
-        a[I].w.y = a[I].w.y - w * v[I].w.x;
-        a[I].v.x = a[I].v.x + w * v[I].v.y;
-        a[I].v.y = a[I].v.y - w * v[I].v.x;
-      }
-      if constexpr (HAS_QDD) a[I].w.z = a[I].w.z + qdd(cidx<TP::vofs(I)>);
-    }
-    const Inr Ib = load_inr<I>(t);
-    f[I] = imul(Ib, a[I]) + crf(v[I], imul(Ib, v[I]));
+    body_motion<TP, I, HAS_QDD>(t, q, qd, mg, R, v, a);
+    if constexpr (HAS_QDD) add_qdd<TP, I>(a, qdd);
+    f[I] = body_force<TP, I, HAS_QDD>(t, v, a);
     if constexpr (FX::kOn) {
       world_pose<TP, I>(t, q, R[I], Rw, pw);
       f[I] = f[I] - fext_body<I>(fx, Rw[I], pw[I]);
@@ -972,34 +1043,12 @@ RBD_DI void fwd_dyn_lane(const float* __restrict__ tab, const QI& q, const QDI& 
 
   sfor<0, N>([&](auto I_) __attribute__((always_inline)) {
     constexpr int I = decltype(I_)::value;
-    constexpr int P = TP::parent(I);
     if constexpr (!BIAS) {
       if constexpr (TP::free_body(I)) R[I] = quat_rot(q(3), q(4), q(5), q(6));
       else R[I] = joint_rot<I>(t, q(cidx<TP::qofs(I)>));
-    } else if constexpr (TP::free_body(I)) {
-      R[I] = quat_rot(q(3), q(4), q(5), q(6));
-      v[I] = {{qd(3), qd(4), qd(5)}, {qd(0), qd(1), qd(2)}};
-      a[I] = {{0.0f, 0.0f, 0.0f}, mulT(R[I], mg)};
     } else {
-      R[I] = joint_rot<I>(t, q(cidx<TP::qofs(I)>));
-      const float w = qd(cidx<TP::vofs(I)>);
-      if constexpr (P < 0) {
-        v[I] = {{0.0f, 0.0f, w}, {0.0f, 0.0f, 0.0f}};
-        a[I] = {{0.0f, 0.0f, 0.0f}, mulT(R[I], mg)};
-      } else {
-        const V3 r = load_r<I>(t);
-        v[I] = xmot(R[I], r, v[P]);
-        v[I].w.z = v[I].w.z + w;
-        a[I] = xmot(R[I], r, a[P]);
-        a[I].w.x = a[I].w.x + w * v[I].w.y;
-        a[I].w.y = a[I].w.y - w * v[I].w.x;
-        a[I].v.x = a[I].v.x + w * v[I].v.y;
-        a[I].v.y = a[I].v.y - w * v[I].v.x;
-      }
-    }
-    if constexpr (BIAS) {
-      const Inr Ib = load_inr<I>(t);
-      f[I] = imul(Ib, a[I]) + crf(v[I], imul(Ib, v[I]));
+      body_motion<TP, I, false>(t, q, qd, mg, R, v, a);
+      f[I] = body_force<TP, I, false>(t, v, a);
       if constexpr (FX::kOn) {
         world_pose<TP, I>(t, q, R[I], Rw, pw);
         f[I] = f[I] - fext_body<I>(fx, Rw[I], pw[I]);
@@ -2036,28 +2085,7 @@ RBD_DI void osc_sweep_bias(const float* __restrict__ t, const QI& q, const QDI& 
 
   sfor<0, N>([&](auto I_) __attribute__((always_inline)) {
     constexpr int I = decltype(I_)::value;
-    constexpr int P = TP::parent(I);
-    if constexpr (TP::free_body(I)) {
-      R[I] = quat_rot(q(3), q(4), q(5), q(6));
-      v[I] = {{qd(3), qd(4), qd(5)}, {qd(0), qd(1), qd(2)}};
-      a[I] = {{0.0f, 0.0f, 0.0f}, mulT(R[I], mg)};
-    } else {
-      R[I] = joint_rot<I>(t, q(cidx<TP::qofs(I)>));
-      const float w = qd(cidx<TP::vofs(I)>);
-      if constexpr (P < 0) {
-        v[I] = {{0.0f, 0.0f, w}, {0.0f, 0.0f, 0.0f}};
-        a[I] = {{0.0f, 0.0f, 0.0f}, mulT(R[I], mg)};
-      } else {
-        const V3 r = load_r<I>(t);
-        v[I] = xmot(R[I], r, v[P]);
-        v[I].w.z = v[I].w.z + w;
-        a[I] = xmot(R[I], r, a[P]);
-        a[I].w.x = a[I].w.x + w * v[I].w.y;
-        a[I].w.y = a[I].w.y - w * v[I].w.x;
-        a[I].v.x = a[I].v.x + w * v[I].v.y;
-        a[I].v.y = a[I].v.y - w * v[I].v.x;
-      }
-    }
+    body_motion<TP, I, false>(t, q, qd, mg, R, v, a);
     if constexpr (TP::is_anc(I, E)) world_pose<TP, I>(t, q, R[I], Rw, pw);
     if constexpr (I == E) {
       float err[6];
@@ -2069,9 +2097,8 @@ RBD_DI void osc_sweep_bias(const float* __restrict__ t, const QI& q, const QDI& 
 #pragma unroll
       for (int i = 0; i < 6; ++i) astar[i] = kp * e6[i] - kd * tw[i];
     }
-    const Inr Ib = load_inr<I>(t);
-    f[I] = imul(Ib, a[I]) + crf(v[I], imul(Ib, v[I]));
-    Ic[I] = Ib;
+    f[I] = body_force<TP, I, false>(t, v, a);
+    Ic[I] = load_inr<I>(t);
     close_subtrees<TP, I, I>(backward);
   });
 }

@@ -259,47 +259,17 @@ struct TeamFd {
   V3 pw[EXT ? TP::N : 1];
 };
 
-// Motion of body I from its parent's: joint rotation, velocity, bias
-// acceleration, world pose (external forces only).
-template <class TP, int I, class QI, class QDI, class ST, class FX>
+// Motion and force of body I (see body_motion), and its world pose where there
+// are external forces.
+template <class TP, int I, bool QDD = false, class QI, class QDI, class ST, class FX>
 RBD_DI void team_fd_motion(const float* __restrict__ t, const QI& q, const QDI& qd, V3 mg, ST& s, const FX&) {
-  constexpr int P = TP::parent(I);
-  if constexpr (TP::free_body(I)) {
-    s.R[I] = quat_rot(q(3), q(4), q(5), q(6));
-    s.v[I] = {{qd(3), qd(4), qd(5)}, {qd(0), qd(1), qd(2)}};
-    s.a[I] = {{0.0f, 0.0f, 0.0f}, mulT(s.R[I], mg)};
-  } else {
-    s.R[I] = joint_rot<I>(t, q(cidx<TP::qofs(I)>));
-    const float w = qd(cidx<TP::vofs(I)>);
-    if constexpr (P < 0) {
-      s.v[I] = {{0.0f, 0.0f, w}, {0.0f, 0.0f, 0.0f}};
-      s.a[I] = {{0.0f, 0.0f, 0.0f}, mulT(s.R[I], mg)};
-    } else {
-      const V3 r = load_r<I>(t);
-      s.v[I] = xmot(s.R[I], r, s.v[P]);
-      s.v[I].w.z = s.v[I].w.z + w;
-      s.a[I] = xmot(s.R[I], r, s.a[P]);
-      s.a[I].w.x = s.a[I].w.x + w * s.v[I].w.y;
-      s.a[I].w.y = s.a[I].w.y - w * s.v[I].w.x;
-      s.a[I].v.x = s.a[I].v.x + w * s.v[I].v.y;
-      s.a[I].v.y = s.a[I].v.y - w * s.v[I].v.x;
-    }
-  }
+  body_motion<TP, I, QDD>(t, q, qd, mg, s.R, s.v, s.a);
   if constexpr (FX::kOn) world_pose<TP, I>(t, q, s.R[I], s.Rw, s.pw);
 }
-// Its acceleration with qdd added.
-template <class TP, int I, class ST, class QDDI>
-RBD_DI void team_add_qdd(ST& s, const QDDI& qdd) {
-  if constexpr (TP::free_body(I)) s.a[I] = s.a[I] + Mot{{qdd(3), qdd(4), qdd(5)}, {qdd(0), qdd(1), qdd(2)}};
-  else s.a[I].w.z = s.a[I].w.z + qdd(cidx<TP::vofs(I)>);
-}
-// Its force.
-template <class TP, int I, class ST, class FX>
+template <class TP, int I, bool QDD = false, class ST, class FX>
 RBD_DI void team_fd_force(const float* __restrict__ t, ST& s, const FX& fx) {
-  const Inr Ib = load_inr<I>(t);
-  s.f[I] = imul(Ib, s.a[I]) + crf(s.v[I], imul(Ib, s.v[I]));
+  s.f[I] = body_force<TP, I, QDD>(t, s.v, s.a);
   if constexpr (FX::kOn) s.f[I] = s.f[I] - fext_body<I>(fx, s.Rw[I], s.pw[I]);
-  s.Ic[I] = Ib;
 }
 
 // The trunk's rows of the factor only see the trunk's own rows: the branches'
@@ -604,13 +574,13 @@ RBD_DI void team_id_up(const float* __restrict__ t, const float* __restrict__ tb
   sfor<0, TP::N>([&](auto I_) __attribute__((always_inline)) {
     constexpr int I = decltype(I_)::value;
     if constexpr (TM::above(W, I)) {
-      team_fd_motion<TP, I>(t, q, qd, mg, s, fx);
-      if constexpr (HAS_QDD) team_add_qdd<TP, I>(s, qdd);
+      team_fd_motion<TP, I, HAS_QDD>(t, q, qd, mg, s, fx);
+      if constexpr (HAS_QDD) add_qdd<TP, I>(s.a, qdd);
       if constexpr (TM::attach(W, I)) s.f[I] = Frc{};
     } else if constexpr (TM::in(W, I)) {
-      team_fd_motion<TP, I>(tb, q, qd, mg, s, fx);
-      if constexpr (HAS_QDD) team_add_qdd<TP, I>(s, qdd);
-      team_fd_force<TP, I>(tb, s, fx);
+      team_fd_motion<TP, I, HAS_QDD>(tb, q, qd, mg, s, fx);
+      if constexpr (HAS_QDD) add_qdd<TP, I>(s.a, qdd);
+      team_fd_force<TP, I, HAS_QDD>(tb, s, fx);
       close_subtrees<TP, I, I>(backward);
     }
   });
@@ -629,10 +599,10 @@ RBD_DI void team_id_trunk_down(const float* __restrict__ t, const QV& q, const Q
     constexpr int I = decltype(I_)::value;
     if constexpr (TM::trunk(I)) {
       if constexpr (!TM::above(W, I)) {
-        team_fd_motion<TP, I>(t, q, qd, mg, s, fx);
-        if constexpr (HAS_QDD) team_add_qdd<TP, I>(s, qdd);
+        team_fd_motion<TP, I, HAS_QDD>(t, q, qd, mg, s, fx);
+        if constexpr (HAS_QDD) add_qdd<TP, I>(s.a, qdd);
       }
-      team_fd_force<TP, I>(t, s, fx);
+      team_fd_force<TP, I, HAS_QDD>(t, s, fx);
     }
   });
 }
