@@ -195,7 +195,6 @@ __global__ __launch_bounds__(kBlock) void k_aba(const float* __restrict__ tab, i
                                                 const float* __restrict__ tau, const float* __restrict__ fext,
                                                 float* __restrict__ qdd) {
   if constexpr (!Team<TP>::kAlways) {
-    RBD_LANE_IO(TP);
     const uint32_t b = lane_id();
     if (b >= batch) return;
     const auto fx = fext_view<EXT>(fext, ld, b);
@@ -769,13 +768,13 @@ struct TeamLds {
 // down. Shared out over a team it needs a third of the L^T L form's hand-over
 // (27 rows of LDS per trunk body against 16 and the trunk's rows of the factor)
 // and few enough registers (168) for three waves per SIMD, and it is the more
-// accurate of the two (humanoid: 1.9e-7 against 1.0e-6 in the Frobenius norm,
+// accurate of the two (humanoid: 1.7e-7 against 1.0e-6 in the Frobenius norm,
 // 2.5e-7 against 5.7e-7 with contact forces). Bound: the longest branch's and
 // the trunk's chain of vector instructions while the batch leaves SIMDs idle,
 // their issue rate after that. Humanoid, against one lane per instance (L^T L):
-// 33.8 -> 12.4 us at batch 64, 34.9 -> 13.4 at 16384, 37.2 -> 17.6 at 32768, 39.5
-// -> 29.4 at 65536, 160 -> 93 at 262144; the L^T L form as a team took 13.7, 15.0,
-// 20.7, 34.5 and 119.
+// 33.8 -> 11.5 us at batch 64, 34.9 -> 12.7 at 16384, 37.2 -> 17.4 at 32768, 39.5 ->
+// 26.4 at 65536, 88 -> 47.6 at 131072; the L^T L form as a team took 13.7, 15.0,
+// 20.7, 34.5 and 64.9.
 template <class TP, bool EXT, int W, class IO>
 RBD_DI void team_aba(const TeamLane& tl, const float* __restrict__ tab, const IO& io, float* lds_rows, const float* q,
                      const float* qd, const float* tau, const float* fext, int64_t ld, float* qdd) {
@@ -826,9 +825,9 @@ __global__ __launch_bounds__(Team<TP>::kThreads, EXT ? 2 : 3) void k_aba_team(
   }
 }
 
-// Inverse dynamics: the way up alone (humanoid 17.5 -> 8.6 us at
-// batch 20001, 22.6 -> 14.1 at 65536, 57 -> 47 at 262144, where the 139 MB it
-// reads and writes take 27).
+// Inverse dynamics: the way up alone (humanoid 17.5 -> 7.8 us at batch 20001,
+// 22.6 -> 12.6 at 65536, 57 -> 44 at 262144, where the 148 MB it reads and writes
+// take 29).
 template <class TP, bool HAS_QDD, bool EXT, int W, class IO>
 RBD_DI void team_rnea(const TeamLane& tl, const float* __restrict__ tab, const IO& io, float* lds_rows, const float* q,
                       const float* qd, const float* qdd, const float* fext, int64_t ld, float* tau) {
@@ -882,8 +881,8 @@ RBD_DI auto team_gf(float* p, int64_t ld, int shift, uint32_t b) {
 // the waves park qdd and lam in LDS (the trunk's are there already), then the
 // adjoint sweep, branches first, on fresh views and loading where it uses (held
 // in registers, its inputs and qdd and lam spilled 220 B/lane at two waves per
-// SIMD). Humanoid: 65.3 -> 25.8 us at batch 64, 74.4 -> 37.3 at 32768, 86.9 ->
-// 67.6 at 65536, 169 -> 125 at 131072.
+// SIMD). Humanoid: 65.3 -> 25.0 us at batch 64, 74.4 -> 36.0 at 32768, 169 -> 119
+// at 131072.
 template <class TP, bool EXT, int W, class IO>
 RBD_DI void team_fwd_dyn_vjp(const TeamLane& tl, const float* __restrict__ tab, const IO& io, float* lds_rows,
                              const float* q, const float* qd, const float* tau, const float* gqdd, float* gq,
@@ -965,8 +964,8 @@ __global__ __launch_bounds__(Team<TP>::kThreads, EXT ? 1 : 2) void k_fwd_dyn_vjp
 
 // Forward dynamics' tangent: the solve for qdd (parked in LDS), the tangent of
 // inverse dynamics at it on fresh views, and a second solve with the factor
-// that each wave still holds, so M is factored once (humanoid 61.6 -> 24.3 us at
-// batch 2048, 68.5 -> 37.6 at 32768, 110 -> 69 at 65536).
+// that each wave still holds, so M is factored once (humanoid 61.6 -> 23.4 us at
+// batch 2048, 68.5 -> 35.5 at 32768, 219 -> 121 at 131072).
 template <class TP, bool EXT>
 __global__ __launch_bounds__(Team<TP>::kThreads, EXT ? 1 : 2) void k_fwd_dyn_jvp_team(
     const float* __restrict__ tab, int64_t batch, int64_t ld, const float* __restrict__ q,
@@ -1084,8 +1083,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads) void k_fk_team(const float* __r
 }
 
 // Jacobians: the frames of a body are written by the wave that has the body
-// (humanoid, feet and hands: 45.5 -> 10.8 us at batch 1024, 46.7 -> 16.5 at
-// 16384, where the 56 MB it writes take 11).
+// (humanoid, feet and hands: 45.5 -> 6.2 us at batch 1024).
 template <class TP>
 __global__ __launch_bounds__(Team<TP>::kThreads) void k_jacobian_team(const float* __restrict__ tab, int64_t batch,
                                                                      int64_t ld, const float* __restrict__ q,
@@ -1188,7 +1186,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads) void k_crba_team(const float* _
 
 // Inverse dynamics' tangent and adjoint: one sweep each, as in the middle of
 // forward dynamics' (inputs loaded at entry). Adjoint of the humanoid: 33.4 ->
-// 12.4 us at batch 64, 38.1 -> 20.9 at 32768, 50.0 -> 36.8 at 65536.
+// 12.4 us at batch 64, 38.1 -> 19.9 at 32768.
 template <class TP, bool EXT>
 __global__ __launch_bounds__(Team<TP>::kThreads) void k_rnea_jvp_team(
     const float* __restrict__ tab, int64_t batch, int64_t ld, const float* __restrict__ q,
@@ -1299,7 +1297,8 @@ __global__ __launch_bounds__(Team<TP>::kThreads) void k_rnea_vjp_team(
 // batch 65536 with the sweeps fused).
 // A team: branches up, the trunk and the 6x6 task solve by the owner, then J^T z
 // on E's branch by the wave that has it; path torques are held back until z is
-// known.
+// known (humanoid, right hand: 65.5 -> 20.1 us at batch 1024, 74.5 -> 45.1 at
+// 65536).
 template <class TP, int E = TP::N - 1>
 __global__ __launch_bounds__(Team<TP>::kOn ? Team<TP>::kThreads : kBlock, Team<TP>::kOn ? 2 : 1) void k_osc(
     const float* __restrict__ tab, int64_t batch, int64_t ld, const float* __restrict__ q,

@@ -1534,8 +1534,9 @@ struct AInrP {
 // acc (= or +=) X^T Ia X for the child frame at r with axes R (parent
 // coordinates). X = rot(R^T) * [[1, 0], [-[r]x, 1]]: the rotation acts
 // first, blockwise R M R^T, then the shift to the parent origin gives
-//   A_p = A' - (B' [r]x) - (B' [r]x)^T - [r]x C' [r]x,  B_p = B' + [r]x C',
-//   C_p = C'.
+//   B_p = B' + [r]x C',  A_p = A' - B_p [r]x + [r]x B'^T,  C_p = C'
+// (A_p is A' - B' [r]x - (B' [r]x)^T - [r]x C' [r]x with the first and the last
+// of these products taken together).
 template <bool INIT>
 RBD_DI void xainr_acc(const M3& R, V3 r, const AInrP& I, AInr& acc) {
   const float* Ra = R.a;
@@ -1546,11 +1547,6 @@ RBD_DI void xainr_acc(const M3& R, V3 r, const AInrP& I, AInr& acc) {
     wa[i][0] = __builtin_fmaf(Ra[3 * i], I.a00, Ra[3 * i + 1] * I.a01);
     wa[i][1] = __builtin_fmaf(Ra[3 * i], I.a01, Ra[3 * i + 1] * I.a11);
   }
-  float Ap[3][3];
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = i; j < 3; ++j) Ap[i][j] = __builtin_fmaf(wa[i][0], Ra[3 * j], wa[i][1] * Ra[3 * j + 1]);
   // B' = (P B2) R^T, B2 = the first two rows of B
   float wb[3][3];
 #pragma unroll
@@ -1578,50 +1574,40 @@ RBD_DI void xainr_acc(const M3& R, V3 r, const AInrP& I, AInr& acc) {
     for (int j = i; j < 3; ++j)
       Cp[i][j] = __builtin_fmaf(wc[i][0], Ra[3 * j], __builtin_fmaf(wc[i][1], Ra[3 * j + 1], wc[i][2] * Ra[3 * j + 2]));
   Cp[1][0] = Cp[0][1]; Cp[2][0] = Cp[0][2]; Cp[2][1] = Cp[1][2];
-  // [r]x C' (row i of [r]x times C')
-  float rc[3][3];
+  // B_p
+  float Bn[3][3];
 #pragma unroll
   for (int j = 0; j < 3; ++j) {
-    rc[0][j] = __builtin_fmaf(r.y, Cp[2][j], -r.z * Cp[1][j]);
-    rc[1][j] = __builtin_fmaf(r.z, Cp[0][j], -r.x * Cp[2][j]);
-    rc[2][j] = __builtin_fmaf(r.x, Cp[1][j], -r.y * Cp[0][j]);
+    Bn[0][j] = __builtin_fmaf(r.y, Cp[2][j], __builtin_fmaf(-r.z, Cp[1][j], Bp[0][j]));
+    Bn[1][j] = __builtin_fmaf(r.z, Cp[0][j], __builtin_fmaf(-r.x, Cp[2][j], Bp[1][j]));
+    Bn[2][j] = __builtin_fmaf(r.x, Cp[1][j], __builtin_fmaf(-r.y, Cp[0][j], Bp[2][j]));
   }
-  // T = B' [r]x and Q = ([r]x C') [r]x (symmetric), column j of [r]x:
-  // (0, rz, -ry), (-rz, 0, rx), (ry, -rx, 0)
-  auto times_rx = [&](const float (&M)[3][3], int i, int j) __attribute__((always_inline)) {
-    return j == 0 ? __builtin_fmaf(M[i][1], r.z, -M[i][2] * r.y)
-                  : (j == 1 ? __builtin_fmaf(M[i][2], r.x, -M[i][0] * r.z) : __builtin_fmaf(M[i][0], r.y, -M[i][1] * r.x));
+  // acc + A_p, upper triangle; column j of [r]x is (0, rz, -ry), (-rz, 0, rx), (ry, -rx, 0)
+  auto entry = [&](int i, int j, float x) __attribute__((always_inline)) {
+    const float rr[3] = {r.x, r.y, r.z};
+    const int j1 = (j + 1) % 3, j2 = (j + 2) % 3, i1 = (i + 1) % 3, i2 = (i + 2) % 3;
+    // - (B_p [r]x)_ij = B_p[i][j2] r_j1 - B_p[i][j1] r_j2
+    x = __builtin_fmaf(Bn[i][j2], rr[j1], __builtin_fmaf(-Bn[i][j1], rr[j2], x));
+    // ([r]x B'^T)_ij = r_i1 B'[j][i2] - r_i2 B'[j][i1]
+    x = __builtin_fmaf(rr[i1], Bp[j][i2], __builtin_fmaf(-rr[i2], Bp[j][i1], x));
+    return __builtin_fmaf(wa[i][0], Ra[3 * j], __builtin_fmaf(wa[i][1], Ra[3 * j + 1], x));
   };
-  float T[3][3];
+  acc.a00 = entry(0, 0, INIT ? 0.0f : acc.a00);
+  acc.a11 = entry(1, 1, INIT ? 0.0f : acc.a11);
+  acc.a22 = entry(2, 2, INIT ? 0.0f : acc.a22);
+  acc.a01 = entry(0, 1, INIT ? 0.0f : acc.a01);
+  acc.a02 = entry(0, 2, INIT ? 0.0f : acc.a02);
+  acc.a12 = entry(1, 2, INIT ? 0.0f : acc.a12);
 #pragma unroll
   for (int i = 0; i < 3; ++i)
 #pragma unroll
-    for (int j = 0; j < 3; ++j) T[i][j] = times_rx(Bp, i, j);
-  float An[6], Bn[9], Cn[6];
-  const int ii[6] = {0, 1, 2, 0, 0, 1}, jj[6] = {0, 1, 2, 1, 2, 2};
-#pragma unroll
-  for (int e = 0; e < 6; ++e) {
-    const int i = ii[e], j = jj[e];
-    An[e] = Ap[i][j] - T[i][j] - T[j][i] - times_rx(rc, i, j);
-    Cn[e] = Cp[i][j];
-  }
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) Bn[3 * i + j] = Bp[i][j] + rc[i][j];
-  if constexpr (INIT) {
-    acc.a00 = An[0]; acc.a11 = An[1]; acc.a22 = An[2]; acc.a01 = An[3]; acc.a02 = An[4]; acc.a12 = An[5];
-#pragma unroll
-    for (int e = 0; e < 9; ++e) acc.b[e] = Bn[e];
-    acc.c00 = Cn[0]; acc.c11 = Cn[1]; acc.c22 = Cn[2]; acc.c01 = Cn[3]; acc.c02 = Cn[4]; acc.c12 = Cn[5];
-  } else {
-    acc.a00 = acc.a00 + An[0]; acc.a11 = acc.a11 + An[1]; acc.a22 = acc.a22 + An[2];
-    acc.a01 = acc.a01 + An[3]; acc.a02 = acc.a02 + An[4]; acc.a12 = acc.a12 + An[5];
-#pragma unroll
-    for (int e = 0; e < 9; ++e) acc.b[e] = acc.b[e] + Bn[e];
-    acc.c00 = acc.c00 + Cn[0]; acc.c11 = acc.c11 + Cn[1]; acc.c22 = acc.c22 + Cn[2];
-    acc.c01 = acc.c01 + Cn[3]; acc.c02 = acc.c02 + Cn[4]; acc.c12 = acc.c12 + Cn[5];
-  }
+    for (int j = 0; j < 3; ++j) acc.b[3 * i + j] = INIT ? Bn[i][j] : acc.b[3 * i + j] + Bn[i][j];
+  acc.c00 = INIT ? Cp[0][0] : acc.c00 + Cp[0][0];
+  acc.c11 = INIT ? Cp[1][1] : acc.c11 + Cp[1][1];
+  acc.c22 = INIT ? Cp[2][2] : acc.c22 + Cp[2][2];
+  acc.c01 = INIT ? Cp[0][1] : acc.c01 + Cp[0][1];
+  acc.c02 = INIT ? Cp[0][2] : acc.c02 + Cp[0][2];
+  acc.c12 = INIT ? Cp[1][2] : acc.c12 + Cp[1][2];
 }
 
 // Solves M x = b for a symmetric positive definite n x n M, n <= 6 (unpivoted
@@ -1678,11 +1664,13 @@ RBD_DI Mot ainr_solve(const AInr& I, const Frc& rhs) {
 // the O(n) alternative to forming and factoring M. One depth-first sweep does
 // the velocity pass on the way down and, as each subtree closes, the
 // articulated-inertia pass (leaves to root):
-//   IA_i = I_i + sum X^T Ia_c X,  pA_i = v_i x* I_i v_i + sum X^T pa_c,
+//   IA_i = I_i + sum X^T Ia_c X,
+//   pA_i = [w_i x Ibar_i w_i; w_i x (w_i x h_i)] + sum X^T pa_c,
 //   U = IA_i S, D = S^T U, u = tau_i - S^T pA_i,
 //   Ia_i = IA_i - U U^T / D,  pa_i = pA_i + Ia_i c_i + U u / D,
-// with c_i = v_i x S qd_i. Only U/D and u/D outlive a body's subtree; the
-// acceleration pass (root to leaves) rebuilds X and v from q and qd, which is
+// in classical accelerations, as the Newton-Euler steps above: no linear
+// velocities, and c_i = [w_i x S qd_i; R^T (w_p x (w_p x r_i))]. Only U/D and u/D outlive a body's subtree; the
+// acceleration pass (root to leaves) rebuilds X and w from q and qd, which is
 // cheaper than holding them for every body:
 //   a' = X a_parent + c_i,  qdd_i = u/D - (U/D)^T a',  a_i = a' + S qdd_i.
 // Gravity is the fictitious base acceleration -g; external forces are
@@ -1700,16 +1688,17 @@ struct AbaState {
   V3 pw[NW];
   Frc fe[NW];  // external force in body coordinates, subtracted from pA
   float cq[N], sq[N];
-  Mot v[N];
+  V3 w[N], cl[N];  // angular velocity, linear part of c
   Frc Ud[N];
   float ud[N];
   AInr acc[N];
   Frc accp[N];
-  Mot a0;  // free base: total spatial acceleration (gravity included)
+  Mot a0;  // free base: total acceleration (gravity included)
 };
 template <class TP>
 struct AbaDown {
-  Mot a[TP::N], vv[TP::N];
+  Mot a[TP::N];
+  V3 w[TP::N];
 };
 
 template <class TP, int J, bool FIRST, class FX, class ST, class QDI, class TI>
@@ -1718,7 +1707,7 @@ RBD_DI void aba_close(const float* __restrict__ t, ST& s, const QDI& qd, const T
   constexpr bool kKids = TP::last(J) > J;
   const float* const tc = opaque_table(t);  // read again, not held since the velocity pass
   const Inr Ib = load_inr<J>(tc);
-  Frc bias = crf(s.v[J], imul(Ib, s.v[J]));
+  Frc bias = {cross(s.w[J], isym(Ib, s.w[J])), cross(s.w[J], cross(s.w[J], Ib.h))};
   if constexpr (FX::kOn) bias = bias - s.fe[J];
   AInr IA;
   Frc pA;
@@ -1757,20 +1746,21 @@ RBD_DI void aba_close(const float* __restrict__ t, ST& s, const QDI& qd, const T
       Ia.c01 = __builtin_fmaf(-U.f.x, W.f.y, IA.c01);
       Ia.c02 = __builtin_fmaf(-U.f.x, W.f.z, IA.c02);
       Ia.c12 = __builtin_fmaf(-U.f.y, W.f.z, IA.c12);
-      // pa = pA + Ia c + U u / D; c = w [wy, -wx, 0; vy, -vx, 0]
+      // pa = pA + Ia c + U u / D; c = [w wy, -w wx, 0; cl]
       const float w = qd(cidx<TP::vofs(J)>);
-      const float cwx = w * s.v[J].w.y, cwy = -w * s.v[J].w.x, cvx = w * s.v[J].v.y, cvy = -w * s.v[J].v.x;
+      const float cwx = w * s.w[J].y, cwy = -w * s.w[J].x;
+      const V3 cl = s.cl[J];
       const float ud_ = s.ud[J];
       Frc pa;
-      pa.n.x = pA.n.x + Ia.a00 * cwx + Ia.a01 * cwy + Ia.b[0] * cvx + Ia.b[1] * cvy + U.n.x * ud_;
-      pa.n.y = pA.n.y + Ia.a01 * cwx + Ia.a11 * cwy + Ia.b[3] * cvx + Ia.b[4] * cvy + U.n.y * ud_;
+      pa.n.x = pA.n.x + Ia.a00 * cwx + Ia.a01 * cwy + Ia.b[0] * cl.x + Ia.b[1] * cl.y + Ia.b[2] * cl.z + U.n.x * ud_;
+      pa.n.y = pA.n.y + Ia.a01 * cwx + Ia.a11 * cwy + Ia.b[3] * cl.x + Ia.b[4] * cl.y + Ia.b[5] * cl.z + U.n.y * ud_;
       pa.n.z = pA.n.z + U.n.z * ud_;
-      pa.f.x = pA.f.x + Ia.b[0] * cwx + Ia.b[3] * cwy + Ia.c00 * cvx + Ia.c01 * cvy + U.f.x * ud_;
-      pa.f.y = pA.f.y + Ia.b[1] * cwx + Ia.b[4] * cwy + Ia.c01 * cvx + Ia.c11 * cvy + U.f.y * ud_;
-      pa.f.z = pA.f.z + Ia.b[2] * cwx + Ia.b[5] * cwy + Ia.c02 * cvx + Ia.c12 * cvy + U.f.z * ud_;
+      pa.f.x = pA.f.x + Ia.b[0] * cwx + Ia.b[3] * cwy + Ia.c00 * cl.x + Ia.c01 * cl.y + Ia.c02 * cl.z + U.f.x * ud_;
+      pa.f.y = pA.f.y + Ia.b[1] * cwx + Ia.b[4] * cwy + Ia.c01 * cl.x + Ia.c11 * cl.y + Ia.c12 * cl.z + U.f.y * ud_;
+      pa.f.z = pA.f.z + Ia.b[2] * cwx + Ia.b[5] * cwy + Ia.c02 * cl.x + Ia.c12 * cl.y + Ia.c22 * cl.z + U.f.z * ud_;
       const V3 r = load_r<J>(tc);
       const M3 RJ = joint_rot_cs<J>(tc, s.cq[J], s.sq[J]);
-        xainr_acc<FIRST>(RJ, r, Ia, s.acc[P]);
+      xainr_acc<FIRST>(RJ, r, Ia, s.acc[P]);
       if constexpr (FIRST) s.accp[P] = xfrc(RJ, r, pa);
       else xfrc_acc(RJ, r, pa, s.accp[P]);
     }
@@ -1781,17 +1771,19 @@ template <class TP, int I, class FX, class ST, class QI, class QDI>
 RBD_DI void aba_motion(const float* __restrict__ t, ST& s, const QI& q, const QDI& qd, const FX& fx) {
   constexpr int P = TP::parent(I);
   if constexpr (TP::free_body(I)) {
-    s.v[I] = {{qd(3), qd(4), qd(5)}, {qd(0), qd(1), qd(2)}};
+    s.w[I] = {qd(3), qd(4), qd(5)};
     if constexpr (FX::kOn) world_pose<TP, I>(t, q, quat_rot(q(3), q(4), q(5), q(6)), s.Rw, s.pw);
   } else {
     fsincos(q(cidx<TP::qofs(I)>), s.sq[I], s.cq[I]);
     const float w = qd(cidx<TP::vofs(I)>);
     const M3 RI = joint_rot_cs<I>(t, s.cq[I], s.sq[I]);
     if constexpr (P < 0) {
-      s.v[I] = {{0.0f, 0.0f, w}, {0.0f, 0.0f, 0.0f}};
+      s.w[I] = {0.0f, 0.0f, w};
+      s.cl[I] = {0.0f, 0.0f, 0.0f};
     } else {
-      s.v[I] = xmot(RI, load_r<I>(t), s.v[P]);
-      s.v[I].w.z = s.v[I].w.z + w;
+      s.w[I] = mulT(RI, s.w[P]);
+      s.w[I].z = s.w[I].z + w;
+      s.cl[I] = mulT(RI, cross(s.w[P], cross(s.w[P], load_r<I>(t))));
     }
     if constexpr (FX::kOn) world_pose<TP, I>(t, q, RI, s.Rw, s.pw);
   }
@@ -1803,10 +1795,13 @@ RBD_DI void aba_down(const float* __restrict__ t, V3 mg, const ST& s, AbaDown<TP
                      const QDDO& qdd) {
   constexpr int P = TP::parent(I);
   if constexpr (TP::free_body(I)) {
+    // spatial: a' - w x v, less gravity
     const V3 ag = mulT(quat_rot(q(3), q(4), q(5), q(6)), mg);
+    const V3 w = {qd(3), qd(4), qd(5)}, v = {qd(0), qd(1), qd(2)};
+    const V3 x = cross_add(v, w, s.a0.v - ag);
     d.a[I] = s.a0;
-    d.vv[I] = {{qd(3), qd(4), qd(5)}, {qd(0), qd(1), qd(2)}};
-    qdd(0, s.a0.v.x - ag.x); qdd(1, s.a0.v.y - ag.y); qdd(2, s.a0.v.z - ag.z);
+    d.w[I] = w;
+    qdd(0, x.x); qdd(1, x.y); qdd(2, x.z);
     qdd(3, s.a0.w.x); qdd(4, s.a0.w.y); qdd(5, s.a0.w.z);
   } else {
     float sn, cs;
@@ -1815,17 +1810,14 @@ RBD_DI void aba_down(const float* __restrict__ t, V3 mg, const ST& s, AbaDown<TP
     const float w = qd(cidx<TP::vofs(I)>);
     Mot ap;
     if constexpr (P < 0) {
-      d.vv[I] = {{0.0f, 0.0f, w}, {0.0f, 0.0f, 0.0f}};
+      d.w[I] = {0.0f, 0.0f, w};
       ap = {{0.0f, 0.0f, 0.0f}, mulT(RI, mg)};
     } else {
-      const V3 r = load_r<I>(t);
-      d.vv[I] = xmot(RI, r, d.vv[P]);
-      d.vv[I].w.z = d.vv[I].w.z + w;
-      ap = xmot(RI, r, d.a[P]);
-      ap.w.x = __builtin_fmaf(w, d.vv[I].w.y, ap.w.x);
-      ap.w.y = __builtin_fmaf(-w, d.vv[I].w.x, ap.w.y);
-      ap.v.x = __builtin_fmaf(w, d.vv[I].v.y, ap.v.x);
-      ap.v.y = __builtin_fmaf(-w, d.vv[I].v.x, ap.v.y);
+      d.w[I] = mulT(RI, d.w[P]);
+      d.w[I].z = d.w[I].z + w;
+      ap = {mulT(RI, d.a[P].w), mulT(RI, point_acc(d.a[P], d.w[P], load_r<I>(t)))};
+      ap.w.x = __builtin_fmaf(w, d.w[I].y, ap.w.x);
+      ap.w.y = __builtin_fmaf(-w, d.w[I].x, ap.w.y);
     }
     const float x = s.ud[I] - pair(s.Ud[I], ap);
     qdd(cidx<TP::vofs(I)>, x);

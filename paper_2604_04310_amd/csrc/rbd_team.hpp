@@ -7,15 +7,15 @@
 // registers admit one wave per SIMD, which then issues one instruction every
 // 5.8 cycles. Split by branches, the chain is the longest branch, the trunk
 // bodies above it and the trunk (118 tenths of a body of 300, rbd_team_plan.hpp),
-// a batch fills four times as many waves, and a wave holds only its own rows of
-// the factor, so two waves fit on a SIMD and hide each other's latency.
+// a batch fills four times as many waves, and a wave holds only what its own
+// branches need, so two or three waves fit on a SIMD and hide each other's latency.
 //
 // The branches of different waves meet in the trunk only: what a branch hands
-// over is the force and the composite inertia it exerts on the trunk body it
-// hangs on, and its share of the trunk's rows of the factor (the Schur
-// complement sum_D L[D][K] L[D][J] over its DoFs D, and the same with y), all
-// parked in LDS as rows of 64 lanes. The trunk's solution goes back the same
-// way.
+// over is the force and the (composite or articulated) inertia it exerts on the
+// trunk body it hangs on and, where M is factored, its share of the trunk's
+// rows of the factor (the Schur complement sum_D L[D][K] L[D][J] over its DoFs D,
+// and the same with y), all parked in LDS as rows of 64 lanes. The trunk's
+// solution goes back the same way.
 #pragma once
 
 #include "rbd_lane.hpp"
@@ -917,7 +917,7 @@ RBD_DI void team_aba_down(const float* __restrict__ t, const float* __restrict__
     if constexpr (TM::attach(W, I)) {
       const Frc a = get_frc(acc, 6 * cidx<TrunkRows<TP>::body(I)>);
       d.a[I] = {a.n, a.f};
-      d.vv[I] = s.v[I];
+      d.w[I] = s.w[I];
     } else if constexpr (TM::in(W, I)) {
       aba_down<TP, I>(tb, mg, s, d, q, qd, qdd);
     }

@@ -9,8 +9,8 @@ constexpr int kTeamWaves = 4;     // most waves of a team: one per SIMD of a com
 constexpr int kTeamMinDofs = 16;  // smaller trees stay one instance per lane
 // Above this many DoFs a lane that does the whole tree holds more than the 256
 // registers that two waves per SIMD leave it, and a team is faster at every
-// batch (humanoid forward dynamics, team against one lane: 14 / 34 us at 4096,
-// 35 / 39 at 65536, 121 / 160 at 262144); up to it, only while one instance per
+// batch (humanoid forward dynamics, team against one lane: 12 / 34 us at 4096,
+// 26 / 39 at 65536, 48 / 88 at 131072); up to it, only while one instance per
 // lane leaves SIMDs idle (quadruped, 18 DoFs: 20.5 / 19.0 us at 131072).
 constexpr int kTeamAlwaysDofs = 24;
 
