@@ -818,6 +818,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads, EXT ? 2 : 3) void k_aba_team(
     const float* __restrict__ qd, const float* __restrict__ tau, const float* __restrict__ fext,
     float* __restrict__ qdd) {
   if constexpr (Team<TP>::kOn) {
+    static_assert(TeamLds<TP>::kAba <= kTeamRows);
     __shared__ float lds_team[TeamLds<TP>::kAba * kTileLanes];
     team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       team_aba<TP, EXT, decltype(W_)::value>(tl, tab, SoaIo<TP>{ld}, lds_team, q, qd, tau, fext, ld, qdd);
@@ -860,6 +861,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads) void k_rnea_team(
     const float* __restrict__ qd, const float* __restrict__ qdd, const float* __restrict__ fext,
     float* __restrict__ tau) {
   if constexpr (Team<TP>::kOn) {
+    static_assert(TeamLds<TP>::kId <= kTeamRows);
     __shared__ float lds_team[TeamLds<TP>::kId * kTileLanes];
     team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       team_rnea<TP, HAS_QDD, EXT, decltype(W_)::value>(tl, tab, SoaIo<TP>{ld}, lds_team, q, qd, qdd, fext, ld, tau);
@@ -954,6 +956,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads, EXT ? 1 : 2) void k_fwd_dyn_vjp
     const float* __restrict__ qd, const float* __restrict__ tau, const float* __restrict__ gqdd, float* gq, float* gqd,
     float* gtau, const float* __restrict__ fext, float* gfext) {
   if constexpr (Team<TP>::kOn) {
+    static_assert(TeamLds<TP>::template vjp<EXT>() <= kTeamRows);
     __shared__ float lds_team[TeamLds<TP>::template vjp<EXT>() * kTileLanes];
     team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       team_fwd_dyn_vjp<TP, EXT, decltype(W_)::value>(tl, tab, SoaIo<TP>{ld}, lds_team, q, qd, tau, gqdd, gq, gqd,
@@ -980,6 +983,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads, EXT ? 1 : 2) void k_fwd_dyn_jvp
     using TROWS = TeamRows<TP, 12, false, 1>;
     // after the first solve its rows hold [qdd | what the tangent hands to the trunk]
     constexpr int kTan = NV + TROWS::total(), kRows = ROWS::total() > kTan ? ROWS::total() : kTan;
+    static_assert((kRows + T) <= kTeamRows);
     __shared__ float lds_team[(kRows + T) * kTileLanes];
     team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       constexpr int W = decltype(W_)::value;
@@ -1121,6 +1125,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads) void k_crba_team(const float* _
   if constexpr (TM::kOn) {
     constexpr int N = TP::N, NV = TP::NV;
     using ROWS = TeamRows<TP, 10, false, 0>;
+    static_assert(ROWS::total() <= kTeamRows);
     __shared__ float lds_team[ROWS::total() * kTileLanes];
     team_waves<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       constexpr int W = decltype(W_)::value;
@@ -1198,6 +1203,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads) void k_rnea_jvp_team(
     RBD_LANE_IO(TP);
     constexpr int NQ = TP::NQ, NV = TP::NV;
     using ROWS = TeamRows<TP, 12, false, 0>;
+    static_assert(ROWS::total() <= kTeamRows);
     __shared__ float lds_team[ROWS::total() * kTileLanes];
     team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       constexpr int W = decltype(W_)::value;
@@ -1244,6 +1250,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads) void k_rnea_vjp_team(
     RBD_LANE_IO(TP);
     constexpr int NQ = TP::NQ, NV = TP::NV;
     using ROWS = TeamRows<TP, EXT ? 30 : 18, false, 0>;
+    static_assert(ROWS::total() <= kTeamRows);
     __shared__ float lds_team[ROWS::total() * kTileLanes];
     team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       constexpr int W = decltype(W_)::value;
@@ -1310,6 +1317,7 @@ __global__ __launch_bounds__(Team<TP>::kOn ? Team<TP>::kThreads : kBlock, Team<T
     using ROWS = TeamRows<TP, 16, true, 1>;
     using EROWS = OscRows<TP, E>;
     using MASK = OscRhs<TP, E>;
+    static_assert((ROWS::total() + EROWS::total()) <= kTeamRows);
     __shared__ float lds_team[(ROWS::total() + EROWS::total()) * kTileLanes];
     team_waves<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       constexpr int W = decltype(W_)::value;
@@ -1451,6 +1459,7 @@ __global__ __launch_bounds__((PackedShape<TP, OP>::kThreads), (PackedShape<TP, O
     // a team per tile, the same code as the direct calls
     using L = TeamLds<TP>;
     constexpr int kRows = OP == kOpFwdDyn ? L::kAba : (OP == kOpRnea ? L::kId : L::template vjp<false>());
+    static_assert(kRows <= kTeamRows);
     __shared__ float lds_team[kRows * kTileLanes];
     for (int t = blockIdx.x; t < n_tiles; t += gridDim.x) {
       const PackedReq& R = reqs[__builtin_amdgcn_readfirstlane(tile_req[t])];

@@ -10,9 +10,14 @@ constexpr int kTeamMinDofs = 16;  // smaller trees stay one instance per lane
 // Above this many DoFs a lane that does the whole tree holds more than the 256
 // registers that two waves per SIMD leave it, and a team is faster at every
 // batch (humanoid forward dynamics, team against one lane: 12 / 34 us at 4096,
-// 26 / 39 at 65536, 48 / 88 at 131072); up to it, only while one instance per
-// lane leaves SIMDs idle (quadruped, 18 DoFs: 20.5 / 19.0 us at 131072).
+// 26 / 39 at 65536, 48 / 88 at 131072); up to it some operations are faster one
+// instance per lane once the batch fills the SIMDs (quadruped, 18 DoFs, forward
+// dynamics: 14 / 15 us at 81920, 20 / 16 at 131072).
 constexpr int kTeamAlwaysDofs = 24;
+// Most rows of LDS (64 lanes, 256 bytes each) that a block of a team uses: two
+// blocks share the 160 KB of a compute unit. What a trunk costs grows with its
+// length and with the branches along it (the humanoid's four bodies: 319).
+constexpr int kTeamRows = 320;
 
 // The trunk is an ancestor-closed set of bodies; what hangs on it are the
 // branches (whole subtrees). Every branch belongs to one wave; the trunk's own
@@ -34,10 +39,16 @@ struct TeamPlan {
 // bodies above them that it runs down again (2), then the trunk (10 a body),
 // which the other waves wait for. Branches go to waves largest first, each to
 // the least loaded wave. The best trunk is taken if that chain is at most
-// three quarters of the whole tree's work.
+// three quarters of the whole tree's work. Trunks whose waves hand over more than
+// kTeamRows in any operation are left out.
 constexpr TeamPlan team_plan(bool floating, int n, const int* parent) {
   TeamPlan best;
-  int size[64] = {};
+  int size[64] = {}, dofs[64] = {}, above_dofs[64] = {}, nv = 0;
+  for (int i = 0; i < n; ++i) {
+    dofs[i] = floating && i == 0 ? 6 : 1;
+    above_dofs[i] = parent[i] < 0 ? 0 : above_dofs[parent[i]] + dofs[parent[i]];
+    nv += dofs[i];
+  }
   for (int i = n - 1; i >= 0; --i) {
     size[i] += 1;
     if (parent[i] >= 0) size[parent[i]] += size[i];
@@ -65,15 +76,25 @@ constexpr TeamPlan team_plan(bool floating, int n, const int* parent) {
         wave[k] = w;
       }
       int longest = 0, owner = 0, least = 0, used = 0;
+      int att = 0, schur = 0, rhs = 0, nvt = 0;  // over the waves: trunk bodies with branches, rows of the factor,
+                                                 // DoFs above; DoFs of the trunk
       for (int w = 0; w < kTeamWaves; ++w) {
-        bool above[64] = {};
+        bool above[64] = {}, holds[64] = {};
         int anc = 0;
-        for (int k = 0; k < nb; ++k)
-          if (wave[k] == w)
-            for (int a = parent[br[k]]; a >= 0 && !above[a]; a = parent[a]) {
-              above[a] = true;
-              anc += 2;
-            }
+        for (int k = 0; k < nb; ++k) {
+          if (wave[k] != w) continue;
+          const int on = parent[br[k]];
+          if (on >= 0 && !holds[on]) {
+            holds[on] = true;
+            ++att;
+          }
+          for (int a = on; a >= 0 && !above[a]; a = parent[a]) {
+            above[a] = true;
+            anc += 2;
+            for (int d = 0; d < dofs[a]; ++d) schur += above_dofs[a] + d + 1;
+            rhs += dofs[a];
+          }
+        }
         if (load[w] == 0) continue;
         ++used;
         if (load[w] + anc > longest) longest = load[w] + anc;
@@ -82,8 +103,19 @@ constexpr TeamPlan team_plan(bool floating, int n, const int* parent) {
           owner = w;
         }
       }
+      for (int i = 0; i < n; ++i) nvt += trunk[i] ? dofs[i] : 0;
+      // the blocks' rows as the kernels count them: articulated-body form,
+      // adjoint, tangent, operational-space control
+      const int rows[] = {27 * att + 6 * nt,
+                          16 * att + schur + 2 * rhs + 2 * nvt,
+                          2 * nv + 30 * att + 2 * nvt,
+                          16 * att + schur + rhs + nvt,
+                          nv + 12 * att + rhs + nvt,
+                          16 * att + schur + rhs + 6 * nvt + 39};
+      bool fits = true;
+      for (int r : rows) fits = fits && r <= kTeamRows;
       const int cost = longest + 10 * nt;
-      if (used > 1 && (best.waves == 0 || cost < best_cost)) {
+      if (fits && used > 1 && (best.waves == 0 || cost < best_cost)) {
         best_cost = cost;
         best.waves = used;  // waves 0 .. used - 1 have work
         best.owner = owner;

@@ -72,3 +72,51 @@ def test_plans_of_random_trees(tmp_path):
                 pi, pj = par[i], par[j]
                 assert pi == pj if pj < 0 or wave[pj] < 0 else pi == pj + d
     assert teams > 50
+
+
+def comb(spine, rib):
+    """A chain of `spine` bodies, each with a chain of `rib` bodies hanging on it."""
+    par, last = [], -1
+    for _ in range(spine):
+        me = at = len(par)
+        par.append(last)
+        for _ in range(rib):
+            par.append(at)
+            at = len(par) - 1
+        last = me
+    return par
+
+
+@pytest.mark.parametrize("floating", [False, True])
+def test_rows_of_a_block_fit(tmp_path, floating):
+    """Long trunks with branches all along hand over the most: the rows of LDS of the largest block (the
+    adjoint's and operational-space control's) stay within the 320 that let two blocks share a compute unit."""
+    trees = [(floating, comb(s, r)) for s in range(2, 32) for r in range(1, 64 // s)]
+    rng = np.random.default_rng(6)
+    trees += [(floating, [int(x) for x in W.random_dfs_parents(64, int(rng.integers(1 << 30)))]) for _ in range(200)]
+    teams = 0
+    for (_, par), t in zip(trees, plans(trees, tmp_path)):
+        n, waves, wave = len(par), t[0], t[10:]
+        if waves == 0:
+            continue
+        teams += 1
+        dofs = [6 if floating and i == 0 else 1 for i in range(n)]
+        depth = np.zeros(n, int)
+        for i, p in enumerate(par):
+            depth[i] = 0 if p < 0 else depth[p] + dofs[p]
+        trunk_dofs = sum(d for d, w in zip(dofs, wave) if w < 0)
+        att = factor = rhs = 0
+        for w in range(waves):
+            on = {par[i] for i in range(n) if wave[i] == w and par[i] >= 0 and wave[par[i]] < 0}
+            att += len(on)
+            above = set()
+            for a in on:
+                while a >= 0:
+                    above.add(a)
+                    a = par[a]
+            factor += sum(depth[a] + d + 1 for a in above for d in range(dofs[a]))
+            rhs += sum(dofs[a] for a in above)
+        adjoint = max(16 * att + factor + 2 * rhs, 2 * sum(dofs) + 30 * att) + 2 * trunk_dofs
+        control = 16 * att + factor + rhs + 6 * trunk_dofs + 39
+        assert max(adjoint, control, 27 * att + 6 * int((wave < 0).sum())) <= 320
+    assert teams > 50
