@@ -125,18 +125,32 @@ static inline Shape plain_shape(int64_t batch) { return {dim3(grid_for(batch)), 
 // (scalar-base addressing is chosen in the kernels themselves).
 static inline bool large(const rbd_model* m) { return m->nv > 16; }
 
-// Whether the model's tree is shared out over a team of waves, and the shape
-// of such a launch: one block per 64 instances.
+// Whether the model's tree is shared out over a team of waves: above
+// kTeamAlwaysDofs at every batch, below it up to the batch where one instance
+// per lane catches up. Quadruped (18 DoFs), team against one lane, in us:
+//                    65600      98304      131072     262144
+//   forward dynamics 13.3/14.7  16.3/15.5  20.4/16.3  37.0/31.0   (14.1/15.5 at 81920)
+//     with forces    16.1/28.0  20.0/30.4  24.9/32.4  45.2/58.1
+//   its adjoint      23.8/31.9  28.5/33.7  36.6/34.3  66.1/64.8
+//   its tangent      22.6/37.1  27.3/43.9  35.0/47.8  65.8/82.5
+//   inverse dynamics  8.6/8.3    8.9/8.7    9.4/9.4   17.7/18.0
+//     its adjoint    13.7/19.3  18.5/22.4  22.4/24.4  38.4/44.1
+//     its tangent    12.9/14.9  16.9/19.6  20.7/22.0  37.1/35.7
+// so forward dynamics with forces, its tangent and the adjoint of inverse
+// dynamics are shared out at every batch, the others up to 81920.
 static inline bool teamed(const rbd_model* m, int64_t batch) {
-  return m->team.waves > 1 && (m->nv > kTeamAlwaysDofs || batch <= kOneWavePerSimd);
+  return m->team.waves > 1 && (m->nv > kTeamAlwaysDofs || batch <= kOneWavePerSimd * 5 / 4);
 }
-// The same for the operations that mostly write (poses, Jacobians, mass
-// matrices): one instance per lane reaches the memory's rate once the batch
-// fills the SIMDs, and writes longer runs of a row at a time than the waves of
-// a team (humanoid, team against one lane: mass matrix 17 / 36 us at 16384, 33 /
-// 42 at 32768, 66 / 58 at 65536; poses 10 / 17 at 32768, 24 / 18 at 65536).
-static inline bool teamed_store(const rbd_model* m, int64_t batch) {
-  return m->team.waves > 1 && batch <= kOneWavePerSimd / 2;
+static inline bool teamed_always(const rbd_model* m) { return m->team.waves > 1; }
+// The operations that mostly write: one instance per lane reaches the memory's
+// rate once the batch fills the SIMDs, and writes longer runs of a row at a
+// time than the waves of a team. Team against one lane, in us: poses of the
+// humanoid 10.6/16.7 at 32832, 16.6/17.1 at 57344, 19.2/17.2 at 65536; its mass
+// matrix 35.1/43.6 at 32832, 42.0/45.2 at 40960, 57.7/52.2 at 57344; its
+// Jacobians of four frames 21.9/22.4 at 32832, 27.0/25.1 at 40960 (the quadruped
+// turns at the same batches). `eighths` of a batch of 65536.
+static inline bool teamed_store(const rbd_model* m, int64_t batch, int eighths) {
+  return m->team.waves > 1 && batch <= kOneWavePerSimd / 8 * eighths;
 }
 static inline Shape team_shape(const rbd_model* m, int64_t batch) {
   return {dim3((unsigned)((batch + kTileLanes - 1) / kTileLanes)), dim3((unsigned)(m->team.waves * kTileLanes))};
@@ -167,7 +181,7 @@ rbd_status launch_fk(const rbd_model* m, int64_t batch, int64_t ld, const float*
   if (batch == 0) return RBD_OK;
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &T};
-  if (teamed_store(m, batch)) return launch(m, KID_FK_TEAM, team_shape(m, batch), a, s, "rbd_fk");
+  if (teamed_store(m, batch, 7)) return launch(m, KID_FK_TEAM, team_shape(m, batch), a, s, "rbd_fk");
   return launch(m, KID_FK, plain_shape(batch), a, s, "rbd_fk");
 }
 
@@ -187,7 +201,7 @@ rbd_status launch_jacobian(const rbd_model* m, int64_t batch, int64_t ld, const 
   }
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &js, &J};
-  if (teamed_store(m, batch)) return launch(m, KID_JACOBIAN_TEAM, team_shape(m, batch), a, s, "rbd_jacobian");
+  if (teamed_store(m, batch, 4)) return launch(m, KID_JACOBIAN_TEAM, team_shape(m, batch), a, s, "rbd_jacobian");
   return launch(m, KID_JACOBIAN, plain_shape(batch), a, s, "rbd_jacobian");
 }
 
@@ -213,7 +227,7 @@ rbd_status launch_crba(const rbd_model* m, int64_t batch, int64_t ld, const floa
   if (batch == 0) return RBD_OK;
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &M};
-  if (teamed_store(m, batch)) return launch(m, KID_CRBA_TEAM, team_shape(m, batch), a, s, "rbd_crba");
+  if (teamed_store(m, batch, 5)) return launch(m, KID_CRBA_TEAM, team_shape(m, batch), a, s, "rbd_crba");
   return launch(m, KID_CRBA, plain_shape(batch), a, s, "rbd_crba");
 }
 
@@ -225,7 +239,7 @@ rbd_status launch_fwd_dyn(const rbd_model* m, int64_t batch, int64_t ld, const f
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &qd, &tau, &fext, &qdd};
   // (a team runs the articulated-body form: faster and more accurate there, see team_aba)
-  if (teamed(m, batch))
+  if (fext ? teamed_always(m) : teamed(m, batch))
     return launch(m, fext ? KID_ABA_EXT_TEAM : KID_ABA_TEAM, team_shape(m, batch), a, s, "rbd_fwd_dyn");
   return launch(m, id, heavy_shape(batch), a, s, "rbd_fwd_dyn");
 }
@@ -239,7 +253,8 @@ rbd_status launch_aba(const rbd_model* m, int64_t batch, int64_t ld, const float
   const KernelId id = fext ? (pre ? KID_ABA_PRE_EXT : KID_ABA_EXT) : (pre ? KID_ABA_PRE : KID_ABA);
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &qd, &tau, &fext, &qdd};
-  if (teamed(m, batch)) return launch(m, fext ? KID_ABA_EXT_TEAM : KID_ABA_TEAM, team_shape(m, batch), a, s, "rbd_aba");
+  if (fext ? teamed_always(m) : teamed(m, batch))
+    return launch(m, fext ? KID_ABA_EXT_TEAM : KID_ABA_TEAM, team_shape(m, batch), a, s, "rbd_aba");
   return launch(m, id, heavy_shape(batch), a, s, "rbd_aba");
 }
 
@@ -250,7 +265,7 @@ rbd_status launch_fwd_dyn_jvp(const rbd_model* m, int64_t batch, int64_t ld, con
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &qd, &tau, &dq, &dqd, &dtau, &qdd, &dqdd, &fext, &dfext};
   const bool ext = fext || dfext;
-  if (teamed(m, batch))
+  if (teamed_always(m))
     return launch(m, ext ? KID_JVP_EXT_TEAM : KID_JVP_TEAM, team_shape(m, batch), a, s, "rbd_fwd_dyn_jvp");
   if (large(m) && batch <= kOneWavePerSimd / 2) {
     // two waves per 64 instances: the factor of M on its own wave, in
@@ -283,7 +298,7 @@ rbd_status launch_rnea_vjp(const rbd_model* m, int64_t batch, int64_t ld, const 
   const bool ext = gfext || (fext && gq);
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &qd, &qdd, &lam, &gq, &gqd, &gqdd, &fext, &gfext};
-  if (teamed(m, batch))
+  if (teamed_always(m))
     return launch(m, ext ? KID_RNEA_VJP_EXT_TEAM : KID_RNEA_VJP_TEAM, team_shape(m, batch), a, s, "rbd_rnea_vjp");
   return launch(m, ext ? KID_RNEA_VJP_EXT : KID_RNEA_VJP, heavy_shape(batch), a, s, "rbd_rnea_vjp");
 }

@@ -78,8 +78,9 @@ RBD_DI void preload_inputs(float (&x)[n], float (&y)[n], const A& a, const B& b)
   });
 }
 
-// A tree that always runs as a team (Team::kAlways) launches the team's kernel
-// of an operation in place of the one below, which is then left empty.
+// Where a tree runs an operation as a team at every batch (Team::kAlways; for
+// some operations every tree that has a team, Team::kOn), the kernel of the
+// operation below is never launched and left empty.
 
 template <class TP>
 __global__ __launch_bounds__(kBlock) void k_fk(const float* __restrict__ tab, int64_t batch, int64_t ld,
@@ -165,7 +166,7 @@ __global__ __launch_bounds__(kBlock) void k_fwd_dyn(const float* __restrict__ ta
                                                     const float* __restrict__ q, const float* __restrict__ qd,
                                                     const float* __restrict__ tau, const float* __restrict__ fext,
                                                     float* __restrict__ qdd) {
-  if constexpr (!Team<TP>::kAlways) {
+  if constexpr (!(EXT ? Team<TP>::kOn : Team<TP>::kAlways)) {
     const uint32_t b = lane_id();
     if (b >= batch) return;
     const auto fx = fext_view<EXT>(fext, ld, b);
@@ -194,7 +195,7 @@ __global__ __launch_bounds__(kBlock) void k_aba(const float* __restrict__ tab, i
                                                 const float* __restrict__ q, const float* __restrict__ qd,
                                                 const float* __restrict__ tau, const float* __restrict__ fext,
                                                 float* __restrict__ qdd) {
-  if constexpr (!Team<TP>::kAlways) {
+  if constexpr (!(EXT ? Team<TP>::kOn : Team<TP>::kAlways)) {
     const uint32_t b = lane_id();
     if (b >= batch) return;
     const auto fx = fext_view<EXT>(fext, ld, b);
@@ -371,7 +372,7 @@ __global__ __launch_bounds__(2 * kTileLanes) void k_fwd_dyn_vjp_split(
     const float* __restrict__ tab, int64_t batch, int64_t ld, const float* __restrict__ q,
     const float* __restrict__ qd, const float* __restrict__ tau, const float* __restrict__ gqdd, float* gq,
     float* gqd, float* gtau, const float* __restrict__ fext, float* gfext) {
-  if constexpr (!Team<TP>::kAlways) {
+  if constexpr (!Team<TP>::kOn) {
     RBD_LANE_IO(TP);
     constexpr int NQ = TP::NQ, NV = TP::NV;
     extern __shared__ float lds_vjp[];
@@ -440,7 +441,7 @@ __global__ __launch_bounds__(kBlock) void k_fwd_dyn_jvp(const float* __restrict_
                                                         const float* __restrict__ dtau, float* qdd, float* dqdd,
                                                         const float* __restrict__ fext,
                                                         const float* __restrict__ dfext) {
-  if constexpr (!Team<TP>::kAlways) {
+  if constexpr (!Team<TP>::kOn) {
     RBD_LANE_IO(TP);
     const uint32_t b = lane_id();
     if (b >= batch) return;
@@ -495,7 +496,7 @@ __global__ __launch_bounds__(2 * kTileLanes) void k_fwd_dyn_jvp_split(
     const float* __restrict__ qd, const float* __restrict__ tau, const float* __restrict__ dq,
     const float* __restrict__ dqd, const float* __restrict__ dtau, float* qdd, float* dqdd,
     const float* __restrict__ fext, const float* __restrict__ dfext) {
-  if constexpr (!Team<TP>::kAlways) {
+  if constexpr (!Team<TP>::kOn) {
     RBD_LANE_IO(TP);
     constexpr int NV = TP::NV;
     extern __shared__ float lds_jvp[];
@@ -615,7 +616,7 @@ __global__ __launch_bounds__(kBlock) void k_rnea_vjp(const float* __restrict__ t
                                                      float* __restrict__ gq, float* __restrict__ gqd,
                                                      float* __restrict__ gqdd, const float* __restrict__ fext,
                                                      float* __restrict__ gfext) {
-  if constexpr (!Team<TP>::kAlways) {
+  if constexpr (!Team<TP>::kOn) {
     RBD_LANE_IO(TP);
     const uint32_t b = lane_id();
     if (b >= batch) return;
