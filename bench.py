@@ -35,7 +35,8 @@ COUNTERS_FILE = os.path.join(ROOT, "profiles", "kernel_counters_humanoid30_chain
 CSRC = os.path.join(ROOT, "paper_2604_04310_amd", "csrc")
 
 
-KERNEL_SOURCES = ["rbd_lane.hpp", "rbd_kernels.hpp", "rbd_kern_topo.hip", "rbd_shared.hpp", "rbd_topologies.hpp"]
+KERNEL_SOURCES = ["rbd_lane.hpp", "rbd_team.hpp", "rbd_team_plan.hpp", "rbd_kernels.hpp", "rbd_kern_topo.hip",
+                  "rbd_shared.hpp", "rbd_topologies.hpp"]
 
 
 def kernel_source_hash() -> str:
@@ -230,9 +231,18 @@ def _kernel_key(short):
     topo = rest.split(",")[0].rstrip(">").strip()
     key = {"k_fwd_dyn": "fwd_dyn", "k_rnea": "rnea_bias", "k_aba": "aba", "k_crba": "crba", "k_fk": "fk",
            "k_jacobian": "jacobian", "k_osc": "osc", "k_diff_ik": "diff_ik", "k_fwd_dyn_vjp": "fwd_dyn_vjp",
-           "k_fwd_dyn_jvp": "fwd_dyn_jvp", "k_fwd_dyn_jvp_split": "fwd_dyn_jvp", "k_fwd_dyn_vjp_split": "fwd_dyn_vjp",
-           "k_rnea_jvp": "rnea_jvp", "k_rnea_vjp": "rnea_vjp"}.get(base)
+           "k_fwd_dyn_jvp": "fwd_dyn_jvp",
+           "k_rnea_jvp": "rnea_jvp", "k_rnea_vjp": "rnea_vjp",
+           # one team of waves per 64 instances; forward dynamics and the articulated-body entry point share a kernel
+           "k_aba_team": "fwd_dyn", "k_rnea_team": "rnea_bias", "k_fwd_dyn_vjp_team": "fwd_dyn_vjp",
+           "k_fwd_dyn_jvp_team": "fwd_dyn_jvp", "k_rnea_jvp_team": "rnea_jvp", "k_rnea_vjp_team": "rnea_vjp"}.get(base)
     return f"{key}_{topo}" if key and topo in ("humanoid30", "chain7") else None
+
+
+def _waves_per_tile(short):
+    """Waves that share 64 instances: the four of a humanoid's team, else one."""
+    base, _, rest = short.partition("<")
+    return 4.0 if base.endswith("_team") or (base == "k_osc" and rest.startswith("humanoid30")) else 1.0
 
 
 def summarize_profiles(out_dir):
@@ -292,7 +302,7 @@ def summarize_profiles(out_dir):
            f"# Calibration on a plain 512 MiB device copy: FETCH_SIZE scale {fscale:.4f}, WRITE_SIZE scale "
            f"{wscale:.4f} (bytes = KiB x 1024 x scale).",
            "# flops_per_eval = SQ_INSTS_VALU_FLOPS_FP32 / SQ_WAVES (FP32 FLOPs of one lane, one instance per lane;",
-           "# twice that for the tangent and the adjoint of the 35-DoF tree at batch 32768, which run two waves per 64 instances);",
+           "# four times that for the kernels of a team of waves, which share 64 instances);",
            "# valu_insts_per_wave = SQ_INSTS_VALU / SQ_WAVES; quad-cycles per wave: wave_cycles, wait_any "
            "(dependency and memory waits), wait_inst_any (issue waits), active_inst_any (issuing).",
            f"source_hash = {kernel_source_hash()}"]
@@ -302,14 +312,14 @@ def summarize_profiles(out_dir):
             continue
         c = {k: med(v) for k, v in sq[name].items()}
         w = max(c.get("SQ_WAVES", 0.0), 1.0)
-        # waves per 64 instances: two for the tangent split over two waves
-        per = 2.0 if _short_kernel(name, topo).startswith(("k_fwd_dyn_jvp_split", "k_fwd_dyn_vjp_split")) else 1.0
+        per = _waves_per_tile(_short_kernel(name, topo))
         fb = med(fetch[name]["FETCH_SIZE"]) * 1024.0 * fscale
         wb = med(write[name]["WRITE_SIZE"]) * 1024.0 * wscale
-        out.append(f"kernel={key} flops_per_eval={c['SQ_INSTS_VALU_FLOPS_FP32'] * per / w:.0f} "
-                   f"valu_insts_per_wave={c['SQ_INSTS_VALU'] / w:.0f} waves={w:.0f} fetch_bytes={fb:.0f} "
-                   f"write_bytes={wb:.0f} wave_cycles={c['SQ_WAVE_CYCLES'] / w:.0f} wait_any={c['SQ_WAIT_ANY'] / w:.0f} "
-                   f"wait_inst_any={c['SQ_WAIT_INST_ANY'] / w:.0f} active_inst_any={c['SQ_ACTIVE_INST_ANY'] / w:.0f}")
+        for k in [key] + ([key.replace("fwd_dyn", "aba")] if "k_aba_team" in name else []):
+            out.append(f"kernel={k} flops_per_eval={c['SQ_INSTS_VALU_FLOPS_FP32'] * per / w:.0f} "
+                       f"valu_insts_per_wave={c['SQ_INSTS_VALU'] / w:.0f} waves={w:.0f} fetch_bytes={fb:.0f} "
+                       f"write_bytes={wb:.0f} wave_cycles={c['SQ_WAVE_CYCLES'] / w:.0f} wait_any={c['SQ_WAIT_ANY'] / w:.0f} "
+                       f"wait_inst_any={c['SQ_WAIT_INST_ANY'] / w:.0f} active_inst_any={c['SQ_ACTIVE_INST_ANY'] / w:.0f}")
     with open(COUNTERS_FILE, "w") as fh:
         fh.write("\n".join(out) + "\n")
     print("\n".join(out))
@@ -629,11 +639,11 @@ def main():
     cnt = read_counters()
     head = cnt.get("fwd_dyn_humanoid30", {})
     traffic = (head["fetch_bytes"] + head["write_bytes"]) if "fetch_bytes" in head else None
-    ceiling = rbd.fma_rate(256, 16)  # measured FMA issue ceiling at this launch shape
+    ceiling = rbd.fma_rate(1024, 16)  # measured FMA issue ceiling at this launch shape (four waves per 64 instances)
     exe = head.get("flops_per_eval")
     roofline = {"bound": "alu", "achieved": round(achieved, 2), "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(achieved / PEAK_FP32_TFLOPS, 4), "traffic": traffic,
-                "kernel": "k_fwd_dyn<humanoid30>", "kernel_ms": round(kernel_ms, 5),
+                "kernel": "k_aba_team<humanoid30>", "kernel_ms": round(kernel_ms, 5),
                 "flops_per_eval": per_eval,
                 "flops_source": "oracle count (FP64 counting scalar: state-dependent add/sub/mul, transforms shared "
                                 "by RNEA and CRBA, trivial operations not counted)",
@@ -724,7 +734,7 @@ def main():
         "warmup": args.warmup, "ms_per_step": ms_per_step, "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "f32", "data": "synthetic",
         "config": {"workload": "humanoid30 fwd_dyn: floating base + 29 revolute joints (35 DoF, 30 bodies), "
-                               "batch 65536 resident states, one instance per lane",
+                               "batch 65536 resident states",
                    "batch": BATCH, "nq": desc.nq, "nv": desc.nv, "parallelism": "none (1 GPU)"},
         "parity_max_rel_err_sample": max_rel,
         "fwd_dyn_graph_replay_us": round(graph_us, 2),

@@ -179,7 +179,9 @@ rbd_status rbd_crba(const rbd_model* model, int64_t batch, int64_t ld, const flo
 
 /* Forward dynamics, Eq. (2): qdd = M(q)^-1 (tau - h(q, qd) + sum_i J_i^T F_i),
  * f_ext as above (NULL: none). One fused kernel: bias force, mass matrix and
- * its branch-sparse L^T L factorisation never leave the lane. q: [nq][ld];
+ * its branch-sparse L^T L factorisation never leave the lane; for trees whose
+ * branches are shared out over several waves (more than 16 DoFs, see
+ * rbd_fwd_dyn_vjp) the articulated-body form, as rbd_aba runs it. q: [nq][ld];
  * qd, tau, qdd: [nv][ld]. */
 rbd_status rbd_fwd_dyn(const rbd_model* model, int64_t batch, int64_t ld, const float* q, const float* qd,
                        const float* tau, const float* f_ext, float* qdd, hipStream_t stream);
@@ -200,10 +202,10 @@ rbd_status rbd_aba(const rbd_model* model, int64_t batch, int64_t ld, const floa
  * f_ext (nullable: none; layout as for rbd_rnea). Computed as
  * M^-1 (dtau - dID/dq dq - dID/dqd dqd) at qdd = FD(q, qd, tau, F), with ID
  * including -sum_i J_i(q)^T F_i: the fused forward dynamics, a sweep of
- * tangent inverse dynamics, then a solve with M, all in one kernel (for a
- * tree of more than 16 DoFs at a batch of at most 32768, on two waves per 64
- * instances: one runs the first two sweeps while the other factors M, and
- * the right-hand side passes between them through LDS). With forces, a free
+ * tangent inverse dynamics, then a solve with M, all in one kernel (shared
+ * out over a team of waves, see rbd_fwd_dyn_vjp, each wave keeps its part of the
+ * factor for the second solve; else, for a tree of more than 16 DoFs at a batch
+ * of at most 32768, on two waves per 64 instances). With forces, a free
  * base's position tangent moves them relative to the robot. qdd (nullable)
  * also receives the forward dynamics. The forward dynamics may be kept in qdd
  * (or in dqdd) between the sweeps, so qdd and dqdd must not overlap
@@ -249,10 +251,14 @@ rbd_status rbd_rnea_vjp(const rbd_model* model, int64_t batch, int64_t ld, const
  * then an adjoint sweep of inverse dynamics; between the two the solutions
  * are kept in LDS (trees of more than 16 DoFs) or in the requested g_qd and
  * g_tau outputs, so the outputs must not overlap one another (RBD_E_INVAL).
- * For a tree of more than 16 DoFs at a batch of at most 32768 the two solves
- * run on two waves per 64 instances, each with its own factor, and meet in
- * LDS before the adjoint sweep (the environment variable RBD_VJP_SPLIT=0
- * turns this off, for measurement). */
+ * A tree of more than 16 DoFs whose branches balance is shared out over a team
+ * of up to four waves per 64 instances, each with its own branches, here and in
+ * the other operations (up to 24 DoFs here and in some others for batches of at
+ * most 81920; poses, Jacobians and mass matrices of any tree only for batches
+ * that leave part of the SIMDs idle). Any other tree of more than 16 DoFs runs
+ * the two solves on two waves per 64 instances at a batch of at most 32768, each
+ * with its own factor; they meet in LDS before the adjoint sweep (the environment
+ * variable RBD_VJP_SPLIT=0 turns this off, for measurement). */
 rbd_status rbd_fwd_dyn_vjp(const rbd_model* model, int64_t batch, int64_t ld, const float* q, const float* qd,
                            const float* tau, const float* f_ext, const float* g_qdd, float* g_q, float* g_qd,
                            float* g_tau, float* g_f_ext, hipStream_t stream);
