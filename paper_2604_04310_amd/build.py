@@ -33,17 +33,23 @@ DEVICE = ["--offload-arch=gfx950", "-ffp-contract=fast"]
 # installed with the library (the "_jit" cache beside librbd.so, built by
 # build()), so that their models load without compiling: a quadruped (free
 # trunk, four 3-joint legs), random depth-first trees of 9 and 20 bodies on a
-# fixed base and one of 40 bodies on a free base. Name: (floating, parents).
+# fixed base and one of 40 bodies on a free base, and three with several roots:
+# three 6-joint arms, four of 7 and 6 joints, a free body beside two.
+# Name: (floating, parents).
 PREBUILT = {
     "quadruped13f": (True, [-1, 0, 1, 2, 0, 4, 5, 0, 7, 8, 0, 10, 11]),
     "tree9": (False, [-1, 0, 1, 1, 3, 0, 5, 6, 7]),
     "tree20": (False, [-1, 0, 1, 0, 3, 4, 3, 6, 7, 8, 9, 7, 0, 12, 12, 14, 14, 0, 17, 18]),
     "tree40f": (True, [-1, 0, 1, 0, 0, 0, 0, 6, 7, 8, 9, 10, 9, 0, 13, 0, 15, 16, 0, 0, 0, 0, 21, 0, 23, 24, 25, 0,
                        27, 28, 29, 30, 31, 32, 29, 34, 27, 0, 37, 38]),
+    "arms18": (False, [-1, *range(5), -1, *range(6, 11), -1, *range(12, 17)]),
+    "arms25": (False, [-1, *range(6), -1, *range(7, 12), -1, *range(13, 18), -1, *range(19, 24)]),
+    "arms18f": (True, [-1, -1, *range(1, 6), -1, *range(7, 12)]),
 }
 # Controller kernels of frames other than the last body, installed the same
 # way: topology name (compiled or PREBUILT) -> frames.
-PREBUILT_FRAMES = {"humanoid30": [6, 22], "chain7": [3], "quadruped13f": [3]}
+PREBUILT_FRAMES = {"humanoid30": [6, 22], "chain7": [3], "quadruped13f": [3], "arms18": [5], "arms25": [6],
+                   "arms18f": [0, 6]}
 JIT_DIR = os.path.join(PKG, "_jit")
 N_KERNELS = 57  # RBD_N_KERNELS
 

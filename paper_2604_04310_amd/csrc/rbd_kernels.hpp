@@ -820,7 +820,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads, EXT ? 2 : 3) void k_aba_team(
     float* __restrict__ qdd) {
   if constexpr (Team<TP>::kOn) {
     static_assert(TeamLds<TP>::kAba <= kTeamRows);
-    __shared__ float lds_team[TeamLds<TP>::kAba * kTileLanes];
+    __shared__ float lds_team[team_lds(TeamLds<TP>::kAba)];
     team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       team_aba<TP, EXT, decltype(W_)::value>(tl, tab, SoaIo<TP>{ld}, lds_team, q, qd, tau, fext, ld, qdd);
     });
@@ -863,7 +863,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads) void k_rnea_team(
     float* __restrict__ tau) {
   if constexpr (Team<TP>::kOn) {
     static_assert(TeamLds<TP>::kId <= kTeamRows);
-    __shared__ float lds_team[TeamLds<TP>::kId * kTileLanes];
+    __shared__ float lds_team[team_lds(TeamLds<TP>::kId)];
     team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       team_rnea<TP, HAS_QDD, EXT, decltype(W_)::value>(tl, tab, SoaIo<TP>{ld}, lds_team, q, qd, qdd, fext, ld, tau);
     });
@@ -958,7 +958,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads, EXT ? 1 : 2) void k_fwd_dyn_vjp
     float* gtau, const float* __restrict__ fext, float* gfext) {
   if constexpr (Team<TP>::kOn) {
     static_assert(TeamLds<TP>::template vjp<EXT>() <= kTeamRows);
-    __shared__ float lds_team[TeamLds<TP>::template vjp<EXT>() * kTileLanes];
+    __shared__ float lds_team[team_lds(TeamLds<TP>::template vjp<EXT>())];
     team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       team_fwd_dyn_vjp<TP, EXT, decltype(W_)::value>(tl, tab, SoaIo<TP>{ld}, lds_team, q, qd, tau, gqdd, gq, gqd,
                                                      gtau, fext, gfext, ld);
@@ -985,7 +985,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads, EXT ? 1 : 2) void k_fwd_dyn_jvp
     // after the first solve its rows hold [qdd | what the tangent hands to the trunk]
     constexpr int kTan = NV + TROWS::total(), kRows = ROWS::total() > kTan ? ROWS::total() : kTan;
     static_assert((kRows + T) <= kTeamRows);
-    __shared__ float lds_team[(kRows + T) * kTileLanes];
+    __shared__ float lds_team[team_lds(kRows + T)];
     team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       constexpr int W = decltype(W_)::value;
       const LdsCol lds{lds_team + tl.lane}, xrow = lds.at(kRows), park = lds.at(tl.shift);
@@ -1127,7 +1127,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads) void k_crba_team(const float* _
     constexpr int N = TP::N, NV = TP::NV;
     using ROWS = TeamRows<TP, 10, false, 0>;
     static_assert(ROWS::total() <= kTeamRows);
-    __shared__ float lds_team[ROWS::total() * kTileLanes];
+    __shared__ float lds_team[team_lds(ROWS::total())];
     team_waves<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       constexpr int W = decltype(W_)::value;
       constexpr bool kOwner = W == TM::kOwner;
@@ -1205,7 +1205,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads) void k_rnea_jvp_team(
     constexpr int NQ = TP::NQ, NV = TP::NV;
     using ROWS = TeamRows<TP, 12, false, 0>;
     static_assert(ROWS::total() <= kTeamRows);
-    __shared__ float lds_team[ROWS::total() * kTileLanes];
+    __shared__ float lds_team[team_lds(ROWS::total())];
     team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       constexpr int W = decltype(W_)::value;
       const LdsCol lds{lds_team + tl.lane};
@@ -1252,7 +1252,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads) void k_rnea_vjp_team(
     constexpr int NQ = TP::NQ, NV = TP::NV;
     using ROWS = TeamRows<TP, EXT ? 30 : 18, false, 0>;
     static_assert(ROWS::total() <= kTeamRows);
-    __shared__ float lds_team[ROWS::total() * kTileLanes];
+    __shared__ float lds_team[team_lds(ROWS::total())];
     team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       constexpr int W = decltype(W_)::value;
       const LdsCol lds{lds_team + tl.lane};
@@ -1319,7 +1319,7 @@ __global__ __launch_bounds__(Team<TP>::kOn ? Team<TP>::kThreads : kBlock, Team<T
     using EROWS = OscRows<TP, E>;
     using MASK = OscRhs<TP, E>;
     static_assert((ROWS::total() + EROWS::total()) <= kTeamRows);
-    __shared__ float lds_team[(ROWS::total() + EROWS::total()) * kTileLanes];
+    __shared__ float lds_team[team_lds(ROWS::total() + EROWS::total())];
     team_waves<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       constexpr int W = decltype(W_)::value;
       constexpr bool kOwner = W == TM::kOwner, kTask = W == EROWS::kWave;
@@ -1403,8 +1403,10 @@ __global__ __launch_bounds__(Team<TP>::kOn ? Team<TP>::kThreads : kBlock, Team<T
         Ltl<TP, 7> Ft;
         team_fd_trunk<TP, 7, ROWS, MASK>(t, OscTrunkHook<TP, E, decltype(top)>{top, ex}, s, lds, Ft);
         chol6_solve(top.G, top.a, z);
+        if constexpr (EROWS::kWave >= 0) {
 #pragma unroll
-        for (int i = 0; i < 6; ++i) lds.put(i, z[i]);
+          for (int i = 0; i < 6; ++i) lds.put(i, z[i]);
+        }
         sfor<0, NV>([&](auto K_) __attribute__((always_inline)) {
           constexpr int K = decltype(K_)::value;
           if constexpr (TM::trunk(TP::body_of(K)) && TP::is_anc(TP::body_of(K), E))
@@ -1461,7 +1463,7 @@ __global__ __launch_bounds__((PackedShape<TP, OP>::kThreads), (PackedShape<TP, O
     using L = TeamLds<TP>;
     constexpr int kRows = OP == kOpFwdDyn ? L::kAba : (OP == kOpRnea ? L::kId : L::template vjp<false>());
     static_assert(kRows <= kTeamRows);
-    __shared__ float lds_team[kRows * kTileLanes];
+    __shared__ float lds_team[team_lds(kRows)];
     for (int t = blockIdx.x; t < n_tiles; t += gridDim.x) {
       const PackedReq& R = reqs[__builtin_amdgcn_readfirstlane(tile_req[t])];
       const float* const q = R.in[0];

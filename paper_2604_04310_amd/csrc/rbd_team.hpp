@@ -112,6 +112,10 @@ struct TrunkRows {
   }
 };
 
+// Floats of a block's LDS for a number of rows. One row at least: where every
+// branch hangs on the world nothing is handed over, and an array may not be empty.
+constexpr int team_lds(int rows) { return (rows > 0 ? rows : 1) * kTileLanes; }
+
 // A lane's column of a run of LDS rows.
 struct LdsCol {
   float* p;
@@ -1011,7 +1015,7 @@ struct OscHook {
     const float hb[6] = {s.f[0].f.x, s.f[0].f.y, s.f[0].f.z, s.f[0].n.x, s.f[0].n.y, s.f[0].n.z};
     b[0] = -kn * qd(k);
     tau(k, __builtin_fmaf(-kn, qd(k), hb[k]));
-    if constexpr (n > 1) {  // the base is on every path
+    if constexpr (n > 1 && TP::is_anc(0, E)) {  // (not where E's root stands beside the base)
       const int c = k % 3;
       const V3 ax = {A.a[c], A.a[3 + c], A.a[6 + c]};
       const V3 lin = k < 3 ? ax : cross(o, ax);
@@ -1070,7 +1074,7 @@ struct OscTrunkHook {
   template <class ST, int n>
   RBD_DI void base_sides(int k, const ST& s, float (&b)[n]) {
     h.base_sides(k, s, b);
-    share<true>(k, b);
+    share<TP::is_anc(0, E)>(k, b);
   }
   template <class J, class ST, class LF>
   RBD_DI void closed(J j, const ST& s, const LF& F) {
