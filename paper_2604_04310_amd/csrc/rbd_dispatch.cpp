@@ -153,7 +153,8 @@ static inline bool teamed_store(const rbd_model* m, int64_t batch, int eighths) 
   return m->team.waves > 1 && batch <= kOneWavePerSimd / 8 * eighths;
 }
 static inline Shape team_shape(const rbd_model* m, int64_t batch) {
-  return {dim3((unsigned)((batch + kTileLanes - 1) / kTileLanes)), dim3((unsigned)(m->team.waves * kTileLanes))};
+  const TeamGrid g = team_grid(batch, m->team.waves);
+  return {dim3(g.x, g.y), dim3((unsigned)(m->team.waves * kTileLanes))};
 }
 
 // Launches kernel `id` of the model's set; args point to the kernel's
@@ -396,7 +397,10 @@ rbd_status launch_packed(const rbd_model* m, int op, const void* d_table, int gr
   void* a[] = {&tab, &t};
   // `grid` blocks of kBlock lanes stride over the tiles, or as many teams
   Shape sh{dim3((unsigned)grid), dim3(kBlock)};
-  if (m->team.waves > 1) sh = team_shape(m, (int64_t)grid * kBlock);
+  if (m->team.waves > 1) {
+    sh = team_shape(m, (int64_t)grid * kBlock);
+    sh.grid.y = 1;  // (one row: its blocks stride over all tiles)
+  }
   return launch(m, id, sh, a, s, "packed launch");
 }
 

@@ -821,7 +821,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads, EXT ? 2 : 3) void k_aba_team(
   if constexpr (Team<TP>::kOn) {
     static_assert(TeamLds<TP>::kAba <= kTeamRows);
     __shared__ float lds_team[team_lds(TeamLds<TP>::kAba)];
-    team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
+    team_roles<TP>(team_first(), batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       team_aba<TP, EXT, decltype(W_)::value>(tl, tab, SoaIo<TP>{ld}, lds_team, q, qd, tau, fext, ld, qdd);
     });
   }
@@ -864,7 +864,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads) void k_rnea_team(
   if constexpr (Team<TP>::kOn) {
     static_assert(TeamLds<TP>::kId <= kTeamRows);
     __shared__ float lds_team[team_lds(TeamLds<TP>::kId)];
-    team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
+    team_roles<TP>(team_first(), batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       team_rnea<TP, HAS_QDD, EXT, decltype(W_)::value>(tl, tab, SoaIo<TP>{ld}, lds_team, q, qd, qdd, fext, ld, tau);
     });
   }
@@ -959,7 +959,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads, EXT ? 1 : 2) void k_fwd_dyn_vjp
   if constexpr (Team<TP>::kOn) {
     static_assert(TeamLds<TP>::template vjp<EXT>() <= kTeamRows);
     __shared__ float lds_team[team_lds(TeamLds<TP>::template vjp<EXT>())];
-    team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
+    team_roles<TP>(team_first(), batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       team_fwd_dyn_vjp<TP, EXT, decltype(W_)::value>(tl, tab, SoaIo<TP>{ld}, lds_team, q, qd, tau, gqdd, gq, gqd,
                                                      gtau, fext, gfext, ld);
     });
@@ -986,7 +986,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads, EXT ? 1 : 2) void k_fwd_dyn_jvp
     constexpr int kTan = NV + TROWS::total(), kRows = ROWS::total() > kTan ? ROWS::total() : kTan;
     static_assert((kRows + T) <= kTeamRows);
     __shared__ float lds_team[team_lds(kRows + T)];
-    team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
+    team_roles<TP>(team_first(), batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       constexpr int W = decltype(W_)::value;
       const LdsCol lds{lds_team + tl.lane}, xrow = lds.at(kRows), park = lds.at(tl.shift);
       const uint32_t b = tl.b;
@@ -1068,7 +1068,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads) void k_fk_team(const float* __r
                                                                float* __restrict__ T) {
   using TM = Team<TP>;
   if constexpr (TM::kOn) {
-    team_waves<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
+    team_waves<TP>(team_first(), batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       constexpr int W = decltype(W_)::value;
       constexpr bool kOwner = W == TM::kOwner;
       M3 Rw[TP::N];
@@ -1095,7 +1095,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads) void k_jacobian_team(const floa
                                                                      JacSlots js, float* __restrict__ J) {
   using TM = Team<TP>;
   if constexpr (TM::kOn) {
-    team_waves<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
+    team_waves<TP>(team_first(), batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       constexpr int W = decltype(W_)::value;
       constexpr bool kOwner = W == TM::kOwner;
       M3 Rw[TP::N];
@@ -1128,7 +1128,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads) void k_crba_team(const float* _
     using ROWS = TeamRows<TP, 10, false, 0>;
     static_assert(ROWS::total() <= kTeamRows);
     __shared__ float lds_team[team_lds(ROWS::total())];
-    team_waves<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
+    team_waves<TP>(team_first(), batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       constexpr int W = decltype(W_)::value;
       constexpr bool kOwner = W == TM::kOwner;
       const LdsCol lds{lds_team + tl.lane}, c = lds.at(ROWS::base(W));
@@ -1206,7 +1206,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads) void k_rnea_jvp_team(
     using ROWS = TeamRows<TP, 12, false, 0>;
     static_assert(ROWS::total() <= kTeamRows);
     __shared__ float lds_team[team_lds(ROWS::total())];
-    team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
+    team_roles<TP>(team_first(), batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       constexpr int W = decltype(W_)::value;
       const LdsCol lds{lds_team + tl.lane};
       const uint32_t b = tl.b;
@@ -1253,7 +1253,7 @@ __global__ __launch_bounds__(Team<TP>::kThreads) void k_rnea_vjp_team(
     using ROWS = TeamRows<TP, EXT ? 30 : 18, false, 0>;
     static_assert(ROWS::total() <= kTeamRows);
     __shared__ float lds_team[team_lds(ROWS::total())];
-    team_roles<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
+    team_roles<TP>(team_first(), batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       constexpr int W = decltype(W_)::value;
       const LdsCol lds{lds_team + tl.lane};
       const uint32_t b = tl.b;
@@ -1320,7 +1320,7 @@ __global__ __launch_bounds__(Team<TP>::kOn ? Team<TP>::kThreads : kBlock, Team<T
     using MASK = OscRhs<TP, E>;
     static_assert((ROWS::total() + EROWS::total()) <= kTeamRows);
     __shared__ float lds_team[team_lds(ROWS::total() + EROWS::total())];
-    team_waves<TP>(blockIdx.x * kTileLanes, batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
+    team_waves<TP>(team_first(), batch, [&](auto W_, const TeamLane& tl) __attribute__((always_inline)) {
       constexpr int W = decltype(W_)::value;
       constexpr bool kOwner = W == TM::kOwner, kTask = W == EROWS::kWave;
       const LdsCol lds{lds_team + tl.lane}, ex = lds.at(ROWS::total());

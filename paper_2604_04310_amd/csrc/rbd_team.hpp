@@ -150,6 +150,9 @@ struct TeamLane {
   uint32_t b;     // the lane's instance; lanes past the batch redo the last one
 };
 
+// The first instance of the calling block (see team_grid).
+RBD_DI uint32_t team_first() { return (blockIdx.y * kTeamRowBlocks + blockIdx.x) * kTileLanes; }
+
 // Calls body(ic<W>, TeamLane) with W the role of the calling wave, for the 64
 // instances from `first` of `batch`. The branch is the same for a whole wave,
 // and every wave meets the barriers inside.

@@ -170,4 +170,17 @@ constexpr TeamPlan team_plan(bool floating, int n, const int* parent) {
   return best;
 }
 
+// The grid of a team kernel, one block of waves * 64 lanes per 64 instances. A
+// launch holds less than 2^32 lanes along an axis, which four waves reach at the
+// largest batch (2^30: 2^24 blocks): that one goes out as two rows of blocks.
+constexpr unsigned kTeamRowBlocks = 1u << 23;
+struct TeamGrid {
+  unsigned x, y;
+};
+constexpr TeamGrid team_grid(long long batch, int waves) {
+  const unsigned long long blocks = (unsigned long long)(batch + 63) / 64;
+  if (blocks * waves * 64 < (1ull << 32)) return {(unsigned)blocks, 1};
+  return {kTeamRowBlocks, (unsigned)((blocks + kTeamRowBlocks - 1) / kTeamRowBlocks)};
+}
+
 }  // namespace rbd
