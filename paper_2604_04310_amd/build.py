@@ -48,7 +48,7 @@ PREBUILT = {
 }
 # Controller kernels of frames other than the last body, installed the same
 # way: topology name (compiled or PREBUILT) -> frames.
-PREBUILT_FRAMES = {"humanoid30": [6, 22], "chain7": [3], "quadruped13f": [3], "arms18": [5], "arms25": [6],
+PREBUILT_FRAMES = {"humanoid30": [0, 6, 15, 22], "chain7": [3], "quadruped13f": [3], "arms18": [5], "arms25": [6],
                    "arms18f": [0, 6]}
 JIT_DIR = os.path.join(PKG, "_jit")
 N_KERNELS = 57  # RBD_N_KERNELS
