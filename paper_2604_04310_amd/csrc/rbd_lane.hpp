@@ -366,18 +366,27 @@ RBD_DI M3 quat_rot(float w, float x, float y, float z) {
 // of being held in registers across all of them.
 // The asm operand keeps the pointer's address space (global for inputs,
 // constant for the model table), so loads through the copy stay global loads
-// with a scalar base, and table reads stay scalar loads.
+// with a scalar base, and table reads stay scalar loads. It is read through
+// readfirstlane, which costs nothing for a value in scalar registers: a uniform
+// pointer that the compiler has computed in vector registers (a team's moved
+// table, in some trees) cannot be an operand by itself, and compilation ended
+// the process ("illegal VGPR to SGPR copy").
+RBD_DI uint64_t scalar64(uint64_t x) {
+  return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32 |
+         (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+}
 RBD_DI const float* opaque(const float* p) {
-  auto g = (const __attribute__((address_space(1))) float*)p;
+  auto g = (const __attribute__((address_space(1))) float*)scalar64((uint64_t)p);
   asm volatile("" : "+s"(g));
   return (const float*)g;
 }
 RBD_DI const float* opaque_table(const float* p) {
-  auto c = (const __attribute__((address_space(4))) float*)p;
+  auto c = (const __attribute__((address_space(4))) float*)scalar64((uint64_t)p);
   asm volatile("" : "+s"(c));
   return (const float*)c;
 }
 RBD_DI int64_t opaque(int64_t x) {
+  x = (int64_t)scalar64((uint64_t)x);
   asm volatile("" : "+s"(x));
   return x;
 }
