@@ -2149,7 +2149,8 @@ RBD_DI void osc_sweep_task(const float* __restrict__ t, const QI& q, const float
         cols[c + 3][3] = ax.x; cols[c + 3][4] = ax.y; cols[c + 3][5] = ax.z;
       }
       ltl_base_rows<TP, 6>(F, Ic[J], [&](int r, int K) __attribute__((always_inline)) { return cols[K][r]; }, MK{});
-      sfor<0, 6>([&](auto K_) __attribute__((always_inline)) { accumulate(K_); });
+      // (not where E's root stands beside the base: its right-hand sides are masked out)
+      if constexpr (kPath) sfor<0, 6>([&](auto K_) __attribute__((always_inline)) { accumulate(K_); });
     } else {
       constexpr int k = TP::vofs(J);
       float Mr[NV > 1 ? NV : 1];

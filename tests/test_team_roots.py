@@ -112,15 +112,9 @@ def test_served_and_packed(rbd, name):
             check(op, [x.double().cpu().numpy() for x in outs], ref)
 
 
-@pytest.mark.gpu
-@pytest.mark.parametrize("batch", [1, 65])
-@pytest.mark.parametrize("name,frame", [("arms18", 5), ("arms18", 17), ("arms25", 6), ("arms25", 24),
-                                        ("arms18f", 0), ("arms18f", 6), ("arms18f", 12)])
-def test_osc(rbd, name, frame, batch):
-    """Frames at the end of an arm and on a free body that carries nothing."""
+def check_osc(rbd, desc, frame, batch):
     import torch
     from tests.test_gpu_controllers import KD, KN, KP, floor_osc, within_bar
-    desc = desc_of(name)
     m = rbd.Model(desc, 0)
     st = W.states(desc, batch, 880 + frame)
     tgt = W._f32(targets_near(O.fk(desc, st.q)[:, frame], 881 + frame))
@@ -130,3 +124,18 @@ def test_osc(rbd, name, frame, batch):
     torch.cuda.synchronize()
     ref = CT.osc(desc, st.q, st.qd, frame, tgt, KP, KD, KN)
     assert within_bar(tau.double().cpu().numpy().T, ref, floor_osc(desc, st.q, frame, ref)) < 1.0
+
+
+@pytest.mark.gpu
+def test_osc_beside_a_free_body(rbd):
+    """A small tree (one instance per lane): the frame's root stands beside the free base."""
+    check_osc(rbd, W.random_tree([-1, -1, 1, 2, 3, 4, 5], True, 865, rotated=True), 6, 65)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("batch", [1, 65])
+@pytest.mark.parametrize("name,frame", [("arms18", 5), ("arms18", 17), ("arms25", 6), ("arms25", 24),
+                                        ("arms18f", 0), ("arms18f", 6), ("arms18f", 12)])
+def test_osc(rbd, name, frame, batch):
+    """Frames at the end of an arm and on a free body that carries nothing."""
+    check_osc(rbd, desc_of(name), frame, batch)
