@@ -179,8 +179,8 @@ rbd_status rbd_crba(const rbd_model* model, int64_t batch, int64_t ld, const flo
 
 /* Forward dynamics, Eq. (2): qdd = M(q)^-1 (tau - h(q, qd) + sum_i J_i^T F_i),
  * f_ext as above (NULL: none). One fused kernel: bias force, mass matrix and
- * its branch-sparse L^T L factorisation never leave the lane; for trees whose
- * branches are shared out over several waves (more than 16 DoFs, see
+ * its branch-sparse L^T L factorisation never leave the lane; where the branches
+ * are shared out over several waves (trees of more than 16 DoFs, see
  * rbd_fwd_dyn_vjp) the articulated-body form, as rbd_aba runs it. q: [nq][ld];
  * qd, tau, qdd: [nv][ld]. */
 rbd_status rbd_fwd_dyn(const rbd_model* model, int64_t batch, int64_t ld, const float* q, const float* qd,
@@ -251,14 +251,16 @@ rbd_status rbd_rnea_vjp(const rbd_model* model, int64_t batch, int64_t ld, const
  * then an adjoint sweep of inverse dynamics; between the two the solutions
  * are kept in LDS (trees of more than 16 DoFs) or in the requested g_qd and
  * g_tau outputs, so the outputs must not overlap one another (RBD_E_INVAL).
- * A tree of more than 16 DoFs whose branches balance is shared out over a team
- * of up to four waves per 64 instances, each with its own branches, here and in
- * the other operations (up to 24 DoFs here and in some others for batches of at
- * most 81920; poses, Jacobians and mass matrices of any tree only for batches
- * that leave part of the SIMDs idle). Any other tree of more than 16 DoFs runs
- * the two solves on two waves per 64 instances at a batch of at most 32768, each
- * with its own factor; they meet in LDS before the adjoint sweep (the environment
- * variable RBD_VJP_SPLIT=0 turns this off, for measurement). */
+ * A tree of more than 16 DoFs whose branches can be shared out is worked on by a
+ * team of up to four waves per 64 instances, each with its own branches, here and
+ * in the other operations, up to a batch that depends on the operation and on how
+ * evenly the branches share out the work: 16384 or 32768 for uneven trees, 81920
+ * or 98304 for some operations of even ones, every batch for the rest (poses,
+ * Jacobians and mass matrices of any tree only for batches that leave part of the
+ * SIMDs idle). Otherwise a tree of more than 16 DoFs runs the two solves on two
+ * waves per 64 instances at a batch of at most 32768, each with its own factor;
+ * they meet in LDS before the adjoint sweep (the environment variable
+ * RBD_VJP_SPLIT=0 turns this off, for measurement). */
 rbd_status rbd_fwd_dyn_vjp(const rbd_model* model, int64_t batch, int64_t ld, const float* q, const float* qd,
                            const float* tau, const float* f_ext, const float* g_qdd, float* g_q, float* g_qd,
                            float* g_tau, float* g_f_ext, hipStream_t stream);

@@ -110,7 +110,6 @@ static inline unsigned grid_for(int64_t batch) { return (unsigned)((batch + kBlo
 // CU (the humanoid's VJP and JVP at batch 32768 measured 3-5 % faster; at
 // 65536 the two shapes are equal). Larger batches keep 256-lane blocks, which
 // are as fast or faster there.
-constexpr int64_t kOneWavePerSimd = 256 * 4 * 64;
 struct Shape {
   dim3 grid, block;
   unsigned lds = 0;  // dynamic LDS bytes per block
@@ -125,23 +124,10 @@ static inline Shape plain_shape(int64_t batch) { return {dim3(grid_for(batch)), 
 // (scalar-base addressing is chosen in the kernels themselves).
 static inline bool large(const rbd_model* m) { return m->nv > 16; }
 
-// Whether the model's tree is shared out over a team of waves: above
-// kTeamAlwaysDofs at every batch, below it up to the batch where one instance
-// per lane catches up. Quadruped (18 DoFs), team against one lane, in us:
-//                    65600      98304      131072     262144
-//   forward dynamics 13.3/14.7  16.3/15.5  20.4/16.3  37.0/31.0   (14.1/15.5 at 81920)
-//     with forces    16.1/28.0  20.0/30.4  24.9/32.4  45.2/58.1
-//   its adjoint      23.8/31.9  28.5/33.7  36.6/34.3  66.1/64.8
-//   its tangent      22.6/37.1  27.3/43.9  35.0/47.8  65.8/82.5
-//   inverse dynamics  8.6/8.3    8.9/8.7    9.4/9.4   17.7/18.0
-//     its adjoint    13.7/19.3  18.5/22.4  22.4/24.4  38.4/44.1
-//     its tangent    12.9/14.9  16.9/19.6  20.7/22.0  37.1/35.7
-// so forward dynamics with forces, its tangent and the adjoint of inverse
-// dynamics are shared out at every batch, the others up to 81920.
-static inline bool teamed(const rbd_model* m, int64_t batch) {
-  return m->team.waves > 1 && (m->nv > kTeamAlwaysDofs || batch <= kOneWavePerSimd * 5 / 4);
+// Whether the model's tree is shared out over a team of waves at this batch.
+static inline bool teamed(const rbd_model* m, int64_t batch, TeamOp op) {
+  return batch <= team_limit(m->team, m->nv, op);
 }
-static inline bool teamed_always(const rbd_model* m) { return m->team.waves > 1; }
 // The operations that mostly write: one instance per lane reaches the memory's
 // rate once the batch fills the SIMDs, and writes longer runs of a row at a
 // time than the waves of a team. Team against one lane, in us: poses of the
@@ -217,7 +203,7 @@ rbd_status launch_rnea(const rbd_model* m, int64_t batch, int64_t ld, const floa
   else id = qdd ? KID_RNEA : KID_RNEA_BIAS;
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &qd, &qdd, &fext, &tau};
-  if (teamed(m, batch)) {
+  if (teamed(m, batch, TeamOp::kId)) {
     id = fext ? (qdd ? KID_RNEA_EXT_TEAM : KID_RNEA_BIAS_EXT_TEAM) : (qdd ? KID_RNEA_TEAM : KID_RNEA_BIAS_TEAM);
     return launch(m, id, team_shape(m, batch), a, s, "rbd_rnea");
   }
@@ -240,7 +226,7 @@ rbd_status launch_fwd_dyn(const rbd_model* m, int64_t batch, int64_t ld, const f
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &qd, &tau, &fext, &qdd};
   // (a team runs the articulated-body form: faster and more accurate there, see team_aba)
-  if (fext ? teamed_always(m) : teamed(m, batch))
+  if (teamed(m, batch, fext ? TeamOp::kFdExt : TeamOp::kFd))
     return launch(m, fext ? KID_ABA_EXT_TEAM : KID_ABA_TEAM, team_shape(m, batch), a, s, "rbd_fwd_dyn");
   return launch(m, id, heavy_shape(batch), a, s, "rbd_fwd_dyn");
 }
@@ -254,7 +240,7 @@ rbd_status launch_aba(const rbd_model* m, int64_t batch, int64_t ld, const float
   const KernelId id = fext ? (pre ? KID_ABA_PRE_EXT : KID_ABA_EXT) : (pre ? KID_ABA_PRE : KID_ABA);
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &qd, &tau, &fext, &qdd};
-  if (fext ? teamed_always(m) : teamed(m, batch))
+  if (teamed(m, batch, fext ? TeamOp::kFdExt : TeamOp::kFd))
     return launch(m, fext ? KID_ABA_EXT_TEAM : KID_ABA_TEAM, team_shape(m, batch), a, s, "rbd_aba");
   return launch(m, id, heavy_shape(batch), a, s, "rbd_aba");
 }
@@ -266,9 +252,9 @@ rbd_status launch_fwd_dyn_jvp(const rbd_model* m, int64_t batch, int64_t ld, con
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &qd, &tau, &dq, &dqd, &dtau, &qdd, &dqdd, &fext, &dfext};
   const bool ext = fext || dfext;
-  if (teamed_always(m))
+  if (teamed(m, batch, TeamOp::kJvp))
     return launch(m, ext ? KID_JVP_EXT_TEAM : KID_JVP_TEAM, team_shape(m, batch), a, s, "rbd_fwd_dyn_jvp");
-  if (large(m) && batch <= kOneWavePerSimd / 2) {
+  if (large(m) && batch <= kHalfWavePerSimd) {
     // two waves per 64 instances: the factor of M on its own wave, in
     // parallel with the solve for qdd and the tangent
     const Shape sh{dim3((unsigned)((batch + kTileLanes - 1) / kTileLanes)), dim3(2 * kTileLanes),
@@ -285,7 +271,7 @@ rbd_status launch_rnea_jvp(const rbd_model* m, int64_t batch, int64_t ld, const 
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &qd, &qdd, &dq, &dqd, &dqdd, &dtau, &fext, &dfext};
   const bool ext = fext || dfext;
-  if (teamed(m, batch))
+  if (teamed(m, batch, ext ? TeamOp::kIdJvpExt : TeamOp::kIdJvp))
     return launch(m, ext ? KID_RNEA_JVP_EXT_TEAM : KID_RNEA_JVP_TEAM, team_shape(m, batch), a, s, "rbd_rnea_jvp");
   const KernelId id = ext ? KID_RNEA_JVP_EXT : (preload_inputs(large(m)) ? KID_RNEA_JVP_PRE : KID_RNEA_JVP);
   return launch(m, id, heavy_shape(batch), a, s, "rbd_rnea_jvp");
@@ -299,7 +285,7 @@ rbd_status launch_rnea_vjp(const rbd_model* m, int64_t batch, int64_t ld, const 
   const bool ext = gfext || (fext && gq);
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &qd, &qdd, &lam, &gq, &gqd, &gqdd, &fext, &gfext};
-  if (teamed_always(m))
+  if (teamed(m, batch, ext ? TeamOp::kIdVjpExt : TeamOp::kIdVjp))
     return launch(m, ext ? KID_RNEA_VJP_EXT_TEAM : KID_RNEA_VJP_TEAM, team_shape(m, batch), a, s, "rbd_rnea_vjp");
   return launch(m, ext ? KID_RNEA_VJP_EXT : KID_RNEA_VJP, heavy_shape(batch), a, s, "rbd_rnea_vjp");
 }
@@ -349,12 +335,12 @@ rbd_status launch_fwd_dyn_vjp(const rbd_model* m, int64_t batch, int64_t ld, con
   const bool ext = gfext || (fext && (gq || gqd));
   const float* tab = m->d_tab;
   void* a[] = {&tab, &batch, &ld, &q, &qd, &tau, &gqdd, &gq, &gqd, &gtau, &fext, &gfext};
-  if (teamed(m, batch) && (gq || gqd || gfext))
+  if (teamed(m, batch, ext ? TeamOp::kVjpExt : TeamOp::kVjp) && (gq || gqd || gfext))
     return launch(m, ext ? KID_VJP_EXT_TEAM : KID_VJP_TEAM, team_shape(m, batch), a, s, "rbd_fwd_dyn_vjp");
   if (large(m) && (gq || gqd || gfext)) {
     const unsigned grid = (unsigned)((batch + kTileLanes - 1) / kTileLanes);
     const unsigned lds = (unsigned)(2 * m->nv * kTileLanes * sizeof(float));
-    if (batch <= kOneWavePerSimd / 2 && split_adjoint()) {
+    if (batch <= kHalfWavePerSimd && split_adjoint()) {
       // two waves per 64 instances: lam = M^-1 g_qdd on its own wave, in
       // parallel with the solve for qdd
       return launch(m, ext ? KID_VJP_EXT_SPLIT : KID_VJP_SPLIT, Shape{dim3(grid), dim3(2 * kTileLanes), lds}, a, s,

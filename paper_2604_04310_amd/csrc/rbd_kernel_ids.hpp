@@ -7,7 +7,7 @@
 // launches; 3 the adjoint and its packed launch; 4 the articulated-body
 // algorithm; 5 the external-force variants; 6 the forward-mode derivative;
 // 7 the controllers; 8 the derivatives with external forces;
-// 9 to 11 the kernels of a team of waves (dynamics; derivatives; the rest).
+// 9 to 12 the kernels of a team of waves (dynamics; adjoint; tangent; the rest).
 #pragma once
 
 #define RBD_KERNELS(X)                                    \

@@ -78,9 +78,11 @@ RBD_DI void preload_inputs(float (&x)[n], float (&y)[n], const A& a, const B& b)
   });
 }
 
-// Where a tree runs an operation as a team at every batch (Team::kAlways; for
-// some operations every tree that has a team, Team::kOn), the kernel of the
-// operation below is never launched and left empty.
+// Where a tree runs an operation as a team at every batch (or, for the kernels
+// of two waves per 64 instances, at every batch that they would run), the kernel
+// of the operation below is never launched and left empty.
+template <class TP, TeamOp OP, long long BATCH = kTeamEvery>
+inline constexpr bool kLanes = Team<TP>::template kLimit<OP> < BATCH;
 
 template <class TP>
 __global__ __launch_bounds__(kBlock) void k_fk(const float* __restrict__ tab, int64_t batch, int64_t ld,
@@ -104,12 +106,15 @@ __global__ __launch_bounds__(kBlock) void k_jacobian(const float* __restrict__ t
 // EXT: per-body external forces (fext, [6 n][ld]) enter the force balance.
 // PRE (no external forces): every input load is issued at entry, as in
 // k_fwd_dyn.
+// Two waves per SIMD for branched trees up to 36 DoFs, where the sweep comes near
+// the 256 registers that leaves them (31 bodies: 259 of its own accord, then 45 us
+// at batch 131072; 231 without a spill when told so; a chain of 36 would spill).
 template <class TP, bool HAS_QDD, bool EXT, bool PRE = false>
-__global__ __launch_bounds__(kBlock) void k_rnea(const float* __restrict__ tab, int64_t batch, int64_t ld,
-                                                 const float* __restrict__ q, const float* __restrict__ qd,
-                                                 const float* __restrict__ qdd, const float* __restrict__ fext,
-                                                 float* __restrict__ tau) {
-  if constexpr (!Team<TP>::kAlways) {
+__global__ __launch_bounds__(kBlock, (!EXT && Team<TP>::kOn && TP::NV <= 36 ? 2 : 1)) void k_rnea(
+    const float* __restrict__ tab, int64_t batch, int64_t ld, const float* __restrict__ q,
+    const float* __restrict__ qd, const float* __restrict__ qdd, const float* __restrict__ fext,
+    float* __restrict__ tau) {
+  if constexpr (kLanes<TP, TeamOp::kId>) {
     const uint32_t b = lane_id();
     if (b >= batch) return;
     if constexpr (PRE && !EXT) {
@@ -166,7 +171,7 @@ __global__ __launch_bounds__(kBlock) void k_fwd_dyn(const float* __restrict__ ta
                                                     const float* __restrict__ q, const float* __restrict__ qd,
                                                     const float* __restrict__ tau, const float* __restrict__ fext,
                                                     float* __restrict__ qdd) {
-  if constexpr (!(EXT ? Team<TP>::kOn : Team<TP>::kAlways)) {
+  if constexpr (kLanes<TP, EXT ? TeamOp::kFdExt : TeamOp::kFd>) {
     const uint32_t b = lane_id();
     if (b >= batch) return;
     const auto fx = fext_view<EXT>(fext, ld, b);
@@ -195,7 +200,7 @@ __global__ __launch_bounds__(kBlock) void k_aba(const float* __restrict__ tab, i
                                                 const float* __restrict__ q, const float* __restrict__ qd,
                                                 const float* __restrict__ tau, const float* __restrict__ fext,
                                                 float* __restrict__ qdd) {
-  if constexpr (!(EXT ? Team<TP>::kOn : Team<TP>::kAlways)) {
+  if constexpr (kLanes<TP, EXT ? TeamOp::kFdExt : TeamOp::kFd>) {
     const uint32_t b = lane_id();
     if (b >= batch) return;
     const auto fx = fext_view<EXT>(fext, ld, b);
@@ -301,13 +306,15 @@ struct RowAlias {
 // memory, 2 NV floats per lane), the adjoint on fresh views. EXT (modes 1 to
 // 3): external forces fext (nullable: zero) in the dynamics and the force
 // cotangent g_fext (nullable).
+// Two waves per SIMD for branched trees of 17 and 18 DoFs, where the two sweeps
+// come near the 256 registers that leaves them (18 DoFs: 256 and 265 of their own
+// accord, and with 265 45.1 us at batch 98304 against 36.4).
 template <class TP, int MODE, bool EXT = false>
-__global__ __launch_bounds__(kBlock) void k_fwd_dyn_vjp(const float* __restrict__ tab, int64_t batch, int64_t ld,
-                                                        const float* __restrict__ q, const float* __restrict__ qd,
-                                                        const float* __restrict__ tau,
-                                                        const float* __restrict__ gqdd, float* gq, float* gqd,
-                                                        float* gtau, const float* __restrict__ fext, float* gfext) {
-  if constexpr (MODE == 0 || !Team<TP>::kAlways) {
+__global__ __launch_bounds__(kBlock, (!EXT && MODE == 3 && Team<TP>::kOn && TP::NV <= 18 ? 2 : 1)) void k_fwd_dyn_vjp(
+    const float* __restrict__ tab, int64_t batch, int64_t ld, const float* __restrict__ q,
+    const float* __restrict__ qd, const float* __restrict__ tau, const float* __restrict__ gqdd, float* gq, float* gqd,
+    float* gtau, const float* __restrict__ fext, float* gfext) {
+  if constexpr (MODE == 0 || kLanes<TP, EXT ? TeamOp::kVjpExt : TeamOp::kVjp>) {
     static_assert(!EXT || MODE >= 1, "external forces: modes 1 to 3");
     RBD_LANE_IO(TP);
     const uint32_t b = lane_id();
@@ -372,7 +379,7 @@ __global__ __launch_bounds__(2 * kTileLanes) void k_fwd_dyn_vjp_split(
     const float* __restrict__ tab, int64_t batch, int64_t ld, const float* __restrict__ q,
     const float* __restrict__ qd, const float* __restrict__ tau, const float* __restrict__ gqdd, float* gq,
     float* gqd, float* gtau, const float* __restrict__ fext, float* gfext) {
-  if constexpr (!Team<TP>::kOn) {
+  if constexpr (kLanes<TP, EXT ? TeamOp::kVjpExt : TeamOp::kVjp, kHalfWavePerSimd>) {
     RBD_LANE_IO(TP);
     constexpr int NQ = TP::NQ, NV = TP::NV;
     extern __shared__ float lds_vjp[];
@@ -441,7 +448,7 @@ __global__ __launch_bounds__(kBlock) void k_fwd_dyn_jvp(const float* __restrict_
                                                         const float* __restrict__ dtau, float* qdd, float* dqdd,
                                                         const float* __restrict__ fext,
                                                         const float* __restrict__ dfext) {
-  if constexpr (!Team<TP>::kOn) {
+  if constexpr (kLanes<TP, TeamOp::kJvp>) {
     RBD_LANE_IO(TP);
     const uint32_t b = lane_id();
     if (b >= batch) return;
@@ -500,7 +507,7 @@ __global__ __launch_bounds__(2 * kTileLanes) void k_fwd_dyn_jvp_split(
     const float* __restrict__ qd, const float* __restrict__ tau, const float* __restrict__ dq,
     const float* __restrict__ dqd, const float* __restrict__ dtau, float* qdd, float* dqdd,
     const float* __restrict__ fext, const float* __restrict__ dfext) {
-  if constexpr (!Team<TP>::kOn) {
+  if constexpr (kLanes<TP, TeamOp::kJvp, kHalfWavePerSimd>) {
     RBD_LANE_IO(TP);
     constexpr int NV = TP::NV;
     extern __shared__ float lds_jvp[];
@@ -576,7 +583,7 @@ __global__ __launch_bounds__(kBlock) void k_rnea_jvp(const float* __restrict__ t
                                                      const float* __restrict__ dqd, const float* __restrict__ dqdd,
                                                      float* __restrict__ dtau, const float* __restrict__ fext,
                                                      const float* __restrict__ dfext) {
-  if constexpr (!Team<TP>::kAlways) {
+  if constexpr (kLanes<TP, EXT ? TeamOp::kIdJvpExt : TeamOp::kIdJvp>) {
     RBD_LANE_IO(TP);
     const uint32_t b = lane_id();
     if (b >= batch) return;
@@ -620,7 +627,7 @@ __global__ __launch_bounds__(kBlock) void k_rnea_vjp(const float* __restrict__ t
                                                      float* __restrict__ gq, float* __restrict__ gqd,
                                                      float* __restrict__ gqdd, const float* __restrict__ fext,
                                                      float* __restrict__ gfext) {
-  if constexpr (!Team<TP>::kOn) {
+  if constexpr (kLanes<TP, EXT ? TeamOp::kIdVjpExt : TeamOp::kIdVjp>) {
     RBD_LANE_IO(TP);
     const uint32_t b = lane_id();
     if (b >= batch) return;
@@ -770,8 +777,9 @@ struct TeamLds {
 
 // Forward dynamics of the calling wave's 64 instances, by the articulated-body
 // algorithm for either entry point: branches up, the trunk up and down, branches
-// down. Shared out over a team it needs a third of the L^T L form's hand-over
-// (27 rows of LDS per trunk body against 16 and the trunk's rows of the factor)
+// down. Shared out over a team it needs half of the L^T L form's hand-over
+// (27 rows of LDS per trunk body that carries branches against 16 and the trunk's
+// rows of the factor: 108 against 226 for the humanoid)
 // and few enough registers (168) for three waves per SIMD, and it is the more
 // accurate of the two (humanoid: 1.7e-7 against 1.0e-6 in the Frobenius norm,
 // 2.5e-7 against 5.7e-7 with contact forces). Bound: the longest branch's and
@@ -1448,7 +1456,8 @@ __global__ __launch_bounds__(Team<TP>::kOn ? Team<TP>::kThreads : kBlock, Team<T
 // wave), every tile belongs to one request, and a fixed grid of waves strides
 // over the tiles, so the same launch (and a graph that captured it) serves any
 // number of requests. A tree that is shared out over a team gives every tile to
-// a block, any other to a wave. Request arrays are instance-major, exactly as the client
+// a block, any other to a wave (at every size: a group that is large enough for
+// one instance per lane to be better takes longer to copy than to compute). Request arrays are instance-major, exactly as the client
 // handed them over: coordinate c of instance i at p[i * n + c].
 template <class TP, int OP>
 struct PackedShape {  // threads of a block and waves per SIMD to leave registers for

@@ -9,6 +9,10 @@ namespace rbd {
 // kernels choose their own block size, see the launchers).
 constexpr int kBlock = 256;
 
+// Instances that give every SIMD (256 compute units of four) one wave of 64, and
+// half as many.
+constexpr int64_t kOneWavePerSimd = 256 * 4 * 64, kHalfWavePerSimd = kOneWavePerSimd / 2;
+
 // Operations of a packed serving launch (equal to rbd_op's values).
 constexpr int kOpFwdDyn = 0, kOpRnea = 1, kOpFwdDynVjp = 2;
 

@@ -27,7 +27,9 @@ template <class TP>
 struct Team {
   static constexpr TeamPlan kPlan = team_plan(TP::kFree, TP::N, TP::par_.v);
   static constexpr bool kOn = TP::NV > kTeamMinDofs && kPlan.waves > 1;
-  static constexpr bool kAlways = kOn && TP::NV > kTeamAlwaysDofs;
+  // the largest batch that runs OP as a team (0: none)
+  template <TeamOp OP>
+  static constexpr long long kLimit = kOn ? team_limit(kPlan, TP::NV, OP) : 0;
   static constexpr int kWaves = kOn ? kPlan.waves : 1;
   static constexpr int kThreads = kWaves * kTileLanes;
   static constexpr int kOwner = kPlan.owner;
