@@ -105,9 +105,11 @@ typedef struct rbd_model rbd_model; /* opaque: device-resident tables */
  * for the tree with hiprtc at run time, one kernel at a time, the first time
  * that kernel is launched on a device (so the first call of each operation on
  * a new topology is host-synchronous and takes seconds for small trees, up to
- * minutes for a 40-body tree; the first call must not be made during stream
- * capture; controller kernels of other frames, see rbd_osc, are compiled the
- * same way). Code objects are cached on disk and looked up in $RBD_JIT_CACHE
+ * minutes for a 40-body tree; a tree whose branches are shared out over several
+ * waves, see rbd_fwd_dyn_vjp, has a second kernel for larger batches of most
+ * operations, compiled when first used; a first use must not be made during
+ * stream capture; controller kernels of other frames, see rbd_osc, are compiled
+ * the same way). Code objects are cached on disk and looked up in $RBD_JIT_CACHE
  * (if set), then in "_jit" beside librbd.so (code objects installed with the
  * library, see rbd_precompile_topology), then in $XDG_CACHE_HOME/rbd-jit or
  * ~/.cache/rbd-jit; new ones are written to $RBD_JIT_CACHE, else the user
